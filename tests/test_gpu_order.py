@@ -61,6 +61,27 @@ def test_bfs_sequence_random_graphs(B, N, max_deg, dtype):
         assert np.array_equal(got, oracle.bfs_sequence(rp, col, train, root))
 
 
+@pytest.mark.parametrize("degrees,hub,dtype", [((0, 1, 2), 300_000, np.int32), ((64, 256, 0), 5_000, np.int64),
+                                               ((1,), 1_100_000, np.int32), ((255, 257), 0, np.int32)])
+def test_bfs_sequence_rows_across_wavefront_shares(B, degrees, hub, dtype):
+    """Edges are dealt to wavefronts in runs of multiples of 256, whatever the rows: rows that end on
+    such a boundary or one beside it, rows of many shares, levels of more than a share per wavefront,
+    and nodes without out-edges between them."""
+    import oracle
+    rng = np.random.default_rng(len(degrees) * 1000 + hub)
+    N = 12_000
+    deg = rng.choice(degrees, N)
+    if hub:
+        deg[rng.choice(N, 3, replace=False)] = hub
+    rp = np.zeros(N + 1, dtype=dtype)
+    rp[1:] = np.cumsum(deg)
+    col = rng.integers(0, N, int(rp[-1])).astype(np.int32)
+    g = B.Graph(rp, col)
+    train = rng.choice(N, N // 2, replace=False)
+    for root in (int(np.argmax(deg)), 0, N - 1):
+        assert np.array_equal(B.order_bfs_sequence(g, train, root), oracle.bfs_sequence(rp, col, train, root))
+
+
 def test_bfs_sequence_chain_of_open_components(B):
     """Several multi-node components that are only reachable by restarts, interleaved by id
     with closed singletons (the bulk restart must keep the sequential order)."""
