@@ -2,26 +2,30 @@
 // (BGL paper, Sec. 3.1: samplers iteratively sample next-hop neighbors of the
 // training nodes; Sec. 5.1: Neighbor Sampling with one fanout per hop).
 //
-// One call runs 1 + num_hops stages on one stream without any host round trip:
-// stage 0 removes repeated seeds, stage h+1 samples hop h.  Every stage is four
-// kernels:
-//   sample/insert  a group of G lanes (G = power of two >= fanout) per frontier
-//                  node draws the node's edge positions (Floyd's subset
-//                  algorithm resolved with wavefront ballots), reads the
-//                  neighbor ids, removes repeats inside the workgroup in an LDS
-//                  hash table and enters the survivors in a global hash table
-//                  with atomicMin on their position, so that the entry of every
-//                  id ends up holding its first position in (node, slot) order
-//   flag           marks the positions that are first occurrences of a new id
-//                  and ranks them inside each tile
-//   scan           one workgroup turns the per-tile totals into prefixes and
-//                  publishes the stage's sizes
-//   finalize       gives every new id its local id (old frontier size + rank),
-//                  appends it to the frontier, and writes the hop's CSR block
-// A stage of at most TILE tiles (262,144 padded positions) has no scan launch:
-// every workgroup of finalize turns the tile totals into prefixes itself, in LDS
-// (one block scan), and the first one publishes the sizes.
-// Launches are sized by upper bounds; the real sizes stay on the device.
+// One call runs on one stream without any host round trip: a launch that clears
+// the dedup map and removes repeated seeds, then three kernels per hop:
+//   sample    a group of G lanes (G = power of two >= fanout) per frontier node
+//             draws the node's edge positions (Floyd's subset algorithm resolved
+//             with wavefront ballots), reads the neighbor ids and enters each in
+//             the dedup map with the smallest position (node, slot) that holds it
+//   mark      positions that are first occurrences of a new id: a bit each, and
+//             how many precede every 64 positions
+//   finalize  gives every new id its local id (old frontier size + rank),
+//             appends it to the frontier, and writes the hop's CSR block
+// The dedup map is an array indexed by node id where the graph is small enough
+// for its clearing to cost less than hashing (k_sample_direct), else a hash table
+// that a workgroup enters its ids into after removing repeats in LDS
+// (k_sample_insert).  mark and finalize deal the positions to at most SHARES
+// workgroups in contiguous shares, so that each of them can turn the shares'
+// totals into prefixes itself, in LDS: no launch for a scan at any size.
+//   What bounds a call: up to ~50,000 neighbors the launches, each 4 to 6 us of
+// dependent reads; beyond, the random lines (row ends, column ids, map).  Measured
+// per call, host included, with 11 to 15 launches and the hash table everywhere /
+// now (7 to 10 launches): 512 seeds, fanout 10,5 on 10,000 nodes 87 / 61 us;
+// 1,024 seeds, fanout 15,10,5 on 2.45 M nodes / 122 M edges 160 / 124 us; 4,096
+// seeds, fanout 25,10 on 8 M nodes 124 / 100 us.
+// Launches are sized by upper bounds; the real sizes stay on the device, and the
+// last kernel stores them into the caller's page-locked counts.
 #include "bgl_internal.h"
 
 namespace {
@@ -29,7 +33,19 @@ namespace {
 using namespace bgl;
 
 constexpr int TILE = 512;                      // threads (= padded positions) per workgroup
+constexpr int SHARES = 1024;                   // workgroups of mark / finalize at most
+constexpr int MARK_TILES = 4;                  // tiles a workgroup of mark has in flight
+constexpr int SEEDS_LDS = 4096;                // seeds whose repeats one workgroup removes in LDS
+constexpr int PREP = 1024;                     // threads per workgroup of k_prepare
+constexpr int FILL_PER_THREAD = 4;             // 16-byte stores per thread that clears the map
 constexpr uint64_t EMPTY64 = ~0ull;
+constexpr uint32_t EMPTY32 = ~0u;
+// Largest graph whose dedup map is indexed by node id.  Clearing it costs 4 bytes per node (4 us at
+// 2.45 M nodes, 12 us at 16 M), the hash table's chains of probes and the removal of repeats in front
+// of them 3 to 6 us per hop.  Measured on 16 M nodes, by id / hashed: 64 seeds, fanout 10,5: 53 / 59 us
+// a call; 1,024 seeds, fanout 15,10,5: 139 / 155 us; 4,096 seeds, fanout 25,10: 94 / 109 us; at twice as
+// many nodes the small calls would lose what the large ones gain.
+constexpr int64_t DIRECT_MAX_NODES = 1 << 24;
 constexpr uint32_t TENT = 0x80000000u;         // value is a tentative position, not yet a local id
 constexpr uint64_t GOLDEN = 0x9E3779B97F4A7C15ull;
 constexpr int STATUS = BGL_COUNTS_LEN - 1;
@@ -47,13 +63,87 @@ __host__ __device__ __forceinline__ uint64_t mix64(uint64_t z)
     return z;
 }
 
-// Start of a call: empty table, counts at zero.
-__global__ void k_prepare(uint64_t *p, int64_t n, uint64_t v, int32_t *cnt)
+// The dedup map.  Direct: value[id], 32 bits.  Hash: (id << 32 | value), 64 bits.  Either way the
+// value is TENT | position while an id of the hop is new, later its local id, and an empty entry
+// (all ones) is larger than any value.
+template <bool DIRECT>
+__device__ __forceinline__ uint32_t map_value(const void *tab, int32_t entry)
 {
-    if (blockIdx.x == 0 && threadIdx.x < BGL_COUNTS_LEN) cnt[threadIdx.x] = 0;
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) p[i] = v;
+    // (cached: a value that is about to become a local id decodes to the same id in either form)
+    if constexpr (DIRECT)
+        return __hip_atomic_load(static_cast<const uint32_t *>(tab) + entry, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else
+        return __hip_atomic_load(reinterpret_cast<const uint32_t *>(static_cast<const uint64_t *>(tab) + entry), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Start of a call: empty map, counts at zero.  With num_seeds > 0 (at most SEEDS_LDS) the first
+// workgroup also writes frontier_0, the seeds without repeats (first occurrence kept): an LDS hash
+// table of seed indices finds them.  The sample kernel of the first hop enters them in the map.
+// LDS (dynamic): 2^tab_log >= 2 * num_seeds indices, then the seeds.
+__global__ __launch_bounds__(PREP) void k_prepare(uint4 *p, int64_t n, int32_t *cnt, const int32_t *__restrict__ seeds,
+                                                  int num_seeds, int tab_log, int64_t num_nodes, int32_t *frontier)
+{
+    constexpr int PER = SEEDS_LDS / PREP, NW = PREP / kWave;
+    static_assert(PER * NW == kWave, "one count per lane");
+    extern __shared__ uint32_t sh_tab[];
+    __shared__ int sh_pop[kWave];
+    if (blockIdx.x > 0) {
+        const int64_t at = (int64_t)(blockIdx.x - 1) * (FILL_PER_THREAD * PREP) + threadIdx.x;
+#pragma unroll
+        for (int k = 0; k < FILL_PER_THREAD; ++k)
+            if (at + k * PREP < n) p[at + k * PREP] = uint4{EMPTY32, EMPTY32, EMPTY32, EMPTY32};
+        return;
+    }
+    if (threadIdx.x < BGL_COUNTS_LEN) cnt[threadIdx.x] = 0;
+    if (num_seeds == 0) return;
+    const uint32_t tab_mask = (1u << tab_log) - 1u;
+    int32_t *sh_seed = reinterpret_cast<int32_t *>(sh_tab + tab_mask + 1);
+    int32_t v[PER];
+    uint32_t at[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = k * PREP + threadIdx.x;
+        v[k] = i < num_seeds ? seeds[i] : -1;
+        if (i < num_seeds) sh_seed[i] = v[k];
+    }
+    for (uint32_t i = threadIdx.x; i <= tab_mask; i += PREP) sh_tab[i] = EMPTY32;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = k * PREP + threadIdx.x;
+        at[k] = 0;
+        if (i >= num_seeds) continue;
+        if (v[k] < 0 || (int64_t)v[k] >= num_nodes) {
+            cnt[STATUS] = BGL_EINVAL;
+            v[k] = -1;
+            continue;
+        }
+        for (at[k] = hash32((uint32_t)v[k]) & tab_mask;; at[k] = (at[k] + 1) & tab_mask) {  // at most half full: ends
+            const uint32_t old = atomicCAS(&sh_tab[at[k]], EMPTY32, (uint32_t)i);
+            if (old == EMPTY32) break;
+            if (sh_seed[old] == v[k]) {
+                atomicMin(&sh_tab[at[k]], (uint32_t)i);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    uint64_t first[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        first[k] = __ballot(v[k] >= 0 && sh_tab[at[k]] == (uint32_t)(k * PREP + threadIdx.x));
+        if (lane == 0) sh_pop[k * NW + w] = __popcll(first[k]);
+    }
+    __syncthreads();
+    const int pop = sh_pop[lane], inc = wave_incl_scan(pop);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int before = __shfl(inc - pop, k * NW + w);
+        if ((first[k] >> lane) & 1ull) frontier[before + __popcll(first[k] & ((1ull << lane) - 1ull))] = v[k];
+    }
+    if (threadIdx.x == kWave - 1) cnt[0] = inc;
 }
 
 // Enter (key, val) in the global table, keeping the smallest val per key.
@@ -64,7 +154,8 @@ __device__ __forceinline__ int table_insert_min(uint64_t *tab, uint32_t mask, ui
     const uint64_t mine = ((uint64_t)key << 32) | val;
     uint32_t s = hash32(key) & mask;
     for (uint32_t tries = 0; tries <= mask; ++tries) {
-        uint64_t cur = __hip_atomic_load(&tab[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (a stale entry is one that was still empty or held a larger value: the atomics decide)
+        uint64_t cur = __hip_atomic_load(&tab[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (cur == EMPTY64) {
             unsigned long long old = atomicCAS((unsigned long long *)&tab[s], EMPTY64, mine);
             if (old == EMPTY64) return (int)s;
@@ -110,16 +201,13 @@ __device__ __forceinline__ void dedup_and_insert(bool valid, uint32_t key, uint3
     slotidx[p] = valid ? sh_gs[ls] : -1;
 }
 
-// Stage 0: the seeds themselves are the keys, position = index in the seed list.
+// More seeds than k_prepare takes: the seeds themselves are the keys, position = index in the seed list.
+template <bool DIRECT>
 __global__ __launch_bounds__(TILE) void k_seed_insert(const int32_t *seeds, int32_t num_seeds,
-                                                      int64_t num_nodes, uint64_t *tab,
+                                                      int64_t num_nodes, void *tab,
                                                       uint32_t mask, int32_t *slotidx,
                                                       int32_t *cnt)
 {
-    __shared__ uint64_t sh_tab[2 * TILE];
-    __shared__ int32_t sh_gs[2 * TILE];
-    for (int i = threadIdx.x; i < 2 * TILE; i += TILE) sh_tab[i] = EMPTY64;
-    __syncthreads();
     const uint32_t p = blockIdx.x * TILE + threadIdx.x;
     bool valid = p < (uint32_t)num_seeds;
     int32_t v = valid ? seeds[p] : 0;
@@ -127,15 +215,115 @@ __global__ __launch_bounds__(TILE) void k_seed_insert(const int32_t *seeds, int3
         cnt[STATUS] = BGL_EINVAL;
         valid = false;
     }
-    dedup_and_insert(valid, (uint32_t)v, p, tab, mask, slotidx, sh_tab, sh_gs, cnt);
+    if constexpr (DIRECT) {
+        if (valid) atomicMin(static_cast<uint32_t *>(tab) + v, TENT | p);
+        slotidx[p] = valid ? v : -1;
+    } else {
+        __shared__ uint64_t sh_tab[2 * TILE];
+        __shared__ int32_t sh_gs[2 * TILE];
+        for (int i = threadIdx.x; i < 2 * TILE; i += TILE) sh_tab[i] = EMPTY64;
+        __syncthreads();
+        dedup_and_insert(valid, (uint32_t)v, p, static_cast<uint64_t *>(tab), mask, slotidx, sh_tab, sh_gs, cnt);
+    }
 }
 
-// Stage h+1: sample hop h.  G lanes per frontier node; lane s owns slot s.
+// One sampled position: group of G lanes per frontier node, lane s owns slot s.
+template <int G, typename RP>
+struct Draw {
+    int i, s, c;     // frontier index, slot, neighbors the node gets
+    uint32_t v;      // the node
+    uint32_t u;      // the neighbor in this slot
+    bool active, valid;
+
+    __device__ __forceinline__ Draw(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
+                                    const int32_t *__restrict__ frontier, uint32_t p, int n_dst, int fanout, uint64_t h0)
+    {
+        i = (int)(p / G);
+        s = (int)(p & (G - 1));
+        const int lane = threadIdx.x & (kWave - 1);
+        const int gshift = lane & ~(G - 1);
+        active = i < n_dst;
+        int64_t lo = 0, d = 0;
+        v = 0;
+        if (active) {
+            v = (uint32_t)frontier[i];
+            // both ends of the row with one read (the pair is only 4 or 8 bytes aligned)
+            typedef RP Ends __attribute__((ext_vector_type(2), aligned(sizeof(RP))));
+            const Ends ends = *reinterpret_cast<const Ends *>(row_ptr + v);
+            lo = (int64_t)ends.x;
+            d = (int64_t)ends.y - lo;
+        }
+        c = (int)(d < (int64_t)fanout ? d : (int64_t)fanout);
+        const bool need = active && d > (int64_t)fanout;  // Floyd's algorithm, else the whole row
+        const int64_t J = d - fanout + s;
+        uint32_t pos = (uint32_t)s;
+        if (need && s < fanout) {
+            const uint64_t h1 = mix64(h0 ^ (uint64_t)v);
+            const uint64_t w = mix64(h1 + GOLDEN * (uint64_t)(s + 1));
+            pos = (uint32_t)__umul64hi(w, (uint64_t)(J + 1));
+        }
+        if (__ballot(need) != 0) {
+            // Slot q keeps its draw unless an earlier slot already holds that
+            // position, in which case it takes J_q.  Lanes below q are final.
+            for (int q = 1; q < fanout; ++q) {
+                const uint32_t tq = __shfl(pos, q, G);
+                const bool coll = need && s < q && pos == tq;
+                const uint64_t bal = __ballot(coll);
+                const bool any = (G == kWave) ? (bal != 0)
+                                              : (((bal >> gshift) & ((1ull << (G & 63)) - 1ull)) != 0);
+                if (need && s == q && any) pos = (uint32_t)J;
+            }
+        }
+        valid = active && s < c;
+        u = 0;
+        if (valid) u = (uint32_t)col[lo + (int64_t)pos];
+    }
+};
+
+// Hop `hop` with the direct map.  enter_frontier: the first hop after k_prepare has written frontier_0;
+// its nodes get their local ids here (smaller than any position's value, so the order does not matter).
+template <int G, typename RP>
+__global__ __launch_bounds__(TILE) void k_sample_direct(
+    const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
+    const int32_t *__restrict__ frontier, const int32_t *__restrict__ cnt, int hop, int fanout, uint64_t h0,
+    uint32_t *tab, int32_t *slotidx, int32_t *lrow, int32_t *cbs, int enter_frontier)
+{
+    __shared__ int sh_scan[TILE / kWave];
+    __shared__ uint32_t sh_first[2 * TILE], sh_id[TILE];
+    const int n_dst = cnt[hop];
+    const uint32_t p = blockIdx.x * TILE + threadIdx.x;
+    if ((int64_t)blockIdx.x * TILE >= (int64_t)n_dst * G) return;  // whole workgroup
+    sh_first[threadIdx.x] = sh_first[threadIdx.x + TILE] = EMPTY32;
+    const Draw<G, RP> d(row_ptr, col, frontier, p, n_dst, fanout, h0);
+    const uint32_t seen = d.valid ? __hip_atomic_load(&tab[d.u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (enter_frontier && d.active && d.s == 0) atomicMin(&tab[d.v], (uint32_t)d.i);
+    slotidx[p] = d.valid ? (int32_t)d.u : -1;
+    // per-node counts -> row starts inside this tile, tile total
+    int total;
+    const int ex = block_excl_scan<TILE>((d.active && d.s == 0) ? d.c : 0, sh_scan, total);
+    if (d.active && d.s == 0) lrow[d.i] = ex;
+    if (threadIdx.x == 0) cbs[blockIdx.x] = total;
+    // A repeat inside the workgroup need not go to the map.  Most repeats (those whose first occurrence
+    // is the first of all ids with its LDS slot) are found here: without it, a graph whose edges lead to
+    // one node for the most part makes every lane lower the same word, 7 ns each (10 % of the edges to
+    // one node: 166 us a call of 16,384 seeds, fanout 10; 64 us with it).
+    // (block_excl_scan ended with a barrier: sh_first is initialised for everyone)
+    const uint32_t at = (hash32(d.u) >> 8) & (2 * TILE - 1);
+    sh_id[threadIdx.x] = d.u;
+    if (d.valid) atomicMin(&sh_first[at], threadIdx.x);
+    __syncthreads();
+    if (d.valid && seen > (TENT | p)) {
+        const uint32_t w = sh_first[at];
+        if (w == threadIdx.x || sh_id[w] != d.u) atomicMin(&tab[d.u], TENT | p);
+    }
+}
+
+// The same with the hash table.
 template <int G, typename RP>
 __global__ __launch_bounds__(TILE) void k_sample_insert(
     const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
     const int32_t *__restrict__ frontier, int32_t *cnt, int hop, int fanout, uint64_t h0,
-    uint64_t *tab, uint32_t mask, int32_t *slotidx, int32_t *lrow, int32_t *cbs)
+    uint64_t *tab, uint32_t mask, int32_t *slotidx, int32_t *lrow, int32_t *cbs, int enter_frontier)
 {
     __shared__ uint64_t sh_tab[2 * TILE];
     __shared__ int32_t sh_gs[2 * TILE];
@@ -146,174 +334,172 @@ __global__ __launch_bounds__(TILE) void k_sample_insert(
     if ((int64_t)blockIdx.x * TILE >= (int64_t)n_dst * G) return;  // whole workgroup
 
     for (int i = threadIdx.x; i < 2 * TILE; i += TILE) sh_tab[i] = EMPTY64;
-
-    const int i = (int)(p / G);
-    const int s = (int)(p & (G - 1));
-    const int lane = threadIdx.x & (kWave - 1);
-    const int gshift = lane & ~(G - 1);
-    const bool active = i < n_dst;
-
-    int64_t lo = 0, d = 0;
-    uint32_t v = 0;
-    if (active) {
-        v = (uint32_t)frontier[i];
-        // both ends of the row with one read (the pair is only 4 or 8 bytes aligned)
-        typedef RP Ends __attribute__((ext_vector_type(2), aligned(sizeof(RP))));
-        const Ends ends = *reinterpret_cast<const Ends *>(row_ptr + v);
-        lo = (int64_t)ends.x;
-        d = (int64_t)ends.y - lo;
-    }
-    const int c = (int)(d < (int64_t)fanout ? d : (int64_t)fanout);
-    const bool need = active && d > (int64_t)fanout;  // Floyd's algorithm, else the whole row
-    const int64_t J = d - fanout + s;
-    uint32_t pos = (uint32_t)s;
-    if (need && s < fanout) {
-        const uint64_t h1 = mix64(h0 ^ (uint64_t)v);
-        const uint64_t w = mix64(h1 + GOLDEN * (uint64_t)(s + 1));
-        pos = (uint32_t)__umul64hi(w, (uint64_t)(J + 1));
-    }
-    if (__ballot(need) != 0) {
-        // Slot q keeps its draw unless an earlier slot already holds that
-        // position, in which case it takes J_q.  Lanes below q are final.
-        for (int q = 1; q < fanout; ++q) {
-            const uint32_t tq = __shfl(pos, q, G);
-            const bool coll = need && s < q && pos == tq;
-            const uint64_t bal = __ballot(coll);
-            const bool any = (G == kWave) ? (bal != 0)
-                                          : (((bal >> gshift) & ((1ull << (G & 63)) - 1ull)) != 0);
-            if (need && s == q && any) pos = (uint32_t)J;
-        }
-    }
-    const bool valid = active && s < c;
-    uint32_t u = 0;
-    if (valid) u = (uint32_t)col[lo + (int64_t)pos];
-
+    const Draw<G, RP> d(row_ptr, col, frontier, p, n_dst, fanout, h0);
+    if (enter_frontier && d.active && d.s == 0) (void)table_insert_min(tab, mask, d.v, (uint32_t)d.i, cnt);
     // per-node counts -> row starts inside this tile, tile total
     int total;
-    const int ex = block_excl_scan<TILE>((active && s == 0) ? c : 0, sh_scan, total);
-    if (active && s == 0) lrow[i] = ex;
+    const int ex = block_excl_scan<TILE>((d.active && d.s == 0) ? d.c : 0, sh_scan, total);
+    if (d.active && d.s == 0) lrow[d.i] = ex;
     if (threadIdx.x == 0) cbs[blockIdx.x] = total;
     // (block_excl_scan ended with a barrier: sh_tab is initialised for everyone)
-    dedup_and_insert(valid, u, p, tab, mask, slotidx, sh_tab, sh_gs, cnt);
+    dedup_and_insert(d.valid, d.u, p, tab, mask, slotidx, sh_tab, sh_gs, cnt);
 }
 
-// Which positions introduced a new id?  Rank them inside the tile.
-__global__ __launch_bounds__(TILE) void k_flag(const int32_t *cnt, int stage, int G,
-                                               int32_t num_seeds, const uint64_t *tab,
-                                               const int32_t *slotidx, int32_t *lrank,
-                                               int32_t *fbs)
-{
-    __shared__ int sh_scan[TILE / kWave];
-    const int64_t P = stage == 0 ? (int64_t)num_seeds : (int64_t)cnt[stage - 1] * G;
-    if ((int64_t)blockIdx.x * TILE >= P) return;
-    const uint32_t p = blockIdx.x * TILE + threadIdx.x;
-    int flag = 0;
-    if ((int64_t)p < P) {
-        const int gs = slotidx[p];
-        if (gs >= 0) flag = ((uint32_t)tab[gs] == (TENT | p)) ? 1 : 0;
+// How the tiles of a stage are dealt to the workgroups of mark and finalize: 2^log contiguous tiles each.
+struct Shares {
+    int64_t positions, tiles;
+    int log;
+    __device__ __forceinline__ Shares(int64_t positions_) : positions(positions_), tiles((positions_ + TILE - 1) / TILE), log(0)
+    {
+        while ((tiles + (1 << log) - 1) >> log > SHARES) ++log;
     }
-    int total;
-    const int ex = block_excl_scan<TILE>(flag, sh_scan, total);
-    if ((int64_t)p < P) lrank[p] = ex;
-    if (threadIdx.x == 0) fbs[blockIdx.x] = total;
-}
+    __device__ __forceinline__ int count() const { return (int)((tiles + (1 << log) - 1) >> log); }
+    __device__ __forceinline__ int64_t first_tile(int share) const { return (int64_t)share << log; }
+    __device__ __forceinline__ int64_t end_tile(int share) const { return min((int64_t)(share + 1) << log, tiles); }
+};
 
-// Prefixes over tiles and the sizes of this stage.
-__global__ __launch_bounds__(1024) void k_scan_sums(int32_t *cnt, int stage, int G,
-                                                    int32_t num_seeds, const int32_t *fbs,
-                                                    const int32_t *cbs, int32_t *fpre,
-                                                    int32_t *cpre, int32_t *row_ptr_h)
+// Which positions introduced a new id?  A bit per position, the number of bits before every 64
+// positions inside the share, the share's total; and the share's number of sampled neighbors.
+template <bool DIRECT>
+__global__ __launch_bounds__(TILE) void k_mark(const int32_t *__restrict__ cnt, int stage, int logG, int32_t num_seeds,
+                                               const void *tab, const int32_t *__restrict__ slotidx, uint64_t *bits,
+                                               int32_t *before, const int32_t *__restrict__ cbs, int32_t *fsum, int32_t *csum)
 {
-    __shared__ int sh_scan[1024 / kWave];
-    const int n_dst = stage == 0 ? 0 : cnt[stage - 1];
-    const int64_t P = stage == 0 ? (int64_t)num_seeds : (int64_t)n_dst * G;
-    const int nb = (int)((P + TILE - 1) / TILE);
-    int carry_f = 0, carry_c = 0;
-    for (int base = 0; base < nb; base += 1024) {
-        const int idx = base + threadIdx.x;
-        const int f = idx < nb ? fbs[idx] : 0;
-        const int c = (cbs && idx < nb) ? cbs[idx] : 0;
-        int tf, tc;
-        const int ef = block_excl_scan<1024>(f, sh_scan, tf);
-        const int ec = block_excl_scan<1024>(c, sh_scan, tc);
-        if (idx < nb) {
-            fpre[idx] = carry_f + ef;
-            cpre[idx] = carry_c + ec;
+    constexpr int NW = TILE / kWave;
+    __shared__ int sh_pop[MARK_TILES][NW];
+    __shared__ int sh_scan[NW];
+    const Shares sh(stage == 0 ? (int64_t)num_seeds : (int64_t)cnt[stage - 1] << logG);
+    const int64_t t0 = sh.first_tile(blockIdx.x), t1 = sh.end_tile(blockIdx.x);
+    if (t0 >= t1) return;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    int carry = 0;
+    for (int64_t t = t0; t < t1; t += MARK_TILES) {
+        int32_t gs[MARK_TILES];
+        uint32_t val[MARK_TILES];
+        uint64_t b[MARK_TILES];
+        // tiles beyond the share's end read its last tile again and drop it
+#pragma unroll
+        for (int k = 0; k < MARK_TILES; ++k) gs[k] = slotidx[min(t + k, t1 - 1) * TILE + threadIdx.x];
+#pragma unroll
+        for (int k = 0; k < MARK_TILES; ++k) val[k] = map_value<DIRECT>(tab, max(gs[k], 0));
+#pragma unroll
+        for (int k = 0; k < MARK_TILES; ++k) {
+            const int64_t p = (t + k) * TILE + threadIdx.x;
+            b[k] = __ballot(t + k < t1 && p < sh.positions && gs[k] >= 0 && val[k] == (TENT | (uint32_t)p));
+            if (lane == 0) sh_pop[k][w] = __popcll(b[k]);
         }
-        carry_f += tf;
-        carry_c += tc;
-    }
-    if (threadIdx.x == 0) {
-        cnt[stage] = n_dst + carry_f;
-        if (stage > 0) {
-            cnt[NNZ0 + stage - 1] = carry_c;
-            row_ptr_h[n_dst] = carry_c;
-        }
-    }
-}
-
-// Local ids, frontier append, CSR block.  SELF_SCAN: the stage has at most TILE tiles and no scan
-// launch; fpre / cpre then hold the tile TOTALS (what k_flag and k_sample_insert wrote), every
-// workgroup scans them in LDS, and workgroup 0 publishes the stage's sizes.
-template <bool SELF_SCAN>
-__global__ __launch_bounds__(TILE) void k_finalize(int32_t *cnt, int stage, int logG,
-                                                   int32_t num_seeds, uint64_t *tab,
-                                                   const int32_t *slotidx, const int32_t *lrank,
-                                                   const int32_t *fpre, const int32_t *cpre,
-                                                   const int32_t *lrow, int32_t *frontier,
-                                                   int32_t *row_ptr_h, int32_t *col_local)
-{
-    __shared__ int sh_scan[TILE / kWave];
-    __shared__ int32_t sh_f[SELF_SCAN ? TILE : 1], sh_c[SELF_SCAN ? TILE : 1];
-    const int n_dst = stage == 0 ? 0 : cnt[stage - 1];
-    const int64_t P = stage == 0 ? (int64_t)num_seeds : ((int64_t)n_dst << logG);
-    // (whole workgroups; the one that publishes the sizes stays, also for an empty stage)
-    if ((int64_t)blockIdx.x * TILE >= P && !(SELF_SCAN && blockIdx.x == 0)) return;
-    if constexpr (SELF_SCAN) {
-        const int nb = (int)((P + TILE - 1) / TILE);  // <= TILE
-        const int t = threadIdx.x;
-        int tf, tc;
-        sh_f[t] = block_excl_scan<TILE>(t < nb ? fpre[t] : 0, sh_scan, tf);
-        sh_c[t] = block_excl_scan<TILE>((stage > 0 && t < nb) ? cpre[t] : 0, sh_scan, tc);
         __syncthreads();
-        if (blockIdx.x == 0 && t == 0) {
-            cnt[stage] = n_dst + tf;
+#pragma unroll
+        for (int k = 0; k < MARK_TILES; ++k) {
+            int mine = 0, all = 0;
+#pragma unroll
+            for (int x = 0; x < NW; ++x) {
+                if (x < w) mine += sh_pop[k][x];
+                all += sh_pop[k][x];
+            }
+            if (lane == 0 && t + k < t1) {
+                const int64_t word = (t + k) * NW + w;
+                bits[word] = b[k];
+                before[word] = carry + mine;
+            }
+            carry += all;
+        }
+        __syncthreads();
+    }
+    int edges = 0;
+    if (stage > 0)
+        for (int64_t t = t0 + threadIdx.x; t < t1; t += TILE) edges += cbs[t];
+    int total;
+    (void)block_excl_scan<TILE>(edges, sh_scan, total);
+    if (threadIdx.x == 0) {
+        fsum[blockIdx.x] = carry;
+        csum[blockIdx.x] = total;
+    }
+}
+
+// Local ids, frontier append, CSR block.  Every workgroup scans the shares' totals in LDS; the first
+// one publishes the stage's sizes and, after the last hop, stores all counts into the caller's
+// page-locked copy.  last: nobody looks the hop's new ids up any more.
+template <bool DIRECT>
+__global__ __launch_bounds__(TILE) void k_finalize(int32_t *cnt, int stage, int logG, int32_t num_seeds, void *tab,
+                                                   const int32_t *__restrict__ slotidx, const uint64_t *__restrict__ bits,
+                                                   const int32_t *__restrict__ before, const int32_t *__restrict__ fsum,
+                                                   const int32_t *__restrict__ csum, const int32_t *__restrict__ cbs,
+                                                   const int32_t *__restrict__ lrow, int32_t *frontier,
+                                                   int32_t *row_ptr_h, int32_t *col_local, int last, int32_t *counts_host)
+{
+    static_assert(SHARES == 2 * TILE, "two totals per thread");
+    __shared__ int sh_scan[TILE / kWave];
+    __shared__ int32_t sh_f[SHARES], sh_c[SHARES];
+    const int n_dst = stage == 0 ? 0 : cnt[stage - 1];
+    const Shares sh(stage == 0 ? (int64_t)num_seeds : (int64_t)n_dst << logG);
+    // (whole workgroups; the one that publishes the sizes stays, also for an empty stage)
+    if ((int)blockIdx.x >= sh.count() && blockIdx.x > 0) return;
+    {
+        const int n = sh.count(), t = threadIdx.x;
+        const int f0 = 2 * t < n ? fsum[2 * t] : 0, f1 = 2 * t + 1 < n ? fsum[2 * t + 1] : 0;
+        const int c0 = 2 * t < n ? csum[2 * t] : 0, c1 = 2 * t + 1 < n ? csum[2 * t + 1] : 0;
+        int tf, tc;
+        const int ef = block_excl_scan<TILE>(f0 + f1, sh_scan, tf);
+        const int ec = block_excl_scan<TILE>(c0 + c1, sh_scan, tc);
+        sh_f[2 * t] = ef;
+        sh_f[2 * t + 1] = ef + f0;
+        sh_c[2 * t] = ec;
+        sh_c[2 * t + 1] = ec + c0;
+        if (blockIdx.x == 0) {
+            if (t == 0) {
+                cnt[stage] = n_dst + tf;
+                if (stage > 0) {
+                    cnt[NNZ0 + stage - 1] = tc;
+                    row_ptr_h[n_dst] = tc;
+                }
+            }
+            __syncthreads();
+            if (counts_host && t < BGL_COUNTS_LEN) counts_host[t] = cnt[t];
+        }
+        __syncthreads();
+    }
+    int edges = sh_c[blockIdx.x];
+    for (int64_t tile = sh.first_tile(blockIdx.x); tile < sh.end_tile(blockIdx.x); ++tile) {
+        const int64_t p64 = tile * TILE + threadIdx.x;
+        if (p64 < sh.positions) {
+            const uint32_t p = (uint32_t)p64;
+            const int gs = slotidx[p];
+            const uint64_t own = bits[p / kWave];
+            const int lane = p & (kWave - 1);
+            int local = -1;
+            if ((own >> lane) & 1ull) {
+                local = n_dst + sh_f[blockIdx.x] + before[p / kWave] + __popcll(own & ((1ull << lane) - 1ull));
+                if constexpr (DIRECT) {
+                    frontier[local] = gs;
+                    if (!last) __hip_atomic_store(static_cast<uint32_t *>(tab) + gs, (uint32_t)local, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    uint32_t *e = reinterpret_cast<uint32_t *>(static_cast<uint64_t *>(tab) + gs);
+                    frontier[local] = (int32_t)e[1];
+                    // Other positions of the same id may read the entry while it
+                    // turns from "first position" into "local id"; both forms
+                    // decode to the same local id.
+                    if (!last) __hip_atomic_store(e, (uint32_t)local, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            } else if (gs >= 0) {
+                const uint32_t val = map_value<DIRECT>(tab, gs);
+                if (val & TENT) {
+                    const uint32_t q = val & ~TENT;  // first position of this id
+                    local = n_dst + sh_f[(q / TILE) >> sh.log] + before[q / kWave] +
+                            __popcll(bits[q / kWave] & ((1ull << (q & (kWave - 1))) - 1ull));
+                } else {
+                    local = (int)val;
+                }
+            }
             if (stage > 0) {
-                cnt[NNZ0 + stage - 1] = tc;
-                row_ptr_h[n_dst] = tc;
+                const int i = (int)(p >> logG);
+                const int s = (int)(p & ((1u << logG) - 1));
+                const int base = edges + lrow[i];
+                if (s == 0) row_ptr_h[i] = base;
+                if (gs >= 0) col_local[base + s] = local;
             }
         }
-        fpre = sh_f;
-        cpre = sh_c;
-    }
-    const uint32_t p = blockIdx.x * TILE + threadIdx.x;
-    if ((int64_t)p >= P) return;
-    const int gs = slotidx[p];
-    int local = -1;
-    if (gs >= 0) {
-        const uint64_t e = __hip_atomic_load(&tab[gs], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint32_t val = (uint32_t)e;
-        if (val & TENT) {
-            const uint32_t q = val & ~TENT;  // first position of this id
-            local = n_dst + fpre[q / TILE] + lrank[q];
-            if (q == p) {
-                frontier[local] = (int32_t)(e >> 32);
-                // Other positions of the same id may read the entry while it
-                // turns from "first position" into "local id"; both forms
-                // decode to the same local id.
-                __hip_atomic_store(reinterpret_cast<uint32_t *>(&tab[gs]), (uint32_t)local,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        } else {
-            local = (int)val;
-        }
-    }
-    if (stage > 0) {
-        const int i = (int)(p >> logG);
-        const int s = (int)(p & ((1u << logG) - 1));
-        const int base = cpre[p / TILE] + lrow[i];
-        if (s == 0) row_ptr_h[i] = base;
-        if (gs >= 0) col_local[base + s] = local;
+        if (stage > 0) edges += cbs[tile];
     }
 }
 
@@ -323,9 +509,11 @@ struct Layout {
     int G[BGL_MAX_HOPS], logG[BGL_MAX_HOPS];
     int64_t ubf[BGL_MAX_HOPS + 1], ube[BGL_MAX_HOPS];
     int64_t P[BGL_MAX_HOPS + 1];  // padded positions per stage
+    bool direct;                  // the dedup map is indexed by node id
     int64_t table_entries;
+    size_t table_bytes;
     size_t off_counts, off_frontier, off_row_ptr[BGL_MAX_HOPS], off_col[BGL_MAX_HOPS];
-    size_t off_table, off_slotidx, off_lrank, off_lrow, off_fbs, off_cbs, off_fpre, off_cpre;
+    size_t off_table, off_slotidx, off_bits, off_before, off_lrow, off_cbs, off_fsum, off_csum;
     size_t bytes;
 };
 
@@ -363,7 +551,9 @@ int make_layout(int32_t num_seeds, const int32_t *fanouts, int32_t num_hops, int
     int64_t need = L.ubf[num_hops] + L.ubf[num_hops] / 3 + 1;
     int64_t ts = 1024;
     while (ts < need) ts <<= 1;
-    L.table_entries = ts;
+    L.direct = num_nodes <= DIRECT_MAX_NODES;
+    L.table_entries = L.direct ? (int64_t)bgl::round_up((size_t)num_nodes, 4) : ts;
+    L.table_bytes = L.direct ? sizeof(uint32_t) * (size_t)L.table_entries : sizeof(uint64_t) * (size_t)ts;
     const int64_t nbmax = bgl::ceil_div(pmax, TILE) + 1;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off += bgl::round_up(bytes, 256); return o; };
@@ -373,40 +563,50 @@ int make_layout(int32_t num_seeds, const int32_t *fanouts, int32_t num_hops, int
         L.off_row_ptr[h] = take(sizeof(int32_t) * (size_t)(L.ubf[h] + 1));
         L.off_col[h] = take(sizeof(int32_t) * (size_t)L.ube[h]);
     }
-    L.off_table = take(sizeof(uint64_t) * (size_t)ts);
+    L.off_table = take(L.table_bytes);
     const size_t ppad = bgl::round_up((size_t)pmax, TILE);
     L.off_slotidx = take(sizeof(int32_t) * ppad);
-    L.off_lrank = take(sizeof(int32_t) * ppad);
+    L.off_bits = take(sizeof(uint64_t) * (ppad / kWave));
+    L.off_before = take(sizeof(int32_t) * (ppad / kWave));
     L.off_lrow = take(sizeof(int32_t) * (size_t)fmax);
-    L.off_fbs = take(sizeof(int32_t) * (size_t)nbmax);
     L.off_cbs = take(sizeof(int32_t) * (size_t)nbmax);
-    L.off_fpre = take(sizeof(int32_t) * (size_t)nbmax);
-    L.off_cpre = take(sizeof(int32_t) * (size_t)nbmax);
+    L.off_fsum = take(sizeof(int32_t) * SHARES);
+    L.off_csum = take(sizeof(int32_t) * SHARES);
     L.bytes = off;
     return BGL_OK;
 }
 
+// What the kernels of one call share.
+struct Call {
+    const bgl_graph *g;
+    bool direct;
+    void *tab;
+    uint32_t mask;
+    int32_t *cnt, *frontier, *slotidx, *lrow, *cbs;
+    hipStream_t st;
+};
+
 template <int G, typename RP>
-void launch_sample(const bgl_graph *g, int blocks, hipStream_t st, const int32_t *frontier,
-                   int32_t *cnt, int hop, int fanout, uint64_t h0, uint64_t *tab, uint32_t mask,
-                   int32_t *slotidx, int32_t *lrow, int32_t *cbs)
+void launch_sample(const Call &k, int blocks, int hop, int fanout, uint64_t h0, int enter_frontier)
 {
-    hipLaunchKernelGGL((k_sample_insert<G, RP>), dim3(blocks), dim3(TILE), 0, st,
-                       static_cast<const RP *>(g->row_ptr), g->col, frontier, cnt, hop, fanout,
-                       h0, tab, mask, slotidx, lrow, cbs);
+    const RP *rp = static_cast<const RP *>(k.g->row_ptr);
+    if (k.direct)
+        hipLaunchKernelGGL((k_sample_direct<G, RP>), dim3(blocks), dim3(TILE), 0, k.st, rp, k.g->col, k.frontier, k.cnt, hop, fanout,
+                           h0, static_cast<uint32_t *>(k.tab), k.slotidx, k.lrow, k.cbs, enter_frontier);
+    else
+        hipLaunchKernelGGL((k_sample_insert<G, RP>), dim3(blocks), dim3(TILE), 0, k.st, rp, k.g->col, k.frontier, k.cnt, hop, fanout,
+                           h0, static_cast<uint64_t *>(k.tab), k.mask, k.slotidx, k.lrow, k.cbs, enter_frontier);
 }
 
 template <typename RP>
-void launch_sample_g(int G, const bgl_graph *g, int blocks, hipStream_t st,
-                     const int32_t *frontier, int32_t *cnt, int hop, int fanout, uint64_t h0,
-                     uint64_t *tab, uint32_t mask, int32_t *slotidx, int32_t *lrow, int32_t *cbs)
+void launch_sample_g(int G, const Call &k, int blocks, int hop, int fanout, uint64_t h0, int enter_frontier)
 {
     switch (G) {
-    case 4: launch_sample<4, RP>(g, blocks, st, frontier, cnt, hop, fanout, h0, tab, mask, slotidx, lrow, cbs); break;
-    case 8: launch_sample<8, RP>(g, blocks, st, frontier, cnt, hop, fanout, h0, tab, mask, slotidx, lrow, cbs); break;
-    case 16: launch_sample<16, RP>(g, blocks, st, frontier, cnt, hop, fanout, h0, tab, mask, slotidx, lrow, cbs); break;
-    case 32: launch_sample<32, RP>(g, blocks, st, frontier, cnt, hop, fanout, h0, tab, mask, slotidx, lrow, cbs); break;
-    default: launch_sample<64, RP>(g, blocks, st, frontier, cnt, hop, fanout, h0, tab, mask, slotidx, lrow, cbs); break;
+    case 4: launch_sample<4, RP>(k, blocks, hop, fanout, h0, enter_frontier); break;
+    case 8: launch_sample<8, RP>(k, blocks, hop, fanout, h0, enter_frontier); break;
+    case 16: launch_sample<16, RP>(k, blocks, hop, fanout, h0, enter_frontier); break;
+    case 32: launch_sample<32, RP>(k, blocks, hop, fanout, h0, enter_frontier); break;
+    default: launch_sample<64, RP>(k, blocks, hop, fanout, h0, enter_frontier); break;
     }
 }
 
@@ -443,15 +643,24 @@ try {
     char *ws = static_cast<char *>(workspace);
     int32_t *cnt = reinterpret_cast<int32_t *>(ws + L.off_counts);
     int32_t *frontier = reinterpret_cast<int32_t *>(ws + L.off_frontier);
-    uint64_t *tab = reinterpret_cast<uint64_t *>(ws + L.off_table);
+    void *tab = ws + L.off_table;
     int32_t *slotidx = reinterpret_cast<int32_t *>(ws + L.off_slotidx);
-    int32_t *lrank = reinterpret_cast<int32_t *>(ws + L.off_lrank);
+    uint64_t *bits = reinterpret_cast<uint64_t *>(ws + L.off_bits);
+    int32_t *before = reinterpret_cast<int32_t *>(ws + L.off_before);
     int32_t *lrow = reinterpret_cast<int32_t *>(ws + L.off_lrow);
-    int32_t *fbs = reinterpret_cast<int32_t *>(ws + L.off_fbs);
     int32_t *cbs = reinterpret_cast<int32_t *>(ws + L.off_cbs);
-    int32_t *fpre = reinterpret_cast<int32_t *>(ws + L.off_fpre);
-    int32_t *cpre = reinterpret_cast<int32_t *>(ws + L.off_cpre);
+    int32_t *fsum = reinterpret_cast<int32_t *>(ws + L.off_fsum);
+    int32_t *csum = reinterpret_cast<int32_t *>(ws + L.off_csum);
     const uint32_t mask = (uint32_t)(L.table_entries - 1);
+    // page-locked counts are stored by the last kernel; anything else is copied to behind it
+    int32_t *counts_dev = nullptr;
+    if (counts_host) {
+        hipPointerAttribute_t attr;
+        if (hipPointerGetAttributes(&attr, counts_host) == hipSuccess && attr.type == hipMemoryTypeHost)
+            counts_dev = static_cast<int32_t *>(attr.devicePointer);
+        else
+            (void)hipGetLastError();
+    }
 
     out->num_hops = num_hops;
     out->input_nodes = frontier;
@@ -463,53 +672,38 @@ try {
         out->cap_edges[h] = h < num_hops ? L.ube[h] : 0;
     }
 
-    {
-        int blocks = (int)std::min<int64_t>(bgl::ceil_div(L.table_entries, 1024), 4096);
-        hipLaunchKernelGGL(k_prepare, dim3(blocks), dim3(256), 0, st, tab, L.table_entries, EMPTY64, cnt);
-    }
-    // stage 0: unique seeds
-    {
-        const int blocks = (int)bgl::ceil_div(L.P[0], TILE);
-        hipLaunchKernelGGL(k_seed_insert, dim3(blocks), dim3(TILE), 0, st, seeds, num_seeds,
-                           g->num_nodes, tab, mask, slotidx, cnt);
-        hipLaunchKernelGGL(k_flag, dim3(blocks), dim3(TILE), 0, st, cnt, 0, 1, num_seeds, tab,
-                           slotidx, lrank, fbs);
-        if (blocks <= TILE) {
-            hipLaunchKernelGGL(k_finalize<true>, dim3(blocks), dim3(TILE), 0, st, cnt, 0, 0, num_seeds, tab,
-                               slotidx, lrank, fbs, cbs, lrow, frontier, (int32_t *)nullptr, (int32_t *)nullptr);
-        } else {
-            hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, cnt, 0, 1, num_seeds, fbs,
-                               (const int32_t *)nullptr, fpre, cpre, (int32_t *)nullptr);
-            hipLaunchKernelGGL(k_finalize<false>, dim3(blocks), dim3(TILE), 0, st, cnt, 0, 0, num_seeds, tab,
-                               slotidx, lrank, fpre, cpre, lrow, frontier, (int32_t *)nullptr,
-                               (int32_t *)nullptr);
-        }
+    const Call k{g, L.direct, tab, mask, cnt, frontier, slotidx, lrow, cbs, st};
+    // mark and finalize of one stage
+    auto place = [&](int stage, int logG, int64_t positions, int32_t *row_ptr_h, int32_t *col_local, bool last) {
+        const int blocks = (int)std::min<int64_t>(bgl::ceil_div(positions, TILE), SHARES);
+        hipLaunchKernelGGL((L.direct ? k_mark<true> : k_mark<false>), dim3(blocks), dim3(TILE), 0, st, cnt, stage, logG, num_seeds,
+                           tab, slotidx, bits, before, cbs, fsum, csum);
+        hipLaunchKernelGGL((L.direct ? k_finalize<true> : k_finalize<false>), dim3(blocks), dim3(TILE), 0, st, cnt, stage, logG,
+                           num_seeds, tab, slotidx, bits, before, fsum, csum, cbs, lrow, frontier, row_ptr_h, col_local,
+                           last ? 1 : 0, last ? counts_dev : nullptr);
+    };
+    const bool few_seeds = num_seeds <= SEEDS_LDS;
+    const int64_t chunks = (int64_t)(L.table_bytes / 16);
+    int tab_log = 10;
+    while ((1 << tab_log) < 2 * std::min(num_seeds, SEEDS_LDS)) ++tab_log;
+    const size_t lds = few_seeds ? sizeof(uint32_t) * (((size_t)1 << tab_log) + (size_t)num_seeds) : 0;
+    hipLaunchKernelGGL(k_prepare, dim3(1 + (unsigned)bgl::ceil_div(chunks, FILL_PER_THREAD * PREP)), dim3(PREP), lds, st,
+                       static_cast<uint4 *>(tab), chunks, cnt, seeds, few_seeds ? num_seeds : 0, tab_log, g->num_nodes, frontier);
+    if (!few_seeds) {
+        hipLaunchKernelGGL((L.direct ? k_seed_insert<true> : k_seed_insert<false>), dim3((unsigned)bgl::ceil_div(L.P[0], TILE)),
+                           dim3(TILE), 0, st, seeds, num_seeds, g->num_nodes, tab, mask, slotidx, cnt);
+        place(0, 0, L.P[0], nullptr, nullptr, false);
     }
     for (int h = 0; h < num_hops; ++h) {
         const int blocks = (int)bgl::ceil_div(L.P[h + 1], TILE);
         const uint64_t h0 = mix64(rng_seed + GOLDEN * (uint64_t)(h + 1));
-        if (g->bits == 64)
-            launch_sample_g<int64_t>(L.G[h], g, blocks, st, frontier, cnt, h, fanouts[h], h0, tab,
-                                     mask, slotidx, lrow, cbs);
-        else
-            launch_sample_g<int32_t>(L.G[h], g, blocks, st, frontier, cnt, h, fanouts[h], h0, tab,
-                                     mask, slotidx, lrow, cbs);
-        hipLaunchKernelGGL(k_flag, dim3(blocks), dim3(TILE), 0, st, cnt, h + 1, L.G[h], num_seeds,
-                           tab, slotidx, lrank, fbs);
-        if (blocks <= TILE) {
-            hipLaunchKernelGGL(k_finalize<true>, dim3(blocks), dim3(TILE), 0, st, cnt, h + 1, L.logG[h],
-                               num_seeds, tab, slotidx, lrank, fbs, cbs, lrow, frontier,
-                               out->row_ptr[h], out->col_local[h]);
-        } else {
-            hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, cnt, h + 1, L.G[h], num_seeds,
-                               fbs, cbs, fpre, cpre, out->row_ptr[h]);
-            hipLaunchKernelGGL(k_finalize<false>, dim3(blocks), dim3(TILE), 0, st, cnt, h + 1, L.logG[h],
-                               num_seeds, tab, slotidx, lrank, fpre, cpre, lrow, frontier,
-                               out->row_ptr[h], out->col_local[h]);
-        }
+        const int enter = h == 0 && few_seeds;
+        if (g->bits == 64) launch_sample_g<int64_t>(L.G[h], k, blocks, h, fanouts[h], h0, enter);
+        else launch_sample_g<int32_t>(L.G[h], k, blocks, h, fanouts[h], h0, enter);
+        place(h + 1, L.logG[h], L.P[h + 1], out->row_ptr[h], out->col_local[h], h == num_hops - 1);
     }
     BGL_HIP(hipGetLastError());
-    if (counts_host)
+    if (counts_host && !counts_dev)
         BGL_HIP(hipMemcpyAsync(counts_host, cnt, sizeof(int32_t) * BGL_COUNTS_LEN,
                                hipMemcpyDeviceToHost, st));
     return BGL_OK;

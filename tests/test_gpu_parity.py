@@ -145,6 +145,27 @@ def test_sample_stage_sizes_around_the_scan_threshold(B, torch_mod, num_seeds):
     assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, [10, 3], 4242))
 
 
+@pytest.mark.parametrize("num_nodes", [2**24, 2**24 + 1])
+@pytest.mark.parametrize("num_seeds,fanouts", [(4096, [25, 10]), (4097, [6, 3]), (700, [33, 10, 5])])
+def test_sample_map_by_node_id_and_by_hash(B, torch_mod, num_nodes, num_seeds, fanouts):
+    """The dedup map is indexed by node id up to 2**24 nodes and hashed beyond; up to 4,096 seeds lose
+    their repeats in LDS.  Sparse ids over the whole range, a third of the edges to one node (repeats
+    inside workgroups and across them), and stages of more than 1,024 tiles (shares of several tiles)."""
+    import oracle
+    rng = np.random.default_rng(num_seeds)
+    nodes = np.sort(rng.choice(num_nodes, 150_000, replace=False))
+    nodes[-1] = num_nodes - 1
+    deg = np.zeros(num_nodes, dtype=np.int64)
+    deg[nodes] = rng.integers(0, 45, len(nodes))
+    rp = np.zeros(num_nodes + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(deg)
+    col = nodes[rng.integers(0, len(nodes), int(rp[-1]))].astype(np.int32)
+    col[rng.random(len(col)) < 0.33] = nodes[-1]
+    seeds = nodes[rng.integers(0, len(nodes), num_seeds)].astype(np.int32)     # with repeats
+    res = gpu_sample(B, torch_mod, rp, col, seeds.tolist(), fanouts, 77)
+    assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, fanouts, 77))
+
+
 def test_sample_high_degree_hub_and_host_pinned_graph(B, torch_mod):
     import oracle
     rng = np.random.default_rng(11)
