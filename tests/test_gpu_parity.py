@@ -314,6 +314,19 @@ def test_cache_write_through_mode(B, torch_mod, dim, dtype, side, spare):
     run_cache_stream(B, torch_mod, feats, 1, batches[:6], side=side, write_through=True, spare=spare)
 
 
+@pytest.mark.parametrize("row_bytes", [16, 48, 272, 496, 512, 528, 1008, 1024, 1040])
+@pytest.mark.parametrize("write_through", [False, True])
+def test_cache_misses_in_place_by_row_width(B, torch_mod, row_bytes, write_through):
+    """Misses read in place: wavefronts take whole rows, 64 // (row_bytes / 16) side by side, up to rows
+    of 64 chunks; wider rows are dealt chunk by chunk.  Widths on both sides of every change of the
+    number of rows, batches of one row, of a group more or less, and of several rounds."""
+    rng = np.random.default_rng(row_bytes)
+    N = 40_000
+    feats = rng.integers(0, 256, (N, row_bytes)).astype(np.uint8)
+    batches = [rng.permutation(N)[:n].astype(np.int32) for n in (1, 3, 63, 1025, 30_011, 5)]
+    run_cache_stream(B, torch_mod, feats, 7_001, batches, write_through=write_through)
+
+
 @pytest.mark.parametrize("early", ["own", "with_insert", "alternate"])
 @pytest.mark.parametrize("side", [True, False])
 def test_cache_early_lookup(B, torch_mod, early, side):
