@@ -12,10 +12,9 @@
 // its id's bucket (one line) and goes on to the next bucket only while that
 // count is not zero (one id per lane: a wavefront keeps 64 independent line
 // reads in flight; a 16-lanes-per-id lookup that found the id with a ballot was
-// measured at half the speed, the lookup being latency bound).  An insertion is
-// done by a group of 16 lanes that reads the bucket with one coalesced request,
-// picks a free word with a wavefront ballot and claims it with a CAS; every full
-// bucket it walks past gets its count raised by one.  An eviction blanks its
+// measured at half the speed, the lookup being latency bound).  An insertion
+// (one per lane too) reads the bucket, claims a free word with a CAS, and raises
+// the count of every full bucket it walks past by one.  An eviction blanks its
 // word (slot_to_entry[slot] remembers the word that maps a slot's occupant, so
 // no search) and lowers the counts of the buckets between the evicted id's home
 // bucket (recomputed from the id) and that word's bucket: what one insertion
@@ -237,14 +236,22 @@ __global__ void k_empty_lookup(CacheDev *dev, int64_t *n_hit_host, int gen)
 // insertions evict stay readable until the next batch, so nothing has to be read "before it
 // is overwritten".  The live rows are the last min(tail, capacity) insertions; slot and
 // position of a live row follow from each other and tail by additions alone.
+__device__ __forceinline__ unsigned long long uniform(unsigned long long v)  // keeps the divisions below off the vector unit
+{
+    return (unsigned long long)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
 struct RowRing {
     int64_t capacity, rows;
     int64_t newest_slot, newest_pos;  // of insertion tail - 1 (tail > 0)
     // this call's insertions: ranks start <= r < start + count stay, rank r goes to position first_pos + (r - start)
     int64_t start, count, first_pos;
+    // (tail and n_miss are the same for all lanes)
     __device__ __forceinline__ RowRing(unsigned long long tail, int64_t capacity_, int64_t rows_, int64_t n_miss = 0)
         : capacity(capacity_), rows(rows_)
     {
+        tail = uniform(tail);
+        n_miss = (int64_t)uniform((unsigned long long)n_miss);
         const unsigned long long newest = tail > 0 ? tail - 1 : 0;
         newest_slot = (int64_t)(newest % (unsigned long long)capacity);
         newest_pos = (int64_t)(newest % (unsigned long long)rows);
@@ -317,7 +324,7 @@ __global__ __launch_bounds__(KEYS_PER_TILE) void k_split_list(const int32_t *__r
         }
     } else if (i < n) {
         // the kernels that read the row get its position in the cache buffer (see RowRing)
-        const int32_t pos = (int32_t)RowRing(dev->tail[par], capacity, rows).pos_of_slot(slot);
+        const int32_t pos = rows == capacity ? slot : (int32_t)RowRing(dev->tail[par], capacity, rows).pos_of_slot(slot);
         if (!src_of) {
             hit_pos[i - mrank] = (int32_t)i;
             hit_slot[i - mrank] = pos;
@@ -363,6 +370,7 @@ struct RowSplit {
 };
 
 constexpr int COPY_THREADS = 256;
+constexpr int MAP_THREADS = 64;  // rows per workgroup of the map update: a short batch spreads over many CUs
 constexpr int COPY_UNROLL = 4;  // (the kernels name the four chunks of a lane by hand)
 // Workgroups of a kernel that reads rows over the host link.  Each lane keeps
 // four 16-byte loads in flight, so 64 x 256 lanes hold 1 MiB: that saturates
@@ -747,85 +755,75 @@ __global__ __launch_bounds__(COPY_THREADS) void k_assemble_rows(
     }
 }
 
-// Map update: 16 lanes per inserted row.  Evict the slot's occupant (blank its
-// word, found through slot_to_entry, and take one off the pushed-past count of
-// every bucket from the evicted id's home bucket up to the word's bucket), then
-// read the new id's bucket with one coalesced request, pick a free word with a
-// wavefront ballot and claim it with a CAS; a bucket without a free word gets
-// one added to its count before the group moves on.  Counts change by atomic
-// adds only and no lookup runs beside an update, so after the launch every
-// count is exact whatever the order of the groups.  Bucket words are read with
-// device-scope atomic loads so that the retry after a lost CAS sees the winner's
-// word.  (One row per lane was measured too: no faster, the update is bound by
-// its random lines, not by lane count.)
+// Map update, one inserted row per lane.  Evict the slot's occupant (blank its word, found through
+// slot_to_entry, and take one off the pushed-past count of every bucket from the evicted id's home
+// bucket up to the word's bucket), then read the new id's bucket whole (as k_probe does), and claim a
+// free word with a CAS; a bucket without a free word gets one added to its count before the lane moves
+// on.  Counts change by atomic adds only and no lookup runs beside an update, so after the launch every
+// count is exact whatever the order of the lanes.  The bucket may be read from a cache that does not
+// see other lanes' changes: a word that looks free is decided by the CAS, and one that looks taken and
+// is being blanked is passed over.  The update is bound by dependent random accesses, so what counts is
+// how many rows are in flight and how often a CAS is lost: a batch brings several ids per bucket (4.8 at
+// 315 K misses, 65,536 buckets), so every lane starts at a word of its own choice.  Measured, against
+// 16 lanes per row, four rows per wavefront, all starting at the first free word: 315 K rows 49 -> 34 us,
+// 100 K rows 22 -> 19, 4 K rows (an overlapped loop's small batches) 10.6 -> 6.7.
 __device__ __forceinline__ void insert_map_part(
-    int64_t block, const int32_t *__restrict__ ids, const int32_t *__restrict__ miss_pos,
-    int64_t n_miss, int64_t start, unsigned long long tail, int64_t capacity, int64_t num_nodes,
+    int64_t r, const int32_t *__restrict__ ids, const int32_t *__restrict__ miss_pos,
+    int64_t start, unsigned long long tail, int64_t capacity, int64_t num_nodes,
     uint64_t *table, uint32_t bucket_mask, int32_t *slot_to_node, uint32_t *slot_to_entry,
     CacheDev *dev)
 {
-    const int l = threadIdx.x & (BUCKET - 1);
-    const int gshift = (threadIdx.x & (kWave - 1)) & ~(BUCKET - 1);
-    const int64_t r = start + (block * COPY_THREADS + threadIdx.x) / BUCKET;
-    if (r >= n_miss) return;  // uniform inside the group
-    const int64_t slot = (int64_t)((tail + (unsigned long long)r) % (unsigned long long)capacity);
+    // (the ranks from start on cover at most one turn of the slots)
+    int64_t slot = (int64_t)((tail + (unsigned long long)start) % (unsigned long long)capacity) + (r - start);
+    if (slot >= capacity) slot -= capacity;
     const int32_t key = ids[miss_pos[r]];
     const int32_t old = slot_to_node[slot];
-    if (old >= 0 && l == 0) {
+    const bool ok = key >= 0 && (int64_t)key < num_nodes;
+    uint32_t b = hash32((uint32_t)key) & bucket_mask;
+    if (old >= 0) {
         const uint32_t word = slot_to_entry[slot];
         __hip_atomic_store(&table[word], EMPTY64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // the buckets this entry had been pushed past (none for an entry in its home bucket)
         const uint32_t rest = word / BUCKET;
-        for (uint32_t b = hash32((uint32_t)old) & bucket_mask; b != rest; b = (b + 1) & bucket_mask)
-            atomicAdd((unsigned long long *)&table[(size_t)b * BUCKET + (BUCKET - 1)], ~0ull);  // -1
+        for (uint32_t p = hash32((uint32_t)old) & bucket_mask; p != rest; p = (p + 1) & bucket_mask)
+            atomicAdd((unsigned long long *)&table[(size_t)p * BUCKET + (BUCKET - 1)], ~0ull);  // -1
     }
-    if (key < 0 || (int64_t)key >= num_nodes) {
+    if (!ok) {
         // reported by the lookup already: the slot's row will be overwritten, so
         // leave the slot unmapped rather than mapped to the wrong bytes
-        if (l == 0) {
-            slot_to_node[slot] = -1;
-            dev->status = BGL_EINVAL;
-        }
+        slot_to_node[slot] = -1;
+        dev->status = BGL_EINVAL;
         return;
     }
     const uint64_t mine = ((uint64_t)(uint32_t)key << 32) | (uint32_t)slot;
-    uint32_t b = hash32((uint32_t)key) & bucket_mask;
-    uint32_t entry = 0;
-    bool done = false;
-    // every lost CAS means another group filled a word: at most 15 retries per
-    // bucket, and a table at load <= 1/2 always has a bucket with a free word
-    for (uint32_t tries = 0; tries < 16u * (bucket_mask + 1u) && !done; ++tries) {
-        const uint64_t e = __hip_atomic_load(&table[(size_t)b * BUCKET + l], __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-        const bool free_word = l < BUCKET - 1 && e == EMPTY64;
-        const uint32_t fm = (uint32_t)(__ballot(free_word) >> gshift) & 0xffffu;
-        if (fm) {
-            const int t = __ffs(fm) - 1;
-            int won = 0;
-            if (l == t) {
-                unsigned long long prev = atomicCAS(
-                    (unsigned long long *)&table[(size_t)b * BUCKET + t], EMPTY64, mine);
-                won = prev == EMPTY64;
-            }
-            won = __shfl(won, t, BUCKET);
-            if (won) {
-                entry = b * BUCKET + (uint32_t)t;
-                done = true;
-            }
-        } else {
-            // full: this entry will rest beyond bucket b (its eviction takes the one off again)
-            if (l == BUCKET - 1) atomicAdd((unsigned long long *)&table[(size_t)b * BUCKET + l], 1ull);
-            b = (b + 1) & bucket_mask;
+    const uint32_t first = (hash32((uint32_t)key) >> 27) % (BUCKET - 1);  // (bucket numbers use the low bits)
+    // a table at load <= 1/2 always has a bucket with a free word
+    for (uint32_t tries = 0; tries <= bucket_mask; ++tries) {
+        const ulonglong2 *bp = reinterpret_cast<const ulonglong2 *>(table + (size_t)b * BUCKET);
+        uint32_t free_words = 0;
+#pragma unroll
+        for (int k = 0; k < BUCKET / 2; ++k) {
+            const ulonglong2 w = bp[k];
+            free_words |= (w.x == EMPTY64 ? 1u : 0u) << (2 * k);
+            if (k < BUCKET / 2 - 1) free_words |= (w.y == EMPTY64 ? 1u : 0u) << (2 * k + 1);
         }
-    }
-    if (l == 0) {
-        if (done) {
-            slot_to_node[slot] = key;
-            slot_to_entry[slot] = entry;
-        } else {
-            dev->status = BGL_ECAPACITY;
+        while (free_words) {
+            const uint32_t after = free_words >> first << first;
+            const uint32_t t = (uint32_t)__ffs(after ? after : free_words) - 1u;
+            const unsigned long long prev =
+                atomicCAS((unsigned long long *)&table[(size_t)b * BUCKET + t], EMPTY64, (unsigned long long)mine);
+            if (prev == EMPTY64) {
+                slot_to_node[slot] = key;
+                slot_to_entry[slot] = b * BUCKET + t;
+                return;
+            }
+            free_words &= ~(1u << t);  // another lane has it now
         }
+        // full: this entry will rest beyond bucket b (its eviction takes the one off again)
+        atomicAdd((unsigned long long *)&table[(size_t)b * BUCKET + (BUCKET - 1)], 1ull);
+        b = (b + 1) & bucket_mask;
     }
+    dev->status = BGL_ECAPACITY;
 }
 
 // buffer[(tail + r) % capacity] = out[miss_pos[r]]: the destination is a
@@ -868,7 +866,7 @@ __device__ __forceinline__ void insert_rows_part(
 // rows: the map update is enqueued ahead of the wait for the miss fetch and runs
 // while the host link is still busy.  Both read tail[par]; the row copy stores the
 // advanced value in tail[par ^ 1] for the next update.
-__global__ __launch_bounds__(COPY_THREADS) void k_insert_map(
+__global__ __launch_bounds__(MAP_THREADS) void k_insert_map(
     const int32_t *__restrict__ ids, const int32_t *__restrict__ miss_pos, int64_t n_miss_arg,
     int64_t capacity, int64_t num_nodes, uint64_t *table, uint32_t bucket_mask,
     int32_t *slot_to_node, uint32_t *slot_to_entry, CacheDev *dev, int par, int advance)
@@ -878,8 +876,10 @@ __global__ __launch_bounds__(COPY_THREADS) void k_insert_map(
     const unsigned long long tail = dev->tail[par];
     // write-through mode has no row-copy launch: then this one advances tail
     if (advance && blockIdx.x == 0 && threadIdx.x == 0) dev->tail[par ^ 1] = tail + (unsigned long long)n_miss;
-    insert_map_part(blockIdx.x, ids, miss_pos, n_miss, start, tail, capacity, num_nodes,
-                    table, bucket_mask, slot_to_node, slot_to_entry, dev);
+    const int64_t r = start + (int64_t)blockIdx.x * MAP_THREADS + threadIdx.x;
+    if (r < n_miss)
+        insert_map_part(r, ids, miss_pos, start, uniform(tail), capacity, num_nodes, table, bucket_mask, slot_to_node,
+                        slot_to_entry, dev);
 }
 
 template <int Q>
@@ -1826,8 +1826,8 @@ try {
         c->awaiting_insert = false;
         if (eff > 0) {
             Prof p(c, BGL_STAGE_INSERT_MAP, st);
-            launch(c, st, k_insert_map, dim3((unsigned)bgl::ceil_div(eff * BUCKET, COPY_THREADS)),
-                   dim3(COPY_THREADS), ids, miss_pos, n_miss, c->capacity, c->num_nodes, c->table,
+            launch(c, st, k_insert_map, dim3((unsigned)bgl::ceil_div(eff, MAP_THREADS)),
+                   dim3(MAP_THREADS), ids, miss_pos, n_miss, c->capacity, c->num_nodes, c->table,
                    c->num_buckets - 1, c->slot_to_node, c->slot_to_entry, c->dev, par, 1);
         } else {
             hipLaunchKernelGGL(k_advance_tail, dim3(1), dim3(64), 0, st, c->dev, n_miss, par);
@@ -1843,8 +1843,8 @@ try {
     if (eff > 0) {
         {
             Prof p(c, BGL_STAGE_INSERT_MAP, st);
-            launch(c, st, k_insert_map, dim3((unsigned)bgl::ceil_div(eff * BUCKET, COPY_THREADS)),
-                   dim3(COPY_THREADS), ids, miss_pos, n_miss, c->capacity, c->num_nodes, c->table,
+            launch(c, st, k_insert_map, dim3((unsigned)bgl::ceil_div(eff, MAP_THREADS)),
+                   dim3(MAP_THREADS), ids, miss_pos, n_miss, c->capacity, c->num_nodes, c->table,
                    c->num_buckets - 1, c->slot_to_node, c->slot_to_entry, c->dev, par, 0);
         }
         if (c->fetch_pending && c->fetch_stream != st)
