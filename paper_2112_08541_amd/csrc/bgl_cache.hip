@@ -92,6 +92,7 @@ struct bgl_cache {
     // update's stream when that is not the lookup's main stream).
     hipEvent_t ev_listed = nullptr, ev_miss = nullptr, ev_map = nullptr;
     hipEvent_t ev_ids = nullptr;     // the lists of a lookup are complete (tiered: the missed ids have reached the host)
+    hipEvent_t ev_lists = nullptr;   // the same for this cache's own miss fetch on the side stream
     hipStream_t last_main = nullptr, fetch_stream = nullptr, map_stream = nullptr;
     bool fetch_pending = false;      // ev_miss marks a miss fetch that later work may have to wait for
     bool fetch_reads_caller_lists = true;  // that fetch reads the caller's miss_pos (not the library's copy)
@@ -381,6 +382,16 @@ constexpr int COPY_UNROLL = 4;  // (the kernels name the four chunks of a lane b
 // lookup, and with it the packing of its rows, starts late.
 constexpr int FETCH_BLOCKS = 64;
 constexpr int RING_FETCH_BLOCKS = 32;
+// The overlapped loop's small batches (write-through mode: the next batch's sampling and the map update
+// run beside the fetch): the bytes a lookup asks for at most, and the workgroups.  Every host read in
+// flight beyond what the link needs delays the other kernels' HBM reads (with 64 workgroups the map
+// update of 315 K rows took 700 us beside the fetch, with 24 it took 85), and a small batch is bound by
+// those kernels' launches as much as by the link.  Microseconds per batch with 8 / 16 / 24 / 64
+// workgroups: 2.6 MB asked 106 / 112 / 121 / 124; 4.2 MB 160 / 141 / 155 / 164; 8.4 MB 278 / 228 / 232 /
+// 246; 16.8 MB 517 / 404 / 406 / 412.  A larger batch is bound by the fetch alone, which takes 7 % longer
+// with 16 workgroups (3,270 against 3,055 us at 128 MB of misses).
+constexpr int64_t SMALL_LOOKUP_BYTES = 16 << 20;
+constexpr int SMALL_FETCH_BLOCKS = 16;
 // Tiered lookup: rows the host threads copy per chunk before that chunk's fetch is launched.
 constexpr int64_t TIER_CHUNK_ROWS = 49152;
 constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
@@ -1066,8 +1077,10 @@ try {
 #undef TRY_ALLOC
     if (hipEventCreateWithFlags(&c->ev_listed, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_miss, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_map, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_ids, hipEventDisableTiming) != hipSuccess) {
+        hipEventCreateWithFlags(&c->ev_ids, hipEventDisableTiming) != hipSuccess ||
+        // only this library's kernels on this device wait for these two: no release to the system
+        hipEventCreateWithFlags(&c->ev_lists, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_map, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
         bgl::set_error("stream/event creation failed");
         return fail(BGL_EHIP);
     }
@@ -1093,6 +1106,7 @@ try {
     if (c->ev_miss) (void)hipEventDestroy(c->ev_miss);
     if (c->ev_map) (void)hipEventDestroy(c->ev_map);
     if (c->ev_ids) (void)hipEventDestroy(c->ev_ids);
+    if (c->ev_lists) (void)hipEventDestroy(c->ev_lists);
     if (c->own_side) (void)hipStreamDestroy(c->own_side);
     (void)hipFree(c->buffer);
     (void)hipFree(c->table);
@@ -1130,7 +1144,7 @@ struct LookupLists {
 int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, int32_t *out_slot,
                  int32_t *miss_pos, int64_t *n_hit_dev, hipStream_t ms, hipStream_t ls, bgl_host_tier *tier,
                  const int32_t **mpos_used, int *gen_used, const LookupLists *fixed = nullptr,
-                 const int32_t **src_of_used = nullptr)
+                 const int32_t **src_of_used = nullptr, bool record_lists = false)
 {
     const bool early = ls != ms;
     const int gen = (int)(c->lookup_calls & 1);  // which copy of the per-call device state this call owns
@@ -1231,6 +1245,7 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
         if (rc != BGL_OK) return rc;
     }
     if (tier || early) BGL_HIP(hipEventRecord(c->ev_ids, ls));  // the lists are complete
+    if (record_lists) BGL_HIP(hipEventRecord(c->ev_lists, ls));
     if (early) {
         // the hit gather reads rows the previous fetch may still be writing, and needs the lists
         if (c->fetch_pending && c->fetch_stream != ms) BGL_HIP(hipStreamWaitEvent(ms, c->ev_miss, 0));
@@ -1248,10 +1263,6 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
                    reinterpret_cast<uint4 *>(out_rows), c->dev);
         });
     }
-    // The miss fetch starts once the hit gather is done: host-link reads
-    // queued in the memory pipeline would otherwise stall the gather's HBM
-    // reads, and the fetch (milliseconds) loses nothing by starting a few
-    // tens of microseconds later.
     BGL_HIP(hipEventRecord(c->ev_listed, ms));
     return BGL_OK;
 }
@@ -1319,10 +1330,18 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
     hipStream_t ls = early ? static_cast<hipStream_t>(lookup_stream) : ms;
     const int32_t *mpos = nullptr;
     int gen = 0;
-    rc = lookup_phase(c, ids, n, out_rows, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, fixed);
+    // On a stream of its own the miss fetch starts once the hit gather is done: its host reads would hold
+    // up the gather's HBM reads (428,377 ids, three quarters of them missed: gather 20 -> 140 us), and a
+    // fetch of milliseconds loses nothing by waiting for it.  A cache that can hold every node misses a
+    // node once: there the fetch starts as soon as the lists are there, beside the gather, so that the
+    // FIFO update finds its (mostly empty) work done when the gather ends instead of waiting for two more
+    // hand-overs between streams.  Lookup + update of 302,709 resident ids of 1,024 bytes: 183 / 169 us.
+    // (Write-through mode: the fetch overwrites rows that the gather may have to read.)
+    const bool beside = n > 0 && ss != ms && !c->write_through && c->capacity >= c->num_nodes;
+    rc = lookup_phase(c, ids, n, out_rows, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, fixed, nullptr, beside);
     if (rc != BGL_OK) return rc;
     if (n > 0) {
-        if (ss != ms) BGL_HIP(hipStreamWaitEvent(ss, c->ev_listed, 0));
+        if (ss != ms) BGL_HIP(hipStreamWaitEvent(ss, beside ? c->ev_lists : c->ev_listed, 0));
         {
             Prof p(c, BGL_STAGE_FETCH_MISS, ss);
             // The small grid and the dealing of whole rows to wavefronts are for the host link only; an
@@ -1332,8 +1351,9 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
             const uint4 *features = reinterpret_cast<const uint4 *>(c->features);
             uint4 *out = reinterpret_cast<uint4 *>(out_rows), *buffer = reinterpret_cast<uint4 *>(c->buffer);
             if (!c->features_in_hbm && q <= kWave) {
+                const bool few = c->write_through && n * c->row_bytes <= SMALL_LOOKUP_BYTES;
                 const int64_t rows_per_block = (int64_t)(COPY_THREADS / kWave) * COPY_UNROLL * (kWave / q);
-                const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, rows_per_block), FETCH_BLOCKS);
+                const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, rows_per_block), few ? SMALL_FETCH_BLOCKS : FETCH_BLOCKS);
                 launch(c, ss, c->write_through ? k_fetch_link<true> : k_fetch_link<false>, dim3(blocks), dim3(COPY_THREADS), mpos, ids,
                        q, c->num_nodes, features, out, c->dev, buffer, c->capacity, c->rows, par, gen);
             } else {

@@ -327,6 +327,19 @@ def test_cache_misses_in_place_by_row_width(B, torch_mod, row_bytes, write_throu
     run_cache_stream(B, torch_mod, feats, 7_001, batches, write_through=write_through)
 
 
+@pytest.mark.parametrize("spare,over", [(0, 0), (0, -1), (500, 3)])
+@pytest.mark.parametrize("side", [True, False])
+@pytest.mark.parametrize("device_n_miss", [True, False])
+def test_cache_that_can_hold_every_node(B, torch_mod, spare, over, side, device_n_miss):
+    """With capacity >= num_nodes the miss fetch runs beside the hit gather on its own stream (one row
+    less: behind it).  Cold, mixed and all-hit batches, each stream held up in turn."""
+    rng = np.random.default_rng(7 + over)
+    N = 9_000
+    feats = rng.integers(0, 256, (N, 400)).astype(np.uint8)
+    batches = [rng.permutation(N)[:n].astype(np.int32) for n in (4000, 4000, 1, 8999, 9000, 2500, 9000)]
+    run_cache_stream(B, torch_mod, feats, N + over, batches, device_n_miss=device_n_miss, side=side, spare=spare)
+
+
 @pytest.mark.parametrize("early", ["own", "with_insert", "alternate"])
 @pytest.mark.parametrize("side", [True, False])
 def test_cache_early_lookup(B, torch_mod, early, side):
