@@ -235,8 +235,9 @@ struct Draw {
     uint32_t u;      // the neighbor in this slot
     bool active, valid;
 
+    // node: frontier[p / G], which the caller has read beside n_dst
     __device__ __forceinline__ Draw(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                    const int32_t *__restrict__ frontier, uint32_t p, int n_dst, int fanout, uint64_t h0)
+                                    int32_t node, uint32_t p, int n_dst, int fanout, uint64_t h0)
     {
         i = (int)(p / G);
         s = (int)(p & (G - 1));
@@ -246,7 +247,7 @@ struct Draw {
         int64_t lo = 0, d = 0;
         v = 0;
         if (active) {
-            v = (uint32_t)frontier[i];
+            v = (uint32_t)node;
             // both ends of the row with one read (the pair is only 4 or 8 bytes aligned)
             typedef RP Ends __attribute__((ext_vector_type(2), aligned(sizeof(RP))));
             const Ends ends = *reinterpret_cast<const Ends *>(row_ptr + v);
@@ -290,11 +291,13 @@ __global__ __launch_bounds__(TILE) void k_sample_direct(
 {
     __shared__ int sh_scan[TILE / kWave];
     __shared__ uint32_t sh_first[2 * TILE], sh_id[TILE];
-    const int n_dst = cnt[hop];
     const uint32_t p = blockIdx.x * TILE + threadIdx.x;
+    // (the grid ends less than a tile beyond the frontier's bound, and other arrays of the workspace follow it)
+    const int32_t node = frontier[p / G];
+    const int n_dst = cnt[hop];
     if ((int64_t)blockIdx.x * TILE >= (int64_t)n_dst * G) return;  // whole workgroup
     sh_first[threadIdx.x] = sh_first[threadIdx.x + TILE] = EMPTY32;
-    const Draw<G, RP> d(row_ptr, col, frontier, p, n_dst, fanout, h0);
+    const Draw<G, RP> d(row_ptr, col, node, p, n_dst, fanout, h0);
     const uint32_t seen = d.valid ? __hip_atomic_load(&tab[d.u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     if (enter_frontier && d.active && d.s == 0) atomicMin(&tab[d.v], (uint32_t)d.i);
     slotidx[p] = d.valid ? (int32_t)d.u : -1;
@@ -329,12 +332,14 @@ __global__ __launch_bounds__(TILE) void k_sample_insert(
     __shared__ int32_t sh_gs[2 * TILE];
     __shared__ int sh_scan[TILE / kWave];
 
-    const int n_dst = cnt[hop];
     const uint32_t p = blockIdx.x * TILE + threadIdx.x;
+    // (the grid ends less than a tile beyond the frontier's bound, and other arrays of the workspace follow it)
+    const int32_t node = frontier[p / G];
+    const int n_dst = cnt[hop];
     if ((int64_t)blockIdx.x * TILE >= (int64_t)n_dst * G) return;  // whole workgroup
 
     for (int i = threadIdx.x; i < 2 * TILE; i += TILE) sh_tab[i] = EMPTY64;
-    const Draw<G, RP> d(row_ptr, col, frontier, p, n_dst, fanout, h0);
+    const Draw<G, RP> d(row_ptr, col, node, p, n_dst, fanout, h0);
     if (enter_frontier && d.active && d.s == 0) (void)table_insert_min(tab, mask, d.v, (uint32_t)d.i, cnt);
     // per-node counts -> row starts inside this tile, tile total
     int total;
@@ -360,37 +365,47 @@ struct Shares {
 
 // Which positions introduced a new id?  A bit per position, the number of bits before every 64
 // positions inside the share, the share's total; and the share's number of sampled neighbors.
-template <bool DIRECT>
+// ONE: the stage's bound is at most SHARES tiles, a share is a tile: its entries are read beside the
+// stage's size (a workgroup beyond the stage's real end reads what earlier calls left there, or the
+// map entry that is the nearest valid one, and drops it).
+template <bool DIRECT, bool ONE>
 __global__ __launch_bounds__(TILE) void k_mark(const int32_t *__restrict__ cnt, int stage, int logG, int32_t num_seeds,
-                                               const void *tab, const int32_t *__restrict__ slotidx, uint64_t *bits,
-                                               int32_t *before, const int32_t *__restrict__ cbs, int32_t *fsum, int32_t *csum)
+                                               const void *tab, uint32_t tab_entries, const int32_t *__restrict__ slotidx,
+                                               uint64_t *bits, int32_t *before, const int32_t *__restrict__ cbs, int32_t *fsum,
+                                               int32_t *csum)
 {
     constexpr int NW = TILE / kWave;
-    __shared__ int sh_pop[MARK_TILES][NW];
+    constexpr int TILES = ONE ? 1 : MARK_TILES;
+    __shared__ int sh_pop[TILES][NW];
     __shared__ int sh_scan[NW];
+    int32_t gs[TILES];
+    uint32_t val[TILES];
+    if constexpr (ONE) {
+        gs[0] = slotidx[(int64_t)blockIdx.x * TILE + threadIdx.x];
+        val[0] = map_value<DIRECT>(tab, (int32_t)min((uint32_t)gs[0], tab_entries - 1));
+    }
     const Shares sh(stage == 0 ? (int64_t)num_seeds : (int64_t)cnt[stage - 1] << logG);
-    const int64_t t0 = sh.first_tile(blockIdx.x), t1 = sh.end_tile(blockIdx.x);
+    const int64_t t0 = ONE ? blockIdx.x : sh.first_tile(blockIdx.x), t1 = ONE ? min(t0 + 1, sh.tiles) : sh.end_tile(blockIdx.x);
     if (t0 >= t1) return;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     int carry = 0;
-    for (int64_t t = t0; t < t1; t += MARK_TILES) {
-        int32_t gs[MARK_TILES];
-        uint32_t val[MARK_TILES];
-        uint64_t b[MARK_TILES];
-        // tiles beyond the share's end read its last tile again and drop it
+    for (int64_t t = t0; t < t1; t += TILES) {
+        uint64_t b[TILES];
+        if constexpr (!ONE) {  // tiles beyond the share's end read its last tile again and drop it
 #pragma unroll
-        for (int k = 0; k < MARK_TILES; ++k) gs[k] = slotidx[min(t + k, t1 - 1) * TILE + threadIdx.x];
+            for (int k = 0; k < TILES; ++k) gs[k] = slotidx[min(t + k, t1 - 1) * TILE + threadIdx.x];
 #pragma unroll
-        for (int k = 0; k < MARK_TILES; ++k) val[k] = map_value<DIRECT>(tab, max(gs[k], 0));
+            for (int k = 0; k < TILES; ++k) val[k] = map_value<DIRECT>(tab, max(gs[k], 0));
+        }
 #pragma unroll
-        for (int k = 0; k < MARK_TILES; ++k) {
+        for (int k = 0; k < TILES; ++k) {
             const int64_t p = (t + k) * TILE + threadIdx.x;
             b[k] = __ballot(t + k < t1 && p < sh.positions && gs[k] >= 0 && val[k] == (TENT | (uint32_t)p));
             if (lane == 0) sh_pop[k][w] = __popcll(b[k]);
         }
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < MARK_TILES; ++k) {
+        for (int k = 0; k < TILES; ++k) {
             int mine = 0, all = 0;
 #pragma unroll
             for (int x = 0; x < NW; ++x) {
@@ -404,13 +419,17 @@ __global__ __launch_bounds__(TILE) void k_mark(const int32_t *__restrict__ cnt, 
             }
             carry += all;
         }
-        __syncthreads();
+        if constexpr (!ONE) __syncthreads();
     }
-    int edges = 0;
-    if (stage > 0)
-        for (int64_t t = t0 + threadIdx.x; t < t1; t += TILE) edges += cbs[t];
-    int total;
-    (void)block_excl_scan<TILE>(edges, sh_scan, total);
+    int total = 0;
+    if constexpr (ONE) {
+        if (stage > 0 && threadIdx.x == 0) total = cbs[t0];
+    } else {
+        int edges = 0;
+        if (stage > 0)
+            for (int64_t t = t0 + threadIdx.x; t < t1; t += TILE) edges += cbs[t];
+        (void)block_excl_scan<TILE>(edges, sh_scan, total);
+    }
     if (threadIdx.x == 0) {
         fsum[blockIdx.x] = carry;
         csum[blockIdx.x] = total;
@@ -419,10 +438,11 @@ __global__ __launch_bounds__(TILE) void k_mark(const int32_t *__restrict__ cnt, 
 
 // Local ids, frontier append, CSR block.  Every workgroup scans the shares' totals in LDS; the first
 // one publishes the stage's sizes and, after the last hop, stores all counts into the caller's
-// page-locked copy.  last: nobody looks the hop's new ids up any more.
-template <bool DIRECT>
+// page-locked copy.  last: nobody looks the hop's new ids up any more.  ONE: as in k_mark.
+template <bool DIRECT, bool ONE>
 __global__ __launch_bounds__(TILE) void k_finalize(int32_t *cnt, int stage, int logG, int32_t num_seeds, void *tab,
-                                                   const int32_t *__restrict__ slotidx, const uint64_t *__restrict__ bits,
+                                                   uint32_t tab_entries, const int32_t *__restrict__ slotidx,
+                                                   const uint64_t *__restrict__ bits,
                                                    const int32_t *__restrict__ before, const int32_t *__restrict__ fsum,
                                                    const int32_t *__restrict__ csum, const int32_t *__restrict__ cbs,
                                                    const int32_t *__restrict__ lrow, int32_t *frontier,
@@ -431,14 +451,35 @@ __global__ __launch_bounds__(TILE) void k_finalize(int32_t *cnt, int stage, int 
     static_assert(SHARES == 2 * TILE, "two totals per thread");
     __shared__ int sh_scan[TILE / kWave];
     __shared__ int32_t sh_f[SHARES], sh_c[SHARES];
+    const int t = threadIdx.x, lane = threadIdx.x & (kWave - 1);
+    // what position p needs: its entry, its word of bits and the bits before it, its node's row start
+    struct Position {
+        int32_t gs, before, row;
+        uint64_t own;
+        uint32_t val;
+    };
+    auto read = [&](int64_t p) {
+        Position x;
+        x.gs = slotidx[p];
+        x.own = bits[p / kWave];
+        x.before = before[p / kWave];
+        x.row = stage > 0 ? lrow[p >> logG] : 0;
+        return x;
+    };
+    Position x;
+    if constexpr (ONE) {  // (the last tile may end a little beyond lrow's bound: the tile counts follow it)
+        x = read((int64_t)blockIdx.x * TILE + t);
+        x.val = map_value<DIRECT>(tab, (int32_t)min((uint32_t)x.gs, tab_entries - 1));
+    }
+    int f0 = fsum[2 * t], f1 = fsum[2 * t + 1], c0 = csum[2 * t], c1 = csum[2 * t + 1];
     const int n_dst = stage == 0 ? 0 : cnt[stage - 1];
     const Shares sh(stage == 0 ? (int64_t)num_seeds : (int64_t)n_dst << logG);
     // (whole workgroups; the one that publishes the sizes stays, also for an empty stage)
     if ((int)blockIdx.x >= sh.count() && blockIdx.x > 0) return;
     {
-        const int n = sh.count(), t = threadIdx.x;
-        const int f0 = 2 * t < n ? fsum[2 * t] : 0, f1 = 2 * t + 1 < n ? fsum[2 * t + 1] : 0;
-        const int c0 = 2 * t < n ? csum[2 * t] : 0, c1 = 2 * t + 1 < n ? csum[2 * t + 1] : 0;
+        const int n = sh.count();
+        if (2 * t >= n) f0 = c0 = 0;
+        if (2 * t + 1 >= n) f1 = c1 = 0;
         int tf, tc;
         const int ef = block_excl_scan<TILE>(f0 + f1, sh_scan, tf);
         const int ec = block_excl_scan<TILE>(c0 + c1, sh_scan, tc);
@@ -460,29 +501,28 @@ __global__ __launch_bounds__(TILE) void k_finalize(int32_t *cnt, int stage, int 
         __syncthreads();
     }
     int edges = sh_c[blockIdx.x];
-    for (int64_t tile = sh.first_tile(blockIdx.x); tile < sh.end_tile(blockIdx.x); ++tile) {
-        const int64_t p64 = tile * TILE + threadIdx.x;
+    const int64_t t0 = ONE ? blockIdx.x : sh.first_tile(blockIdx.x), t1 = ONE ? min(t0 + 1, sh.tiles) : sh.end_tile(blockIdx.x);
+    for (int64_t tile = t0; tile < t1; ++tile) {
+        const int64_t p64 = tile * TILE + t;
         if (p64 < sh.positions) {
             const uint32_t p = (uint32_t)p64;
-            const int gs = slotidx[p];
-            const uint64_t own = bits[p / kWave];
-            const int lane = p & (kWave - 1);
+            if constexpr (!ONE) x = read(p64);
             int local = -1;
-            if ((own >> lane) & 1ull) {
-                local = n_dst + sh_f[blockIdx.x] + before[p / kWave] + __popcll(own & ((1ull << lane) - 1ull));
+            if ((x.own >> lane) & 1ull) {
+                local = n_dst + sh_f[blockIdx.x] + x.before + __popcll(x.own & ((1ull << lane) - 1ull));
                 if constexpr (DIRECT) {
-                    frontier[local] = gs;
-                    if (!last) __hip_atomic_store(static_cast<uint32_t *>(tab) + gs, (uint32_t)local, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    frontier[local] = x.gs;
+                    if (!last) __hip_atomic_store(static_cast<uint32_t *>(tab) + x.gs, (uint32_t)local, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 } else {
-                    uint32_t *e = reinterpret_cast<uint32_t *>(static_cast<uint64_t *>(tab) + gs);
+                    uint32_t *e = reinterpret_cast<uint32_t *>(static_cast<uint64_t *>(tab) + x.gs);
                     frontier[local] = (int32_t)e[1];
                     // Other positions of the same id may read the entry while it
                     // turns from "first position" into "local id"; both forms
                     // decode to the same local id.
                     if (!last) __hip_atomic_store(e, (uint32_t)local, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
-            } else if (gs >= 0) {
-                const uint32_t val = map_value<DIRECT>(tab, gs);
+            } else if (x.gs >= 0) {
+                const uint32_t val = ONE ? x.val : map_value<DIRECT>(tab, x.gs);
                 if (val & TENT) {
                     const uint32_t q = val & ~TENT;  // first position of this id
                     local = n_dst + sh_f[(q / TILE) >> sh.log] + before[q / kWave] +
@@ -494,12 +534,12 @@ __global__ __launch_bounds__(TILE) void k_finalize(int32_t *cnt, int stage, int 
             if (stage > 0) {
                 const int i = (int)(p >> logG);
                 const int s = (int)(p & ((1u << logG) - 1));
-                const int base = edges + lrow[i];
+                const int base = edges + x.row;
                 if (s == 0) row_ptr_h[i] = base;
-                if (gs >= 0) col_local[base + s] = local;
+                if (x.gs >= 0) col_local[base + s] = local;
             }
         }
-        if (stage > 0) edges += cbs[tile];
+        if (!ONE && stage > 0) edges += cbs[tile];
     }
 }
 
@@ -676,11 +716,16 @@ try {
     // mark and finalize of one stage
     auto place = [&](int stage, int logG, int64_t positions, int32_t *row_ptr_h, int32_t *col_local, bool last) {
         const int blocks = (int)std::min<int64_t>(bgl::ceil_div(positions, TILE), SHARES);
-        hipLaunchKernelGGL((L.direct ? k_mark<true> : k_mark<false>), dim3(blocks), dim3(TILE), 0, st, cnt, stage, logG, num_seeds,
-                           tab, slotidx, bits, before, cbs, fsum, csum);
-        hipLaunchKernelGGL((L.direct ? k_finalize<true> : k_finalize<false>), dim3(blocks), dim3(TILE), 0, st, cnt, stage, logG,
-                           num_seeds, tab, slotidx, bits, before, fsum, csum, cbs, lrow, frontier, row_ptr_h, col_local,
-                           last ? 1 : 0, last ? counts_dev : nullptr);
+        const bool one = bgl::ceil_div(positions, TILE) <= SHARES;
+        const uint32_t entries = (uint32_t)std::min<int64_t>(L.table_entries, INT32_MAX);
+        auto mark = L.direct ? (one ? k_mark<true, true> : k_mark<true, false>) : (one ? k_mark<false, true> : k_mark<false, false>);
+        auto finalize = L.direct ? (one ? k_finalize<true, true> : k_finalize<true, false>)
+                                 : (one ? k_finalize<false, true> : k_finalize<false, false>);
+        hipLaunchKernelGGL(mark, dim3(blocks), dim3(TILE), 0, st, cnt, stage, logG, num_seeds, tab, entries,
+                           slotidx, bits, before, cbs, fsum, csum);
+        hipLaunchKernelGGL(finalize, dim3(blocks), dim3(TILE), 0, st, cnt, stage, logG, num_seeds, tab, entries,
+                           slotidx, bits, before, fsum, csum, cbs, lrow, frontier, row_ptr_h, col_local, last ? 1 : 0,
+                           last ? counts_dev : nullptr);
     };
     const bool few_seeds = num_seeds <= SEEDS_LDS;
     const int64_t chunks = (int64_t)(L.table_bytes / 16);
