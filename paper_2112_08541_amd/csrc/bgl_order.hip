@@ -21,9 +21,9 @@
 // a power law, and with a fixed number of lanes per node the longest row sets the
 // pace (16 lanes on a row of 20,000 edges: 1.9 ms for one level).  Measured, two
 // sequences on 2.45 M nodes / 122 M edges: 30.2 ms with 16 lanes per node and a
-// radix sort per level, 6.7 ms now (k_expand 60 us per 8 M edges, bound by the
+// radix sort per level, 5.8 ms now (k_expand 52 us per 8 M edges, bound by the
 // random reads of the visited bitmap and the keys); five sequences on 100,000
-// nodes / 1 M edges, where launches and host round trips count: 19.5 and 2.2 ms.
+// nodes / 1 M edges, where launches and host round trips count: 19.5 and 1.8 ms.
 //   A level is
 // handled in windows of at most WINDOW edges, which bounds the lists whatever the
 // graph's size; a target reached in one window is visited in the next.
@@ -45,11 +45,12 @@ using namespace bgl;
 
 constexpr int BT = 256;
 constexpr int BW = BT / kWave;               // wavefronts per workgroup
-constexpr int BLOCKS = 1024;                 // workgroups of a step's kernels (those without a share leave at once)
+constexpr int BLOCKS = 2048;                 // workgroups of a step's kernels (those without a share leave at once)
 constexpr int WAVES = BLOCKS * BW;
 constexpr int WTILE = 4 * kWave;             // edges a wavefront handles at a time, four per lane
 constexpr int64_t WINDOW = 1 << 23;          // edges per step at most
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
+constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
 constexpr uint32_t NO_KEY = ~0u;
 
 // What a step finds.  Step s reads copy s & 1; its last kernel writes the other.
@@ -69,6 +70,14 @@ struct OrderDev {
     Step step[2];
     int open_min;   // restart: smallest unvisited node that has an unvisited out-neighbor
     int status;
+};
+
+// What the host sees of a traversal (page-locked memory).
+struct Progress {
+    uint32_t step;    // the last step that has begun to append, from 1
+    uint32_t done;    // the traversal has ended
+    int32_t seq_len;  // then: training nodes recorded
+    int32_t status;
 };
 
 // One level's nodes that have out-edges, in queue order.
@@ -110,7 +119,7 @@ __global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uin
 // count as visited), the root's row as the first level.
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, int32_t root, uint32_t *visited,
-                                              int64_t words, uint32_t *key, int64_t num_nodes,
+                                              uint32_t *closed, int64_t words, uint32_t *key, int64_t num_nodes,
                                               const uint32_t *__restrict__ train, Frontier f, int32_t *seq, OrderDev *dev)
 {
     const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x, stride = (int64_t)gridDim.x * BT;
@@ -120,6 +129,7 @@ __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, in
         if (base + 32 > num_nodes) v = num_nodes > base ? ~0u << (uint32_t)(num_nodes - base) : ~0u;
         if (w == root >> 5) v |= 1u << (root & 31);
         visited[w] = v;
+        closed[w] = 0;
     }
     for (int64_t i = t; i < num_nodes; i += stride) key[i] = NO_KEY;
     if (t == 0) {
@@ -154,12 +164,16 @@ __device__ __forceinline__ uint32_t rows_before(const unsigned long long *off, u
 }
 
 // The smallest unvisited node with an unvisited out-neighbor other than itself.  A wavefront takes
-// 64 ids at a time, ascending, 16 lanes walk one node's row; nobody goes on beyond the smallest
-// open node found so far.
+// 64 ids at a time, ascending, 16 lanes walk one node's row, eight reads in flight per lane; nobody
+// goes on beyond the smallest open node found so far.  A node found closed stays closed (the visited
+// set only grows) and is not looked at again: a graph has a restart for every component that no other
+// one leads to, and some rows of the nodes in between are long (2.45 M nodes / 122 M edges, 110 restarts
+// per traversal: 130 to 300 us a search that walks them again each time with one read per lane, 30 to 55
+// now; five such traversals 118 -> 48 ms, 261 ms with the searches and levels this file had before).
 template <typename RP>
 __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                            const uint32_t *__restrict__ visited, int64_t num_nodes, int64_t scan_lo,
-                                            OrderDev *dev)
+                                            const uint32_t *__restrict__ visited, uint32_t *closed, int64_t num_nodes,
+                                            int64_t scan_lo, OrderDev *dev)
 {
     if (blockIdx.x >= SEARCH_BLOCKS) return;
     const int lane = threadIdx.x & (kWave - 1), l = lane & 15, gshift = lane & ~15;
@@ -167,38 +181,45 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
     for (int64_t c = scan_lo / 64 + wave; c * 64 < num_nodes; c += SEARCH_BLOCKS * BW) {
         const int found = __hip_atomic_load(&dev->open_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (c * 64 >= __builtin_amdgcn_readfirstlane(found)) return;
-        // this group's 16 ids (the bitmap ends with a whole number of 64-bit pairs)
-        uint32_t unv = ~(visited[c * 2 + (lane >> 5)] >> (gshift & 16)) & 0xffffu;
-        for (; unv; unv &= unv - 1) {
-            const int64_t v = c * 64 + gshift + (__ffs(unv) - 1);
+        // this group's 16 ids (the bitmaps end with a whole number of 64-bit pairs)
+        const int64_t word = c * 2 + (lane >> 5);
+        uint32_t look = ~((visited[word] | closed[word]) >> (gshift & 16)) & 0xffffu;
+        uint32_t shut = 0;
+        bool open = false;
+        for (; look && !open; look &= look - 1) {
+            const int64_t v = c * 64 + gshift + (__ffs(look) - 1);
             const int64_t hi = (int64_t)row_ptr[v + 1];
-            bool open = false;
-            for (int64_t e = (int64_t)row_ptr[v]; e < hi && !open; e += 16) {
+            for (int64_t e = (int64_t)row_ptr[v]; e < hi && !open; e += 128) {
+                uint32_t u[8], seen[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) u[j] = (uint32_t)col[min(e + j * 16 + l, hi - 1)];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) seen[j] = visited[u[j] >> 5] >> (u[j] & 31);
                 bool mine = false;
-                if (e + l < hi) {
-                    const uint32_t u = (uint32_t)col[e + l];
-                    mine = (int64_t)u != v && !test_bit(visited, u);
-                }
+#pragma unroll
+                for (int j = 0; j < 8; ++j) mine |= (int64_t)u[j] != v && !(seen[j] & 1u);
                 open = ((__ballot(mine) >> gshift) & 0xffffull) != 0;
             }
             if (open) {
                 if (l == 0) atomicMin(&dev->open_min, (int)v);
-                break;
+            } else {
+                shut |= look & (0u - look);
             }
         }
+        if (shut && l == 0) atomicOr(&closed[word], shut << (gshift & 16));
     }
 }
 
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                               const uint32_t *__restrict__ visited, int64_t num_nodes, uint32_t *key,
-                                               Frontier f0, Frontier f1, Lists li, OrderDev *dev, int par)
+                                               const uint32_t *__restrict__ visited, uint32_t *closed, int64_t num_nodes,
+                                               uint32_t *key, Frontier f0, Frontier f1, Lists li, OrderDev *dev, int par)
 {
     __shared__ uint32_t sh_start[BW][kWave];  // per wavefront: WTILE bytes, 1 where a row begins
     const Step st = dev->step[par];
     if (st.done) return;
     if (st.rows == 0) {
-        search_open(row_ptr, col, visited, num_nodes, st.scan_lo, dev);
+        search_open(row_ptr, col, visited, closed, num_nodes, st.scan_lo, dev);
         return;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) dev->open_min = INT_MAX;  // for the next restart
@@ -330,21 +351,38 @@ __global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, co
         const bool active = (unsigned long long)wave * per < win;
         const uint32_t lo = active ? wave * per : 0, n = active ? li.n_cand[wave] : 0;
         uint32_t n_win = 0;
-        // first edges move to the front of the wavefront's own list, in order, with what k_append needs of them
-        for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
-            const unsigned long long c = i0 + lane < n ? li.cand[lo + i0 + lane] : 0ull;
-            const uint32_t u = (uint32_t)(c >> 32);
-            const bool win_edge = i0 + lane < n && key[u] == (uint32_t)c;
-            const uint64_t b = __ballot(win_edge);
-            if (win_edge) {
-                const unsigned long long d = (unsigned long long)((int64_t)row_ptr[u + 1] - (int64_t)row_ptr[u]);
-                const unsigned long long tr = test_bit(train, u) ? 1ull : 0ull;
-                li.cand[lo + n_win + __popcll(b & ((1ull << lane) - 1ull))] = tr << 63 | d << 32 | u;
-                n_rows += d > 0;
-                n_edges += d;
-                n_train += (uint32_t)tr;
+        // First edges move to the front of the wavefront's own list, in order, with what k_append needs of
+        // them.  Four groups of 64 candidates at a time: their keys, then their rows, are in flight together.
+        for (uint32_t i0 = 0; i0 < n; i0 += 4 * kWave) {
+            unsigned long long c[4];
+            uint32_t k[4];
+            bool first[4];
+            unsigned long long d[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c[j] = li.cand[lo + min(i0 + j * kWave + lane, n - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k[j] = key[(uint32_t)(c[j] >> 32)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) first[j] = i0 + j * kWave + lane < n && k[j] == (uint32_t)c[j];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t u = (uint32_t)(c[j] >> 32);
+                d[j] = 0;
+                if (first[j])
+                    d[j] = (unsigned long long)((int64_t)row_ptr[u + 1] - (int64_t)row_ptr[u]) |
+                           (unsigned long long)(train[u >> 5] >> (u & 31) & 1u) << 31;
             }
-            n_win += (uint32_t)__popcll(b);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint64_t b = __ballot(first[j]);
+                if (first[j]) {
+                    li.cand[lo + n_win + __popcll(b & ((1ull << lane) - 1ull))] = d[j] << 32 | c[j] >> 32;
+                    n_rows += (d[j] & 0x7fffffffu) > 0;
+                    n_edges += d[j] & 0x7fffffffu;
+                    n_train += (uint32_t)(d[j] >> 31);
+                }
+                n_win += (uint32_t)__popcll(b);
+            }
         }
         n_rows = wave_sum(n_rows);
         n_train = wave_sum(n_train);
@@ -394,7 +432,7 @@ __device__ __forceinline__ void block_sums(const T *totals, uint32_t mine, uint3
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, uint32_t *visited, int64_t words,
                                                const uint32_t *__restrict__ train, Frontier f0, Frontier f1, int32_t *seq,
-                                               Lists li, OrderDev *dev, int par, uint32_t *done_host)
+                                               Lists li, OrderDev *dev, int par, Progress *host, uint32_t step)
 {
     __shared__ uint32_t sh32[2 * BW];
     __shared__ unsigned long long sh64[2 * BW];
@@ -405,6 +443,8 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
         if (blockIdx.x == 0 && threadIdx.x == 0) next = st;
         return;
     }
+    // (the step is under way: the host may enqueue another)
+    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(&host->step, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     uint32_t train_before, train_all;
     if (st.rows == 0) {
@@ -434,7 +474,8 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
             int32_t len = st.seq_len + (int32_t)train_all;
             if (open == INT_MAX) {  // everything that was left was closed
                 next = Step{0, 0, 0, 0, 0, len, st.scan_lo, 0, 1};
-                *done_host = 1;     // page-locked: visible to the host once the stream has passed
+                host->seq_len = len;
+                __hip_atomic_store(&host->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
             } else {
                 const int64_t lo = (int64_t)row_ptr[open], d = (int64_t)row_ptr[open + 1] - lo;
                 f0.off[0] = 0;
@@ -481,42 +522,50 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
     unsigned long long edge = st.next_edges + edges_at;
     int32_t pos = st.seq_len + (int32_t)train_before;
     const uint32_t n = li.n_win[wave], lo = wave * per;
-    for (uint32_t i0 = 0; i0 < n; i0 += kWave) {
-        const bool mine = i0 + lane < n;
-        const unsigned long long c = mine ? li.cand[lo + i0 + lane] : 0ull;
-        const uint32_t u = (uint32_t)c, d = (uint32_t)(c >> 32) & 0x7fffffffu;
-        const uint64_t has_row = __ballot(mine && d > 0), is_train = __ballot(mine && (c >> 63) != 0);
-        const uint64_t below = (1ull << lane) - 1ull;
-        unsigned long long inc = d;  // out-edges of the nodes up to this one
+    for (uint32_t i0 = 0; i0 < n; i0 += 4 * kWave) {  // four groups of 64 at a time, as in k_count
+        unsigned long long c[4];
+        int64_t row_lo[4];
 #pragma unroll
-        for (int s = 1; s < kWave; s <<= 1) {
-            const unsigned long long x = __shfl_up(inc, s, kWave);
-            if (lane >= s) inc += x;
-        }
-        if (mine) {
-            atomicOr(&visited[u >> 5], 1u << (u & 31));
-            if (d > 0) {
-                const uint32_t r = row + (uint32_t)__popcll(has_row & below);
-                f.off[r] = edge + inc - d;
-                f.base[r] = (int64_t)row_ptr[u] - (int64_t)(edge + inc - d);
+        for (int j = 0; j < 4; ++j) c[j] = li.cand[lo + min(i0 + j * kWave + lane, n - 1)];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) row_lo[j] = (int64_t)row_ptr[(uint32_t)c[j]];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool mine = i0 + j * kWave + lane < n;
+            const uint32_t u = (uint32_t)c[j], d = mine ? (uint32_t)(c[j] >> 32) & 0x7fffffffu : 0u;
+            const bool tr = mine && (c[j] >> 63) != 0;
+            const uint64_t has_row = __ballot(d > 0), is_train = __ballot(tr);
+            const uint64_t below = (1ull << lane) - 1ull;
+            unsigned long long inc = d;  // out-edges of the nodes up to this one
+#pragma unroll
+            for (int s = 1; s < kWave; s <<= 1) {
+                const unsigned long long x = __shfl_up(inc, s, kWave);
+                if (lane >= s) inc += x;
             }
-            if (c >> 63) seq[pos + __popcll(is_train & below)] = (int32_t)u;
+            if (mine) {
+                atomicOr(&visited[u >> 5], 1u << (u & 31));
+                if (d > 0) {
+                    const uint32_t r = row + (uint32_t)__popcll(has_row & below);
+                    f.off[r] = edge + inc - d;
+                    f.base[r] = row_lo[j] - (int64_t)(edge + inc - d);
+                }
+                if (tr) seq[pos + __popcll(is_train & below)] = (int32_t)u;
+            }
+            row += (uint32_t)__popcll(has_row);
+            pos += (int32_t)__popcll(is_train);
+            edge += __shfl(inc, kWave - 1, kWave);
         }
-        row += (uint32_t)__popcll(has_row);
-        pos += (int32_t)__popcll(is_train);
-        edge += __shfl(inc, kWave - 1, kWave);
     }
 }
 
 struct OrderWork {
-    uint32_t *visited = nullptr, *train = nullptr, *key = nullptr;
+    uint32_t *visited = nullptr, *closed = nullptr, *train = nullptr, *key = nullptr;
     Frontier f[2];
     Lists li;
     int32_t *seq = nullptr, *train_ids = nullptr;
     OrderDev *dev = nullptr;
-    struct Host { int32_t status; uint32_t done; int32_t seq_len; };
-    Host *host = nullptr;  // page-locked
-    Host *host_dev = nullptr;
+    Progress *host = nullptr;  // page-locked
+    Progress *host_dev = nullptr;
     char *block = nullptr;     // the one device allocation all of the above are carved from
     ~OrderWork()
     {
@@ -540,6 +589,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, O
         };
         total = 0;
         take(w.visited, (size_t)words);
+        take(w.closed, (size_t)words);
         take(w.train, (size_t)words);
         take(w.key, (size_t)N);
         for (int k = 0; k < 2; ++k) {
@@ -563,7 +613,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, O
     BGL_HIP(hipMalloc((void **)&w.block, total));
     at = w.block;
     carve();
-    BGL_HIP(hipHostMalloc((void **)&w.host, sizeof(OrderWork::Host), hipHostMallocDefault));
+    BGL_HIP(hipHostMalloc((void **)&w.host, sizeof(Progress), hipHostMallocDefault));
     BGL_HIP(hipHostGetDevicePointer((void **)&w.host_dev, w.host, 0));
     BGL_HIP(hipMemsetAsync(w.dev, 0, sizeof(OrderDev), st));
     BGL_HIP(hipMemcpyAsync(w.train_ids, train_nodes, num_train * 4, hipMemcpyHostToDevice, st));
@@ -584,29 +634,38 @@ int bfs_sequence(const bgl_graph *g, int64_t root, int64_t num_train, OrderWork 
 {
     const int64_t N = g->num_nodes, words = round_up(ceil_div(N, 32), 2);
     const RP *rp = static_cast<const RP *>(g->row_ptr);
-    w.host->done = 0;
+    w.host->step = w.host->done = 0;
     hipLaunchKernelGGL(k_reset<RP>, dim3((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096)), dim3(BT), 0, st, rp, (int32_t)root,
-                       w.visited, words, w.key, N, w.train, w.f[0], w.seq, w.dev);
-    // The host looks at the end flag once per batch of steps: a look costs a synchronisation, a step
-    // beyond the end three launches that return at once.  Every step visits a node or ends the
-    // traversal or is one of a level's windows.
-    int64_t left = 2 * N + g->num_edges / WINDOW + 4;
-    int par = 0;
-    for (int batch = 8; !*const_cast<volatile uint32_t *>(&w.host->done); batch = std::min(2 * batch, 32)) {
-        if (left <= 0) BGL_FAIL(BGL_EHIP, "the traversal did not end");
-        for (int k = 0; k < batch; ++k, par ^= 1) {
-            hipLaunchKernelGGL(k_expand<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, g->col, w.visited, N, w.key, w.f[0], w.f[1], w.li,
-                               w.dev, par);
-            hipLaunchKernelGGL(k_count<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.key, w.train, w.li, w.dev, par);
-            hipLaunchKernelGGL(k_append<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.train, w.f[0], w.f[1], w.seq,
-                               w.li, w.dev, par, &w.host_dev->done);
-        }
+                       w.visited, w.closed, words, w.key, N, w.train, w.f[0], w.seq, w.dev);
+    // The device says in page-locked words which step it has come to and when the traversal has ended; the
+    // host stays STEPS_AHEAD steps ahead of it, so the queue never runs empty and at most that many steps,
+    // whose launches return at once, are enqueued beyond the end.  (A synchronisation every 8 to 32 steps
+    // instead: 2.2 ms for five sequences of 13 steps on 100,000 nodes, 1.8 now.)  Every step visits a
+    // node or ends the traversal or is one of a level's windows.
+    const int64_t most = 2 * N + g->num_edges / WINDOW + 4;
+    auto word = [](const uint32_t &x) { return __atomic_load_n(&x, __ATOMIC_ACQUIRE); };
+    for (int64_t step = 1; !word(w.host->done); ++step) {
+        if (step > most + STEPS_AHEAD) BGL_FAIL(BGL_EHIP, "the traversal did not end");
+        const int par = (int)((step - 1) & 1);
+        hipLaunchKernelGGL(k_expand<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, g->col, w.visited, w.closed, N, w.key, w.f[0], w.f[1], w.li,
+                           w.dev, par);
+        hipLaunchKernelGGL(k_count<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.key, w.train, w.li, w.dev, par);
+        hipLaunchKernelGGL(k_append<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.train, w.f[0], w.f[1], w.seq,
+                           w.li, w.dev, par, w.host_dev, (uint32_t)step);
         BGL_HIP(hipGetLastError());
-        BGL_HIP(hipStreamSynchronize(st));
-        left -= batch;
+        for (int64_t spins = 1; !word(w.host->done) && (uint32_t)step - word(w.host->step) >= (uint32_t)STEPS_AHEAD; ++spins) {
+            __builtin_ia32_pause();
+            // a stream that has nothing left to do, or has failed, will not come to the step waited for
+            if (spins % 65536 == 0) {
+                const hipError_t e = hipStreamQuery(st);
+                if (e == hipErrorNotReady) { (void)hipGetLastError(); continue; }
+                BGL_HIP(e);
+                if (!word(w.host->done) && (uint32_t)step - word(w.host->step) >= (uint32_t)STEPS_AHEAD)
+                    BGL_FAIL(BGL_EHIP, "the traversal stopped at step %u of %lld", word(w.host->step), (long long)step);
+            }
+        }
     }
-    BGL_HIP(hipMemcpyAsync(&w.host->seq_len, &w.dev->step[par].seq_len, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    BGL_HIP(hipStreamSynchronize(st));
+    BGL_HIP(hipStreamSynchronize(st));  // the steps beyond the end; w.host may be written anew
     if (w.host->seq_len != num_train)
         BGL_FAIL(BGL_EHIP, "the traversal recorded %d of %lld training nodes", w.host->seq_len, (long long)num_train);
     return BGL_OK;

@@ -82,6 +82,42 @@ def test_bfs_sequence_rows_across_wavefront_shares(B, degrees, hub, dtype):
         assert np.array_equal(B.order_bfs_sequence(g, train, root), oracle.bfs_sequence(rp, col, train, root))
 
 
+@pytest.mark.parametrize("length", [1, 127, 128, 129, 700])
+def test_bfs_sequence_restart_search_walks_long_rows(B, length):
+    """Nodes that only a restart reaches, with rows of `length` edges: into the visited set (closed, at
+    once or only after an earlier restart), with the one open edge first, last or in the middle, to
+    themselves, and plain ones between them."""
+    import oracle
+    rng = np.random.default_rng(length)
+    N, A = 2_000, 600
+    adj = [[(v + 1) % A, int(rng.integers(0, A))] for v in range(A)] + [[] for _ in range(N - A)]
+    for v in range(A, N):
+        kind = v % 7
+        row = rng.integers(0, A, length).tolist()
+        if kind == 1:
+            row[-1] = v                                        # a loop: closed
+        elif kind in (2, 3, 4):
+            row[(0, length // 2, length - 1)[kind - 2]] = int(rng.integers(A, N))
+        elif kind == 5:
+            row = []
+        adj[v] = row
+    rp = np.zeros(N + 1, dtype=np.int32)
+    rp[1:] = np.cumsum([len(a) for a in adj])
+    col = np.array([u for a in adj for u in a], dtype=np.int32)
+    perm = rng.permutation(N)                                  # ids in no order
+    src = np.repeat(np.arange(N), np.diff(rp))
+    order = np.argsort(perm[src], kind="stable")
+    deg = np.zeros(N, dtype=np.int64)
+    deg[perm] = np.diff(rp)
+    rp2 = np.zeros(N + 1, dtype=np.int32)
+    rp2[1:] = np.cumsum(deg)
+    col2 = perm[col[order]].astype(np.int32)
+    g = B.Graph(rp2, col2)
+    train = rng.choice(N, N // 2, replace=False)
+    for root in (int(perm[0]), int(perm[N - 1])):
+        assert np.array_equal(B.order_bfs_sequence(g, train, root), oracle.bfs_sequence(rp2, col2, train, root))
+
+
 def test_bfs_sequence_chain_of_open_components(B):
     """Several multi-node components that are only reachable by restarts, interleaved by id
     with closed singletons (the bulk restart must keep the sequential order)."""
