@@ -395,14 +395,40 @@ constexpr int SMALL_FETCH_BLOCKS = 16;
 // Tiered lookup: rows the host threads copy per chunk before that chunk's fetch is launched.
 constexpr int64_t TIER_CHUNK_ROWS = 49152;
 constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
+// Hit gather: largest output (of the hits) that is still written with ordinary stores.
+constexpr int64_t GATHER_CACHED_OUTPUT_BYTES = 64ll << 20;
 // Assembled output: largest out_rows of a call that is still written with ordinary stores.
 constexpr int64_t ASSEMBLE_CACHED_OUTPUT_BYTES = 128ll << 20;
+
+// 16-byte accesses that say "not needed again soon" (NT) or nothing.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+template <bool NT>
+__device__ __forceinline__ void st16(uint4 *p, const uint4 &v)
+{
+    if (NT) __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(p));
+    else *p = v;
+}
+template <bool NT>
+__device__ __forceinline__ uint4 ld16(const uint4 *p)
+{
+    if (NT) {
+        const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        return uint4{t.x, t.y, t.z, t.w};
+    }
+    return *p;
+}
 
 // out[i] = the cached row of ids[i] for every hit i (taken from the hit list, which holds the
 // rows' positions in the cache buffer, so the work is proportional to the hits).  Consecutive lanes take consecutive
 // 16-byte chunks of a row, so the loads and stores of one row are contiguous;
 // four independent chunks per lane keep loads in flight.  The grid is sized for
-// n rows; workgroups beyond the hit count leave at once.
+// n rows; workgroups beyond the hit count leave at once.  Output beyond
+// GATHER_CACHED_OUTPUT_BYTES is stored non-temporally: it would not stay in the
+// caches, but pushes the rows being read out of them.  Measured, ordinary /
+// non-temporal stores, every id a hit: 310 MB of 1,024-byte rows 111 / 96 us
+// (6.4 TB/s read and written), 171 MB of 400-byte rows 70 / 60, 120 MB 44 / 40,
+// 90 MB 33 / 30, 60 MB 22 / 21 but 1,024-byte rows 21.4 / 22.0; 45 MB of 400-byte
+// rows between misses (lines written in part) 20.2 / 21.5.
 template <int Q>
 __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
     const int32_t *__restrict__ hit_pos, const int32_t *__restrict__ hit_slot, int q,
@@ -432,10 +458,20 @@ __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
     const uint4 v1 = buffer[(int64_t)s1 * qq + c1];
     const uint4 v2 = buffer[(int64_t)s2 * qq + c2];
     const uint4 v3 = buffer[(int64_t)s3 * qq + c3];
-    out[(int64_t)p0 * qq + c0] = v0;
-    out[(int64_t)p1 * qq + c1] = v1;
-    out[(int64_t)p2 * qq + c2] = v2;
-    out[(int64_t)p3 * qq + c3] = v3;
+    if (total * 16 > GATHER_CACHED_OUTPUT_BYTES) {  // uniform
+        // (the markers keep the compiler from merging the two branches' stores into ordinary ones)
+        asm volatile("; streaming stores");
+        st16<true>(&out[(int64_t)p0 * qq + c0], v0);
+        st16<true>(&out[(int64_t)p1 * qq + c1], v1);
+        st16<true>(&out[(int64_t)p2 * qq + c2], v2);
+        st16<true>(&out[(int64_t)p3 * qq + c3], v3);
+        asm volatile("; end of streaming stores");
+    } else {
+        out[(int64_t)p0 * qq + c0] = v0;
+        out[(int64_t)p1 * qq + c1] = v1;
+        out[(int64_t)p2 * qq + c2] = v2;
+        out[(int64_t)p3 * qq + c3] = v3;
+    }
 }
 
 // out[miss_pos[r]] = features[ids[miss_pos[r]]] for every miss r; the loads cross
@@ -557,24 +593,6 @@ __global__ __launch_bounds__(COPY_THREADS) void k_fetch_link(
         m0 = p0; m1 = p1; m2 = p2; m3 = p3;
         i0 = j0; i1 = j1; i2 = j2; i3 = j3;
     }
-}
-
-// 16-byte accesses that say "not needed again soon" (NT) or nothing.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-template <bool NT>
-__device__ __forceinline__ void st16(uint4 *p, const uint4 &v)
-{
-    if (NT) __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(p));
-    else *p = v;
-}
-template <bool NT>
-__device__ __forceinline__ uint4 ld16(const uint4 *p)
-{
-    if (NT) {
-        const u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-        return uint4{t.x, t.y, t.z, t.w};
-    }
-    return *p;
 }
 
 // Tiered lookup: out[miss_pos[r]] = rows[(first + l) mod ring] for listed misses
