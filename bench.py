@@ -405,7 +405,7 @@ def run_config(cfg, args, torch, np, B, inputs, MinibatchPipeline, want_cpu):
         h2d = measure_h2d_peak(torch)
         result["host_link"] = {
             "kernel": {"staged": "hipMemcpyAsync of the packed rows", "staged_scatter": "hipMemcpyAsync of the packed rows",
-                       "staged_kernel": "k_fetch_rows"}.get(miss_path, "k_fetch_miss"),
+                       "staged_kernel": "k_fetch_rows"}.get(miss_path, "k_fetch_link" if rb <= 1024 else "k_fetch_miss"),
             "achieved": link, "unit": "GB/s",
             "nominal_peak": HOST_LINK_NOMINAL_GBS, "measured_h2d_copy_peak": h2d,
             "frac_of_nominal": link / HOST_LINK_NOMINAL_GBS, "frac_of_measured": link / h2d,
