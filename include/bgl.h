@@ -103,7 +103,8 @@ typedef struct {
     const int32_t *counts;               /* device, BGL_COUNTS_LEN ints */
 } bgl_subgraph_t;
 
-/* Bytes of device workspace bgl_sample_khop needs for these arguments. */
+/* Bytes of device workspace bgl_sample_khop needs for these arguments (up to 2^24 nodes it includes 4 bytes
+ * per node, whatever the batch). */
 int bgl_sample_workspace_bytes(int32_t num_seeds, const int32_t *fanouts, int32_t num_hops,
                                int64_t num_nodes, size_t *bytes);
 

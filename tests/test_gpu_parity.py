@@ -195,6 +195,37 @@ def test_sample_is_deterministic_and_seed_sensitive(B, torch_mod):
     assert not np.array_equal(a["input_nodes"], c["input_nodes"])
 
 
+@pytest.mark.parametrize("pinned", [True, False])
+@pytest.mark.parametrize("num_seeds", [300, 5000])
+def test_sample_counts_reach_page_locked_and_pageable_memory(B, torch_mod, pinned, num_seeds):
+    """counts_host in page-locked memory is stored by the last kernel, any other is copied to behind it;
+    the workspace's earlier contents do not matter."""
+    import ctypes as C
+    import oracle
+    rng = np.random.default_rng(num_seeds)
+    N = 9000
+    rp = np.zeros(N + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(rng.integers(0, 20, N))
+    col = rng.integers(0, N, rp[-1]).astype(np.int32)
+    seeds = rng.integers(0, N, num_seeds).astype(np.int32)
+    fanouts = np.array([6, 4], dtype=np.int32)
+    s = B.Sampler(B.Graph(rp, col), num_seeds, fanouts)
+    s.workspace.random_(0, 256)
+    counts = torch_mod.full((B.BGL_COUNTS_LEN,), -9, dtype=torch_mod.int32)
+    if pinned:
+        counts = counts.pin_memory()
+    sd = torch_mod.from_numpy(seeds).cuda()
+    st = B.SubgraphStruct()
+    B._check(B.lib().bgl_sample_khop(s.graph._h, sd.data_ptr(), num_seeds, fanouts.ctypes.data, 2, 99, s.workspace.data_ptr(),
+                                     s.workspace_bytes, C.byref(st), counts.data_ptr(), B._stream_handle(None)))
+    torch_mod.cuda.synchronize()
+    sg = oracle.sample_khop(rp, col, seeds, [6, 4], 99)
+    want = np.zeros(B.BGL_COUNTS_LEN, dtype=np.int64)
+    want[:3] = sg.n_frontier
+    want[B.BGL_MAX_HOPS + 1: B.BGL_MAX_HOPS + 3] = sg.nnz
+    assert counts.tolist() == want.tolist()
+
+
 def test_sample_reports_out_of_range_seed(B, torch_mod):
     rp, col = csr_from_adj(TINY_GRAPHS["path"])
     g = B.Graph(rp, col)
