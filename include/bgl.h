@@ -176,7 +176,8 @@ int bgl_cache_destroy(bgl_cache_t *c);
  *                   hits are complete when the call's work is done
  *   side_stream     the miss fetch runs here (NULL: a stream owned by the
  *                   cache), after the hit gather (beside it when the cache can
- *                   hold every node), so that work enqueued on
+ *                   hold every node; what is enqueued on side_stream behind the
+ *                   call comes after both either way), so that work enqueued on
  *                   main_stream afterwards (the next batch's sampling) overlaps
  *                   the host-link transfer.  The rows of the misses are complete
  *                   for a stream once it has passed bgl_cache_wait_rows or the
@@ -292,9 +293,10 @@ int bgl_cache_set_spare_rows(bgl_cache_t *c, int64_t spare_rows);
 int bgl_cache_set_write_through(bgl_cache_t *c, int enable);
 
 /*
- * Make `stream` wait (on the device, not the host) until the miss rows of the
- * most recent bgl_cache_lookup_gather are in out_rows.  A no-op when that call
- * ran on a single stream.  Consumers of out_rows other than
+ * Make `stream` wait (on the device, not the host) until the rows of the most
+ * recent bgl_cache_lookup_gather, of its hits and of its misses, are in
+ * out_rows.  A no-op when that call ran on a single stream, and for its
+ * side_stream, where they are in stream order.  Consumers of out_rows other than
  * bgl_cache_insert_fifo (the model's first layer) call this first.
  */
 int bgl_cache_wait_rows(bgl_cache_t *c, void *stream);

@@ -87,14 +87,18 @@ struct bgl_cache {
     hipStream_t own_side = nullptr;  // the miss fetch's stream when the caller names none; created on first use
                                      // (a process has few hardware queues: a stream that is never used should not take one)
     // Ordering between streams.  ev_listed: lists and hit rows of the last lookup are complete
-    // (recorded on that lookup's main stream); ev_miss: its miss rows are complete (recorded on
-    // the stream the fetch ran on); ev_map: the last FIFO update is complete (recorded on the
-    // update's stream when that is not the lookup's main stream).
-    hipEvent_t ev_listed = nullptr, ev_miss = nullptr, ev_map = nullptr;
+    // (recorded on that lookup's main stream); ev_miss: its miss rows are complete and so are its hit
+    // rows (recorded on the stream the fetch ran on, behind the hit gather: whoever waits for the rows,
+    // or is behind the call in that stream, has all of them); ev_map: the last FIFO update is complete
+    // (recorded on the update's stream when that is not the lookup's main stream).  ev_fetched: a fetch
+    // that ran beside the hit gather is complete, whatever the gather does (for work that is behind the
+    // gather anyway).
+    hipEvent_t ev_listed = nullptr, ev_miss = nullptr, ev_map = nullptr, ev_fetched = nullptr;
     hipEvent_t ev_ids = nullptr;     // the lists of a lookup are complete (tiered: the missed ids have reached the host)
     hipEvent_t ev_lists = nullptr;   // the same for this cache's own miss fetch on the side stream
     hipStream_t last_main = nullptr, fetch_stream = nullptr, map_stream = nullptr;
     bool fetch_pending = false;      // ev_miss marks a miss fetch that later work may have to wait for
+    bool fetch_beside = false;       // that fetch ran beside its hit gather: ev_fetched marks its own end
     bool fetch_reads_caller_lists = true;  // that fetch reads the caller's miss_pos (not the library's copy)
     bool map_pending = false;        // ev_map marks a FIFO update the next lookup has to wait for
     bool ev_listed_valid = false;    // a lookup has recorded ev_listed
@@ -1095,6 +1099,7 @@ try {
 #undef TRY_ALLOC
     if (hipEventCreateWithFlags(&c->ev_listed, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_miss, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_fetched, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_ids, hipEventDisableTiming) != hipSuccess ||
         // only this library's kernels on this device wait for these two: no release to the system
         hipEventCreateWithFlags(&c->ev_lists, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess ||
@@ -1122,6 +1127,7 @@ try {
     for (auto ev : c->prof_ev) (void)hipEventDestroy(ev);
     if (c->ev_listed) (void)hipEventDestroy(c->ev_listed);
     if (c->ev_miss) (void)hipEventDestroy(c->ev_miss);
+    if (c->ev_fetched) (void)hipEventDestroy(c->ev_fetched);
     if (c->ev_map) (void)hipEventDestroy(c->ev_map);
     if (c->ev_ids) (void)hipEventDestroy(c->ev_ids);
     if (c->ev_lists) (void)hipEventDestroy(c->ev_lists);
@@ -1285,6 +1291,13 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
     return BGL_OK;
 }
 
+// What work on a stream waits for that needs the rows of the last lookup: all of them, or, behind its
+// hit gather, those of the misses.
+hipEvent_t rows_event(const bgl_cache *c, bool behind_gather)
+{
+    return c->fetch_beside && behind_gather ? c->ev_fetched : c->ev_miss;
+}
+
 // The stream of the miss fetch: the caller's, or one of the cache's own.
 int side_stream_of(bgl_cache *c, void *side_stream, hipStream_t *out)
 {
@@ -1384,8 +1397,14 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
                 });
             }
         }
+        if (beside) {
+            // ev_miss, and whatever the caller enqueues on the side stream, come behind the gather as well
+            BGL_HIP(hipEventRecord(c->ev_fetched, ss));
+            BGL_HIP(hipStreamWaitEvent(ss, c->ev_listed, 0));
+        }
         BGL_HIP(hipEventRecord(c->ev_miss, ss));
         c->fetch_pending = true;
+        c->fetch_beside = beside;
         c->fetch_stream = ss;
         c->fetch_reads_caller_lists = mpos == miss_pos;
     }
@@ -1793,6 +1812,7 @@ int tiered_finish(bgl_cache_t *c, int64_t *n_hit)
     guard.armed = false;
     BGL_HIP(hipGetLastError());
     c->fetch_pending = true;
+    c->fetch_beside = false;
     c->fetch_stream = tc.ss;
     c->fetch_reads_caller_lists = tc.mpos == tc.miss_pos;
     if (n_hit) {
@@ -1885,8 +1905,8 @@ try {
                    dim3(MAP_THREADS), ids, miss_pos, n_miss, c->capacity, c->num_nodes, c->table,
                    c->num_buckets - 1, c->slot_to_node, c->slot_to_entry, c->dev, par, 0);
         }
-        if (c->fetch_pending && c->fetch_stream != st)
-            BGL_HIP(hipStreamWaitEvent(st, c->ev_miss, 0));  // rows of the misses
+        if (c->fetch_pending && c->fetch_stream != st)  // rows of the misses (st is behind the hit gather, see above)
+            BGL_HIP(hipStreamWaitEvent(st, rows_event(c, true), 0));
         {
             Prof p(c, BGL_STAGE_INSERT_ROWS, st);
             dispatch_q(q, [&](auto Q) {
@@ -1896,7 +1916,7 @@ try {
             });
         }
     } else {
-        if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, c->ev_miss, 0));
+        if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, rows_event(c, true), 0));
         hipLaunchKernelGGL(k_advance_tail, dim3(1), dim3(64), 0, st, c->dev, n_miss, par);
     }
     c->insert_calls += 1;
@@ -1947,7 +1967,7 @@ extern "C" int bgl_cache_wait_rows(bgl_cache_t *c, void *stream)
 try {
     if (!c) BGL_FAIL(BGL_EINVAL, "cache handle is null");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, c->ev_miss, 0));
+    if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, rows_event(c, st == c->last_main), 0));
     return BGL_OK;
 } BGL_NOTHROW_END
 

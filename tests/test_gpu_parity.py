@@ -371,6 +371,101 @@ def test_cache_that_can_hold_every_node(B, torch_mod, spare, over, side, device_
     run_cache_stream(B, torch_mod, feats, N + over, batches, device_n_miss=device_n_miss, side=side, spare=spare)
 
 
+@pytest.mark.parametrize("consumer", ["third stream", "side stream", "next lookup on another stream"])
+@pytest.mark.parametrize("over,misses", [(0, 0), (0, 7), (0, 60_000), (-1, 7)])
+def test_cache_that_can_hold_every_node_rows_reach_other_streams(B, torch_mod, over, misses, consumer):
+    """The hit gather (200 MB) outlasts the fetch of no or few misses that runs beside it: a stream that
+    waits for the rows, the side stream itself and a lookup on another main stream still come after both.
+    Nothing synchronises the device before the rows are read."""
+    import oracle
+    torch = torch_mod
+    rng = np.random.default_rng(misses)
+    N, rb, n = 260_000, 1024, 190_000
+    feats = rng.integers(0, 256, (N, rb), dtype=np.uint8)
+    feat_t = torch.from_numpy(feats).pin_memory()
+    gc, oc = B.Cache(N + over, feat_t), oracle.Cache(N + over, feats)
+    main, side, third = (torch.cuda.Stream() for _ in range(3))
+    new = lambda: (torch.zeros((n, rb), dtype=torch.uint8, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda"),
+                   torch.empty(n, dtype=torch.int32, device="cuda"))
+    known, unknown = np.split(rng.permutation(N).astype(np.int32), [n])
+    out, slot, miss = new()
+    ids_t = torch.from_numpy(known).cuda()
+    gc.lookup_gather(ids_t, n, out, slot, miss)
+    gc.insert_fifo(ids_t, miss, -1, out)
+    torch.cuda.synchronize()
+    o_out, _, o_miss, _ = oc.lookup_gather(known)
+    oc.insert_fifo(known, o_miss, o_out)
+    for r in range(3):
+        ids = rng.permutation(np.concatenate([known[: n - misses], unknown[:misses]]))
+        other = rng.permutation(known)
+        want, want_slot, _, _ = oc.lookup_gather(ids)
+        ids_t, other_t = torch.from_numpy(ids).cuda(), torch.from_numpy(other).cuda()
+        (out, slot, miss), (out2, slot2, miss2) = new(), new()
+        got = torch.empty_like(out)
+        torch.cuda.synchronize()
+        gc.lookup_gather(ids_t, n, out, slot, miss, main_stream=main, side_stream=side)
+        if consumer == "next lookup on another stream":
+            gc.lookup_gather(other_t, n, out2, slot2, miss2, main_stream=third, side_stream=side)
+            gc.wait_rows(third)
+            torch.cuda.synchronize()
+            assert torch.equal(out2.cpu(), feat_t[torch.from_numpy(other).long()]), r
+            got = out
+        else:
+            st = side if consumer == "side stream" else third
+            gc.wait_rows(st)
+            with torch.cuda.stream(st):
+                got.copy_(out)
+            torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), want), r
+        assert np.array_equal(slot.cpu().numpy(), want_slot), r
+
+
+@pytest.mark.parametrize("over", [0, -1])
+def test_cache_that_can_hold_every_node_under_capture(B, torch_mod, over):
+    """Lookup and FIFO update with a side stream of their own as one graph, replayed with other ids."""
+    import oracle
+    torch = torch_mod
+    rng = np.random.default_rng(3)
+    N, rb, n = 6_000, 400, 2_500
+    feats = rng.integers(0, 256, (N, rb), dtype=np.uint8)
+    feat_t = torch.from_numpy(feats).pin_memory()
+    warm, gc, oc = B.Cache(N + over, feat_t), B.Cache(N + over, feat_t), oracle.Cache(N + over, feats)
+    out, slot = torch.zeros((n, rb), dtype=torch.uint8, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+    miss, ids_t = torch.empty_like(slot), torch.empty_like(slot)
+    main, side = torch.cuda.Stream(), torch.cuda.Stream()
+
+    def twice(c):      # (two updates: the graph ends on the copy of the tail it began with)
+        for _ in range(2):
+            c.lookup_gather(ids_t, n, out, slot, miss, main_stream=main, side_stream=side, noalloc=True)
+            c.insert_fifo(ids_t, miss, -1, out, stream=main)
+
+    ids_t.copy_(torch.arange(n, dtype=torch.int32))
+    torch.cuda.synchronize()
+    twice(warm)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(main):
+        graph.capture_begin()
+        twice(gc)
+        graph.capture_end()
+    for r in range(5):
+        ids = rng.permutation(N)[:n].astype(np.int32)
+        ids_t.copy_(torch.from_numpy(ids))
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for _ in range(2):
+            o_out, o_slot, o_miss, o_hit = oc.lookup_gather(ids)
+            oc.insert_fifo(ids, o_miss, o_out)
+        assert np.array_equal(out.cpu().numpy(), o_out), r
+        assert np.array_equal(slot.cpu().numpy(), o_slot) and int(gc.n_hit_host[0]) == o_hit, r
+        x = torch.randn(500, 500, device="cuda")
+        (x @ x).sum().item()
+    s2n, tail, buf = gc.export_state(True)
+    assert np.array_equal(s2n, oc.slot_to_node)
+
+
 @pytest.mark.parametrize("early", ["own", "with_insert", "alternate"])
 @pytest.mark.parametrize("side", [True, False])
 def test_cache_early_lookup(B, torch_mod, early, side):
