@@ -290,6 +290,7 @@ __global__ __launch_bounds__(TILE) void k_sample_direct(
     uint32_t *tab, int32_t *slotidx, int32_t *lrow, int32_t *cbs, int enter_frontier)
 {
     __shared__ int sh_scan[TILE / kWave];
+    constexpr uint32_t LM = 2 * TILE - 1;
     __shared__ uint32_t sh_first[2 * TILE], sh_id[TILE];
     const uint32_t p = blockIdx.x * TILE + threadIdx.x;
     // (the grid ends less than a tile beyond the frontier's bound, and other arrays of the workspace follow it)
@@ -301,24 +302,32 @@ __global__ __launch_bounds__(TILE) void k_sample_direct(
     const uint32_t seen = d.valid ? __hip_atomic_load(&tab[d.u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     if (enter_frontier && d.active && d.s == 0) atomicMin(&tab[d.v], (uint32_t)d.i);
     slotidx[p] = d.valid ? (int32_t)d.u : -1;
+    sh_id[threadIdx.x] = d.u;
     // per-node counts -> row starts inside this tile, tile total
     int total;
     const int ex = block_excl_scan<TILE>((d.active && d.s == 0) ? d.c : 0, sh_scan, total);
     if (d.active && d.s == 0) lrow[d.i] = ex;
     if (threadIdx.x == 0) cbs[blockIdx.x] = total;
-    // A repeat inside the workgroup need not go to the map.  Most repeats (those whose first occurrence
-    // is the first of all ids with its LDS slot) are found here: without it, a graph whose edges lead to
-    // one node for the most part makes every lane lower the same word, 7 ns each (10 % of the edges to
-    // one node: 166 us a call of 16,384 seeds, fanout 10; 64 us with it).
-    // (block_excl_scan ended with a barrier: sh_first is initialised for everyone)
-    const uint32_t at = (hash32(d.u) >> 8) & (2 * TILE - 1);
-    sh_id[threadIdx.x] = d.u;
-    if (d.valid) atomicMin(&sh_first[at], threadIdx.x);
-    __syncthreads();
-    if (d.valid && seen > (TENT | p)) {
-        const uint32_t w = sh_first[at];
-        if (w == threadIdx.x || sh_id[w] != d.u) atomicMin(&tab[d.u], TENT | p);
+    // A repeat inside the workgroup need not go to the map: without its removal, a graph whose edges lead
+    // to a few nodes for the most part makes every lane lower the same words, 7 ns each (10 % of the edges
+    // to one node: 166 us a call of 16,384 seeds, fanout 10).  An LDS hash table of thread indices finds
+    // the first thread of every id.  It has to resolve ids that meet in a slot: with one probe per id, two
+    // heavy nodes of the same slot left one of them to the map (a quarter of the edges to each: 287 us,
+    // 50 now, 79 with the hash table).
+    // (block_excl_scan ended with a barrier: sh_first and sh_id are there for everyone)
+    uint32_t at = 0;
+    if (d.valid) {
+        for (at = (hash32(d.u) >> 8) & LM;; at = (at + 1) & LM) {  // at most half full: ends
+            const uint32_t first = atomicCAS(&sh_first[at], EMPTY32, threadIdx.x);
+            if (first == EMPTY32) break;
+            if (sh_id[first] == d.u) {
+                if (first > threadIdx.x) atomicMin(&sh_first[at], threadIdx.x);
+                break;
+            }
+        }
     }
+    __syncthreads();
+    if (d.valid && seen > (TENT | p) && sh_first[at] == threadIdx.x) atomicMin(&tab[d.u], TENT | p);
 }
 
 // The same with the hash table.

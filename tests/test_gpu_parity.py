@@ -166,6 +166,51 @@ def test_sample_map_by_node_id_and_by_hash(B, torch_mod, num_nodes, num_seeds, f
     assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, fanouts, 77))
 
 
+def _slot_of(ids, slots):
+    """Where the workgroup's table of first occurrences starts to look for an id (MurmurHash3's finaliser)."""
+    h = np.asarray(ids).astype(np.uint32)
+    for shift, mul in ((16, 0x85EBCA6B), (13, 0xC2B2AE35), (16, 1)):
+        h ^= h >> np.uint32(shift)
+        h = (h.astype(np.uint64) * mul).astype(np.uint32)
+    return (h >> np.uint32(8)) % slots
+
+
+@pytest.mark.parametrize("heavy,share", [(2, 0.5), (2, 1.0), (16, 0.5), (64, 0.9)])
+def test_sample_heavy_nodes_that_share_a_slot(B, torch_mod, heavy, share):
+    """Most edges lead to a few nodes whose ids meet in one slot of a workgroup's table of first
+    occurrences.  The results are the oracle's, and a call takes about as long as with heavy nodes of
+    different slots: a repeat that went to the map instead would queue on one word, 7 ns each (two heavy
+    nodes: 5 times as long; the bound of 2 lies between, and the least of many calls is compared)."""
+    import time
+    import oracle
+    torch = torch_mod
+    N, deg, fanouts, n_seeds = 200_000, 12, [10, 2], 16_384
+    rng = np.random.default_rng(heavy)
+    slot = _slot_of(np.arange(N), 1024)
+    together = np.nonzero(slot == slot[777])[0][:heavy]
+    apart = np.array([np.nonzero(slot == s)[0][1] for s in range(heavy)])
+    assert len(together) == heavy
+    rp = (np.arange(N + 1) * deg).astype(np.int32)
+    seeds = rng.permutation(N)[:n_seeds].astype(np.int32)
+    sd = torch.from_numpy(seeds).cuda()
+    least = {}
+    for name, nodes in (("together", together), ("apart", apart)):
+        col = rng.integers(0, N, N * deg)
+        col = np.where(rng.random(N * deg) < share, nodes[rng.integers(0, heavy, N * deg)], col).astype(np.int32)
+        res = gpu_sample(B, torch, rp, col, seeds.tolist(), fanouts, 5)
+        assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, fanouts, 5))
+        s = B.Sampler(B.Graph(rp, col), n_seeds, fanouts)
+        torch.cuda.synchronize()
+        times = []
+        for k in range(60):
+            t = time.perf_counter()
+            s.sample(sd, k)
+            torch.cuda.current_stream().synchronize()
+            times.append(time.perf_counter() - t)
+        least[name] = min(times)
+    assert least["together"] < 2 * least["apart"], least
+
+
 def test_sample_high_degree_hub_and_host_pinned_graph(B, torch_mod):
     import oracle
     rng = np.random.default_rng(11)
