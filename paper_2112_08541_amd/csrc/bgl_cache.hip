@@ -399,6 +399,13 @@ constexpr int SMALL_FETCH_BLOCKS = 16;
 // Tiered lookup: rows the host threads copy per chunk before that chunk's fetch is launched.
 constexpr int64_t TIER_CHUNK_ROWS = 49152;
 constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
+// Cache that can hold every node: bytes a lookup asks for beyond which its miss fetch runs beside the hit
+// gather.  Saves the update two hand-overs between streams behind the gather, and overlaps a short fetch with
+// a long gather; costs the host three more calls.  Lookup + update behind / beside, microseconds: 2 MB of
+// hits, each call waited for 60 / 83, one after the other 59 / 67; 41 MB 71 / 86, 70 / 66; 82 MB 80 / 95,
+// 75 / 70; 120 MB 101 / 100, 90 / 80; 205 MB 114 / 110, 101 / 94; with 2 % misses 120 MB 157 / 135, 205 MB
+// 187 / 150; with half of the ids missed the link sets the time either way.
+constexpr int64_t BESIDE_LOOKUP_BYTES = 100ll << 20;
 // Hit gather: largest output (of the hits) that is still written with ordinary stores.
 constexpr int64_t GATHER_CACHED_OUTPUT_BYTES = 64ll << 20;
 // Assembled output: largest out_rows of a call that is still written with ordinary stores.
@@ -1364,11 +1371,11 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
     // On a stream of its own the miss fetch starts once the hit gather is done: its host reads would hold
     // up the gather's HBM reads (428,377 ids, three quarters of them missed: gather 20 -> 140 us), and a
     // fetch of milliseconds loses nothing by waiting for it.  A cache that can hold every node misses a
-    // node once: there the fetch starts as soon as the lists are there, beside the gather, so that the
-    // FIFO update finds its (mostly empty) work done when the gather ends instead of waiting for two more
-    // hand-overs between streams.  Lookup + update of 302,709 resident ids of 1,024 bytes: 183 / 169 us.
+    // node once: there the fetch of a large lookup starts as soon as the lists are there, beside the gather,
+    // so that the FIFO update finds its (mostly empty) work done when the gather ends instead of waiting for
+    // two more hand-overs between streams.
     // (Write-through mode: the fetch overwrites rows that the gather may have to read.)
-    const bool beside = n > 0 && ss != ms && !c->write_through && c->capacity >= c->num_nodes;
+    const bool beside = ss != ms && !c->write_through && c->capacity >= c->num_nodes && n * c->row_bytes > BESIDE_LOOKUP_BYTES;
     rc = lookup_phase(c, ids, n, out_rows, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, fixed, nullptr, beside);
     if (rc != BGL_OK) return rc;
     if (n > 0) {

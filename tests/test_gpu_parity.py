@@ -407,13 +407,26 @@ def test_cache_misses_in_place_by_row_width(B, torch_mod, row_bytes, write_throu
 @pytest.mark.parametrize("side", [True, False])
 @pytest.mark.parametrize("device_n_miss", [True, False])
 def test_cache_that_can_hold_every_node(B, torch_mod, spare, over, side, device_n_miss):
-    """With capacity >= num_nodes the miss fetch runs beside the hit gather on its own stream (one row
-    less: behind it).  Cold, mixed and all-hit batches, each stream held up in turn."""
+    """Cold, mixed and all-hit batches, each stream held up in turn."""
     rng = np.random.default_rng(7 + over)
     N = 9_000
     feats = rng.integers(0, 256, (N, 400)).astype(np.uint8)
     batches = [rng.permutation(N)[:n].astype(np.int32) for n in (4000, 4000, 1, 8999, 9000, 2500, 9000)]
     run_cache_stream(B, torch_mod, feats, N + over, batches, device_n_miss=device_n_miss, side=side, spare=spare)
+
+
+@pytest.mark.parametrize("spare,over", [(0, 0), (0, -1), (500, 3)])
+@pytest.mark.parametrize("device_n_miss", [True, False])
+def test_cache_that_can_hold_every_node_large_calls(B, torch_mod, spare, over, device_n_miss):
+    """Beyond 100 MiB asked for, with capacity >= num_nodes, the miss fetch runs beside the hit gather on its
+    own stream (one row less: behind it).  Cold, mixed and all-hit batches, at the limit, one id more, and
+    small ones between them, each stream held up in turn."""
+    rng = np.random.default_rng(70 + over)
+    N, rb = 52_000, 4096
+    limit = (100 << 20) // rb
+    feats = np.tile(rng.integers(0, 256, (N, 64), dtype=np.uint8), (1, rb // 64))
+    batches = [rng.permutation(N)[:n].astype(np.int32) for n in (limit + 1, 700, limit, 30_011, limit + 1, N)]
+    run_cache_stream(B, torch_mod, feats, N + over, batches, device_n_miss=device_n_miss, spare=spare)
 
 
 @pytest.mark.parametrize("consumer", ["third stream", "side stream", "next lookup on another stream"])
@@ -471,7 +484,7 @@ def test_cache_that_can_hold_every_node_under_capture(B, torch_mod, over):
     import oracle
     torch = torch_mod
     rng = np.random.default_rng(3)
-    N, rb, n = 6_000, 400, 2_500
+    N, rb, n = 150_000, 1024, 110_000        # 113 MB asked for: the fetch runs beside the gather (over = -1: behind it)
     feats = rng.integers(0, 256, (N, rb), dtype=np.uint8)
     feat_t = torch.from_numpy(feats).pin_memory()
     warm, gc, oc = B.Cache(N + over, feat_t), B.Cache(N + over, feat_t), oracle.Cache(N + over, feats)
