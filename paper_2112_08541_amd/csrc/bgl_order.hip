@@ -119,7 +119,7 @@ __global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uin
 // count as visited), the root's row as the first level.
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, int32_t root, uint32_t *visited,
-                                              uint32_t *closed, int64_t words, uint32_t *key, int64_t num_nodes,
+                                              uint32_t *closed, int64_t words, uint32_t *key, int32_t *cursor, int64_t num_nodes,
                                               const uint32_t *__restrict__ train, Frontier f, int32_t *seq, OrderDev *dev)
 {
     const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x, stride = (int64_t)gridDim.x * BT;
@@ -131,7 +131,10 @@ __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, in
         visited[w] = v;
         closed[w] = 0;
     }
-    for (int64_t i = t; i < num_nodes; i += stride) key[i] = NO_KEY;
+    for (int64_t i = t; i < num_nodes; i += stride) {
+        key[i] = NO_KEY;
+        cursor[i] = 0;
+    }
     if (t == 0) {
         const int64_t lo = (int64_t)row_ptr[root], d = (int64_t)row_ptr[root + 1] - lo;
         f.off[0] = 0;
@@ -165,15 +168,17 @@ __device__ __forceinline__ uint32_t rows_before(const unsigned long long *off, u
 
 // The smallest unvisited node with an unvisited out-neighbor other than itself.  A wavefront takes
 // 64 ids at a time, ascending, 16 lanes walk one node's row, eight reads in flight per lane; nobody
-// goes on beyond the smallest open node found so far.  A node found closed stays closed (the visited
-// set only grows) and is not looked at again: a graph has a restart for every component that no other
-// one leads to, and some rows of the nodes in between are long (2.45 M nodes / 122 M edges, 110 restarts
-// per traversal: 130 to 300 us a search that walks them again each time with one read per lane, 30 to 55
-// now; five such traversals 118 -> 48 ms, 261 ms with the searches and levels this file had before).
+// goes on beyond the smallest open node found so far.  The visited set only grows, so a node found closed
+// stays closed and is not looked at again, and the leading edges of a row that are known to end at visited
+// nodes (`cursor`, per node) are not read again: a graph has a restart for every component that no other
+// one leads to, some rows of the nodes in between are long, and over a traversal a row is walked once.
+// (2.45 M nodes / 122 M edges, 110 restarts per traversal: 130 to 300 us a search that walks the closed
+// nodes again each time with one read per lane, 30 to 55 now; five such traversals 118 -> 48 ms.  A row of
+// 200,000 edges, the last one open, behind 300 components of two nodes: 203 -> 26 ms.)
 template <typename RP>
 __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                            const uint32_t *__restrict__ visited, uint32_t *closed, int64_t num_nodes,
-                                            int64_t scan_lo, OrderDev *dev)
+                                            const uint32_t *__restrict__ visited, uint32_t *closed, int32_t *cursor,
+                                            int64_t num_nodes, int64_t scan_lo, OrderDev *dev)
 {
     if (blockIdx.x >= SEARCH_BLOCKS) return;
     const int lane = threadIdx.x & (kWave - 1), l = lane & 15, gshift = lane & ~15;
@@ -188,8 +193,9 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
         bool open = false;
         for (; look && !open; look &= look - 1) {
             const int64_t v = c * 64 + gshift + (__ffs(look) - 1);
-            const int64_t hi = (int64_t)row_ptr[v + 1];
-            for (int64_t e = (int64_t)row_ptr[v]; e < hi && !open; e += 128) {
+            const int64_t lo = (int64_t)row_ptr[v], hi = (int64_t)row_ptr[v + 1];
+            int64_t e = lo + cursor[v];
+            while (e < hi) {
                 uint32_t u[8], seen[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) u[j] = (uint32_t)col[min(e + j * 16 + l, hi - 1)];
@@ -199,9 +205,14 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
 #pragma unroll
                 for (int j = 0; j < 8; ++j) mine |= (int64_t)u[j] != v && !(seen[j] & 1u);
                 open = ((__ballot(mine) >> gshift) & 0xffffull) != 0;
+                if (open) break;
+                e += 128;
             }
             if (open) {
-                if (l == 0) atomicMin(&dev->open_min, (int)v);
+                if (l == 0) {
+                    cursor[v] = (int32_t)(e - lo);
+                    atomicMin(&dev->open_min, (int)v);
+                }
             } else {
                 shut |= look & (0u - look);
             }
@@ -212,14 +223,14 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
 
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                               const uint32_t *__restrict__ visited, uint32_t *closed, int64_t num_nodes,
-                                               uint32_t *key, Frontier f0, Frontier f1, Lists li, OrderDev *dev, int par)
+                                               const uint32_t *__restrict__ visited, uint32_t *closed, int32_t *cursor,
+                                               int64_t num_nodes, uint32_t *key, Frontier f0, Frontier f1, Lists li, OrderDev *dev, int par)
 {
     __shared__ uint32_t sh_start[BW][kWave];  // per wavefront: WTILE bytes, 1 where a row begins
     const Step st = dev->step[par];
     if (st.done) return;
     if (st.rows == 0) {
-        search_open(row_ptr, col, visited, closed, num_nodes, st.scan_lo, dev);
+        search_open(row_ptr, col, visited, closed, cursor, num_nodes, st.scan_lo, dev);
         return;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) dev->open_min = INT_MAX;  // for the next restart
@@ -560,6 +571,7 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
 
 struct OrderWork {
     uint32_t *visited = nullptr, *closed = nullptr, *train = nullptr, *key = nullptr;
+    int32_t *cursor = nullptr;  // per node: leading edges of its row known to end at visited nodes (search_open)
     Frontier f[2];
     Lists li;
     int32_t *seq = nullptr, *train_ids = nullptr;
@@ -592,6 +604,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, O
         take(w.closed, (size_t)words);
         take(w.train, (size_t)words);
         take(w.key, (size_t)N);
+        take(w.cursor, (size_t)N);
         for (int k = 0; k < 2; ++k) {
             take(w.f[k].off, (size_t)N);
             take(w.f[k].base, (size_t)N);
@@ -636,7 +649,7 @@ int bfs_sequence(const bgl_graph *g, int64_t root, int64_t num_train, OrderWork 
     const RP *rp = static_cast<const RP *>(g->row_ptr);
     w.host->step = w.host->done = 0;
     hipLaunchKernelGGL(k_reset<RP>, dim3((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096)), dim3(BT), 0, st, rp, (int32_t)root,
-                       w.visited, w.closed, words, w.key, N, w.train, w.f[0], w.seq, w.dev);
+                       w.visited, w.closed, words, w.key, w.cursor, N, w.train, w.f[0], w.seq, w.dev);
     // The device says in page-locked words which step it has come to and when the traversal has ended; the
     // host stays STEPS_AHEAD steps ahead of it, so the queue never runs empty and at most that many steps,
     // whose launches return at once, are enqueued beyond the end.  (A synchronisation every 8 to 32 steps
@@ -647,8 +660,8 @@ int bfs_sequence(const bgl_graph *g, int64_t root, int64_t num_train, OrderWork 
     for (int64_t step = 1; !word(w.host->done); ++step) {
         if (step > most + STEPS_AHEAD) BGL_FAIL(BGL_EHIP, "the traversal did not end");
         const int par = (int)((step - 1) & 1);
-        hipLaunchKernelGGL(k_expand<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, g->col, w.visited, w.closed, N, w.key, w.f[0], w.f[1], w.li,
-                           w.dev, par);
+        hipLaunchKernelGGL(k_expand<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, g->col, w.visited, w.closed, w.cursor, N, w.key, w.f[0],
+                           w.f[1], w.li, w.dev, par);
         hipLaunchKernelGGL(k_count<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.key, w.train, w.li, w.dev, par);
         hipLaunchKernelGGL(k_append<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.train, w.f[0], w.f[1], w.seq,
                            w.li, w.dev, par, w.host_dev, (uint32_t)step);
