@@ -50,6 +50,7 @@ constexpr int WAVES = BLOCKS * BW;
 constexpr int WTILE = 4 * kWave;             // edges a wavefront handles at a time, four per lane
 constexpr int64_t WINDOW = 1 << 23;          // edges per step at most
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
+constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
 constexpr uint32_t NO_KEY = ~0u;
 
@@ -166,8 +167,27 @@ __device__ __forceinline__ uint32_t rows_before(const unsigned long long *off, u
     return lo;
 }
 
+// Does one of eight edges, e, e + step, ..., lead from v to an unvisited node other than v?  Edges from hi on
+// read the last one again.  The eight reads are in flight together.
+__device__ __forceinline__ bool open_edge(const int32_t *__restrict__ col, const uint32_t *__restrict__ visited, int64_t v,
+                                          int64_t e, int step, int64_t hi)
+{
+    uint32_t u[8], seen[8];
+    bool open = false;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) u[j] = (uint32_t)col[min(e + j * step, hi - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) seen[j] = visited[u[j] >> 5] >> (u[j] & 31);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) open |= (int64_t)u[j] != v && !(seen[j] & 1u);
+    return open;
+}
+
 // The smallest unvisited node with an unvisited out-neighbor other than itself.  A wavefront takes
-// 64 ids at a time, ascending, 16 lanes walk one node's row, eight reads in flight per lane; nobody
+// 64 ids at a time, ascending: every lane walks one node's row if it is short, then 16 lanes walk each of
+// the longer rows, eight reads in flight per lane (with 16 lanes for every row a wavefront looks at few
+// nodes at a time: calls on 10 M nodes of one edge / 4 M of 20 edges, all closed, 2.5 / 1.7 ms, 1.1 / 0.9
+// now); nobody
 // goes on beyond the smallest open node found so far.  The visited set only grows, so a node found closed
 // stays closed and is not looked at again, and the leading edges of a row that are known to end at visited
 // nodes (`cursor`, per node) are not read again: a graph has a restart for every component that no other
@@ -186,38 +206,45 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
     for (int64_t c = scan_lo / 64 + wave; c * 64 < num_nodes; c += SEARCH_BLOCKS * BW) {
         const int found = __hip_atomic_load(&dev->open_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (c * 64 >= __builtin_amdgcn_readfirstlane(found)) return;
-        // this group's 16 ids (the bitmaps end with a whole number of 64-bit pairs)
-        const int64_t word = c * 2 + (lane >> 5);
-        uint32_t look = ~((visited[word] | closed[word]) >> (gshift & 16)) & 0xffffu;
-        uint32_t shut = 0;
-        bool open = false;
-        for (; look && !open; look &= look - 1) {
-            const int64_t v = c * 64 + gshift + (__ffs(look) - 1);
+        // (the bitmaps end with a whole number of 64-bit pairs; bits beyond the last id count as visited)
+        const int64_t word = c * 2 + (lane >> 5), own = c * 64 + lane;
+        const bool look = !(((visited[word] | closed[word]) >> (lane & 31)) & 1u);
+        // one row per lane where it is short
+        bool open = false, rest = false;
+        if (look) {
+            const int64_t lo = (int64_t)row_ptr[own], hi = (int64_t)row_ptr[own + 1], e = lo + cursor[own];
+            rest = hi - e > SHORT_ROW;
+            for (int64_t k = e; k < hi && !rest && !open; k += 8) open = open_edge(col, visited, own, k, 1, hi);
+        }
+        const uint64_t opens = __ballot(open);
+        const uint64_t shuts = __ballot(look && !open && !rest);
+        if (opens && lane == __ffsll((unsigned long long)opens) - 1) atomicMin(&dev->open_min, (int)own);
+        const uint32_t shut_word = (uint32_t)(shuts >> (lane & 32));
+        if ((lane & 31) == 0 && shut_word) atomicOr(&closed[word], shut_word);
+        // the longer ones before the first open node: 16 lanes per row
+        const uint64_t longs = __ballot(rest) & (opens ? (opens & (0ull - opens)) - 1ull : ~0ull);
+        uint32_t todo = (uint32_t)(longs >> gshift) & 0xffffu, shut = 0;
+        for (; todo; todo &= todo - 1) {
+            const int64_t v = c * 64 + gshift + (__ffs(todo) - 1);
             const int64_t lo = (int64_t)row_ptr[v], hi = (int64_t)row_ptr[v + 1];
             int64_t e = lo + cursor[v];
+            bool found_one = false;
             while (e < hi) {
-                uint32_t u[8], seen[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) u[j] = (uint32_t)col[min(e + j * 16 + l, hi - 1)];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) seen[j] = visited[u[j] >> 5] >> (u[j] & 31);
-                bool mine = false;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) mine |= (int64_t)u[j] != v && !(seen[j] & 1u);
-                open = ((__ballot(mine) >> gshift) & 0xffffull) != 0;
-                if (open) break;
+                const bool mine = open_edge(col, visited, v, e + l, 16, hi);
+                found_one = ((__ballot(mine) >> gshift) & 0xffffull) != 0;
+                if (found_one) break;
                 e += 128;
             }
-            if (open) {
+            if (found_one) {
                 if (l == 0) {
                     cursor[v] = (int32_t)(e - lo);
                     atomicMin(&dev->open_min, (int)v);
                 }
-            } else {
-                shut |= look & (0u - look);
+                break;
             }
+            shut |= todo & (0u - todo);
         }
-        if (shut && l == 0) atomicOr(&closed[word], shut << (gshift & 16));
+        if (shut && l == 0) atomicOr(&closed[c * 2 + (gshift >> 5)], shut << (gshift & 16));
     }
 }
 

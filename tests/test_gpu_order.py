@@ -82,7 +82,7 @@ def test_bfs_sequence_rows_across_wavefront_shares(B, degrees, hub, dtype):
         assert np.array_equal(B.order_bfs_sequence(g, train, root), oracle.bfs_sequence(rp, col, train, root))
 
 
-@pytest.mark.parametrize("length", [1, 127, 128, 129, 700])
+@pytest.mark.parametrize("length", [1, 8, 9, 31, 32, 33, 127, 128, 129, 700])
 def test_bfs_sequence_restart_search_walks_long_rows(B, length):
     """Nodes that only a restart reaches, with rows of `length` edges: into the visited set (closed, at
     once or only after an earlier restart), with the one open edge first, last or in the middle, to
