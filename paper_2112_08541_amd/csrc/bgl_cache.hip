@@ -386,14 +386,18 @@ constexpr int COPY_UNROLL = 4;  // (the kernels name the four chunks of a lane b
 // lookup, and with it the packing of its rows, starts late.
 constexpr int FETCH_BLOCKS = 64;
 constexpr int RING_FETCH_BLOCKS = 32;
-// The overlapped loop's small batches (write-through mode: the next batch's sampling and the map update
-// run beside the fetch): the bytes a lookup asks for at most, and the workgroups.  Every host read in
+// The overlapped loop's small batches (write-through mode, FIFO updates on another stream than the fetches:
+// the update and the next batch's sampling run beside the fetch): the bytes a lookup asks for at most, and
+// the workgroups.  Every host read in
 // flight beyond what the link needs delays the other kernels' HBM reads (with 64 workgroups the map
 // update of 315 K rows took 700 us beside the fetch, with 24 it took 85), and a small batch is bound by
 // those kernels' launches as much as by the link.  Microseconds per batch with 8 / 16 / 24 / 64
 // workgroups: 2.6 MB asked 106 / 112 / 121 / 124; 4.2 MB 160 / 141 / 155 / 164; 8.4 MB 278 / 228 / 232 /
 // 246; 16.8 MB 517 / 404 / 406 / 412.  A larger batch is bound by the fetch alone, which takes 7 % longer
-// with 16 workgroups (3,270 against 3,055 us at 128 MB of misses).
+// with 16 workgroups (3,270 against 3,055 us at 128 MB of misses), and so is a small one with nothing beside
+// it (16 MB asked, fetch with 16 / 64 workgroups: 400-byte rows 427 / 391 us, 528 bytes 433 / 369, 1,024
+// bytes 317 / 301).  (More workgroups where lanes stay idle, so that as many bytes are in flight: 528-byte
+// rows 16 MB 374 -> 369 us, but 64 MB 1,448 -> 1,483.)
 constexpr int64_t SMALL_LOOKUP_BYTES = 16 << 20;
 constexpr int SMALL_FETCH_BLOCKS = 16;
 // Tiered lookup: rows the host threads copy per chunk before that chunk's fetch is launched.
@@ -1376,6 +1380,7 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
     // two more hand-overs between streams.
     // (Write-through mode: the fetch overwrites rows that the gather may have to read.)
     const bool beside = ss != ms && !c->write_through && c->capacity >= c->num_nodes && n * c->row_bytes > BESIDE_LOOKUP_BYTES;
+    const bool update_beside = c->map_pending && c->map_stream != ms;  // the FIFO updates run on a stream of their own
     rc = lookup_phase(c, ids, n, out_rows, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, fixed, nullptr, beside);
     if (rc != BGL_OK) return rc;
     if (n > 0) {
@@ -1389,7 +1394,7 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
             const uint4 *features = reinterpret_cast<const uint4 *>(c->features);
             uint4 *out = reinterpret_cast<uint4 *>(out_rows), *buffer = reinterpret_cast<uint4 *>(c->buffer);
             if (!c->features_in_hbm && q <= kWave) {
-                const bool few = c->write_through && n * c->row_bytes <= SMALL_LOOKUP_BYTES;
+                const bool few = c->write_through && update_beside && n * c->row_bytes <= SMALL_LOOKUP_BYTES;
                 const int64_t rows_per_block = (int64_t)(COPY_THREADS / kWave) * COPY_UNROLL * (kWave / q);
                 const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, rows_per_block), few ? SMALL_FETCH_BLOCKS : FETCH_BLOCKS);
                 launch(c, ss, c->write_through ? k_fetch_link<true> : k_fetch_link<false>, dim3(blocks), dim3(COPY_THREADS), mpos, ids,
