@@ -653,7 +653,8 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, O
     BGL_HIP(hipMalloc((void **)&w.block, total));
     at = w.block;
     carve();
-    BGL_HIP(hipHostMalloc((void **)&w.host, sizeof(Progress), hipHostMallocDefault));
+    // (coherent whatever HIP_HOST_COHERENT says: the host reads it while kernels run)
+    BGL_HIP(hipHostMalloc((void **)&w.host, sizeof(Progress), hipHostMallocMapped | hipHostMallocCoherent));
     BGL_HIP(hipHostGetDevicePointer((void **)&w.host_dev, w.host, 0));
     BGL_HIP(hipMemsetAsync(w.dev, 0, sizeof(OrderDev), st));
     BGL_HIP(hipMemcpyAsync(w.train_ids, train_nodes, num_train * 4, hipMemcpyHostToDevice, st));

@@ -150,6 +150,26 @@ def test_bfs_sequence_restart_search_walks_a_row_once(B):
     assert least[1] < 4 * least[0], least
 
 
+def test_order_does_not_depend_on_the_default_kind_of_host_memory():
+    """The host follows a traversal through words in page-locked memory, which must be coherent also where
+    the process asks for non-coherent memory by default."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = ("import numpy as np, oracle\n"
+            "from paper_2112_08541_amd import binding as B\n"
+            "rng = np.random.default_rng(1); N = 5000\n"
+            "rp = np.zeros(N + 1, np.int32); rp[1:] = np.cumsum(rng.integers(0, 4, N))\n"
+            "col = rng.integers(0, N, int(rp[-1])).astype(np.int32); train = rng.permutation(N)[:900]\n"
+            "got = B.order_bfs_sequence(B.Graph(rp, col), train, 7)\n"
+            "assert np.array_equal(got, oracle.bfs_sequence(rp, col, train, 7))\n"
+            "print('same order')\n")
+    p = subprocess.run([sys.executable, "-c", code], cwd=root, env={**os.environ, "HIP_HOST_COHERENT": "0"},
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=100)
+    assert p.returncode == 0 and "same order" in p.stdout, p.stdout[-2000:]
+
+
 def test_bfs_sequence_chain_of_open_components(B):
     """Several multi-node components that are only reachable by restarts, interleaved by id
     with closed singletons (the bulk restart must keep the sequential order)."""
