@@ -129,10 +129,9 @@ def test_sample_random_cases_property(B, torch_mod):
 
 
 @pytest.mark.parametrize("num_seeds", [16384, 16385, 511 * 32, 1])
-def test_sample_stage_sizes_around_the_scan_threshold(B, torch_mod, num_seeds):
-    """A stage of at most 512 tiles of 512 padded positions has its tile totals scanned inside the
-    finalize kernel, a larger one by a launch of its own: 16,384 seeds x 16 lanes (fanout 10) are
-    exactly 512 tiles, one seed more is 513; the second hop (fanout 3) is far beyond either way."""
+def test_sample_stage_sizes_of_few_tiles(B, torch_mod, num_seeds):
+    """Stages whose bound is at most 1,024 tiles of 512 padded positions (here a seed's 16 lanes, fanout 10:
+    up to 513 tiles): mark and finalize deal one tile to a workgroup."""
     import oracle
     rng = np.random.default_rng(num_seeds)
     N = 40000
@@ -143,6 +142,29 @@ def test_sample_stage_sizes_around_the_scan_threshold(B, torch_mod, num_seeds):
     seeds = rng.permutation(N)[:num_seeds].astype(np.int32)
     res = gpu_sample(B, torch_mod, rp, col, seeds.tolist(), [10, 3], 4242)
     assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, [10, 3], 4242))
+
+
+@pytest.mark.parametrize("num_nodes", [300_000, 2**24 + 1])
+@pytest.mark.parametrize("num_seeds,fanouts", [(32767, [10, 3]), (32768, [10]), (32769, [10]), (65536, [16]), (65537, [16, 2]),
+                                               (70_000, [20, 2])])
+def test_sample_stage_sizes_around_the_share_limit(B, torch_mod, num_nodes, num_seeds, fanouts):
+    """mark and finalize have at most 1,024 workgroups.  32,768 seeds x 16 lanes (fanout 10) are exactly
+    1,024 tiles of 512 positions, one each; one seed more makes 513 shares of two tiles.  65,536 seeds x
+    16 lanes: 1,024 shares of two tiles, one seed more: of four.  70,000 seeds x 32 lanes (fanout 20): 4,375
+    tiles, shares of eight, so mark's rounds of four tiles carry on from one to the next.  The dedup map by
+    node id and hashed."""
+    import oracle
+    rng = np.random.default_rng(num_seeds)
+    nodes = np.sort(rng.choice(num_nodes, 100_000, replace=False))
+    nodes[-1] = num_nodes - 1
+    deg = np.zeros(num_nodes, dtype=np.int64)
+    deg[nodes] = rng.integers(0, 30, len(nodes))
+    rp = np.zeros(num_nodes + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(deg)
+    col = nodes[rng.integers(0, len(nodes), int(rp[-1]))].astype(np.int32)
+    seeds = rng.permutation(nodes)[:num_seeds].astype(np.int32)                # distinct: the sizes are real, not bounds
+    res = gpu_sample(B, torch_mod, rp, col, seeds.tolist(), fanouts, 4242)
+    assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, fanouts, 4242))
 
 
 @pytest.mark.parametrize("num_nodes", [2**24, 2**24 + 1])
