@@ -142,6 +142,19 @@ def test_null_handles_are_rejected_without_touching_the_gpu(L):
     assert L.bgl_pipeline_run(None, None, 0, None, 0, 0, None, None, None, C.cast(None, B.BATCH_FN), None) == B.BGL_EINVAL
 
 
+def test_graph_load_refuses_rows_beyond_31_bits(L):
+    """The kernels keep a row's length in 31 bits (the ordering packs a flag above it): the longest row a
+    graph may have is 2^31 - 1 edges, refused before a column id is read."""
+    from paper_2112_08541_amd import binding as B
+    h = C.c_void_p()
+    col = np.zeros(1, dtype=np.int32)
+    for ends in ([0, 2**31], [0, 5, 5 + 2**31], [0, 2**40, 2**40]):
+        rp = np.array(ends, dtype=np.int64)
+        rc = L.bgl_graph_load_csr(rp.ctypes.data, 64, col.ctypes.data, len(rp) - 1, int(rp[-1]), 0, C.byref(h))
+        assert rc == B.BGL_EINVAL and b"31 bits" in L.bgl_last_error(), ends
+        assert not h
+
+
 def test_binding_refuses_to_run_without_a_gpu():
     import torch
     if torch.cuda.is_available():
