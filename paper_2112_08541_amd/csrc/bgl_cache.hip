@@ -90,17 +90,18 @@ struct bgl_cache {
     // (recorded on that lookup's main stream); ev_miss: its miss rows are complete and so are its hit
     // rows (recorded on the stream the fetch ran on, behind the hit gather: whoever waits for the rows,
     // or is behind the call in that stream, has all of them); ev_map: the last FIFO update is complete
-    // (recorded on the update's stream when that is not the lookup's main stream).  ev_fetched: a fetch
-    // that ran beside the hit gather is complete, whatever the gather does (for work that is behind the
-    // gather anyway).
+    // (recorded on the update's stream), or ev_map_local: map_event says which (see LONG_LOOKUP_BYTES).
+    // ev_fetched: a fetch that ran beside the hit gather is complete, whatever the gather does (for work
+    // that is behind the gather anyway).
     hipEvent_t ev_listed = nullptr, ev_miss = nullptr, ev_map = nullptr, ev_fetched = nullptr;
+    hipEvent_t ev_map_local = nullptr, map_event = nullptr;
     hipEvent_t ev_ids = nullptr;     // the lists of a lookup are complete (tiered: the missed ids have reached the host)
     hipEvent_t ev_lists = nullptr;   // the same for this cache's own miss fetch on the side stream
     hipStream_t last_main = nullptr, fetch_stream = nullptr, map_stream = nullptr;
     bool fetch_pending = false;      // ev_miss marks a miss fetch that later work may have to wait for
     bool fetch_beside = false;       // that fetch ran beside its hit gather: ev_fetched marks its own end
     bool fetch_reads_caller_lists = true;  // that fetch reads the caller's miss_pos (not the library's copy)
-    bool map_pending = false;        // ev_map marks a FIFO update the next lookup has to wait for
+    bool map_pending = false;        // map_event marks a FIFO update the next lookup has to wait for
     bool ev_listed_valid = false;    // a lookup has recorded ev_listed
     bool write_through = false;      // the miss fetch also fills the cache buffer (see bgl_cache_set_write_through)
     bool awaiting_insert = false;    // write-through: a lookup's misses are in the buffer but not in the map yet
@@ -403,13 +404,21 @@ constexpr int SMALL_FETCH_BLOCKS = 16;
 // Tiered lookup: rows the host threads copy per chunk before that chunk's fetch is launched.
 constexpr int64_t TIER_CHUNK_ROWS = 49152;
 constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
-// Cache that can hold every node: bytes a lookup asks for beyond which its miss fetch runs beside the hit
-// gather.  Saves the update two hand-overs between streams behind the gather, and overlaps a short fetch with
-// a long gather; costs the host three more calls.  Lookup + update behind / beside, microseconds: 2 MB of
-// hits, each call waited for 60 / 83, one after the other 59 / 67; 41 MB 71 / 86, 70 / 66; 82 MB 80 / 95,
-// 75 / 70; 120 MB 101 / 100, 90 / 80; 205 MB 114 / 110, 101 / 94; with 2 % misses 120 MB 157 / 135, 205 MB
-// 187 / 150; with half of the ids missed the link sets the time either way.
-constexpr int64_t BESIDE_LOOKUP_BYTES = 100ll << 20;
+// Lookups that ask for more bytes than this keep the GPU busy for longer than the host takes to enqueue
+// them.  Two things pay only there:
+//  - the FIFO update's event without a release to the system (only this library's kernels on this device
+//    wait for it).  A row of calls saves 5 us of each (lookup + update of 302,709 hits of 1,024 bytes 168 /
+//    163 us), but a host that waits for a stream whose last command it is enqueues another one first: 500
+//    ids of 400 bytes, each call waited for, 63 / 70 us; hidden once the kernels outlast the host.  (Always
+//    without it where the updates have a stream of their own, as in the overlapped loop: 512 seeds on
+//    10,000 nodes, 20 batches 2,110 / 2,060 us.)
+//  - the miss fetch beside the hit gather, in a cache that can hold every node.  It saves the update two
+//    hand-overs between streams behind the gather, and overlaps a short fetch with a long gather; costs the
+//    host three more calls.  Lookup + update behind / beside, microseconds: 2 MB of hits, each call waited
+//    for 60 / 83, one after the other 59 / 67; 41 MB 71 / 86, 70 / 66; 82 MB 80 / 95, 75 / 70; 120 MB 101 /
+//    100, 90 / 80; 205 MB 114 / 110, 101 / 94; with 2 % misses 120 MB 157 / 135, 205 MB 187 / 150; with half
+//    of the ids missed the link sets the time either way.
+constexpr int64_t LONG_LOOKUP_BYTES = 100ll << 20;
 // Hit gather: largest output (of the hits) that is still written with ordinary stores.
 constexpr int64_t GATHER_CACHED_OUTPUT_BYTES = 64ll << 20;
 // Assembled output: largest out_rows of a call that is still written with ordinary stores.
@@ -1111,10 +1120,11 @@ try {
     if (hipEventCreateWithFlags(&c->ev_listed, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_miss, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_fetched, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_map, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_ids, hipEventDisableTiming) != hipSuccess ||
-        // only this library's kernels on this device wait for these two: no release to the system
+        // only this library's kernels on this device wait for these two: no release to the system (LONG_LOOKUP_BYTES)
         hipEventCreateWithFlags(&c->ev_lists, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess ||
-        hipEventCreateWithFlags(&c->ev_map, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
+        hipEventCreateWithFlags(&c->ev_map_local, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) {
         bgl::set_error("stream/event creation failed");
         return fail(BGL_EHIP);
     }
@@ -1140,6 +1150,7 @@ try {
     if (c->ev_miss) (void)hipEventDestroy(c->ev_miss);
     if (c->ev_fetched) (void)hipEventDestroy(c->ev_fetched);
     if (c->ev_map) (void)hipEventDestroy(c->ev_map);
+    if (c->ev_map_local) (void)hipEventDestroy(c->ev_map_local);
     if (c->ev_ids) (void)hipEventDestroy(c->ev_ids);
     if (c->ev_lists) (void)hipEventDestroy(c->ev_lists);
     if (c->own_side) (void)hipStreamDestroy(c->own_side);
@@ -1244,7 +1255,7 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
     c->last_n = n;
     const int q = c->row_bytes / 16;
     if (tier) bgl::tier_prepare(tier);
-    if (c->map_pending && c->map_stream != ls) BGL_HIP(hipStreamWaitEvent(ls, c->ev_map, 0));
+    if (c->map_pending && c->map_stream != ls) BGL_HIP(hipStreamWaitEvent(ls, c->map_event, 0));
     if (!early && c->fetch_pending && c->fetch_stream != ms) {
         // the previous call's fetch still reads that call's lists
         BGL_HIP(hipStreamWaitEvent(ms, c->ev_miss, 0));
@@ -1379,7 +1390,7 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
     // so that the FIFO update finds its (mostly empty) work done when the gather ends instead of waiting for
     // two more hand-overs between streams.
     // (Write-through mode: the fetch overwrites rows that the gather may have to read.)
-    const bool beside = ss != ms && !c->write_through && c->capacity >= c->num_nodes && n * c->row_bytes > BESIDE_LOOKUP_BYTES;
+    const bool beside = ss != ms && !c->write_through && c->capacity >= c->num_nodes && n * c->row_bytes > LONG_LOOKUP_BYTES;
     const bool update_beside = c->map_pending && c->map_stream != ms;  // the FIFO updates run on a stream of their own
     rc = lookup_phase(c, ids, n, out_rows, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, fixed, nullptr, beside);
     if (rc != BGL_OK) return rc;
@@ -1869,6 +1880,22 @@ try {
     return tiered_finish(c, nullptr);
 } BGL_NOTHROW_END
 
+namespace {
+
+// The FIFO update has been enqueued on st: mark its end for the next lookup (on every stream: that lookup
+// may run on another one than this call's lookup did).
+int record_update(bgl_cache *c, hipStream_t st)
+{
+    const bool local = st != c->last_main || c->last_n * c->row_bytes > LONG_LOOKUP_BYTES;
+    c->map_event = local ? c->ev_map_local : c->ev_map;
+    BGL_HIP(hipEventRecord(c->map_event, st));
+    c->map_pending = true;
+    c->map_stream = st;
+    return BGL_OK;
+}
+
+}  // namespace
+
 extern "C" int bgl_cache_insert_fifo(bgl_cache_t *c, const int32_t *ids, const int32_t *miss_pos,
                                      int64_t n_miss, const void *out_rows, void *stream)
 try {
@@ -1904,11 +1931,7 @@ try {
         }
         c->insert_calls += 1;
         BGL_HIP(hipGetLastError());
-        // (recorded on every stream: the next lookup may run on another one than this call's lookup did)
-        BGL_HIP(hipEventRecord(c->ev_map, st));
-        c->map_pending = true;
-        c->map_stream = st;
-        return BGL_OK;
+        return record_update(c, st);
     }
     if (eff > 0) {
         {
@@ -1933,10 +1956,7 @@ try {
     }
     c->insert_calls += 1;
     BGL_HIP(hipGetLastError());
-    BGL_HIP(hipEventRecord(c->ev_map, st));
-    c->map_pending = true;
-    c->map_stream = st;
-    return BGL_OK;
+    return record_update(c, st);
 } BGL_NOTHROW_END
 
 extern "C" int bgl_cache_set_spare_rows(bgl_cache_t *c, int64_t spare_rows)

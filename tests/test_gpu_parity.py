@@ -528,6 +528,40 @@ def test_cache_that_can_hold_every_node_rows_reach_other_streams(B, torch_mod, o
         assert np.array_equal(slot.cpu().numpy(), want_slot), r
 
 
+@pytest.mark.parametrize("rows", [600, 110_000])
+@pytest.mark.parametrize("updates", ["with the lookup", "own stream"])
+@pytest.mark.parametrize("write_through", [False, True])
+def test_cache_next_lookup_on_another_stream_follows_the_update(B, torch_mod, rows, updates, write_through):
+    """Lookup and update alternate between two main streams, or all updates have a stream of their own, with
+    nothing but the library's own events between the calls; of more and of less than 100 MiB asked for."""
+    import oracle
+    torch = torch_mod
+    rng = np.random.default_rng(rows)
+    N, rb = 2 * rows, 1024
+    feats = np.tile(rng.integers(0, 256, (N, 32), dtype=np.uint8), (1, rb // 32))
+    gc, oc = B.Cache(rows + 11, torch.from_numpy(feats).pin_memory()), oracle.Cache(rows + 11, feats)
+    gc.set_write_through(write_through)
+    mains = [torch.cuda.Stream(), torch.cuda.Stream()]
+    own = torch.cuda.Stream()
+    idl = [rng.permutation(N)[:rows - k].astype(np.int32) for k in range(6)]
+    idt = [torch.from_numpy(x).cuda() for x in idl]
+    bufs = [(torch.zeros((rows, rb), dtype=torch.uint8, device="cuda"), torch.empty(rows, dtype=torch.int32, device="cuda"),
+             torch.empty(rows, dtype=torch.int32, device="cuda")) for _ in idl]
+    torch.cuda.synchronize()
+    for k, ids in enumerate(idt):
+        out, slot, miss = bufs[k]
+        main = mains[k % 2]
+        gc.lookup_gather(ids, len(ids), out, slot, miss, main_stream=main)
+        gc.insert_fifo(ids, miss, -1, out, stream=own if updates == "own stream" else main)
+    torch.cuda.synchronize()
+    for k, ids in enumerate(idl):
+        o_out, o_slot, o_miss, _ = oc.lookup_gather(ids)
+        oc.insert_fifo(ids, o_miss, o_out)
+        assert np.array_equal(bufs[k][1][:len(ids)].cpu().numpy(), o_slot), k
+        assert np.array_equal(bufs[k][0][:len(ids)].cpu().numpy(), o_out), k
+    assert_state_equal(gc, oc)
+
+
 @pytest.mark.parametrize("over", [0, -1])
 def test_cache_that_can_hold_every_node_under_capture(B, torch_mod, over):
     """Lookup and FIFO update with a side stream of their own as one graph, replayed with other ids."""
