@@ -451,8 +451,9 @@ __device__ __forceinline__ uint4 ld16(const uint4 *p)
 // caches, but pushes the rows being read out of them.  Measured, ordinary /
 // non-temporal stores, every id a hit: 310 MB of 1,024-byte rows 111 / 96 us
 // (6.4 TB/s read and written), 171 MB of 400-byte rows 70 / 60, 120 MB 44 / 40,
-// 90 MB 33 / 30, 60 MB 22 / 21 but 1,024-byte rows 21.4 / 22.0; 45 MB of 400-byte
-// rows between misses (lines written in part) 20.2 / 21.5.
+// 90 MB 33 / 30, 60 MB 22 / 21 but 1,024-byte rows 21.4 / 22.0; between misses
+// (400-byte rows write lines in part) 45 MB of hits 20.2 / 21.5, but 80 MB 36.2 /
+// 34.8, 144 MB 55.6 / 51.3, 102 MB of 1,024-byte rows 44.8 / 38.1.
 template <int Q>
 __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
     const int32_t *__restrict__ hit_pos, const int32_t *__restrict__ hit_slot, int q,

@@ -16,16 +16,17 @@
 //   k_append   prefixes of those totals give every new node its place: the next
 //              frontier and the training-node sequence are written in order
 // No sort, and the sizes stay on the device: the host enqueues steps (three
-// launches each) and looks every few steps whether the traversal has ended.
+// launches each) a few ahead of the one that the device says, in page-locked
+// words, it has come to.
 //   Every wavefront owns a contiguous run of EDGES, not of nodes: out-degrees are
 // a power law, and with a fixed number of lanes per node the longest row sets the
 // pace (16 lanes on a row of 20,000 edges: 1.9 ms for one level).  Measured, two
-// sequences on 2.45 M nodes / 122 M edges: 30.2 ms with 16 lanes per node and a
-// radix sort per level, 5.8 ms now (k_expand 52 us per 8 M edges, bound by the
-// random reads of the visited bitmap and the keys); five sequences on 100,000
-// nodes / 1 M edges, where launches and host round trips count: 19.5 and 1.8 ms.
-//   A level is
-// handled in windows of at most WINDOW edges, which bounds the lists whatever the
+// sequences on 2.45 M nodes / 122 M edges: 26 to 28 ms with 16 lanes per node and a
+// radix sort per level, 5.3 ms now (k_expand 2.8 ms, 89 G edges/s, bound by the
+// random reads of the visited bitmap and the keys, 87 % of which hit the L2);
+// five sequences on 100,000 nodes / 1 M edges, where launches and host round
+// trips count: 14 to 19 and 1.7 ms.
+//   A level is handled in windows of at most WINDOW edges, which bounds the lists whatever the
 // graph's size; a target reached in one window is visited in the next.
 //   When the frontier is empty the same three kernels restart the traversal.
 // Nodes all of whose out-neighbors are visited ("closed") would each be a one-node
@@ -193,7 +194,7 @@ __device__ __forceinline__ bool open_edge(const int32_t *__restrict__ col, const
 // nodes (`cursor`, per node) are not read again: a graph has a restart for every component that no other
 // one leads to, some rows of the nodes in between are long, and over a traversal a row is walked once.
 // (2.45 M nodes / 122 M edges, 110 restarts per traversal: 130 to 300 us a search that walks the closed
-// nodes again each time with one read per lane, 30 to 55 now; five such traversals 118 -> 48 ms.  A row of
+// nodes again each time with one read per lane, 30 to 55 now; five such traversals 118 -> 40 ms.  A row of
 // 200,000 edges, the last one open, behind 300 components of two nodes: 203 -> 26 ms.)
 template <typename RP>
 __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, co
             for (int j = 0; j < 4; ++j) {
                 const uint32_t u = (uint32_t)(c[j] >> 32);
                 d[j] = 0;
-                if (first[j])
+                if (first[j])  // (a row has at most 2^31 - 1 edges: checked when the graph is loaded)
                     d[j] = (unsigned long long)((int64_t)row_ptr[u + 1] - (int64_t)row_ptr[u]) |
                            (unsigned long long)(train[u >> 5] >> (u & 31) & 1u) << 31;
             }
@@ -680,8 +681,9 @@ int bfs_sequence(const bgl_graph *g, int64_t root, int64_t num_train, OrderWork 
                        w.visited, w.closed, words, w.key, w.cursor, N, w.train, w.f[0], w.seq, w.dev);
     // The device says in page-locked words which step it has come to and when the traversal has ended; the
     // host stays STEPS_AHEAD steps ahead of it, so the queue never runs empty and at most that many steps,
-    // whose launches return at once, are enqueued beyond the end.  (A synchronisation every 8 to 32 steps
-    // instead: 2.2 ms for five sequences of 13 steps on 100,000 nodes, 1.8 now.)  Every step visits a
+    // whose launches return at once, are enqueued beyond the end.  The calling thread spins meanwhile.  (A
+    // synchronisation every 8 to 32 steps instead: 2.2 ms for five sequences of 13 steps on 100,000 nodes,
+    // 1.7 now.)  Every step visits a
     // node or ends the traversal or is one of a level's windows.
     const int64_t most = 2 * N + g->num_edges / WINDOW + 4;
     auto word = [](const uint32_t &x) { return __atomic_load_n(&x, __ATOMIC_ACQUIRE); };

@@ -21,9 +21,9 @@
 //   What bounds a call: up to ~50,000 neighbors the launches, each 4 to 6 us of
 // dependent reads; beyond, the random lines (row ends, column ids, map).  Measured
 // per call, host included, with 11 to 15 launches and the hash table everywhere /
-// now (7 to 10 launches): 512 seeds, fanout 10,5 on 10,000 nodes 87 / 61 us;
-// 1,024 seeds, fanout 15,10,5 on 2.45 M nodes / 122 M edges 160 / 124 us; 4,096
-// seeds, fanout 25,10 on 8 M nodes 124 / 100 us.
+// now (7 to 10 launches): 512 seeds, fanout 10,5 on 10,000 nodes 91 / 55 us;
+// 1,024 seeds, fanout 15,10,5 on 2.45 M nodes / 122 M edges 163 / 125 us; 4,096
+// seeds, fanout 25,10 on 8 M nodes 124 / 95 us.
 // Launches are sized by upper bounds; the real sizes stay on the device, and the
 // last kernel stores them into the caller's page-locked counts.
 #include "bgl_internal.h"
