@@ -53,7 +53,10 @@ constexpr int64_t WINDOW = 1 << 23;          // edges per step at most
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
 constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
-constexpr uint32_t NO_KEY = ~0u;
+// A node's key: below WINDOW the smallest edge of the current window that reaches it (it is visited by the
+// end of the step), else none, and the excess says how many leading edges of its own row are known to end
+// at visited nodes (search_open; rows have fewer than 2^31 edges).
+constexpr uint32_t NO_KEY = (uint32_t)WINDOW;
 
 // What a step finds.  Step s reads copy s & 1; its last kernel writes the other.
 struct Step {
@@ -121,7 +124,7 @@ __global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uin
 // count as visited), the root's row as the first level.
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, int32_t root, uint32_t *visited,
-                                              uint32_t *closed, int64_t words, uint32_t *key, int32_t *cursor, int64_t num_nodes,
+                                              uint32_t *closed, int64_t words, uint32_t *key, int64_t num_nodes,
                                               const uint32_t *__restrict__ train, Frontier f, int32_t *seq, OrderDev *dev)
 {
     const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x, stride = (int64_t)gridDim.x * BT;
@@ -133,10 +136,7 @@ __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, in
         visited[w] = v;
         closed[w] = 0;
     }
-    for (int64_t i = t; i < num_nodes; i += stride) {
-        key[i] = NO_KEY;
-        cursor[i] = 0;
-    }
+    for (int64_t i = t; i < num_nodes; i += stride) key[i] = NO_KEY;
     if (t == 0) {
         const int64_t lo = (int64_t)row_ptr[root], d = (int64_t)row_ptr[root + 1] - lo;
         f.off[0] = 0;
@@ -191,14 +191,14 @@ __device__ __forceinline__ bool open_edge(const int32_t *__restrict__ col, const
 // now); nobody
 // goes on beyond the smallest open node found so far.  The visited set only grows, so a node found closed
 // stays closed and is not looked at again, and the leading edges of a row that are known to end at visited
-// nodes (`cursor`, per node) are not read again: a graph has a restart for every component that no other
+// nodes (their number is kept in the node's key) are not read again: a graph has a restart for every component that no other
 // one leads to, some rows of the nodes in between are long, and over a traversal a row is walked once.
 // (2.45 M nodes / 122 M edges, 110 restarts per traversal: 130 to 300 us a search that walks the closed
 // nodes again each time with one read per lane, 30 to 55 now; five such traversals 118 -> 40 ms.  A row of
 // 200,000 edges, the last one open, behind 300 components of two nodes: 203 -> 26 ms.)
 template <typename RP>
 __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                            const uint32_t *__restrict__ visited, uint32_t *closed, int32_t *cursor,
+                                            const uint32_t *__restrict__ visited, uint32_t *closed, uint32_t *key,
                                             int64_t num_nodes, int64_t scan_lo, OrderDev *dev)
 {
     if (blockIdx.x >= SEARCH_BLOCKS) return;
@@ -213,7 +213,7 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
         // one row per lane where it is short
         bool open = false, rest = false;
         if (look) {
-            const int64_t lo = (int64_t)row_ptr[own], hi = (int64_t)row_ptr[own + 1], e = lo + cursor[own];
+            const int64_t lo = (int64_t)row_ptr[own], hi = (int64_t)row_ptr[own + 1], e = lo + (key[own] - NO_KEY);
             rest = hi - e > SHORT_ROW;
             for (int64_t k = e; k < hi && !rest && !open; k += 8) open = open_edge(col, visited, own, k, 1, hi);
         }
@@ -228,7 +228,7 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
         for (; todo; todo &= todo - 1) {
             const int64_t v = c * 64 + gshift + (__ffs(todo) - 1);
             const int64_t lo = (int64_t)row_ptr[v], hi = (int64_t)row_ptr[v + 1];
-            int64_t e = lo + cursor[v];
+            int64_t e = lo + (key[v] - NO_KEY);
             bool found_one = false;
             while (e < hi) {
                 const bool mine = open_edge(col, visited, v, e + l, 16, hi);
@@ -238,7 +238,7 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
             }
             if (found_one) {
                 if (l == 0) {
-                    cursor[v] = (int32_t)(e - lo);
+                    key[v] = NO_KEY + (uint32_t)(e - lo);
                     atomicMin(&dev->open_min, (int)v);
                 }
                 break;
@@ -251,14 +251,14 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
 
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                               const uint32_t *__restrict__ visited, uint32_t *closed, int32_t *cursor,
-                                               int64_t num_nodes, uint32_t *key, Frontier f0, Frontier f1, Lists li, OrderDev *dev, int par)
+                                               const uint32_t *__restrict__ visited, uint32_t *closed, int64_t num_nodes,
+                                               uint32_t *key, Frontier f0, Frontier f1, Lists li, OrderDev *dev, int par)
 {
     __shared__ uint32_t sh_start[BW][kWave];  // per wavefront: WTILE bytes, 1 where a row begins
     const Step st = dev->step[par];
     if (st.done) return;
     if (st.rows == 0) {
-        search_open(row_ptr, col, visited, closed, cursor, num_nodes, st.scan_lo, dev);
+        search_open(row_ptr, col, visited, closed, key, num_nodes, st.scan_lo, dev);
         return;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) dev->open_min = INT_MAX;  // for the next restart
@@ -599,7 +599,6 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
 
 struct OrderWork {
     uint32_t *visited = nullptr, *closed = nullptr, *train = nullptr, *key = nullptr;
-    int32_t *cursor = nullptr;  // per node: leading edges of its row known to end at visited nodes (search_open)
     Frontier f[2];
     Lists li;
     int32_t *seq = nullptr, *train_ids = nullptr;
@@ -632,7 +631,6 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, O
         take(w.closed, (size_t)words);
         take(w.train, (size_t)words);
         take(w.key, (size_t)N);
-        take(w.cursor, (size_t)N);
         for (int k = 0; k < 2; ++k) {
             take(w.f[k].off, (size_t)N);
             take(w.f[k].base, (size_t)N);
@@ -678,7 +676,7 @@ int bfs_sequence(const bgl_graph *g, int64_t root, int64_t num_train, OrderWork 
     const RP *rp = static_cast<const RP *>(g->row_ptr);
     w.host->step = w.host->done = 0;
     hipLaunchKernelGGL(k_reset<RP>, dim3((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096)), dim3(BT), 0, st, rp, (int32_t)root,
-                       w.visited, w.closed, words, w.key, w.cursor, N, w.train, w.f[0], w.seq, w.dev);
+                       w.visited, w.closed, words, w.key, N, w.train, w.f[0], w.seq, w.dev);
     // The device says in page-locked words which step it has come to and when the traversal has ended; the
     // host stays STEPS_AHEAD steps ahead of it, so the queue never runs empty and at most that many steps,
     // whose launches return at once, are enqueued beyond the end.  The calling thread spins meanwhile.  (A
@@ -690,8 +688,8 @@ int bfs_sequence(const bgl_graph *g, int64_t root, int64_t num_train, OrderWork 
     for (int64_t step = 1; !word(w.host->done); ++step) {
         if (step > most + STEPS_AHEAD) BGL_FAIL(BGL_EHIP, "the traversal did not end");
         const int par = (int)((step - 1) & 1);
-        hipLaunchKernelGGL(k_expand<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, g->col, w.visited, w.closed, w.cursor, N, w.key, w.f[0],
-                           w.f[1], w.li, w.dev, par);
+        hipLaunchKernelGGL(k_expand<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, g->col, w.visited, w.closed, N, w.key, w.f[0], w.f[1], w.li,
+                           w.dev, par);
         hipLaunchKernelGGL(k_count<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.key, w.train, w.li, w.dev, par);
         hipLaunchKernelGGL(k_append<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.train, w.f[0], w.f[1], w.seq,
                            w.li, w.dev, par, w.host_dev, (uint32_t)step);
