@@ -407,8 +407,7 @@ constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
 // Lookups that ask for more bytes than this keep the GPU busy for longer than the host takes to enqueue
 // them.  Two things pay only there:
 //  - the FIFO update's event without a release to the system (only this library's kernels on this device
-//    wait for it).  A row of calls saves 5 us of each (lookup + update of 302,709 hits of 1,024 bytes 168 /
-//    163 us), but a host that waits for a stream whose last command it is enqueues another one first: 500
+//    wait for it).  A row of calls saves 5 us of each (lookup + update of 302,709 hits of 1,024 bytes), but a host that waits for a stream whose last command it is enqueues another one first: 500
 //    ids of 400 bytes, each call waited for, 63 / 70 us; hidden once the kernels outlast the host.  (Always
 //    without it where the updates have a stream of their own, as in the overlapped loop: 512 seeds on
 //    10,000 nodes, 20 batches 2,110 / 2,060 us.)
@@ -419,8 +418,10 @@ constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
 //    100, 90 / 80; 205 MB 114 / 110, 101 / 94; with 2 % misses 120 MB 157 / 135, 205 MB 187 / 150; with half
 //    of the ids missed the link sets the time either way.
 constexpr int64_t LONG_LOOKUP_BYTES = 100ll << 20;
-// Hit gather: largest output (of the hits) that is still written with ordinary stores.
-constexpr int64_t GATHER_CACHED_OUTPUT_BYTES = 64ll << 20;
+// Hit gather: largest output (of the hits) whose rows are read with ordinary loads, and largest one that is
+// written with ordinary stores (the size of the last-level cache).
+constexpr int64_t GATHER_CACHED_ROWS_BYTES = 96ll << 20;
+constexpr int64_t GATHER_CACHED_OUTPUT_BYTES = 256ll << 20;
 // Assembled output: largest out_rows of a call that is still written with ordinary stores.
 constexpr int64_t ASSEMBLE_CACHED_OUTPUT_BYTES = 128ll << 20;
 
@@ -446,14 +447,20 @@ __device__ __forceinline__ uint4 ld16(const uint4 *p)
 // rows' positions in the cache buffer, so the work is proportional to the hits).  Consecutive lanes take consecutive
 // 16-byte chunks of a row, so the loads and stores of one row are contiguous;
 // four independent chunks per lane keep loads in flight.  The grid is sized for
-// n rows; workgroups beyond the hit count leave at once.  Output beyond
-// GATHER_CACHED_OUTPUT_BYTES is stored non-temporally: it would not stay in the
-// caches, but pushes the rows being read out of them.  Measured, ordinary /
-// non-temporal stores, every id a hit: 310 MB of 1,024-byte rows 111 / 96 us
-// (6.4 TB/s read and written), 171 MB of 400-byte rows 70 / 60, 120 MB 44 / 40,
-// 90 MB 33 / 30, 60 MB 22 / 21 but 1,024-byte rows 21.4 / 22.0; between misses
-// (400-byte rows write lines in part) 45 MB of hits 20.2 / 21.5, but 80 MB 36.2 /
-// 34.8, 144 MB 55.6 / 51.3, 102 MB of 1,024-byte rows 44.8 / 38.1.
+// n rows; workgroups beyond the hit count leave at once.
+//   What the caches keep: a row is read once per launch, so beyond GATHER_CACHED_ROWS_BYTES its loads say
+// so and leave the last-level cache (256 MB) to the output; output beyond GATHER_CACHED_OUTPUT_BYTES would
+// not stay there either and is stored non-temporally too.  Microseconds, loads and stores ordinary / loads
+// non-temporal / stores non-temporal / both; launches in a row with other ids | a 512 MiB copy before each:
+//   72 MB from a buffer of 196 MB   25 / 27 / 23 / 31 | 35 / 29 / 39 / 31
+//   102 MB from 614 MB              31 / 30 / 33 / 38 | 43 / 34 / 50 / 38
+//   160 MB (400-byte rows) from 800 68 / 53 / 59 / 65 | 72 / 59 / 84 / 65
+//   256 MB from 256 MB              96 / 69 / 70 / 89 | 99 / 75 / 119 / 89
+//   310 MB from 614 MB              120 / 117 / 102 / 108 | 119 / 92 / 138 / 108
+//   512 MB from 1,024 MB            196 / 184 / 185 / 179 | 195 / 164 / 210 / 179
+//   1.6 GB (400 bytes), 4.1 GB      after a copy: 688 / 649 / 661 / 626, 1,584 / 1,522 / 1,556 / 1,484
+// (Non-temporal stores alone are the fastest where nothing else has used the caches since the last launch,
+// and the slowest where something has.)
 template <int Q>
 __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
     const int32_t *__restrict__ hit_pos, const int32_t *__restrict__ hit_slot, int q,
@@ -479,24 +486,23 @@ __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
     RowSplit<Q>::split(min(base + 3 * COPY_THREADS, last), q, r3, c3);
     const int32_t s0 = hit_slot[r0], s1 = hit_slot[r1], s2 = hit_slot[r2], s3 = hit_slot[r3];
     const int32_t p0 = hit_pos[r0], p1 = hit_pos[r1], p2 = hit_pos[r2], p3 = hit_pos[r3];
-    const uint4 v0 = buffer[(int64_t)s0 * qq + c0];
-    const uint4 v1 = buffer[(int64_t)s1 * qq + c1];
-    const uint4 v2 = buffer[(int64_t)s2 * qq + c2];
-    const uint4 v3 = buffer[(int64_t)s3 * qq + c3];
-    if (total * 16 > GATHER_CACHED_OUTPUT_BYTES) {  // uniform
-        // (the markers keep the compiler from merging the two branches' stores into ordinary ones)
-        asm volatile("; streaming stores");
-        st16<true>(&out[(int64_t)p0 * qq + c0], v0);
-        st16<true>(&out[(int64_t)p1 * qq + c1], v1);
-        st16<true>(&out[(int64_t)p2 * qq + c2], v2);
-        st16<true>(&out[(int64_t)p3 * qq + c3], v3);
-        asm volatile("; end of streaming stores");
-    } else {
-        out[(int64_t)p0 * qq + c0] = v0;
-        out[(int64_t)p1 * qq + c1] = v1;
-        out[(int64_t)p2 * qq + c2] = v2;
-        out[(int64_t)p3 * qq + c3] = v3;
-    }
+    auto copy = [&](auto nt_loads, auto nt_stores) {
+        // (the markers keep the compiler from merging the branches' accesses into ordinary ones)
+        asm volatile("; rows");
+        const uint4 v0 = ld16<nt_loads.value>(&buffer[(int64_t)s0 * qq + c0]);
+        const uint4 v1 = ld16<nt_loads.value>(&buffer[(int64_t)s1 * qq + c1]);
+        const uint4 v2 = ld16<nt_loads.value>(&buffer[(int64_t)s2 * qq + c2]);
+        const uint4 v3 = ld16<nt_loads.value>(&buffer[(int64_t)s3 * qq + c3]);
+        st16<nt_stores.value>(&out[(int64_t)p0 * qq + c0], v0);
+        st16<nt_stores.value>(&out[(int64_t)p1 * qq + c1], v1);
+        st16<nt_stores.value>(&out[(int64_t)p2 * qq + c2], v2);
+        st16<nt_stores.value>(&out[(int64_t)p3 * qq + c3], v3);
+        asm volatile("; end of rows");
+    };
+    const int64_t bytes = total * 16;  // uniform
+    if (bytes > GATHER_CACHED_OUTPUT_BYTES) copy(std::true_type{}, std::true_type{});
+    else if (bytes > GATHER_CACHED_ROWS_BYTES) copy(std::true_type{}, std::false_type{});
+    else copy(std::false_type{}, std::false_type{});
 }
 
 // out[miss_pos[r]] = features[ids[miss_pos[r]]] for every miss r; the loads cross

@@ -528,6 +528,33 @@ def test_cache_that_can_hold_every_node_rows_reach_other_streams(B, torch_mod, o
         assert np.array_equal(slot.cpu().numpy(), want_slot), r
 
 
+@pytest.mark.parametrize("limit_mib", [96, 256])
+@pytest.mark.parametrize("row_bytes", [400, 1024, 4096])
+def test_cache_hit_gather_around_its_limits(B, torch_mod, limit_mib, row_bytes):
+    """The hit gather changes its loads beyond 96 MiB of hits and its stores beyond 256 MiB: exactly the
+    limit (or the last row below it), one row more, and misses between the hits."""
+    torch = torch_mod
+    most = (limit_mib << 20) // row_bytes
+    N = most + 5_000
+    table = torch.randint(0, 256, (N, row_bytes), dtype=torch.uint8, device="cuda")
+    c = B.Cache(N - 1_000, table)
+    out = torch.empty((N, row_bytes), dtype=torch.uint8, device="cuda")
+    slot, miss = torch.empty(N, dtype=torch.int32, device="cuda"), torch.empty(N, dtype=torch.int32, device="cuda")
+    first = torch.arange(N - 1_000, dtype=torch.int32, device="cuda")
+    c.lookup_gather(first, len(first), out, slot, miss)
+    c.insert_fifo(first, miss, -1, out)
+    for hits, misses in ((most, 0), (most + 1, 0), (most, 1_000), (most + 1, 999)):
+        ids = torch.cat([torch.randperm(N - 1_000, device="cuda")[:hits], N - 1 - torch.arange(misses, device="cuda")])
+        ids = ids[torch.randperm(len(ids), device="cuda")].to(torch.int32)
+        out.fill_(0xA5)
+        c.lookup_gather(ids, len(ids), out, slot, miss)
+        c.wait_rows()
+        torch.cuda.synchronize()
+        assert int(c.n_hit_host[0]) == hits
+        assert torch.equal(out[:len(ids)], table[ids.long()]), (hits, misses)
+        assert bool((out[len(ids):] == 0xA5).all())
+
+
 @pytest.mark.parametrize("rows", [600, 110_000])
 @pytest.mark.parametrize("updates", ["with the lookup", "own stream"])
 @pytest.mark.parametrize("write_through", [False, True])
