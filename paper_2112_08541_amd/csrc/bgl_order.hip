@@ -53,6 +53,8 @@ constexpr int64_t WINDOW = 1 << 23;          // edges per step at most
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
 constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
+constexpr int SIDE_BY_SIDE = 16;             // traversals that share their launches at most
+constexpr int64_t SIDE_BY_SIDE_BYTES = 2ll << 30;  // and the memory they may take together (one alone: whatever it needs)
 // A node's key: below WINDOW the smallest edge of the current window that reaches it (it is visited by the
 // end of the step), else none, and the excess says how many leading edges of its own row are known to end
 // at visited nodes (search_open; rows have fewer than 2^31 edges).
@@ -101,6 +103,37 @@ struct Lists {
     unsigned long long *block_edges;
 };
 
+// What one traversal works on.  The traversals of a call run side by side, blockIdx.y says which: their
+// memory has the same layout, `stride` bytes apart.
+struct Traversal {
+    uint32_t *visited, *closed, *key;
+    Frontier f0, f1;
+    Lists li;
+    OrderDev *dev;
+    int32_t *seq;       // num_train ids each, densely packed
+    Progress *host;     // one each
+    int64_t stride, num_train;
+
+    __device__ __forceinline__ Traversal mine() const
+    {
+        Traversal t = *this;
+        const int64_t by = (int64_t)blockIdx.y * stride;
+        auto move = [&](auto *&p) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(reinterpret_cast<char *>(p) + by); };
+        move(t.visited), move(t.closed), move(t.key);
+        move(t.f0.off), move(t.f0.base), move(t.f1.off), move(t.f1.base);
+        move(t.li.cand), move(t.li.n_cand), move(t.li.n_win);
+        move(t.li.wave_rows), move(t.li.wave_train), move(t.li.wave_edges);
+        move(t.li.block_rows), move(t.li.block_train), move(t.li.block_edges);
+        move(t.dev);
+        t.seq += (int64_t)blockIdx.y * num_train;
+        t.host += blockIdx.y;
+        return t;
+    }
+};
+struct Roots {
+    int32_t of[SIDE_BY_SIDE];
+};
+
 __device__ __forceinline__ bool test_bit(const uint32_t *bm, uint32_t v) { return (bm[v >> 5] >> (v & 31)) & 1u; }
 
 __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
@@ -120,13 +153,17 @@ __global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uin
     if (old & (1u << (v & 31))) dev->status = BGL_EINVAL;  // listed twice
 }
 
-// A fresh traversal from root: no keys, nothing visited but the root (bits at and above num_nodes
+// A fresh traversal from its root: no keys, nothing visited but the root (bits at and above num_nodes
 // count as visited), the root's row as the first level.
 template <typename RP>
-__global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, int32_t root, uint32_t *visited,
-                                              uint32_t *closed, int64_t words, uint32_t *key, int64_t num_nodes,
-                                              const uint32_t *__restrict__ train, Frontier f, int32_t *seq, OrderDev *dev)
+__global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, Roots roots, int64_t words, int64_t num_nodes,
+                                              const uint32_t *__restrict__ train, Traversal all)
 {
+    const Traversal me = all.mine();
+    const int32_t root = roots.of[blockIdx.y];
+    uint32_t *visited = me.visited, *closed = me.closed, *key = me.key;
+    const Frontier f = me.f0;
+    OrderDev *dev = me.dev;
     const int64_t t = (int64_t)blockIdx.x * BT + threadIdx.x, stride = (int64_t)gridDim.x * BT;
     for (int64_t w = t; w < words; w += stride) {
         uint32_t v = 0;
@@ -142,7 +179,7 @@ __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, in
         f.off[0] = 0;
         f.base[0] = lo;
         const bool tr = test_bit(train, (uint32_t)root);
-        if (tr) seq[0] = root;
+        if (tr) me.seq[0] = root;
         dev->step[0] = Step{(unsigned long long)d, 0, 0, d > 0 ? 1u : 0u, 0, tr ? 1 : 0, 0, 0, 0};
         dev->open_min = INT_MAX;
     }
@@ -201,10 +238,11 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
                                             const uint32_t *__restrict__ visited, uint32_t *closed, uint32_t *key,
                                             int64_t num_nodes, int64_t scan_lo, OrderDev *dev)
 {
-    if (blockIdx.x >= SEARCH_BLOCKS) return;
+    const int blocks = min((int)gridDim.x, SEARCH_BLOCKS);
+    if ((int)blockIdx.x >= blocks) return;
     const int lane = threadIdx.x & (kWave - 1), l = lane & 15, gshift = lane & ~15;
     const int64_t wave = (int64_t)blockIdx.x * BW + threadIdx.x / kWave;
-    for (int64_t c = scan_lo / 64 + wave; c * 64 < num_nodes; c += SEARCH_BLOCKS * BW) {
+    for (int64_t c = scan_lo / 64 + wave; c * 64 < num_nodes; c += blocks * BW) {
         const int found = __hip_atomic_load(&dev->open_min, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (c * 64 >= __builtin_amdgcn_readfirstlane(found)) return;
         // (the bitmaps end with a whole number of 64-bit pairs; bits beyond the last id count as visited)
@@ -251,18 +289,22 @@ __device__ __forceinline__ void search_open(const RP *__restrict__ row_ptr, cons
 
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                               const uint32_t *__restrict__ visited, uint32_t *closed, int64_t num_nodes,
-                                               uint32_t *key, Frontier f0, Frontier f1, Lists li, OrderDev *dev, int par)
+                                               int64_t num_nodes, Traversal all, int par)
 {
     __shared__ uint32_t sh_start[BW][kWave];  // per wavefront: WTILE bytes, 1 where a row begins
+    const Traversal me = all.mine();
+    OrderDev *const dev = me.dev;
+    const Lists &li = me.li;
+    const uint32_t *__restrict__ visited = me.visited;
+    uint32_t *const key = me.key;
     const Step st = dev->step[par];
     if (st.done) return;
     if (st.rows == 0) {
-        search_open(row_ptr, col, visited, closed, key, num_nodes, st.scan_lo, dev);
+        search_open(row_ptr, col, visited, me.closed, key, num_nodes, st.scan_lo, dev);
         return;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) dev->open_min = INT_MAX;  // for the next restart
-    const Frontier f = st.buf ? f1 : f0;
+    const Frontier f = st.buf ? me.f1 : me.f0;
     const uint32_t win = (uint32_t)min((unsigned long long)WINDOW, st.edges - st.win_lo);
     const uint32_t per = edges_per_wave(win);
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -365,12 +407,16 @@ __device__ __forceinline__ uint32_t closed_bits(uint32_t visited_word, int64_t w
 }
 
 template <typename RP>
-__global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, const uint32_t *__restrict__ visited,
-                                              int64_t words, const uint32_t *__restrict__ key,
-                                              const uint32_t *__restrict__ train, Lists li, const OrderDev *dev, int par)
+__global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, int64_t words,
+                                              const uint32_t *__restrict__ train, Traversal all, int par)
 {
     __shared__ uint32_t sh_rows[BW], sh_train[BW];
     __shared__ unsigned long long sh_edges[BW];
+    const Traversal me = all.mine();
+    const OrderDev *const dev = me.dev;
+    const Lists &li = me.li;
+    const uint32_t *__restrict__ visited = me.visited;
+    const uint32_t *__restrict__ key = me.key;
     const Step st = dev->step[par];
     if (st.done) return;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
@@ -469,13 +515,18 @@ __device__ __forceinline__ void block_sums(const T *totals, uint32_t mine, uint3
 }
 
 template <typename RP>
-__global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, uint32_t *visited, int64_t words,
-                                               const uint32_t *__restrict__ train, Frontier f0, Frontier f1, int32_t *seq,
-                                               Lists li, OrderDev *dev, int par, Progress *host, uint32_t step)
+__global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, int64_t words, const uint32_t *__restrict__ train,
+                                               Traversal all, int par, uint32_t step)
 {
     __shared__ uint32_t sh32[2 * BW];
     __shared__ unsigned long long sh64[2 * BW];
     __shared__ int sh_scan[BW];
+    const Traversal me = all.mine();
+    OrderDev *const dev = me.dev;
+    const Lists &li = me.li;
+    uint32_t *const visited = me.visited;
+    int32_t *const seq = me.seq;
+    Progress *const host = me.host;
     const Step st = dev->step[par];
     Step &next = dev->step[par ^ 1];
     if (st.done) {
@@ -517,8 +568,8 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
                 __hip_atomic_store(&host->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
             } else {
                 const int64_t lo = (int64_t)row_ptr[open], d = (int64_t)row_ptr[open + 1] - lo;
-                f0.off[0] = 0;
-                f0.base[0] = lo;
+                me.f0.off[0] = 0;
+                me.f0.base[0] = lo;
                 if (test_bit(train, (uint32_t)open)) seq[len++] = open;
                 next = Step{(unsigned long long)d, 0, 0, d > 0 ? 1u : 0u, 0, len, open, 0, 0};
             }
@@ -556,7 +607,7 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
         rows_at += li.wave_rows[k];
         edges_at += li.wave_edges[k];
     }
-    const Frontier f = st.buf ? f0 : f1;  // the next level's
+    const Frontier f = st.buf ? me.f0 : me.f1;  // the next level's
     uint32_t row = st.next_rows + rows_at;
     unsigned long long edge = st.next_edges + edges_at;
     int32_t pos = st.seq_len + (int32_t)train_before;
@@ -598,14 +649,12 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, u
 }
 
 struct OrderWork {
-    uint32_t *visited = nullptr, *closed = nullptr, *train = nullptr, *key = nullptr;
-    Frontier f[2];
-    Lists li;
-    int32_t *seq = nullptr, *train_ids = nullptr;
-    OrderDev *dev = nullptr;
-    Progress *host = nullptr;  // page-locked
-    Progress *host_dev = nullptr;
-    char *block = nullptr;     // the one device allocation all of the above are carved from
+    Traversal t = {};            // of the first traversal
+    int side = 1;                // traversals that run side by side
+    uint32_t *train = nullptr;
+    int32_t *train_ids = nullptr;
+    Progress *host = nullptr;    // page-locked, one per traversal
+    char *block = nullptr;       // the one device allocation all of the above are carved from
     ~OrderWork()
     {
         (void)hipFree(block);
@@ -613,102 +662,135 @@ struct OrderWork {
     }
 };
 
-int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, OrderWork &w, hipStream_t st)
+int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, int num_sequences, OrderWork &w, hipStream_t st)
 {
     const int64_t N = g->num_nodes, words = round_up(ceil_div(N, 32), 2);
-    // one device allocation for the whole call, sized up front and carved into 256-byte aligned parts
+    // one device allocation for the whole call, sized up front and carved into 256-byte aligned parts: what
+    // the traversals share, then one equal part per traversal
     const size_t nt = (size_t)std::max<int64_t>(num_train, 1);
     const size_t win = (size_t)std::max<int64_t>(std::min<int64_t>(g->num_edges, WINDOW), 1);
-    size_t total = 0;
+    size_t shared = 0, total = 0;
     char *at = nullptr;
-    auto carve = [&]() {
+    auto carve = [&](int side) {
         auto take = [&](auto *&p, size_t n) {
             p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(at + total);
             total += round_up(n * sizeof(*p), 256);
         };
         total = 0;
-        take(w.visited, (size_t)words);
-        take(w.closed, (size_t)words);
         take(w.train, (size_t)words);
-        take(w.key, (size_t)N);
-        for (int k = 0; k < 2; ++k) {
-            take(w.f[k].off, (size_t)N);
-            take(w.f[k].base, (size_t)N);
-        }
-        take(w.li.cand, win);
-        take(w.li.n_cand, WAVES);
-        take(w.li.n_win, WAVES);
-        take(w.li.wave_rows, WAVES);
-        take(w.li.wave_train, WAVES);
-        take(w.li.wave_edges, WAVES);
-        take(w.li.block_rows, BLOCKS);
-        take(w.li.block_train, BLOCKS);
-        take(w.li.block_edges, BLOCKS);
-        take(w.seq, nt);
         take(w.train_ids, nt);
-        take(w.dev, 1);
+        take(w.t.seq, nt * (size_t)side);
+        shared = total;
+        take(w.t.visited, (size_t)words);
+        take(w.t.closed, (size_t)words);
+        take(w.t.key, (size_t)N);
+        for (Frontier *f : {&w.t.f0, &w.t.f1}) {
+            take(f->off, (size_t)N);
+            take(f->base, (size_t)N);
+        }
+        take(w.t.li.cand, win);
+        take(w.t.li.n_cand, WAVES);
+        take(w.t.li.n_win, WAVES);
+        take(w.t.li.wave_rows, WAVES);
+        take(w.t.li.wave_train, WAVES);
+        take(w.t.li.wave_edges, WAVES);
+        take(w.t.li.block_rows, BLOCKS);
+        take(w.t.li.block_train, BLOCKS);
+        take(w.t.li.block_edges, BLOCKS);
+        take(w.t.dev, 1);
+        w.t.stride = (int64_t)(total - shared);
+        total = shared + (total - shared) * (size_t)side;
     };
-    carve();
-    BGL_HIP(hipMalloc((void **)&w.block, total));
+    carve(1);
+    // Side by side a traversal's small steps, which are launches and latency, cost next to nothing beside
+    // the others'.  Where the memory for that is not there, fewer at a time.
+    w.side = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(num_sequences, SIDE_BY_SIDE), SIDE_BY_SIDE_BYTES / w.t.stride));
+    for (;; w.side = (w.side + 1) / 2) {
+        carve(w.side);
+        const hipError_t e = hipMalloc((void **)&w.block, total);
+        if (e == hipSuccess) break;
+        w.block = nullptr;
+        if (e != hipErrorOutOfMemory || w.side == 1) BGL_HIP(e);
+        (void)hipGetLastError();
+    }
     at = w.block;
-    carve();
+    carve(w.side);
+    w.t.num_train = num_train;
     // (coherent whatever HIP_HOST_COHERENT says: the host reads it while kernels run)
-    BGL_HIP(hipHostMalloc((void **)&w.host, sizeof(Progress), hipHostMallocMapped | hipHostMallocCoherent));
-    BGL_HIP(hipHostGetDevicePointer((void **)&w.host_dev, w.host, 0));
-    BGL_HIP(hipMemsetAsync(w.dev, 0, sizeof(OrderDev), st));
+    BGL_HIP(hipHostMalloc((void **)&w.host, sizeof(Progress) * SIDE_BY_SIDE, hipHostMallocMapped | hipHostMallocCoherent));
+    BGL_HIP(hipHostGetDevicePointer((void **)&w.t.host, w.host, 0));
+    BGL_HIP(hipMemsetAsync(w.t.dev, 0, sizeof(OrderDev), st));
     BGL_HIP(hipMemcpyAsync(w.train_ids, train_nodes, num_train * 4, hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_fill_u32, dim3(std::min<int64_t>(ceil_div(words, BT), 4096)), dim3(BT), 0, st, w.train, words, 0u);
     if (num_train > 0)
         hipLaunchKernelGGL(k_set_bits, dim3((unsigned)ceil_div(num_train, BT)), dim3(BT), 0, st, w.train_ids,
-                           num_train, N, w.train, w.dev);
+                           num_train, N, w.train, w.t.dev);
     BGL_HIP(hipGetLastError());
-    BGL_HIP(hipMemcpyAsync(&w.host->status, &w.dev->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    BGL_HIP(hipMemcpyAsync(&w.host->status, &w.t.dev->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     BGL_HIP(hipStreamSynchronize(st));
     if (w.host->status != 0) BGL_FAIL(BGL_EINVAL, "train_nodes holds an id outside [0, num_nodes) or a repeated id");
     return BGL_OK;
 }
 
-// One traversal; leaves the sequence (num_train ids) in w.seq.
+// `count` <= w.side traversals side by side; their sequences (num_train ids each) go to seqs, in host memory.
 template <typename RP>
-int bfs_sequence(const bgl_graph *g, int64_t root, int64_t num_train, OrderWork &w, hipStream_t st)
+int bfs_sequences(const bgl_graph *g, const int64_t *roots, int count, int64_t num_train, OrderWork &w, int32_t *seqs, hipStream_t st)
 {
     const int64_t N = g->num_nodes, words = round_up(ceil_div(N, 32), 2);
     const RP *rp = static_cast<const RP *>(g->row_ptr);
-    w.host->step = w.host->done = 0;
-    hipLaunchKernelGGL(k_reset<RP>, dim3((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096)), dim3(BT), 0, st, rp, (int32_t)root,
-                       w.visited, w.closed, words, w.key, N, w.train, w.f[0], w.seq, w.dev);
-    // The device says in page-locked words which step it has come to and when the traversal has ended; the
-    // host stays STEPS_AHEAD steps ahead of it, so the queue never runs empty and at most that many steps,
+    Roots r = {};
+    for (int j = 0; j < count; ++j) {
+        r.of[j] = (int32_t)roots[j];
+        w.host[j].step = w.host[j].done = 0;
+    }
+    const dim3 reset_grid((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096), (unsigned)count);
+    hipLaunchKernelGGL(k_reset<RP>, reset_grid, dim3(BT), 0, st, rp, r, words, N, w.train, w.t);
+    // As many workgroups as the largest step of this graph has shares for.
+    const int64_t shares = std::max({ceil_div(std::min(g->num_edges, WINDOW), WTILE * BW), ceil_div(words, BT),
+                                     std::min<int64_t>(ceil_div(N, 64 * BW), SEARCH_BLOCKS), (int64_t)1});
+    const dim3 grid((unsigned)std::min<int64_t>(shares, BLOCKS), (unsigned)count);
+    // The device says in page-locked words which step each traversal has come to and when it has ended; the
+    // host stays STEPS_AHEAD steps ahead of the foremost, so the queue never runs empty and at most that many steps,
     // whose launches return at once, are enqueued beyond the end.  The calling thread spins meanwhile.  (A
-    // synchronisation every 8 to 32 steps instead: 2.2 ms for five sequences of 13 steps on 100,000 nodes,
-    // 1.7 now.)  Every step visits a
+    // synchronisation every 8 to 32 steps instead: 2.2 ms for five sequences of 13 steps on 100,000 nodes
+    // one after the other, 1.7 with the words.)  Every step visits a
     // node or ends the traversal or is one of a level's windows.
     const int64_t most = 2 * N + g->num_edges / WINDOW + 4;
     auto word = [](const uint32_t &x) { return __atomic_load_n(&x, __ATOMIC_ACQUIRE); };
-    for (int64_t step = 1; !word(w.host->done); ++step) {
+    auto all_done = [&] {
+        for (int j = 0; j < count; ++j)
+            if (!word(w.host[j].done)) return false;
+        return true;
+    };
+    auto come_to = [&] {
+        uint32_t s = 0;
+        for (int j = 0; j < count; ++j) s = std::max(s, word(w.host[j].step));
+        return (int64_t)s;
+    };
+    for (int64_t step = 1; !all_done(); ++step) {
         if (step > most + STEPS_AHEAD) BGL_FAIL(BGL_EHIP, "the traversal did not end");
         const int par = (int)((step - 1) & 1);
-        hipLaunchKernelGGL(k_expand<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, g->col, w.visited, w.closed, N, w.key, w.f[0], w.f[1], w.li,
-                           w.dev, par);
-        hipLaunchKernelGGL(k_count<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.key, w.train, w.li, w.dev, par);
-        hipLaunchKernelGGL(k_append<RP>, dim3(BLOCKS), dim3(BT), 0, st, rp, w.visited, words, w.train, w.f[0], w.f[1], w.seq,
-                           w.li, w.dev, par, w.host_dev, (uint32_t)step);
+        hipLaunchKernelGGL(k_expand<RP>, grid, dim3(BT), 0, st, rp, g->col, N, w.t, par);
+        hipLaunchKernelGGL(k_count<RP>, grid, dim3(BT), 0, st, rp, words, w.train, w.t, par);
+        hipLaunchKernelGGL(k_append<RP>, grid, dim3(BT), 0, st, rp, words, w.train, w.t, par, (uint32_t)step);
         BGL_HIP(hipGetLastError());
-        for (int64_t spins = 1; !word(w.host->done) && (uint32_t)step - word(w.host->step) >= (uint32_t)STEPS_AHEAD; ++spins) {
+        for (int64_t spins = 1; !all_done() && step - come_to() >= STEPS_AHEAD; ++spins) {
             __builtin_ia32_pause();
             // a stream that has nothing left to do, or has failed, will not come to the step waited for
             if (spins % 65536 == 0) {
                 const hipError_t e = hipStreamQuery(st);
                 if (e == hipErrorNotReady) { (void)hipGetLastError(); continue; }
                 BGL_HIP(e);
-                if (!word(w.host->done) && (uint32_t)step - word(w.host->step) >= (uint32_t)STEPS_AHEAD)
-                    BGL_FAIL(BGL_EHIP, "the traversal stopped at step %u of %lld", word(w.host->step), (long long)step);
+                if (!all_done() && step - come_to() >= STEPS_AHEAD)
+                    BGL_FAIL(BGL_EHIP, "the traversal stopped at step %lld of %lld", (long long)come_to(), (long long)step);
             }
         }
     }
-    BGL_HIP(hipStreamSynchronize(st));  // the steps beyond the end; w.host may be written anew
-    if (w.host->seq_len != num_train)
-        BGL_FAIL(BGL_EHIP, "the traversal recorded %d of %lld training nodes", w.host->seq_len, (long long)num_train);
+    BGL_HIP(hipMemcpyAsync(seqs, w.t.seq, (size_t)count * (size_t)num_train * 4, hipMemcpyDeviceToHost, st));
+    BGL_HIP(hipStreamSynchronize(st));  // the steps beyond the end too; w.host may be written anew
+    for (int j = 0; j < count; ++j)
+        if (w.host[j].seq_len != num_train)
+            BGL_FAIL(BGL_EHIP, "the traversal recorded %d of %lld training nodes", w.host[j].seq_len, (long long)num_train);
     return BGL_OK;
 }
 
@@ -731,12 +813,9 @@ try {
     if (!seq) BGL_FAIL(BGL_EINVAL, "seq is null");
     hipStream_t st = static_cast<hipStream_t>(stream);
     OrderWork w;
-    if ((rc = prepare(g, train_nodes, num_train, w, st)) != BGL_OK) return rc;
-    rc = g->bits == 64 ? bfs_sequence<int64_t>(g, root, num_train, w, st) : bfs_sequence<int32_t>(g, root, num_train, w, st);
-    if (rc != BGL_OK) return rc;
-    BGL_HIP(hipMemcpyAsync(seq, w.seq, num_train * 4, hipMemcpyDeviceToHost, st));
-    BGL_HIP(hipStreamSynchronize(st));
-    return BGL_OK;
+    if ((rc = prepare(g, train_nodes, num_train, 1, w, st)) != BGL_OK) return rc;
+    return g->bits == 64 ? bfs_sequences<int64_t>(g, &root, 1, num_train, w, seq, st)
+                         : bfs_sequences<int32_t>(g, &root, 1, num_train, w, seq, st);
 } BGL_NOTHROW_END
 
 namespace {
@@ -754,20 +833,20 @@ int check_proximity_args(const bgl_graph_t *g, const int32_t *train_nodes, int64
     return BGL_OK;
 }
 
+// Sequence j, num_train ids, begins at seqs[j * num_train].
 int compute_sequences(const bgl_graph_t *g, const int32_t *train_nodes, int64_t num_train, int32_t num_sequences,
-                      const int64_t *roots, hipStream_t st, std::vector<std::vector<int32_t>> &seqs)
+                      const int64_t *roots, hipStream_t st, std::vector<int32_t> &seqs)
 {
     OrderWork w;
-    int rc = prepare(g, train_nodes, num_train, w, st);
+    int rc = prepare(g, train_nodes, num_train, num_sequences, w, st);
     if (rc != BGL_OK) return rc;
-    seqs.assign((size_t)num_sequences, std::vector<int32_t>());
-    for (int j = 0; j < num_sequences; ++j) {
-        rc = g->bits == 64 ? bfs_sequence<int64_t>(g, roots[j], num_train, w, st)
-                           : bfs_sequence<int32_t>(g, roots[j], num_train, w, st);
+    seqs.resize((size_t)num_sequences * (size_t)num_train);
+    for (int j = 0; j < num_sequences; j += w.side) {
+        const int count = std::min(num_sequences - j, w.side);
+        int32_t *const to = seqs.data() + (size_t)j * (size_t)num_train;
+        rc = g->bits == 64 ? bfs_sequences<int64_t>(g, roots + j, count, num_train, w, to, st)
+                           : bfs_sequences<int32_t>(g, roots + j, count, num_train, w, to, st);
         if (rc != BGL_OK) return rc;
-        seqs[(size_t)j].resize((size_t)num_train);
-        BGL_HIP(hipMemcpyAsync(seqs[(size_t)j].data(), w.seq, num_train * 4, hipMemcpyDeviceToHost, st));
-        BGL_HIP(hipStreamSynchronize(st));
     }
     return BGL_OK;
 }
@@ -775,14 +854,14 @@ int compute_sequences(const bgl_graph_t *g, const int32_t *train_nodes, int64_t 
 // Turn t takes the next node of sequence t mod S that no earlier turn has taken.  One bit per node says
 // which are taken (a byte each is eight times the cache: 2.45 M nodes, two sequences of 204,800: the merge
 // takes 0.4 ms instead of 0.9).
-void merge_sequences(const std::vector<std::vector<int32_t>> &seqs, int32_t num_sequences, const int64_t *shifts,
+void merge_sequences(const std::vector<int32_t> &seqs, int32_t num_sequences, const int64_t *shifts,
                      int64_t num_train, int64_t num_nodes, int64_t num_out, int32_t *order)
 {
     std::vector<uint64_t> used((size_t)ceil_div(num_nodes, 64), 0);
     std::vector<int64_t> at(shifts, shifts + num_sequences);  // next place of each sequence, cyclically from its shift
     for (int64_t k = 0; k < num_out;) {
         for (int32_t j = 0; j < num_sequences && k < num_out; ++j, ++k) {
-            const int32_t *seq = seqs[(size_t)j].data();
+            const int32_t *seq = seqs.data() + (size_t)j * (size_t)num_train;
             int64_t c = at[(size_t)j];
             int32_t v;
             do {
@@ -806,7 +885,7 @@ try {
     if (rc != BGL_OK) return rc;
     if (num_out < 0 || num_out > num_train) BGL_FAIL(BGL_EINVAL, "num_out must be in [0, num_train]");
     if (num_out > 0 && !order) BGL_FAIL(BGL_EINVAL, "order is null");
-    std::vector<std::vector<int32_t>> seqs;
+    std::vector<int32_t> seqs;
     rc = compute_sequences(g, train_nodes, num_train, num_sequences, roots, static_cast<hipStream_t>(stream), seqs);
     if (rc != BGL_OK) return rc;
     merge_sequences(seqs, num_sequences, shifts, num_train, g->num_nodes, num_out, order);
@@ -822,7 +901,7 @@ try {
     int rc = check_proximity_args(g, train_nodes, num_train, max_sequences, roots, shifts);
     if (rc != BGL_OK) return rc;
     if (!labels || !chosen || !order) BGL_FAIL(BGL_EINVAL, "labels, chosen and order must not be null");
-    std::vector<std::vector<int32_t>> seqs;
+    std::vector<int32_t> seqs;
     rc = compute_sequences(g, train_nodes, num_train, max_sequences, roots, static_cast<hipStream_t>(stream), seqs);
     if (rc != BGL_OK) return rc;
     for (int32_t s = 1; s <= max_sequences; ++s) {

@@ -191,6 +191,26 @@ def test_bfs_sequence_chain_of_open_components(B):
         assert got.tolist() == oracle.bfs_sequence(rp, col, np.arange(N), root).tolist()
 
 
+@pytest.mark.parametrize("sequences", [2, 15, 16, 17, 34])
+def test_traversals_side_by_side_are_independent(B, sequences):
+    """Traversals of one call share their launches, 16 at a time, and end after different numbers of steps:
+    roots in a long path, in random components and in isolated nodes."""
+    import oracle
+    rng = np.random.default_rng(sequences)
+    path, N = 150, 9_000
+    rp, col = random_graph(rng, N, 5)
+    adj = [[v + 1] for v in range(path)] + [(col[rp[v]:rp[v + 1]]).tolist() for v in range(path, N)]
+    rp[1:] = np.cumsum([len(a) for a in adj])
+    col = np.array([u for a in adj for u in a], dtype=np.int32)
+    g = B.Graph(rp, col)
+    train = rng.choice(N, 1_300, replace=False)
+    roots = rng.integers(0, N, sequences)
+    roots[0], roots[-1] = 0, int(np.argmin(np.diff(rp)))
+    shifts = rng.integers(0, len(train), sequences)
+    got = B.order_proximity(g, train, roots, shifts, len(train))
+    assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, len(train)))
+
+
 def test_proximity_order_and_shuffling_error_mid_size(B):
     """The bfs configuration's graph at full size: 5 sequences over 204,800 training nodes."""
     import oracle
