@@ -48,6 +48,8 @@ constexpr int BT = 256;
 constexpr int BW = BT / kWave;               // wavefronts per workgroup
 constexpr int BLOCKS = 2048;                 // workgroups of a step's kernels (those without a share leave at once)
 constexpr int WAVES = BLOCKS * BW;
+constexpr int GROUPS = BLOCKS / kWave;       // groups of 64 workgroups whose totals are added up
+static_assert(GROUPS <= kWave && BW >= 2, "a wavefront sums the groups, another one a group's workgroups");
 constexpr int WTILE = 4 * kWave;             // edges a wavefront handles at a time, four per lane
 constexpr int64_t WINDOW = 1 << 23;          // edges per step at most
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
@@ -93,14 +95,21 @@ struct Frontier {
     int64_t *base;             // the row's first column index - off
 };
 
+// New nodes of a window: how many have out-edges (upper half) and how many are training nodes (lower half; a
+// window has fewer than 2^31 of either), and their out-edges.
+struct Totals {
+    unsigned long long nodes, edges;
+    __device__ __forceinline__ uint32_t rows() const { return (uint32_t)(nodes >> 32); }
+    __device__ __forceinline__ uint32_t train() const { return (uint32_t)nodes; }
+    __device__ __forceinline__ Totals &operator+=(const Totals &o) { nodes += o.nodes; edges += o.edges; return *this; }
+};
+
 // The lists and totals of a step: one share per wavefront.
 struct Lists {
     unsigned long long *cand;      // WINDOW entries: k_expand: target << 32 | edge; k_count: training bit << 63 | degree << 32 | node
     uint32_t *n_cand, *n_win;      // per wavefront
-    uint32_t *wave_rows, *wave_train;
-    unsigned long long *wave_edges;
-    uint32_t *block_rows, *block_train;
-    unsigned long long *block_edges;
+    Totals *wave, *block;          // of a wavefront's, of a workgroup's first edges
+    Totals *group;                 // of 64 workgroups'
 };
 
 // What one traversal works on.  The traversals of a call run side by side, blockIdx.y says which: their
@@ -122,8 +131,7 @@ struct Traversal {
         move(t.visited), move(t.closed), move(t.key);
         move(t.f0.off), move(t.f0.base), move(t.f1.off), move(t.f1.base);
         move(t.li.cand), move(t.li.n_cand), move(t.li.n_win);
-        move(t.li.wave_rows), move(t.li.wave_train), move(t.li.wave_edges);
-        move(t.li.block_rows), move(t.li.block_train), move(t.li.block_edges);
+        move(t.li.wave), move(t.li.block), move(t.li.group);
         move(t.dev);
         t.seq += (int64_t)blockIdx.y * num_train;
         t.host += blockIdx.y;
@@ -299,6 +307,7 @@ __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, c
     uint32_t *const key = me.key;
     const Step st = dev->step[par];
     if (st.done) return;
+    if (blockIdx.x == 0 && threadIdx.x < GROUPS) li.group[threadIdx.x] = Totals{0, 0};  // for k_count
     if (st.rows == 0) {
         search_open(row_ptr, col, visited, me.closed, key, num_nodes, st.scan_lo, dev);
         return;
@@ -372,18 +381,13 @@ __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, c
     if (lane == 0) li.n_cand[wave] = n_cand;
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
-{
-#pragma unroll
-    for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
-    return v;
-}
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v)
 {
 #pragma unroll
     for (int d = kWave / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, kWave);
     return v;
 }
+__device__ __forceinline__ Totals wave_sum(const Totals &t) { return Totals{wave_sum(t.nodes), wave_sum(t.edges)}; }
 
 // Restart: the bitmap words that may hold closed nodes to take, an equal run of them per workgroup.
 struct WordRange {
@@ -410,8 +414,7 @@ template <typename RP>
 __global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, int64_t words,
                                               const uint32_t *__restrict__ train, Traversal all, int par)
 {
-    __shared__ uint32_t sh_rows[BW], sh_train[BW];
-    __shared__ unsigned long long sh_edges[BW];
+    __shared__ Totals sh[BW];
     const Traversal me = all.mine();
     const OrderDev *const dev = me.dev;
     const Lists &li = me.li;
@@ -420,14 +423,13 @@ __global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, in
     const Step st = dev->step[par];
     if (st.done) return;
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    uint32_t n_rows = 0, n_train = 0;
-    unsigned long long n_edges = 0;
+    Totals mine = {0, 0};
     if (st.rows == 0) {
         const WordRange wr(st.scan_lo, dev->open_min, words);
         if (wr.begin_of(blockIdx.x) >= wr.end) return;
         for (int64_t i = wr.begin_of(blockIdx.x) + threadIdx.x; i < wr.end_of(blockIdx.x); i += BT)
-            n_train += (uint32_t)__popc(closed_bits(visited[i], i, dev->open_min) & train[i]);
-        n_train = wave_sum(n_train);
+            mine.nodes += (uint32_t)__popc(closed_bits(visited[i], i, dev->open_min) & train[i]);
+        mine = wave_sum(mine);
     } else {
         const uint32_t win = (uint32_t)min((unsigned long long)WINDOW, st.edges - st.win_lo);
         const uint32_t per = edges_per_wave(win);
@@ -462,64 +464,59 @@ __global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, in
                 const uint64_t b = __ballot(first[j]);
                 if (first[j]) {
                     li.cand[lo + n_win + __popcll(b & ((1ull << lane) - 1ull))] = d[j] << 32 | c[j] >> 32;
-                    n_rows += (d[j] & 0x7fffffffu) > 0;
-                    n_edges += d[j] & 0x7fffffffu;
-                    n_train += (uint32_t)(d[j] >> 31);
+                    const uint32_t degree = (uint32_t)d[j] & 0x7fffffffu;
+                    mine += Totals{(unsigned long long)(degree > 0) << 32 | d[j] >> 31, degree};
                 }
                 n_win += (uint32_t)__popcll(b);
             }
         }
-        n_rows = wave_sum(n_rows);
-        n_train = wave_sum(n_train);
-        n_edges = wave_sum(n_edges);
+        mine = wave_sum(mine);
         if (lane == 0) {
             li.n_win[wave] = n_win;
-            li.wave_rows[wave] = n_rows;
-            li.wave_train[wave] = n_train;
-            li.wave_edges[wave] = n_edges;
+            li.wave[wave] = mine;
         }
     }
-    if (lane == 0) { sh_rows[w] = n_rows; sh_train[w] = n_train; sh_edges[w] = n_edges; }
+    if (lane == 0) sh[w] = mine;
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t r = 0, t = 0;
-        unsigned long long e = 0;
+        Totals all = {0, 0};
 #pragma unroll
-        for (int k = 0; k < BW; ++k) { r += sh_rows[k]; t += sh_train[k]; e += sh_edges[k]; }
-        li.block_rows[blockIdx.x] = r;
-        li.block_train[blockIdx.x] = t;
-        li.block_edges[blockIdx.x] = e;
+        for (int k = 0; k < BW; ++k) all += sh[k];
+        li.block[blockIdx.x] = all;
+        Totals *group = &li.group[blockIdx.x / kWave];
+        if (all.nodes) atomicAdd(&group->nodes, all.nodes);
+        if (all.edges) atomicAdd(&group->edges, all.edges);
     }
 }
 
-// Sums of the first `mine` and of all `n` per-workgroup totals, by the whole workgroup.
-template <typename T>
-__device__ __forceinline__ void block_sums(const T *totals, uint32_t mine, uint32_t n, T *sh, T &before, T &all)
-{
-    T b = 0, a = 0;
-    for (uint32_t i = threadIdx.x; i < n; i += BT) {
-        const T v = totals[i];
-        a += v;
-        if (i < mine) b += v;
+// Totals of the workgroups before this one and of all, by the whole workgroup: one wavefront sums the groups, another the
+// workgroups before this one in its own group.  (With every workgroup adding up the totals of all 2,048 a step
+// of 8 M edges spent a third of k_append on it.)
+struct Before {
+    Totals before, all;
+    __device__ __forceinline__ Before(const Lists &li, uint32_t block, Totals *sh)  // sh: three
+    {
+        const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, group = block / kWave;
+        if (w == 0) {
+            const Totals g = lane < GROUPS ? li.group[lane] : Totals{0, 0};
+            const Totals every = wave_sum(g), lower = wave_sum(lane < group ? g : Totals{0, 0});
+            if (lane == 0) { sh[0] = every; sh[1] = lower; }
+        } else if (w == 1) {
+            const Totals own = wave_sum(group * kWave + lane < block ? li.block[group * kWave + lane] : Totals{0, 0});
+            if (lane == 0) sh[2] = own;
+        }
+        __syncthreads();
+        all = sh[0];
+        before = sh[1];
+        before += sh[2];
     }
-    b = wave_sum(b);
-    a = wave_sum(a);
-    const int w = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) { sh[w] = b; sh[BW + w] = a; }
-    __syncthreads();
-    before = 0;
-    all = 0;
-#pragma unroll
-    for (int k = 0; k < BW; ++k) { before += sh[k]; all += sh[BW + k]; }
-    __syncthreads();
-}
+};
 
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, int64_t words, const uint32_t *__restrict__ train,
                                                Traversal all, int par, uint32_t step)
 {
-    __shared__ uint32_t sh32[2 * BW];
-    __shared__ unsigned long long sh64[2 * BW];
+    __shared__ Totals sh[3];
     __shared__ int sh_scan[BW];
     const Traversal me = all.mine();
     OrderDev *const dev = me.dev;
@@ -536,14 +533,12 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
     // (the step is under way: the host may enqueue another)
     if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(&host->step, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    uint32_t train_before, train_all;
     if (st.rows == 0) {
         const int open = dev->open_min;
         const WordRange wr(st.scan_lo, open, words);
         if (blockIdx.x > 0 && wr.begin_of(blockIdx.x) >= wr.end) return;
-        const uint32_t blocks = wr.per > 0 ? (uint32_t)((wr.end - wr.first + wr.per - 1) / wr.per) : 0u;
-        block_sums(li.block_train, blockIdx.x, blocks, sh32, train_before, train_all);
-        int32_t o = st.seq_len + (int32_t)train_before;
+        const Before t(li, blockIdx.x, sh);
+        int32_t o = st.seq_len + (int32_t)t.before.train();
         for (int64_t i0 = wr.begin_of(blockIdx.x); i0 < wr.end_of(blockIdx.x); i0 += BT) {  // uniform in the workgroup
             const int64_t i = i0 + threadIdx.x;
             uint32_t m = 0;
@@ -561,7 +556,7 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
             o += tot;
         }
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            int32_t len = st.seq_len + (int32_t)train_all;
+            int32_t len = st.seq_len + (int32_t)t.all.train();
             if (open == INT_MAX) {  // everything that was left was closed
                 next = Step{0, 0, 0, 0, 0, len, st.scan_lo, 0, 1};
                 host->seq_len = len;
@@ -579,17 +574,12 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
     const uint32_t win = (uint32_t)min((unsigned long long)WINDOW, st.edges - st.win_lo);
     const uint32_t per = edges_per_wave(win);
     if ((unsigned long long)blockIdx.x * BW * per >= win) return;
-    const uint32_t blocks = (win + BW * per - 1) / (BW * per);
-    uint32_t rows_at, rows_all;
-    unsigned long long edges_at, edges_all;
-    block_sums(li.block_train, blockIdx.x, blocks, sh32, train_before, train_all);
-    block_sums(li.block_rows, blockIdx.x, blocks, sh32, rows_at, rows_all);
-    block_sums(li.block_edges, blockIdx.x, blocks, sh64, edges_at, edges_all);
+    const Before t(li, blockIdx.x, sh);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         Step n = st;
-        n.next_rows += rows_all;
-        n.next_edges += edges_all;
-        n.seq_len += (int32_t)train_all;
+        n.next_rows += t.all.rows();
+        n.next_edges += t.all.edges;
+        n.seq_len += (int32_t)t.all.train();
         n.win_lo += WINDOW;
         if (n.win_lo >= st.edges) {  // that was the level's last window
             n.edges = n.next_edges;
@@ -602,15 +592,12 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
     }
     const uint32_t wave = blockIdx.x * BW + w;
     if ((unsigned long long)wave * per >= win) return;
-    for (uint32_t k = blockIdx.x * BW; k < wave; ++k) {  // the wavefronts before this one in its workgroup
-        train_before += li.wave_train[k];
-        rows_at += li.wave_rows[k];
-        edges_at += li.wave_edges[k];
-    }
+    Totals at = t.before;
+    for (uint32_t k = blockIdx.x * BW; k < wave; ++k) at += li.wave[k];  // the wavefronts before this one in its workgroup
     const Frontier f = st.buf ? me.f0 : me.f1;  // the next level's
-    uint32_t row = st.next_rows + rows_at;
-    unsigned long long edge = st.next_edges + edges_at;
-    int32_t pos = st.seq_len + (int32_t)train_before;
+    uint32_t row = st.next_rows + at.rows();
+    unsigned long long edge = st.next_edges + at.edges;
+    int32_t pos = st.seq_len + (int32_t)at.train();
     const uint32_t n = li.n_win[wave], lo = wave * per;
     for (uint32_t i0 = 0; i0 < n; i0 += 4 * kWave) {  // four groups of 64 at a time, as in k_count
         unsigned long long c[4];
@@ -691,12 +678,9 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
         take(w.t.li.cand, win);
         take(w.t.li.n_cand, WAVES);
         take(w.t.li.n_win, WAVES);
-        take(w.t.li.wave_rows, WAVES);
-        take(w.t.li.wave_train, WAVES);
-        take(w.t.li.wave_edges, WAVES);
-        take(w.t.li.block_rows, BLOCKS);
-        take(w.t.li.block_train, BLOCKS);
-        take(w.t.li.block_edges, BLOCKS);
+        take(w.t.li.wave, WAVES);
+        take(w.t.li.block, BLOCKS);
+        take(w.t.li.group, GROUPS);
         take(w.t.dev, 1);
         w.t.stride = (int64_t)(total - shared);
         total = shared + (total - shared) * (size_t)side;
