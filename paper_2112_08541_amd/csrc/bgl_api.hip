@@ -2,6 +2,7 @@
 // graph handle (CSR validation and placement in HBM or page-locked host memory;
 // the graph structure that the samplers of the BGL paper's Sec. 3.1 work on).
 #include <cstring>
+#include <utility>
 
 #include "bgl_internal.h"
 
@@ -15,6 +16,47 @@ void set_error(const char *fmt, ...)
     va_start(ap, fmt);
     vsnprintf(g_err, sizeof(g_err), fmt, ap);
     va_end(ap);
+}
+
+void order_scratch_free(OrderScratch &s)
+{
+    if (s.device) (void)hipFree(s.device);
+    if (s.host) (void)hipHostFree(s.host);
+    s = OrderScratch();
+}
+
+int order_scratch_take(const bgl_graph *g, size_t device_bytes, size_t host_bytes, OrderScratch &s)
+{
+    int ordinal = -1;
+    BGL_HIP(hipGetDevice(&ordinal));
+    {
+        std::lock_guard<std::mutex> lk(g->order_guard);
+        std::swap(s, g->order_scratch);
+    }
+    if (s.device_bytes >= device_bytes && s.host_bytes >= host_bytes && s.ordinal == ordinal) return BGL_OK;
+    order_scratch_free(s);
+    s.ordinal = ordinal;
+    hipError_t e = hipMalloc(&s.device, device_bytes);
+    if (e != hipSuccess) s.device = nullptr;
+    else if ((e = hipHostMalloc(&s.host, host_bytes, hipHostMallocMapped | hipHostMallocCoherent)) != hipSuccess) s.host = nullptr;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        order_scratch_free(s);
+        BGL_FAIL(e == hipErrorOutOfMemory ? BGL_ENOMEM : BGL_EHIP, "%zu bytes of device and %zu of page-locked memory: %s", device_bytes,
+                 host_bytes, hipGetErrorString(e));
+    }
+    s.device_bytes = device_bytes;
+    s.host_bytes = host_bytes;
+    return BGL_OK;
+}
+
+bool order_scratch_put(const bgl_graph *g, OrderScratch &s)
+{
+    if (s.device_bytes > ORDER_KEEP_DEVICE_BYTES || s.host_bytes > ORDER_KEEP_HOST_BYTES) return false;
+    std::lock_guard<std::mutex> lk(g->order_guard);
+    if (g->order_scratch.device) return false;
+    std::swap(s, g->order_scratch);
+    return true;
 }
 
 }  // namespace bgl
@@ -140,6 +182,7 @@ try {
     if (!g) return BGL_OK;
     (void)hipFree(g->owned_row_ptr);
     (void)hipFree(g->owned_col);
+    bgl::order_scratch_free(g->order_scratch);
     delete g;
     return BGL_OK;
 } BGL_NOTHROW_END

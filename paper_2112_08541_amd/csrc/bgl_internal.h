@@ -9,6 +9,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <exception>
+#include <mutex>
 #include <new>
 
 #include "bgl.h"
@@ -60,6 +61,26 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 }  // namespace bgl
 
 // ----------------------------------------------------------------- handles
+namespace bgl {
+
+// Scratch of an ordering call: device memory, and page-locked host memory that is coherent whatever
+// HIP_HOST_COHERENT says.  A graph keeps what its last call used for the next one: freeing 100 MB or more
+// costs 0.25 ms.  It holds one of each at most, up to the sizes below, and frees them with the graph; a call that
+// finds them taken by another thread's allocates its own.
+struct OrderScratch {
+    void *device = nullptr, *host = nullptr;
+    size_t device_bytes = 0, host_bytes = 0;
+    int ordinal = -1;  // the device's
+};
+constexpr size_t ORDER_KEEP_DEVICE_BYTES = (size_t)5 << 28;  // (1.25 GiB)
+constexpr size_t ORDER_KEEP_HOST_BYTES = (size_t)64 << 20;
+int order_scratch_take(const bgl_graph *g, size_t device_bytes, size_t host_bytes, OrderScratch &s);
+// False: not kept, s is still the caller's.  Nothing enqueued may use s any more.
+bool order_scratch_put(const bgl_graph *g, OrderScratch &s);
+void order_scratch_free(OrderScratch &s);
+
+}  // namespace bgl
+
 struct bgl_graph {
     const void *row_ptr;  // device-visible
     const int32_t *col;   // device-visible
@@ -70,6 +91,8 @@ struct bgl_graph {
     void *owned_row_ptr;  // hipMalloc'd copies (BGL_DEVICE), else null
     void *owned_col;
     int device;
+    mutable std::mutex order_guard;
+    mutable bgl::OrderScratch order_scratch;
 };
 
 // ----------------------------------------------------------------- device helpers

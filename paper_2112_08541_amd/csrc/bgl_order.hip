@@ -56,7 +56,8 @@ constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the res
 constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
 constexpr int SIDE_BY_SIDE = 16;             // traversals that share their launches at most
-constexpr int64_t SIDE_BY_SIDE_BYTES = 2ll << 30;  // and the memory they may take together (one alone: whatever it needs)
+constexpr int64_t SIDE_BY_SIDE_BYTES = 1ll << 30;  // and the memory they may take together (one alone: whatever it needs)
+constexpr size_t PAGE_LOCKED_SEQ_BYTES = 32 << 20;  // sequences of a call that still go to page-locked memory
 // A node's key: below WINDOW the smallest edge of the current window that reaches it (it is visited by the
 // end of the step), else none, and the excess says how many leading edges of its own row are known to end
 // at visited nodes (search_open; rows have fewer than 2^31 edges).
@@ -78,7 +79,6 @@ struct Step {
 struct OrderDev {
     Step step[2];
     int open_min;   // restart: smallest unvisited node that has an unvisited out-neighbor
-    int status;
 };
 
 // What the host sees of a traversal (page-locked memory).
@@ -86,7 +86,7 @@ struct Progress {
     uint32_t step;    // the last step that has begun to append, from 1
     uint32_t done;    // the traversal has ended
     int32_t seq_len;  // then: training nodes recorded
-    int32_t status;
+    int32_t status;   // of the call, in the first one's
 };
 
 // One level's nodes that have out-edges, in queue order.
@@ -151,14 +151,14 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
     for (; i < n; i += stride) p[i] = v;
 }
 
-__global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uint32_t *bm, OrderDev *dev)
+__global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uint32_t *bm, Progress *host)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t v = ids[i];
-    if (v < 0 || (int64_t)v >= num_nodes) { dev->status = BGL_EINVAL; return; }
+    if (v < 0 || (int64_t)v >= num_nodes) { host->status = BGL_EINVAL; return; }
     const uint32_t old = atomicOr(&bm[(uint32_t)v >> 5], 1u << (v & 31));
-    if (old & (1u << (v & 31))) dev->status = BGL_EINVAL;  // listed twice
+    if (old & (1u << (v & 31))) host->status = BGL_EINVAL;  // listed twice
 }
 
 // A fresh traversal from its root: no keys, nothing visited but the root (bits at and above num_nodes
@@ -636,16 +636,21 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
 }
 
 struct OrderWork {
+    const bgl_graph *g;
     Traversal t = {};            // of the first traversal
     int side = 1;                // traversals that run side by side
     uint32_t *train = nullptr;
     int32_t *train_ids = nullptr;
     Progress *host = nullptr;    // page-locked, one per traversal
-    char *block = nullptr;       // the one device allocation all of the above are carved from
+    int32_t *seqs = nullptr;     // host memory: num_train ids per sequence of the call
+    std::vector<int32_t> pageable;  // the same where they are too many to be page-locked
+    bgl::OrderScratch scratch;   // what all of the above are carved from
+    bool keep = false;           // nothing enqueued uses the scratch any more
+    explicit OrderWork(const bgl_graph *g_) : g(g_) {}
+    OrderWork(const OrderWork &) = delete;
     ~OrderWork()
     {
-        (void)hipFree(block);
-        if (host) (void)hipHostFree(host);
+        if (!keep || !bgl::order_scratch_put(g, scratch)) bgl::order_scratch_free(scratch);
     }
 };
 
@@ -689,42 +694,46 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
     // Side by side a traversal's small steps, which are launches and latency, cost next to nothing beside
     // the others'.  Where the memory for that is not there, fewer at a time.
     w.side = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(num_sequences, SIDE_BY_SIDE), SIDE_BY_SIDE_BYTES / w.t.stride));
+    const size_t seq_bytes = sizeof(int32_t) * nt * (size_t)num_sequences;
+    const size_t host_bytes = sizeof(Progress) * SIDE_BY_SIDE + (seq_bytes <= PAGE_LOCKED_SEQ_BYTES ? seq_bytes : 0);
     for (;; w.side = (w.side + 1) / 2) {
         carve(w.side);
-        const hipError_t e = hipMalloc((void **)&w.block, total);
-        if (e == hipSuccess) break;
-        w.block = nullptr;
-        if (e != hipErrorOutOfMemory || w.side == 1) BGL_HIP(e);
-        (void)hipGetLastError();
+        const int rc = bgl::order_scratch_take(g, total, host_bytes, w.scratch);
+        if (rc == BGL_OK) break;
+        if (rc != BGL_ENOMEM || w.side == 1) return rc;
     }
-    at = w.block;
+    at = static_cast<char *>(w.scratch.device);
     carve(w.side);
     w.t.num_train = num_train;
-    // (coherent whatever HIP_HOST_COHERENT says: the host reads it while kernels run)
-    BGL_HIP(hipHostMalloc((void **)&w.host, sizeof(Progress) * SIDE_BY_SIDE, hipHostMallocMapped | hipHostMallocCoherent));
+    w.host = static_cast<Progress *>(w.scratch.host);
+    w.host[0].status = 0;
     BGL_HIP(hipHostGetDevicePointer((void **)&w.t.host, w.host, 0));
-    BGL_HIP(hipMemsetAsync(w.t.dev, 0, sizeof(OrderDev), st));
-    BGL_HIP(hipMemcpyAsync(w.train_ids, train_nodes, num_train * 4, hipMemcpyHostToDevice, st));
+    const int32_t *ids = train_nodes;
+    if (seq_bytes <= PAGE_LOCKED_SEQ_BYTES) {
+        w.seqs = reinterpret_cast<int32_t *>(w.host + SIDE_BY_SIDE);
+        ids = static_cast<const int32_t *>(std::memcpy(w.seqs, train_nodes, sizeof(int32_t) * (size_t)num_train));
+    } else {
+        w.pageable.resize(nt * (size_t)num_sequences);
+        w.seqs = w.pageable.data();
+    }
+    BGL_HIP(hipMemcpyAsync(w.train_ids, ids, sizeof(int32_t) * (size_t)num_train, hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_fill_u32, dim3(std::min<int64_t>(ceil_div(words, BT), 4096)), dim3(BT), 0, st, w.train, words, 0u);
-    if (num_train > 0)
-        hipLaunchKernelGGL(k_set_bits, dim3((unsigned)ceil_div(num_train, BT)), dim3(BT), 0, st, w.train_ids,
-                           num_train, N, w.train, w.t.dev);
+    // (ids that are refused leave the traversals nothing to record: the status is looked at when they are over)
+    hipLaunchKernelGGL(k_set_bits, dim3((unsigned)ceil_div(num_train, BT)), dim3(BT), 0, st, w.train_ids, num_train, N, w.train,
+                       w.t.host);
     BGL_HIP(hipGetLastError());
-    BGL_HIP(hipMemcpyAsync(&w.host->status, &w.t.dev->status, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    BGL_HIP(hipStreamSynchronize(st));
-    if (w.host->status != 0) BGL_FAIL(BGL_EINVAL, "train_nodes holds an id outside [0, num_nodes) or a repeated id");
     return BGL_OK;
 }
 
-// `count` <= w.side traversals side by side; their sequences (num_train ids each) go to seqs, in host memory.
+// `count` <= w.side traversals side by side: sequences number first, first + 1, ... of the call.
 template <typename RP>
-int bfs_sequences(const bgl_graph *g, const int64_t *roots, int count, int64_t num_train, OrderWork &w, int32_t *seqs, hipStream_t st)
+int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count, int64_t num_train, OrderWork &w, hipStream_t st)
 {
     const int64_t N = g->num_nodes, words = round_up(ceil_div(N, 32), 2);
     const RP *rp = static_cast<const RP *>(g->row_ptr);
     Roots r = {};
     for (int j = 0; j < count; ++j) {
-        r.of[j] = (int32_t)roots[j];
+        r.of[j] = (int32_t)roots[first + j];
         w.host[j].step = w.host[j].done = 0;
     }
     const dim3 reset_grid((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096), (unsigned)count);
@@ -770,11 +779,32 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int count, int64_t n
             }
         }
     }
-    BGL_HIP(hipMemcpyAsync(seqs, w.t.seq, (size_t)count * (size_t)num_train * 4, hipMemcpyDeviceToHost, st));
+    const size_t one = (size_t)num_train;
+    BGL_HIP(hipMemcpyAsync(w.seqs + one * (size_t)first, w.t.seq, sizeof(int32_t) * one * (size_t)count, hipMemcpyDeviceToHost, st));
     BGL_HIP(hipStreamSynchronize(st));  // the steps beyond the end too; w.host may be written anew
+    if (w.host->status != 0) {
+        w.keep = true;
+        BGL_FAIL(BGL_EINVAL, "train_nodes holds an id outside [0, num_nodes) or a repeated id");
+    }
     for (int j = 0; j < count; ++j)
         if (w.host[j].seq_len != num_train)
             BGL_FAIL(BGL_EHIP, "the traversal recorded %d of %lld training nodes", w.host[j].seq_len, (long long)num_train);
+    return BGL_OK;
+}
+
+// Leaves sequence j, num_train ids, at w.seqs[j * num_train].
+int compute_sequences(const bgl_graph_t *g, const int32_t *train_nodes, int64_t num_train, int32_t num_sequences,
+                      const int64_t *roots, hipStream_t st, OrderWork &w)
+{
+    int rc = prepare(g, train_nodes, num_train, num_sequences, w, st);
+    if (rc != BGL_OK) return rc;
+    for (int j = 0; j < num_sequences; j += w.side) {
+        const int count = std::min(num_sequences - j, w.side);
+        rc = g->bits == 64 ? bfs_sequences<int64_t>(g, roots, j, count, num_train, w, st)
+                           : bfs_sequences<int32_t>(g, roots, j, count, num_train, w, st);
+        if (rc != BGL_OK) return rc;
+    }
+    w.keep = true;
     return BGL_OK;
 }
 
@@ -796,10 +826,10 @@ try {
     if (root < 0 || root >= g->num_nodes) BGL_FAIL(BGL_EINVAL, "root is outside [0, num_nodes)");
     if (!seq) BGL_FAIL(BGL_EINVAL, "seq is null");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    OrderWork w;
-    if ((rc = prepare(g, train_nodes, num_train, 1, w, st)) != BGL_OK) return rc;
-    return g->bits == 64 ? bfs_sequences<int64_t>(g, &root, 1, num_train, w, seq, st)
-                         : bfs_sequences<int32_t>(g, &root, 1, num_train, w, seq, st);
+    OrderWork w(g);
+    if ((rc = compute_sequences(g, train_nodes, num_train, 1, &root, st, w)) != BGL_OK) return rc;
+    std::memcpy(seq, w.seqs, sizeof(int32_t) * (size_t)num_train);
+    return BGL_OK;
 } BGL_NOTHROW_END
 
 namespace {
@@ -817,35 +847,17 @@ int check_proximity_args(const bgl_graph_t *g, const int32_t *train_nodes, int64
     return BGL_OK;
 }
 
-// Sequence j, num_train ids, begins at seqs[j * num_train].
-int compute_sequences(const bgl_graph_t *g, const int32_t *train_nodes, int64_t num_train, int32_t num_sequences,
-                      const int64_t *roots, hipStream_t st, std::vector<int32_t> &seqs)
-{
-    OrderWork w;
-    int rc = prepare(g, train_nodes, num_train, num_sequences, w, st);
-    if (rc != BGL_OK) return rc;
-    seqs.resize((size_t)num_sequences * (size_t)num_train);
-    for (int j = 0; j < num_sequences; j += w.side) {
-        const int count = std::min(num_sequences - j, w.side);
-        int32_t *const to = seqs.data() + (size_t)j * (size_t)num_train;
-        rc = g->bits == 64 ? bfs_sequences<int64_t>(g, roots + j, count, num_train, w, to, st)
-                           : bfs_sequences<int32_t>(g, roots + j, count, num_train, w, to, st);
-        if (rc != BGL_OK) return rc;
-    }
-    return BGL_OK;
-}
-
 // Turn t takes the next node of sequence t mod S that no earlier turn has taken.  One bit per node says
 // which are taken (a byte each is eight times the cache: 2.45 M nodes, two sequences of 204,800: the merge
 // takes 0.4 ms instead of 0.9).
-void merge_sequences(const std::vector<int32_t> &seqs, int32_t num_sequences, const int64_t *shifts,
+void merge_sequences(const int32_t *seqs, int32_t num_sequences, const int64_t *shifts,
                      int64_t num_train, int64_t num_nodes, int64_t num_out, int32_t *order)
 {
     std::vector<uint64_t> used((size_t)ceil_div(num_nodes, 64), 0);
     std::vector<int64_t> at(shifts, shifts + num_sequences);  // next place of each sequence, cyclically from its shift
     for (int64_t k = 0; k < num_out;) {
         for (int32_t j = 0; j < num_sequences && k < num_out; ++j, ++k) {
-            const int32_t *seq = seqs.data() + (size_t)j * (size_t)num_train;
+            const int32_t *seq = seqs + (size_t)j * (size_t)num_train;
             int64_t c = at[(size_t)j];
             int32_t v;
             do {
@@ -869,10 +881,10 @@ try {
     if (rc != BGL_OK) return rc;
     if (num_out < 0 || num_out > num_train) BGL_FAIL(BGL_EINVAL, "num_out must be in [0, num_train]");
     if (num_out > 0 && !order) BGL_FAIL(BGL_EINVAL, "order is null");
-    std::vector<int32_t> seqs;
-    rc = compute_sequences(g, train_nodes, num_train, num_sequences, roots, static_cast<hipStream_t>(stream), seqs);
+    OrderWork w(g);
+    rc = compute_sequences(g, train_nodes, num_train, num_sequences, roots, static_cast<hipStream_t>(stream), w);
     if (rc != BGL_OK) return rc;
-    merge_sequences(seqs, num_sequences, shifts, num_train, g->num_nodes, num_out, order);
+    merge_sequences(w.seqs, num_sequences, shifts, num_train, g->num_nodes, num_out, order);
     return BGL_OK;
 } BGL_NOTHROW_END
 
@@ -885,11 +897,11 @@ try {
     int rc = check_proximity_args(g, train_nodes, num_train, max_sequences, roots, shifts);
     if (rc != BGL_OK) return rc;
     if (!labels || !chosen || !order) BGL_FAIL(BGL_EINVAL, "labels, chosen and order must not be null");
-    std::vector<int32_t> seqs;
-    rc = compute_sequences(g, train_nodes, num_train, max_sequences, roots, static_cast<hipStream_t>(stream), seqs);
+    OrderWork w(g);
+    rc = compute_sequences(g, train_nodes, num_train, max_sequences, roots, static_cast<hipStream_t>(stream), w);
     if (rc != BGL_OK) return rc;
     for (int32_t s = 1; s <= max_sequences; ++s) {
-        merge_sequences(seqs, s, shifts, num_train, g->num_nodes, num_train, order);
+        merge_sequences(w.seqs, s, shifts, num_train, g->num_nodes, num_train, order);
         double mean_tv = 0.0, max_tv = 0.0;
         rc = bgl_order_shuffling_error(order, num_train, batch, labels, g->num_nodes, num_classes, &mean_tv, &max_tv);
         if (rc != BGL_OK) return rc;

@@ -211,6 +211,43 @@ def test_traversals_side_by_side_are_independent(B, sequences):
     assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, len(train)))
 
 
+def test_a_graph_s_scratch_serves_calls_of_all_sizes_and_threads(B):
+    """A graph keeps an ordering call's scratch for the next one: calls that need more or less of it, a call
+    that is refused in between, and calls of several threads at the same time, each on its own stream."""
+    import threading
+    import oracle
+    import torch
+    rng = np.random.default_rng(31)
+    N = 20_000
+    rp, col = random_graph(rng, N, 4)
+    g = B.Graph(rp, col)
+    calls = []
+    for k, sequences in enumerate((1, 6, 2, 20, 3, 1)):
+        train = rng.choice(N, 300 * (k + 1), replace=False)
+        roots, shifts = rng.integers(0, N, sequences), rng.integers(0, len(train), sequences)
+        calls.append((train, roots, shifts, oracle.proximity_order(rp, col, train, roots, shifts, len(train))))
+    for train, roots, shifts, want in calls:
+        assert np.array_equal(B.order_proximity(g, train, roots, shifts, len(train)), want)
+        with pytest.raises(B.BglError):
+            B.order_proximity(g, np.concatenate([train, train[:1]]), roots, shifts, 1)
+    got = {}
+
+    def work(t):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for k in range(len(calls)):
+                train, roots, shifts, _ = calls[(k + t) % len(calls)]
+                got[t, (k + t) % len(calls)] = B.order_proximity(g, train, roots, shifts, len(train))
+
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(got) == 3 * len(calls)
+    for (_, k), order in got.items():
+        assert np.array_equal(order, calls[k][3])
+
+
 def test_proximity_order_and_shuffling_error_mid_size(B):
     """The bfs configuration's graph at full size: 5 sequences over 204,800 training nodes."""
     import oracle
