@@ -143,8 +143,9 @@ class MinibatchPipeline:
                                                            lookup_stream=work if early else None,
                                                            begin_only=self.write_through)
                 self.tier_hits.append(h2)
-            if self.tier is not None:
-                # the map update first: the next lookup is waiting for it
+            if self.tier is not None or self.write_through:
+                # the map update first: the next lookup is waiting for it (without write-through it ends with a
+                # copy of the fetched rows, which the sampling need not wait for)
                 cache.insert_fifo(ids, self.miss_pos, -1, self.out_rows, stream=work)
             if i + 2 < steps:
                 # workspace (i+2) % 3 was batch i-1's; its fetch ended before hit gather(i)
@@ -152,7 +153,7 @@ class MinibatchPipeline:
                 sbs[i + 2] = sample(i + 2)
             if self.tier is not None and self.write_through:
                 cache.lookup_tiered_finish()
-            if self.tier is None:
+            if self.tier is None and not self.write_through:
                 cache.insert_fifo(ids, self.miss_pos, -1, self.out_rows, stream=work)
             n_list.append(n)
             self.last_ids, self.last_n = ids, n
