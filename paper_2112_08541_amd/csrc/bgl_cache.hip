@@ -99,8 +99,7 @@ struct bgl_cache {
     hipEvent_t ev_lists = nullptr;   // the same for this cache's own miss fetch on the side stream
     hipStream_t last_main = nullptr, fetch_stream = nullptr, map_stream = nullptr;
     bool fetch_pending = false;      // ev_miss marks a miss fetch that later work may have to wait for
-    bool rows_joined = false;        // the FIFO update has made joined_stream wait for that fetch (and for its hit gather)
-    hipStream_t joined_stream = nullptr;
+    bool rows_joined = false;        // a FIFO update on the lookup's main stream has made it wait for that fetch
     bool fetch_beside = false;       // that fetch ran beside its hit gather: ev_fetched marks its own end
     bool fetch_reads_caller_lists = true;  // that fetch reads the caller's miss_pos (not the library's copy)
     bool map_pending = false;        // map_event marks a FIFO update the next lookup has to wait for
@@ -1993,8 +1992,7 @@ try {
         if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, rows_event(c, true), 0));
         rc = launch_marked(c, st, done, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
     }
-    c->rows_joined = c->fetch_pending && c->fetch_stream != st;
-    c->joined_stream = st;
+    if (st == c->last_main) c->rows_joined = true;
     return enqueued();
 } BGL_NOTHROW_END
 
@@ -2038,8 +2036,8 @@ extern "C" int bgl_cache_wait_rows(bgl_cache_t *c, void *stream)
 try {
     if (!c) BGL_FAIL(BGL_EINVAL, "cache handle is null");
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // (a FIFO update on st that copies rows has waited for them already: a wait costs the host 10 us)
-    if (c->fetch_pending && c->fetch_stream != st && !(c->rows_joined && c->joined_stream == st))
+    // (a FIFO update that copies rows has made the main stream wait for them already: a wait costs the host 10 us)
+    if (c->fetch_pending && c->fetch_stream != st && !(c->rows_joined && st == c->last_main))
         BGL_HIP(hipStreamWaitEvent(st, rows_event(c, st == c->last_main), 0));
     return BGL_OK;
 } BGL_NOTHROW_END

@@ -187,13 +187,11 @@ try {
     if (steps > 1 && (rc = sample(1)) != BGL_OK) return rc;
     for (int64_t i = 0; i < steps; ++i) {
         const int k = (int)(i % 3);
-        BGL_HIP(hipEventSynchronize(p->sampled[k]));  // the sizes of batch i
+        BGL_HIP(hipEventSynchronize(p->sampled[k]));  // the sizes of batch i (so no stream need wait for them either)
         const volatile int32_t *counts = p->buf.counts_host[k];
         if (counts[BGL_COUNTS_LEN - 1] != 0) BGL_FAIL(counts[BGL_COUNTS_LEN - 1], "sampling reported an error on the device");
         const int64_t n = counts[p->K];
         const int32_t *ids = p->sg[k].input_nodes;
-        BGL_HIP(hipStreamWaitEvent(chain, p->sampled[k], 0));
-        if (samp != work) BGL_HIP(hipStreamWaitEvent(work, p->sampled[k], 0));
         if (!tiered) {
             // the map lookup and the lists run early, on the work stream, behind the previous batch's map update
             rc = early ? bgl_cache_lookup_gather_early(c, ids, n, p->buf.out_rows, p->buf.out_slot, p->buf.miss_pos,
@@ -217,8 +215,9 @@ try {
         // the update behind seven launches of sampling, 104 us a batch; in front of them 85.)
         if ((rc = bgl_cache_insert_fifo(c, ids, p->buf.miss_pos, -1, p->buf.out_rows, work)) != BGL_OK) return rc;
         if (i + 2 < steps) {
-            // workspace (i+2) % 3 was batch i-1's; its rows were complete before hit gather(i)
-            if ((rc = bgl_cache_wait_lists(c, samp)) != BGL_OK) return rc;
+            // workspace (i+2) % 3 was batch i-1's; its rows were complete before hit gather(i), which the map
+            // update has made the work stream wait for
+            if (samp != work && (rc = bgl_cache_wait_lists(c, samp)) != BGL_OK) return rc;
             if ((rc = sample(i + 2)) != BGL_OK) return rc;
         }
         if (tiered && (rc = bgl_cache_lookup_tiered_finish(c)) != BGL_OK) return rc;
