@@ -419,6 +419,10 @@ constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
 //    100, 90 / 80; 205 MB 114 / 110, 101 / 94; with 2 % misses 120 MB 157 / 135, 205 MB 187 / 150; with half
 //    of the ids missed the link sets the time either way.
 constexpr int64_t LONG_LOOKUP_BYTES = 100ll << 20;
+// Lookups that ask for more than this, or whose updates have a stream of their own, mark the end of their miss
+// fetch with the launch's own event (launch_marked).  Lookup + update, each waited for / one after the other, event behind |
+// own: 2,000 ids x 400 B 70 / 66 | 79 / 64 us; 5,000 ids 100 / 88 | 100 / 84.
+constexpr int64_t OWN_EVENT_BYTES = 3 << 19;
 // Hit gather: largest output (of the hits) whose rows are read with ordinary loads, and largest one that is
 // written with ordinary stores (the size of the last-level cache).
 constexpr int64_t GATHER_CACHED_ROWS_BYTES = 96ll << 20;
@@ -1039,18 +1043,21 @@ void launch(bgl_cache *c, hipStream_t st, void (*kernel)(P...), dim3 grid, dim3 
     }
 }
 
-// The same, and `mark` says when the kernel is over.  As the launch's own completion event it is there 2 us
-// earlier for a stream that waits for it than as a command behind the kernel (a 5 us kernel, a hand-over, a 5 us kernel, a
-// hand-over back, a 5 us kernel: 43 instead of 47 us).  A launch that is captured or timed has it behind.
+// The same, and `mark` says when the kernel is over: with `own` as the launch's own completion event, else (and
+// where the launch is captured or timed) as a command behind it.  Its own event reaches a stream that waits for it
+// 2 us earlier (a 5 us kernel, a hand-over, a 5 us kernel, a hand-over back, a 5 us kernel: 43 instead of 47 us).
+// But a host that waits for a stream whose last event is a kernel's own enqueues another command first: lookup
+// + update of 500 ids x 400 B, each call waited for, 62 us with the hit gather's own event and the fetch's and the
+// update's behind them, 70 with all their own (62 with none; 5,000 ids, one call after the other, 87 / 83 / 92).
 template <typename... P, typename... A>
-int launch_marked(bgl_cache *c, hipStream_t st, hipEvent_t mark, void (*kernel)(P...), dim3 grid, dim3 block, A &&...a)
+int launch_marked(bgl_cache *c, hipStream_t st, hipEvent_t mark, bool own, void (*kernel)(P...), dim3 grid, dim3 block, A &&...a)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
+    if (own && hipStreamIsCapturing(st, &capture) != hipSuccess) {
         (void)hipGetLastError();
-        capture = hipStreamCaptureStatusActive;
+        own = false;
     }
-    if (c->timed_start || capture != hipStreamCaptureStatusNone) {
+    if (!own || c->timed_start || capture != hipStreamCaptureStatusNone) {
         launch(c, st, kernel, grid, block, std::forward<A>(a)...);
         BGL_HIP(hipEventRecord(mark, st));
     } else {
@@ -1334,7 +1341,7 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
         Prof p(c, BGL_STAGE_GATHER_HIT, ms);
         int rc = BGL_OK;
         dispatch_q(q, [&](auto Q) {
-            rc = launch_marked(c, ms, c->ev_listed, k_gather_hits<decltype(Q)::value>, dim3(copy_blocks(n, q)), dim3(COPY_THREADS),
+            rc = launch_marked(c, ms, c->ev_listed, tier == nullptr, k_gather_hits<decltype(Q)::value>, dim3(copy_blocks(n, q)), dim3(COPY_THREADS),
                                hit_pos, hit_pos + hit_cap, q, reinterpret_cast<const uint4 *>(c->buffer),
                                reinterpret_cast<uint4 *>(out_rows), c->dev);
         });
@@ -1429,6 +1436,7 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
         if (ss != ms) BGL_HIP(hipStreamWaitEvent(ss, beside ? c->ev_lists : c->ev_listed, 0));
         // (ev_miss, and whatever the caller enqueues on the side stream, come behind a gather beside the fetch as well)
         const hipEvent_t fetched = beside ? c->ev_fetched : c->ev_miss;
+        const bool own = update_beside || n * c->row_bytes > OWN_EVENT_BYTES;
         {
             Prof p(c, BGL_STAGE_FETCH_MISS, ss);
             // The small grid and the dealing of whole rows to wavefronts are for the host link only; an
@@ -1441,7 +1449,7 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
                 const bool few = c->write_through && update_beside && n * c->row_bytes <= SMALL_LOOKUP_BYTES;
                 const int64_t rows_per_block = (int64_t)(COPY_THREADS / kWave) * COPY_UNROLL * (kWave / q);
                 const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, rows_per_block), few ? SMALL_FETCH_BLOCKS : FETCH_BLOCKS);
-                rc = launch_marked(c, ss, fetched, c->write_through ? k_fetch_link<true> : k_fetch_link<false>, dim3(blocks),
+                rc = launch_marked(c, ss, fetched, own, c->write_through ? k_fetch_link<true> : k_fetch_link<false>, dim3(blocks),
                                    dim3(COPY_THREADS), mpos, ids, q, c->num_nodes, features, out, c->dev, buffer, c->capacity,
                                    c->rows, par, gen);
             } else {
@@ -1449,7 +1457,7 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
                 dispatch_q(q, [&](auto Q) {
                     auto k = c->write_through ? k_fetch_miss<decltype(Q)::value, true>
                                               : k_fetch_miss<decltype(Q)::value, false>;
-                    rc = launch_marked(c, ss, fetched, k, dim3(blocks), dim3(COPY_THREADS), mpos, ids, q, c->num_nodes, features,
+                    rc = launch_marked(c, ss, fetched, own, k, dim3(blocks), dim3(COPY_THREADS), mpos, ids, q, c->num_nodes, features,
                                        out, c->dev, buffer, c->capacity, c->rows, par, gen);
                 });
             }
@@ -1963,11 +1971,11 @@ try {
         c->awaiting_insert = false;
         if (eff > 0) {
             Prof p(c, BGL_STAGE_INSERT_MAP, st);
-            rc = launch_marked(c, st, done, k_insert_map, dim3((unsigned)bgl::ceil_div(eff, MAP_THREADS)),
+            rc = launch_marked(c, st, done, done == c->ev_map_local, k_insert_map, dim3((unsigned)bgl::ceil_div(eff, MAP_THREADS)),
                                dim3(MAP_THREADS), ids, miss_pos, n_miss, c->capacity, c->num_nodes, c->table,
                                c->num_buckets - 1, c->slot_to_node, c->slot_to_entry, c->dev, par, 1);
         } else {
-            rc = launch_marked(c, st, done, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
+            rc = launch_marked(c, st, done, done == c->ev_map_local, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
         }
         return enqueued();
     }
@@ -1983,14 +1991,14 @@ try {
         {
             Prof p(c, BGL_STAGE_INSERT_ROWS, st);
             dispatch_q(q, [&](auto Q) {
-                rc = launch_marked(c, st, done, k_insert_rows<decltype(Q)::value>, dim3(copy_blocks(eff, q)), dim3(COPY_THREADS),
+                rc = launch_marked(c, st, done, done == c->ev_map_local, k_insert_rows<decltype(Q)::value>, dim3(copy_blocks(eff, q)), dim3(COPY_THREADS),
                                    miss_pos, n_miss, c->capacity, c->rows, q, reinterpret_cast<const uint4 *>(out_rows),
                                    reinterpret_cast<uint4 *>(c->buffer), c->dev, par);
             });
         }
     } else {
         if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, rows_event(c, true), 0));
-        rc = launch_marked(c, st, done, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
+        rc = launch_marked(c, st, done, done == c->ev_map_local, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
     }
     if (st == c->last_main) c->rows_joined = true;
     return enqueued();
