@@ -119,6 +119,7 @@ struct bgl_cache {
         void *out_rows = nullptr;
         int64_t n = 0;
         int par = 0, gen = 0;
+        bool in_place = false;
     } tiered;
     // profiling
     unsigned profiling = 0;          // bit s set: stage s is timed
@@ -405,6 +406,9 @@ constexpr int SMALL_FETCH_BLOCKS = 16;
 // Tiered lookup: rows the host threads copy per chunk before that chunk's fetch is launched.
 constexpr int64_t TIER_CHUNK_ROWS = 49152;
 constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
+// Copy-engine transport without the early lookup: bytes that are worth a copy of their own (35 us on the
+// link, beside some 10 us that a copy costs whatever its size).
+constexpr int64_t LINK_CHUNK_BYTES = 2 << 20;
 // Lookups that ask for more bytes than this keep the GPU busy for longer than the host takes to enqueue
 // them.  Two things pay only there:
 //  - the FIFO update's event without a release to the system (only this library's kernels on this device
@@ -628,6 +632,51 @@ __global__ __launch_bounds__(COPY_THREADS) void k_fetch_link(
         if (base - sub >= n_miss) return;
         m0 = p0; m1 = p1; m2 = p2; m3 = p3;
         i0 = j0; i1 = j1; i2 = j2; i3 = j3;
+    }
+}
+
+// Tiered lookup, rows that the host tier holds, read where they lie in its page-locked ring: the h-th
+// listed rank's row, h < count, is ring row hit_ring[h].  Whole rows per wavefront, as in k_fetch_link; for rows of
+// whole 128-byte lines, which cross the link in place as fast as packed.  The launch needs no host thread, so it is
+// under way while the first of the other rows are being packed, and it fills the moments between their copies.
+// Measured, 150,001 ids x 512 B of which 25,600 in the tier, copy engine 1,600 -> 1,390 us a call, kernels
+// reading the packed rows 1,560 -> 1,374; 100,000 ids x 1,024 B 1,960 -> 1,720; 20,000 ids x 512 B 387 -> 320.
+template <bool WT>
+__global__ __launch_bounds__(COPY_THREADS) void k_fetch_ring(
+    const int32_t *__restrict__ hit_rank, const int32_t *__restrict__ hit_ring, int64_t count, const int32_t *__restrict__ miss_pos,
+    int q, const uint4 *__restrict__ ring_rows, uint4 *__restrict__ out, const CacheDev *dev, uint4 *__restrict__ buffer,
+    int64_t capacity, int64_t rows, int par, int64_t n_miss)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int group = kWave / q;                // rows side by side
+    const int sub = lane / q, c = lane - sub * q;
+    if (sub >= group) return;
+    const RowRing ring(WT ? dev->tail[par] : 0ull, capacity, rows, n_miss);
+    const int64_t step = (int64_t)gridDim.x * (COPY_THREADS / kWave) * COPY_UNROLL * group;
+    const int64_t last = count - 1;
+    for (int64_t base = ((int64_t)blockIdx.x * (COPY_THREADS / kWave) + threadIdx.x / kWave) * COPY_UNROLL * group + sub;
+         base - sub < count; base += step) {
+        // Phase by phase for the lane's four chunks, as in k_gather_hits; numbers beyond the end are clamped
+        // to the last row, which is then copied again.
+        const int64_t h0 = min(base, last), h1 = min(base + group, last), h2 = min(base + 2 * group, last), h3 = min(base + 3 * group, last);
+        const int32_t r0 = hit_rank[h0], r1 = hit_rank[h1], r2 = hit_rank[h2], r3 = hit_rank[h3];
+        const int32_t p0 = hit_ring[h0], p1 = hit_ring[h1], p2 = hit_ring[h2], p3 = hit_ring[h3];
+        const int32_t m0 = miss_pos[r0], m1 = miss_pos[r1], m2 = miss_pos[r2], m3 = miss_pos[r3];
+        uint4 v0 = ring_rows[(int64_t)p0 * q + c];
+        uint4 v1 = ring_rows[(int64_t)p1 * q + c];
+        uint4 v2 = ring_rows[(int64_t)p2 * q + c];
+        uint4 v3 = ring_rows[(int64_t)p3 * q + c];
+        // (the four reads stay above the branches that follow: the values are needed here)
+        asm volatile("" : "+v"(v0.x), "+v"(v0.y), "+v"(v0.z), "+v"(v0.w), "+v"(v1.x), "+v"(v1.y), "+v"(v1.z), "+v"(v1.w),
+                          "+v"(v2.x), "+v"(v2.y), "+v"(v2.z), "+v"(v2.w), "+v"(v3.x), "+v"(v3.y), "+v"(v3.z), "+v"(v3.w));
+        auto store = [&](int32_t r, int32_t m, const uint4 &v) {
+            out[(int64_t)m * q + c] = v;
+            if (WT && r >= ring.start) buffer[ring.pos_of_rank(r) * q + c] = v;
+        };
+        store(r0, m0, v0);
+        store(r1, m1, v1);
+        store(r2, m2, v2);
+        store(r3, m3, v3);
     }
 }
 
@@ -1575,8 +1624,10 @@ struct TieredRows {
     const int32_t *mpos;   // this call's miss positions (the caller's list, or the library's copy)
     void *out_rows;
     int64_t n;
+    int64_t staged() const { return in_place ? 0 : plan->n_hit; }  // leading rows of the packed sequence that the tier holds
     int par;               // which copy of the cache's tail the kernels read
     bool early;            // the lookup ran early: the host is ahead of the link
+    bool in_place;         // kernels read the rows the tier holds in its ring: only its misses are packed
     const int32_t *src_of; // assembled output: the source of every position's row (else null)
 
     // out[mpos[rank[l]]] = base[(first + l) mod ring] for l0 <= l < l0 + count.  landed: the rows are in
@@ -1598,6 +1649,18 @@ struct TieredRows {
                    reinterpret_cast<const uint4 *>(base), reinterpret_cast<uint4 *>(out_rows), c->dev,
                    reinterpret_cast<uint4 *>(c->buffer), c->capacity, c->rows, par, n - plan->n_hit_gpu);
         });
+    }
+    // The rows the tier holds, read in its ring.
+    void launch_ring() const
+    {
+        const int q = c->row_bytes / 16;
+        Prof p(c, BGL_STAGE_FETCH_MISS, ss);
+        const int64_t rows_per_block = (int64_t)(COPY_THREADS / kWave) * COPY_UNROLL * (kWave / q);
+        const int blocks = (int)std::min<int64_t>(bgl::ceil_div(plan->n_hit, rows_per_block), FETCH_BLOCKS);
+        launch(c, ss, c->write_through ? k_fetch_ring<true> : k_fetch_ring<false>, dim3(blocks), dim3(COPY_THREADS), plan->hit_rank,
+               plan->hit_ring, plan->n_hit, mpos, q, reinterpret_cast<const uint4 *>(bgl::tier_rows_device(t)),
+               reinterpret_cast<uint4 *>(out_rows), c->dev, reinterpret_cast<uint4 *>(c->buffer), c->capacity, c->rows, par,
+               n - plan->n_hit_gpu);
     }
     // Assembled output, first launch: the hits whose slots this call's misses are about to take.
     void launch_assemble_pre() const
@@ -1645,7 +1708,7 @@ int rows_by_copy_engine(const TieredRows &r, char *land)
     bgl_cache *c = r.c;
     bgl_host_tier *t = r.t;
     const bgl::TierPlan &plan = *r.plan;
-    const int64_t total = plan.n_hit + plan.n_miss;
+    const int64_t staged = r.staged(), total = staged + plan.n_miss;
     const size_t rb = (size_t)c->row_bytes;
     hipStream_t cs = bgl::tier_copy_stream(t);
     const char *ring_rows = bgl::tier_rows_device(t);
@@ -1656,19 +1719,19 @@ int rows_by_copy_engine(const TieredRows &r, char *land)
     };
     // rows x0 <= x < x1 of the packed sequence: the tier's hits (staging rows), then its misses (ring)
     auto copy_rows = [&](int64_t x0, int64_t x1) -> int {
-        if (x0 < plan.n_hit) {
-            const int64_t e = std::min(x1, plan.n_hit);
+        if (x0 < staged) {
+            const int64_t e = std::min(x1, staged);
             const int r1 = copy(land + (size_t)x0 * rb, plan.stage + (size_t)x0 * rb, e - x0);
             if (r1 != BGL_OK) return r1;
         }
-        const int64_t a = std::max(x0, plan.n_hit) - plan.n_hit, b = x1 - plan.n_hit;
+        const int64_t a = std::max(x0, staged) - staged, b = x1 - staged;
         if (b > a) {
             const int64_t pos = (int64_t)((plan.ptail + (uint64_t)a) % (uint64_t)plan.ring);
             const int64_t len1 = std::min(b - a, plan.ring - pos);  // up to the end of the ring
-            const int r1 = copy(land + (size_t)(plan.n_hit + a) * rb, ring_rows + (size_t)pos * rb, len1);
+            const int r1 = copy(land + (size_t)(staged + a) * rb, ring_rows + (size_t)pos * rb, len1);
             if (r1 != BGL_OK) return r1;
             if (len1 < b - a) {
-                const int r2 = copy(land + (size_t)(plan.n_hit + a + len1) * rb, ring_rows, b - a - len1);
+                const int r2 = copy(land + (size_t)(staged + a + len1) * rb, ring_rows, b - a - len1);
                 if (r2 != BGL_OK) return r2;
             }
         }
@@ -1702,7 +1765,9 @@ int rows_by_copy_engine(const TieredRows &r, char *land)
             bgl::tier_set_copy_event_recorded(t);
             link_busy = true;
             launched = ready;
-            chunk = std::min<int64_t>(2 * chunk, TIER_CHUNK_ROWS);
+            // (without an early lookup what has piled up while a copy was on the link goes behind it: waiting for
+            // larger and larger chunks left the link idle between them.  150,001 ids x 512 B, 67 MB: 1,690 -> 1,600 us)
+            chunk = r.early ? std::min<int64_t>(2 * chunk, TIER_CHUNK_ROWS) : bgl::ceil_div(LINK_CHUNK_BYTES, (int64_t)rb);
         } else if (!bgl::tier_copy_help(t)) {  // nothing to send: pack a few rows too
             __builtin_ia32_pause();
         }
@@ -1718,8 +1783,8 @@ int rows_by_copy_engine(const TieredRows &r, char *land)
         return BGL_OK;
     }
     BGL_HIP(hipStreamWaitEvent(r.ss, bgl::tier_copy_event(t), 0));  // (recorded behind the last copy)
-    r.launch_rows(land, 0ull, (int64_t)INT64_MAX, plan.hit_rank, 0, plan.n_hit, true);
-    r.launch_rows(land + (size_t)plan.n_hit * rb, 0ull, (int64_t)INT64_MAX, plan.miss_rank, 0, plan.n_miss, true);
+    r.launch_rows(land, 0ull, (int64_t)INT64_MAX, plan.hit_rank, 0, staged, true);
+    r.launch_rows(land + (size_t)staged * rb, 0ull, (int64_t)INT64_MAX, plan.miss_rank, 0, plan.n_miss, true);
     return BGL_OK;
 }
 
@@ -1731,7 +1796,7 @@ int rows_by_kernels(const TieredRows &r)
     bgl_cache *c = r.c;
     bgl_host_tier *t = r.t;
     const bgl::TierPlan &plan = *r.plan;
-    const int64_t total = plan.n_hit + plan.n_miss;
+    const int64_t staged = r.staged(), total = staged + plan.n_miss;
     const char *ring_rows = bgl::tier_rows_device(t);
     // (an early lookup is ahead of the link anyway: full chunks from the start)
     int64_t chunk = r.early ? TIER_CHUNK_ROWS : TIER_FIRST_CHUNK_ROWS;
@@ -1739,8 +1804,8 @@ int rows_by_kernels(const TieredRows &r)
     for (int64_t launched = 0; launched < total;) {
         const int64_t ready = bgl::tier_copy_progress(t);
         // a chunk does not straddle the two kinds of rows
-        const int64_t limit = launched < plan.n_hit ? std::min(ready, plan.n_hit) : ready;
-        bool go = limit > launched && (limit == plan.n_hit || limit == total);
+        const int64_t limit = launched < staged ? std::min(ready, staged) : ready;
+        bool go = limit > launched && (limit == staged || limit == total);
         if (!go && limit - launched >= chunk) {
             // An early lookup's fetch cannot start before its hit gather has run, which waits for
             // the previous call's fetch: until then the packed rows pile up for one larger launch.
@@ -1751,12 +1816,12 @@ int rows_by_kernels(const TieredRows &r)
             go = gather_done || !r.early;
         }
         if (go) {
-            if (launched < plan.n_hit)
+            if (launched < staged)
                 r.launch_rows(plan.stage, 0ull, (int64_t)INT64_MAX, plan.hit_rank, launched, limit - launched,
                               false);
             else
                 r.launch_rows(ring_rows, (unsigned long long)plan.ptail, plan.ring, plan.miss_rank,
-                              launched - plan.n_hit, limit - launched, false);
+                              launched - staged, limit - launched, false);
             launched = limit;
             chunk = std::min<int64_t>(2 * chunk, TIER_CHUNK_ROWS);
         } else if (!bgl::tier_copy_help(t)) {  // nothing to send: pack a few rows too
@@ -1820,10 +1885,16 @@ int tiered_begin(bgl_cache_t *c, bgl_host_tier_t *t, const int32_t *ids, int64_t
     // (Waking the copy threads earlier, to have them spin until the ids arrive, was measured:
     // slower, the spinning threads get in the way of the wait for the lookup.)
     if (ss != ms) BGL_HIP(hipStreamWaitEvent(ss, c->ev_listed, 0));
-    if (tc.plan.n_hit + tc.plan.n_miss > 0) {
-        rc = bgl::tier_copy_start(t);  // host threads start packing
+    // Rows of whole lines that the tier holds are read in its ring, by a launch that nothing on the host has to
+    // wait for.  (An early lookup's rows are packed a batch ahead of the link; there the copies alone keep it busy.)
+    tc.in_place = ls == ms && tc.plan.n_hit > 0 && c->row_bytes % 128 == 0 && c->row_bytes / 16 <= kWave;
+    if ((tc.in_place ? 0 : tc.plan.n_hit) + tc.plan.n_miss > 0) {
+        rc = bgl::tier_copy_start(t, tc.in_place);  // host threads start packing
         if (rc != BGL_OK) return rc;
     }
+    if (tc.in_place)
+        TieredRows{c, t, &tc.plan, ss, mpos, out_rows, n, (int)(c->insert_calls & 1), false, true, nullptr}.launch_ring();
+    BGL_HIP(hipGetLastError());
     guard.armed = false;
     tc.active = true;
     tc.t = t;
@@ -1859,9 +1930,9 @@ int tiered_finish(bgl_cache_t *c, int64_t *n_hit)
         ~Guard() { if (armed) bgl::tier_abort(t); }
     } guard{t};
     const bgl::TierPlan &plan = tc.plan;
-    const TieredRows rows{c, t, &plan, tc.ss, tc.mpos, tc.out_rows, tc.n, tc.par, tc.ls != tc.ms, tc.src_of};
+    const TieredRows rows{c, t, &plan, tc.ss, tc.mpos, tc.out_rows, tc.n, tc.par, tc.ls != tc.ms, tc.in_place, tc.src_of};
     int rc;
-    if (plan.n_hit + plan.n_miss > 0) {
+    if (rows.staged() + plan.n_miss > 0) {
         char *land = bgl::tier_landing(t, tc.gen);  // device memory the copy engine fills, if that transport is on
         rc = land ? rows_by_copy_engine(rows, land) : rows_by_kernels(rows);
         if (rc != BGL_OK) return rc;

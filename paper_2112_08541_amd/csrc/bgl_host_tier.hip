@@ -8,7 +8,7 @@
 // for the GPU cache's misses right behind that cache's own lookup; the same kernels list the rows the tier holds and the ids
 // it does not.  The host only feeds rows, always packed, because rows that are
 // not multiples of 128 bytes cross the link a quarter faster packed than read in
-// place: its threads copy the rows the tier holds into staging rows, in list
+// place (rows that are may be read in the ring by a kernel, see k_fetch_ring): its threads copy the rows the tier holds into staging rows, in list
 // order, and the missing rows from the store into the positions first-in
 // first-out assigns (consecutive), and the calling thread sends each chunk on
 // as soon as its rows are in place: a plain copy into device memory on the copy
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(TT) void k_tier_lists(const int32_t *__restrict__ i
                                                    const int32_t *__restrict__ rank_pos,
                                                    const int32_t *__restrict__ tile_miss,
                                                    const int32_t *__restrict__ tile_prefix,
-                                                   int32_t *hit_rank, int32_t *hit_pos_host, int32_t *miss_rank,
+                                                   int32_t *hit_rank, int32_t *hit_ring, int32_t *hit_pos_host, int32_t *miss_rank,
                                                    int32_t *miss_ids_host, int64_t *counts_host)
 {
     __shared__ int sh_scan[TT / kWave];
@@ -125,6 +125,7 @@ __global__ __launch_bounds__(TT) void k_tier_lists(const int32_t *__restrict__ i
         miss_ids_host[j] = ids[miss_pos[r]];
     } else if (r < m) {
         hit_rank[r - j] = (int32_t)r;
+        hit_ring[r - j] = p;
         hit_pos_host[r - j] = p;
     }
     if ((int64_t)blockIdx.x == tiles - 1 && threadIdx.x == 0) {
@@ -184,7 +185,7 @@ struct bgl_host_tier {
     int32_t *rank_pos = nullptr, *tile_miss = nullptr;
     // the lists a batch's fetch kernels read, alternating between calls: an early lookup writes the next
     // batch's while the previous batch's are still in use
-    int32_t *hit_rank[2] = {nullptr, nullptr}, *miss_rank[2] = {nullptr, nullptr};
+    int32_t *hit_rank[2] = {nullptr, nullptr}, *hit_ring[2] = {nullptr, nullptr}, *miss_rank[2] = {nullptr, nullptr};
     int cur_gen = 0;
     uint64_t tail = 0;      // insertions so far (host mirrors of what the kernels are told)
     uint64_t ptail = 0;     // next ring position
@@ -193,6 +194,7 @@ struct bgl_host_tier {
     uint64_t batches = 0;
     // the batch being served
     int64_t cur_m = 0, cur_hit = 0, cur_miss = 0;
+    int64_t cur_staged = 0;  // found rows that the host threads copy to the staging rows: cur_hit or none
     bool serving = false;
     bgl::Pool *pool = nullptr;
     bgl::Pool::Fn copy_fn;
@@ -248,7 +250,7 @@ int tier_enqueue_lookup(bgl_host_tier *t, const int32_t *ids, const int32_t *mis
                            tile_prefix);
     }
     hipLaunchKernelGGL(k_tier_lists, dim3(tiles), dim3(TT), 0, st, ids, miss_pos, n_ranks_dev, t->rank_pos,
-                       t->tile_miss, tile_prefix, t->hit_rank[t->cur_gen],
+                       t->tile_miss, tile_prefix, t->hit_rank[t->cur_gen], t->hit_ring[t->cur_gen],
                        reinterpret_cast<int32_t *>(t->pinned_dev + 64 + 4 * (size_t)t->max_batch),
                        t->miss_rank[t->cur_gen], reinterpret_cast<int32_t *>(t->pinned_dev + 64),
                        reinterpret_cast<int64_t *>(t->pinned_dev));
@@ -281,6 +283,7 @@ int tier_begin(bgl_host_tier *t, int64_t n, TierPlan *plan)
     plan->n_hit = n_hit;
     plan->n_miss = n_miss;
     plan->hit_rank = t->hit_rank[t->cur_gen];
+    plan->hit_ring = t->hit_ring[t->cur_gen];
     plan->stage = t->stage_dev ? t->stage_dev + (size_t)t->cur_gen * (size_t)t->max_batch * (size_t)t->row_bytes
                                : nullptr;
     plan->miss_rank = t->capacity > 0 ? t->miss_rank[t->cur_gen] : nullptr;  // capacity 0: every rank, in order
@@ -289,9 +292,10 @@ int tier_begin(bgl_host_tier *t, int64_t n, TierPlan *plan)
     return BGL_OK;
 }
 
-int tier_copy_start(bgl_host_tier *t)
+int tier_copy_start(bgl_host_tier *t, bool in_place)
 {
     if (!t->serving) BGL_FAIL(BGL_EINVAL, "host tier: no batch is being served");
+    t->cur_staged = in_place ? 0 : t->cur_hit;
     t->copy_t0 = std::chrono::steady_clock::now();
     // one sequence of rows: the found ones first (ring -> this call's half of the staging rows, packed in
     // list order), then the missing ones (store -> their ring positions, consecutive)
@@ -300,7 +304,7 @@ int tier_copy_start(bgl_host_tier *t)
         const int32_t *mi = t->miss_ids();
         const int32_t *hp = t->hit_positions();
         char *stage = t->stage + (size_t)t->cur_gen * (size_t)t->max_batch * rb;
-        const int64_t n_hit = t->cur_hit;
+        const int64_t n_hit = t->cur_staged;
         const int64_t hi = std::min<int64_t>(n_hit + t->cur_miss, (k + 1) * COPY_TASK);
         // (asking for the scattered source rows a few rows ahead was measured: no faster, a dozen threads
         // already keep enough reads in flight; writing the packed rows with 16-byte streaming stores was
@@ -317,13 +321,13 @@ int tier_copy_start(bgl_host_tier *t)
     };
     t->copying = true;
     t->copy_timed = false;
-    t->pool->start(bgl::ceil_div(t->cur_hit + t->cur_miss, COPY_TASK), t->copy_fn);
+    t->pool->start(bgl::ceil_div(t->cur_staged + t->cur_miss, COPY_TASK), t->copy_fn);
     return BGL_OK;
 }
 
 int64_t tier_copy_progress(bgl_host_tier *t)
 {
-    const int64_t total = t->cur_hit + t->cur_miss;
+    const int64_t total = t->cur_staged + t->cur_miss;
     const int64_t ready = std::min<int64_t>(total, t->pool->done_prefix() * COPY_TASK);
     if (ready == total && t->copying && !t->copy_timed) {  // the moment the calling thread sees the last row in place
         t->copy_timed = true;
@@ -456,6 +460,7 @@ try {
     TRY_ALLOC(t->tile_miss, 2 * (bgl::ceil_div((int64_t)mb, TT) + 1));  // counts, then their prefixes
     for (int g = 0; g < 2; ++g) {
         TRY_ALLOC(t->hit_rank[g], mb);
+        TRY_ALLOC(t->hit_ring[g], mb);
         TRY_ALLOC(t->miss_rank[g], mb);
     }
 #undef TRY_ALLOC
@@ -548,6 +553,7 @@ try {
     (void)hipFree(t->tile_miss);
     for (int g = 0; g < 2; ++g) {
         (void)hipFree(t->hit_rank[g]);
+        (void)hipFree(t->hit_ring[g]);
         (void)hipFree(t->miss_rank[g]);
     }
     delete t;

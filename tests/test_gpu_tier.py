@@ -208,6 +208,24 @@ def test_tiered_capacity_corners(B, torch_mod, cap1, cap2, threads):
     assert tier.stats()["threads"] == (threads or tier.stats()["threads"])
 
 
+@pytest.mark.parametrize("dim", [32, 96, 160, 256, 288])
+@pytest.mark.parametrize("write_through,early", [(False, None), (True, None), (True, "alternate")])
+@pytest.mark.parametrize("copy_engine", [False, True])
+def test_tier_rows_read_in_the_ring(B, torch_mod, dim, write_through, early, copy_engine):
+    """Rows of whole 128-byte lines that the tier holds are read in its ring (up to 1,024 bytes: several rows
+    to a wavefront, lanes that stay idle, one row), wider ones are packed: one found row, all found and
+    none to be brought in, more than one round of the grid, more found than either cache has slots, found rows that the
+    same batch's insertions evict."""
+    rng = np.random.default_rng(dim)
+    N = 16_000
+    feats = rng.integers(0, 2**32, (N, dim), dtype=np.uint32).view(np.float32)
+    a = rng.permutation(N)[:9_000].tolist()
+    fresh = [x for x in range(N) if x not in set(a)]
+    batches = [a, a[:1], a[:4_000], a[2_000:], [], fresh[:1] + a[100:101], fresh[:3_000] + a[:500], fresh[2_000:] + a[:8_000], a, a]
+    run_tiered_stream(B, torch_mod, feats, 200, 9_500, batches, write_through, threads=3, early=early, copy_engine=copy_engine)
+    run_tiered_stream(B, torch_mod, feats, 200, 700, batches, write_through, threads=3, early=early, copy_engine=copy_engine)
+
+
 @pytest.mark.parametrize("write_through,early", [(False, None), (True, None), (True, "own"), (True, "with_insert"),
                                                  (True, "alternate")])
 @pytest.mark.parametrize("side", [False, True])
