@@ -175,8 +175,9 @@ int bgl_cache_destroy(bgl_cache_t *c);
  *                   order out_slot, miss_pos, the hit count and the rows of the
  *                   hits are complete when the call's work is done
  *   side_stream     the miss fetch runs here (NULL: a stream owned by the
- *                   cache), after the hit gather (beside it in large calls when the
- *                   cache can hold every node; what is enqueued on side_stream behind the
+ *                   cache), after the hit gather (beside it in calls of up to 64 MiB on the
+ *                   cache's own stream without write-through mode, and in calls beyond 100 MiB when
+ *                   the cache can hold every node; what is enqueued on side_stream behind the
  *                   call comes after both either way), so that work enqueued on
  *                   main_stream afterwards (the next batch's sampling) overlaps
  *                   the host-link transfer.  The rows of the misses are complete

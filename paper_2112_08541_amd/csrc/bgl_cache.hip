@@ -100,6 +100,7 @@ struct bgl_cache {
     hipStream_t last_main = nullptr, fetch_stream = nullptr, map_stream = nullptr;
     bool fetch_pending = false;      // ev_miss marks a miss fetch that later work may have to wait for
     bool rows_joined = false;        // a FIFO update on the lookup's main stream has made it wait for that fetch
+    bool rows_split = false;         // ev_miss marks neither: ev_fetched the fetch, ev_listed the hit gather beside it
     bool fetch_beside = false;       // that fetch ran beside its hit gather: ev_fetched marks its own end
     bool fetch_reads_caller_lists = true;  // that fetch reads the caller's miss_pos (not the library's copy)
     bool map_pending = false;        // map_event marks a FIFO update the next lookup has to wait for
@@ -427,6 +428,11 @@ constexpr int64_t LONG_LOOKUP_BYTES = 100ll << 20;
 // fetch with the launch's own event (launch_marked).  Lookup + update, each waited for / one after the other, event behind |
 // own: 2,000 ids x 400 B 70 / 66 | 79 / 64 us; 5,000 ids 100 / 88 | 100 / 84.
 constexpr int64_t OWN_EVENT_BYTES = 3 << 19;
+// Lookups of up to this many bytes whose miss fetch has the cache's own side stream start it beside the hit
+// gather.  Lookup + update, behind the gather | beside it, each waited for / one after the other: 5,000 ids x 400 B 99 / 85 | 98 / 82 us,
+// 20,000 ids 206 / 188 | 201 / 183, 100,000 ids 793 / 769 | 783 / 764; with 70 % hits 40,000 ids x 1,024 B 135 / 137 | 135 / 126.
+// Beyond, a short gather is held up by the host reads (428,377 ids x 400 B 20 -> 140 us) and the whole gains nothing.
+constexpr int64_t BESIDE_BYTES = 64 << 20;
 // Hit gather: largest output (of the hits) whose rows are read with ordinary loads, and largest one that is
 // written with ordinary stores (the size of the last-level cache).
 constexpr int64_t GATHER_CACHED_ROWS_BYTES = 96ll << 20;
@@ -1265,16 +1271,35 @@ struct LookupLists {
     int64_t hit_cap;
 };
 
+// What the hit gather of a lookup needs of its lists.
+struct HitList {
+    const int32_t *pos = nullptr, *slot = nullptr;
+    const int32_t *src_of = nullptr;  // assembled output: there is no hit gather
+};
+
+// Make stream st wait for what a lookup that has not been joined yet still does on other streams: its miss
+// fetch, and its hit gather unless st is that lookup's main stream (then st is behind it).
+int join_rows(bgl_cache *c, hipStream_t st)
+{
+    if (!c->fetch_pending || c->fetch_stream == st) return BGL_OK;
+    if (c->rows_split) {
+        BGL_HIP(hipStreamWaitEvent(st, c->ev_fetched, 0));
+        if (st != c->last_main) BGL_HIP(hipStreamWaitEvent(st, c->ev_listed, 0));
+    } else {
+        BGL_HIP(hipStreamWaitEvent(st, c->fetch_beside && st == c->last_main ? c->ev_fetched : c->ev_miss, 0));
+    }
+    return BGL_OK;
+}
+
 // First half of a lookup: map lookup and lists on stream ls, with a host tier its
-// lookup for the misses (followed by ev_ids), then the hit gather on stream ms,
+// lookup for the misses (followed by ev_ids).  gather_phase enqueues the hit gather on stream ms,
 // ev_listed.  ls == ms unless the lookup runs early (see the tiered call): then
 // the lists go to *mpos_used, the library's own copy of miss_pos, because the
 // caller's miss_pos of the previous call is still being read by that call's
 // fetch while this one's lists are written.
-int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, int32_t *out_slot,
-                 int32_t *miss_pos, int64_t *n_hit_dev, hipStream_t ms, hipStream_t ls, bgl_host_tier *tier,
-                 const int32_t **mpos_used, int *gen_used, const LookupLists *fixed = nullptr,
-                 const int32_t **src_of_used = nullptr, bool record_lists = false)
+int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, int32_t *out_slot, int32_t *miss_pos, int64_t *n_hit_dev, hipStream_t ms, hipStream_t ls, bgl_host_tier *tier,
+                 const int32_t **mpos_used, int *gen_used, HitList *hits, const LookupLists *fixed = nullptr,
+                 bool assemble = false, bool record_lists = false)
 {
     const bool early = ls != ms;
     const int gen = (int)(c->lookup_calls & 1);  // which copy of the per-call device state this call owns
@@ -1317,7 +1342,7 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
     // Assembled output (the caller launches k_assemble_pre / k_assemble_rows once the miss rows have
     // landed): the list kernel records every position's source, and there is no hit gather here.
     int32_t *src_of = nullptr;
-    if (src_of_used) {
+    if (assemble) {
         const int g = gen;
         if (n > c->src_cap[g]) {
             BGL_HIP(hipDeviceSynchronize());
@@ -1329,25 +1354,21 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
             c->src_cap[g] = cap;
         }
         src_of = c->src_of[g];
-        *src_of_used = src_of;
     }
     int32_t *const mbs = fixed ? fixed->mbs : c->mbs;
     const int64_t mbs_cap = fixed ? fixed->mbs_cap : c->mbs_cap;
     int32_t *const hit_pos = fixed ? fixed->hit_pos : c->hit_pos;
     const int64_t hit_cap = fixed ? fixed->hit_cap : c->hit_cap;
+    *hits = HitList{hit_pos, hit_pos + hit_cap, src_of};
     c->lookup_calls += 1;
     c->last_n = n;
-    const int q = c->row_bytes / 16;
     if (tier) bgl::tier_prepare(tier);
     if (c->map_pending && c->map_stream != ls) BGL_HIP(hipStreamWaitEvent(ls, c->map_event, 0));
-    if (!early && c->fetch_pending && c->fetch_stream != ms) {
-        // the previous call's fetch still reads that call's lists
-        BGL_HIP(hipStreamWaitEvent(ms, c->ev_miss, 0));
-    }
-    if (early && c->fetch_pending && c->fetch_reads_caller_lists) {
-        // so does it when that call was not an early one: then this one cannot be early either
-        BGL_HIP(hipStreamWaitEvent(ls, c->ev_miss, 0));
-    }
+    int rc = BGL_OK;
+    // the previous call's fetch still reads that call's lists
+    if (!early && (rc = join_rows(c, ms)) != BGL_OK) return rc;
+    // so does it when that call was not an early one: then this one cannot be early either
+    if (early && c->fetch_reads_caller_lists && (rc = join_rows(c, ls)) != BGL_OK) return rc;
     if (n > 0) {
         {
             Prof p(c, BGL_STAGE_PROBE, ls);
@@ -1361,11 +1382,18 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
                 tile_prefix = mbs + mbs_cap;
                 hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanThreads), 0, ls, mbs, tiles, tile_prefix);
             }
-            hipLaunchKernelGGL(k_split_list, dim3((unsigned)tiles), dim3(KEYS_PER_TILE), 0, ls, out_slot,
-                               n, mbs, tile_prefix, mbs + 2 * mbs_cap, miss_pos, hit_pos, hit_pos + hit_cap, c->dev,
-                               n_hit_dev, ids, c->num_nodes,
-                               tier ? bgl::tier_ids_device_if_passthrough(tier) : nullptr, mpos_copy, gen, src_of,
-                               c->capacity, c->rows, (int)(c->insert_calls & 1));
+            auto split = [&](auto &&launch_it) {
+                return launch_it(k_split_list, dim3((unsigned)tiles), dim3(KEYS_PER_TILE), out_slot, n, mbs, tile_prefix,
+                                 mbs + 2 * mbs_cap, miss_pos, hit_pos, hit_pos + hit_cap, c->dev, n_hit_dev, ids, c->num_nodes,
+                                 tier ? bgl::tier_ids_device_if_passthrough(tier) : nullptr, mpos_copy, gen, src_of,
+                                 c->capacity, c->rows, (int)(c->insert_calls & 1));
+            };
+            rc = split([&](auto kernel, auto &&...a) {
+                if (record_lists) return launch_marked(c, ls, c->ev_lists, true, kernel, a...);
+                launch(c, ls, kernel, a...);
+                return (int)BGL_OK;
+            });
+            if (rc != BGL_OK) return rc;
         }
     } else {
         hipLaunchKernelGGL(k_empty_lookup, dim3(1), dim3(64), 0, ls, c->dev, n_hit_dev, gen);
@@ -1375,23 +1403,28 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
         if (rc != BGL_OK) return rc;
     }
     if (tier || early) BGL_HIP(hipEventRecord(c->ev_ids, ls));  // the lists are complete
-    if (record_lists) BGL_HIP(hipEventRecord(c->ev_lists, ls));
     if (early) {
         // the hit gather reads rows the previous fetch may still be writing, and needs the lists
-        if (c->fetch_pending && c->fetch_stream != ms) BGL_HIP(hipStreamWaitEvent(ms, c->ev_miss, 0));
+        if ((rc = join_rows(c, ms)) != BGL_OK) return rc;
         BGL_HIP(hipStreamWaitEvent(ms, c->ev_ids, 0));
     }
     c->fetch_pending = false;
     c->rows_joined = false;
     c->map_pending = false;
     c->last_main = ms;
+    return BGL_OK;
+}
+
+int gather_phase(bgl_cache *c, int64_t n, void *out_rows, hipStream_t ms, const HitList &hits, bool own)
+{
+    const int q = c->row_bytes / 16;
     c->ev_listed_valid = true;
-    if (n > 0 && !src_of) {
+    if (n > 0 && !hits.src_of) {
         Prof p(c, BGL_STAGE_GATHER_HIT, ms);
         int rc = BGL_OK;
         dispatch_q(q, [&](auto Q) {
-            rc = launch_marked(c, ms, c->ev_listed, tier == nullptr, k_gather_hits<decltype(Q)::value>, dim3(copy_blocks(n, q)), dim3(COPY_THREADS),
-                               hit_pos, hit_pos + hit_cap, q, reinterpret_cast<const uint4 *>(c->buffer),
+            rc = launch_marked(c, ms, c->ev_listed, own, k_gather_hits<decltype(Q)::value>, dim3(copy_blocks(n, q)), dim3(COPY_THREADS),
+                               hits.pos, hits.slot, q, reinterpret_cast<const uint4 *>(c->buffer),
                                reinterpret_cast<uint4 *>(out_rows), c->dev);
         });
         return rc;
@@ -1400,12 +1433,8 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, void *out_rows, in
     return BGL_OK;
 }
 
-// What work on a stream waits for that needs the rows of the last lookup: all of them, or, behind its
-// hit gather, those of the misses.
-hipEvent_t rows_event(const bgl_cache *c, bool behind_gather)
-{
-    return c->fetch_beside && behind_gather ? c->ev_fetched : c->ev_miss;
-}
+// The miss rows of the last lookup, for work that is behind its hit gather.
+hipEvent_t misses_event(const bgl_cache *c) { return c->fetch_beside ? c->ev_fetched : c->ev_miss; }
 
 // The stream of the miss fetch: the caller's, or one of the cache's own.
 int side_stream_of(bgl_cache *c, void *side_stream, hipStream_t *out)
@@ -1479,12 +1508,15 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
     // (Write-through mode: the fetch overwrites rows that the gather may have to read.)
     const bool beside = ss != ms && !c->write_through && c->capacity >= c->num_nodes && n * c->row_bytes > LONG_LOOKUP_BYTES;
     const bool update_beside = c->map_pending && c->map_stream != ms;  // the FIFO updates run on a stream of their own
-    rc = lookup_phase(c, ids, n, out_rows, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, fixed, nullptr, beside);
+    // So does the fetch of a small one on the cache's own side stream: there the host's calls set the pace, and
+    // those for the side stream come before the gather's.
+    const bool few_bytes = ss != ms && !side_stream && !c->write_through && !c->features_in_hbm && n * c->row_bytes <= BESIDE_BYTES;
+    HitList hits;
+    rc = lookup_phase(c, ids, n, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, &hits, fixed, false,
+                      (beside || few_bytes) && n > 0);
     if (rc != BGL_OK) return rc;
-    if (n > 0) {
-        if (ss != ms) BGL_HIP(hipStreamWaitEvent(ss, beside ? c->ev_lists : c->ev_listed, 0));
-        // (ev_miss, and whatever the caller enqueues on the side stream, come behind a gather beside the fetch as well)
-        const hipEvent_t fetched = beside ? c->ev_fetched : c->ev_miss;
+    const hipEvent_t fetched = beside || few_bytes ? c->ev_fetched : c->ev_miss;
+    auto fetch = [&]() -> int {
         const bool own = update_beside || n * c->row_bytes > OWN_EVENT_BYTES;
         {
             Prof p(c, BGL_STAGE_FETCH_MISS, ss);
@@ -1511,13 +1543,25 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
                 });
             }
         }
-        if (rc != BGL_OK) return rc;
-        if (beside) {
+        return rc;
+    };
+    if (n > 0 && (beside || few_bytes)) {
+        BGL_HIP(hipStreamWaitEvent(ss, c->ev_lists, 0));
+        if ((rc = fetch()) != BGL_OK) return rc;
+    }
+    if ((rc = gather_phase(c, n, out_rows, ms, hits, true)) != BGL_OK) return rc;
+    if (n > 0) {
+        if (!beside && !few_bytes) {
+            if (ss != ms) BGL_HIP(hipStreamWaitEvent(ss, c->ev_listed, 0));
+            if ((rc = fetch()) != BGL_OK) return rc;
+        } else if (beside) {
+            // (ev_miss, and whatever the caller enqueues on the side stream, come behind the gather as well)
             BGL_HIP(hipStreamWaitEvent(ss, c->ev_listed, 0));
             BGL_HIP(hipEventRecord(c->ev_miss, ss));
         }
         c->fetch_pending = true;
-        c->fetch_beside = beside;
+        c->fetch_beside = beside || few_bytes;
+        c->rows_split = few_bytes && !beside;
         c->fetch_stream = ss;
         c->fetch_reads_caller_lists = mpos == miss_pos;
     }
@@ -1868,9 +1912,11 @@ int tiered_begin(bgl_cache_t *c, bgl_host_tier_t *t, const int32_t *ids, int64_t
     const bool assemble = bgl::tier_assemble(t) && bgl::tier_capacity(t) == 0 && c->write_through &&
                           bgl::tier_landing(t, (int)(c->lookup_calls & 1)) != nullptr;
     const int32_t *src_of = nullptr;
-    rc = lookup_phase(c, ids, n, out_rows, out_slot, miss_pos, bgl::tier_count_device(t), ms, ls, t, &mpos, &gen,
-                      nullptr, assemble ? &src_of : nullptr);
+    HitList hits;
+    rc = lookup_phase(c, ids, n, out_slot, miss_pos, bgl::tier_count_device(t), ms, ls, t, &mpos, &gen, &hits, nullptr, assemble);
     if (rc != BGL_OK) return rc;
+    src_of = hits.src_of;
+    if ((rc = gather_phase(c, n, out_rows, ms, hits, false)) != BGL_OK) return rc;
     BGL_HIP(hipGetLastError());
     struct Guard {  // whatever goes wrong below, the copy threads are released and the batch is dropped
         bgl_host_tier *t;
@@ -1947,7 +1993,7 @@ int tiered_finish(bgl_cache_t *c, int64_t *n_hit)
     guard.armed = false;
     BGL_HIP(hipGetLastError());
     c->fetch_pending = true;
-    c->fetch_beside = false;
+    c->fetch_beside = c->rows_split = false;
     c->fetch_stream = tc.ss;
     c->fetch_reads_caller_lists = tc.mpos == tc.miss_pos;
     if (n_hit) {
@@ -2058,7 +2104,7 @@ try {
                    c->num_buckets - 1, c->slot_to_node, c->slot_to_entry, c->dev, par, 0);
         }
         if (c->fetch_pending && c->fetch_stream != st)  // rows of the misses (st is behind the hit gather, see above)
-            BGL_HIP(hipStreamWaitEvent(st, rows_event(c, true), 0));
+            BGL_HIP(hipStreamWaitEvent(st, misses_event(c), 0));
         {
             Prof p(c, BGL_STAGE_INSERT_ROWS, st);
             dispatch_q(q, [&](auto Q) {
@@ -2068,7 +2114,7 @@ try {
             });
         }
     } else {
-        if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, rows_event(c, true), 0));
+        if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, misses_event(c), 0));
         rc = launch_marked(c, st, done, done == c->ev_map_local, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
     }
     if (st == c->last_main) c->rows_joined = true;
@@ -2116,9 +2162,8 @@ try {
     if (!c) BGL_FAIL(BGL_EINVAL, "cache handle is null");
     hipStream_t st = static_cast<hipStream_t>(stream);
     // (a FIFO update that copies rows has made the main stream wait for them already: a wait costs the host 10 us)
-    if (c->fetch_pending && c->fetch_stream != st && !(c->rows_joined && st == c->last_main))
-        BGL_HIP(hipStreamWaitEvent(st, rows_event(c, st == c->last_main), 0));
-    return BGL_OK;
+    if (c->rows_joined && st == c->last_main) return BGL_OK;
+    return join_rows(c, st);
 } BGL_NOTHROW_END
 
 extern "C" int bgl_cache_wait_lists(bgl_cache_t *c, void *stream)

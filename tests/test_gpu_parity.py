@@ -528,6 +528,59 @@ def test_cache_that_can_hold_every_node_rows_reach_other_streams(B, torch_mod, o
         assert np.array_equal(slot.cpu().numpy(), want_slot), r
 
 
+@pytest.mark.parametrize("consumer", ["third stream", "next lookup on another stream", "update on a third stream"])
+@pytest.mark.parametrize("misses", [0, 7, 3_000])
+@pytest.mark.parametrize("n", [60_000, 66_000])
+def test_cache_rows_of_small_lookups_reach_other_streams(B, torch_mod, n, misses, consumer):
+    """Up to 64 MiB asked for with no side stream named, the fetch runs beside the hit gather, and either may end
+    first: whoever waits for the rows, and the next lookup, come after both.  (66,000 rows: beyond the limit.)"""
+    import oracle
+    torch = torch_mod
+    rng = np.random.default_rng(n + misses)
+    N, rb = 80_000, 1024
+    feats = np.tile(rng.integers(0, 256, (N, 64), dtype=np.uint8), (1, rb // 64))
+    feat_t = torch.from_numpy(feats).pin_memory()
+    gc, oc = B.Cache(70_000, feat_t), oracle.Cache(70_000, feats)
+    main, other, third = (torch.cuda.Stream() for _ in range(3))
+    new = lambda: (torch.zeros((n, rb), dtype=torch.uint8, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda"),
+                   torch.empty(n, dtype=torch.int32, device="cuda"))
+    known, unknown = np.split(rng.permutation(N).astype(np.int32), [n])
+    out, slot, miss = new()
+    ids_t = torch.from_numpy(known).cuda()
+    gc.lookup_gather(ids_t, n, out, slot, miss)
+    gc.insert_fifo(ids_t, miss, -1, out)
+    torch.cuda.synchronize()
+    o_out, _, o_miss, _ = oc.lookup_gather(known)
+    oc.insert_fifo(known, o_miss, o_out)
+    for r in range(3):
+        ids = rng.permutation(np.concatenate([known[: n - misses], unknown[:misses]]))
+        want, want_slot, want_miss, _ = oc.lookup_gather(ids)
+        ids_t, known_t = torch.from_numpy(ids).cuda(), torch.from_numpy(known).cuda()
+        (out, slot, miss), (out2, slot2, miss2) = new(), new()
+        got = torch.empty_like(out)
+        torch.cuda.synchronize()
+        gc.lookup_gather(ids_t, n, out, slot, miss, main_stream=main)
+        st = third
+        if consumer == "next lookup on another stream":
+            gc.lookup_gather(known_t, n, out2, slot2, miss2, main_stream=other)
+            oc.lookup_gather(known)
+            st = other              # behind that lookup, which is behind the first one's rows
+        elif consumer == "update on a third stream":
+            gc.insert_fifo(ids_t, miss, -1, out, stream=third)
+            oc.insert_fifo(ids, want_miss, want)
+            known, unknown = ids, np.setdiff1d(np.arange(N, dtype=np.int32), ids)
+        if consumer != "next lookup on another stream":
+            gc.wait_rows(third)
+        with torch.cuda.stream(st):
+            got.copy_(out)
+        torch.cuda.synchronize()
+        assert np.array_equal(got.cpu().numpy(), want), r
+        assert np.array_equal(slot.cpu().numpy(), want_slot), r
+        if consumer == "next lookup on another stream":
+            assert torch.equal(out2.cpu(), feat_t[torch.from_numpy(known).long()]), r
+    assert_state_equal(gc, oc)
+
+
 @pytest.mark.parametrize("limit_mib", [96, 256])
 @pytest.mark.parametrize("row_bytes", [400, 1024, 4096])
 def test_cache_hit_gather_around_its_limits(B, torch_mod, limit_mib, row_bytes):
