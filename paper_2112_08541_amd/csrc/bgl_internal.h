@@ -65,8 +65,8 @@ namespace bgl {
 
 // Scratch of an ordering call: device memory, and page-locked host memory that is coherent whatever
 // HIP_HOST_COHERENT says.  A graph keeps what its last call used for the next one: freeing 100 MB or more
-// costs 0.25 ms.  It holds one of each at most, up to the sizes below, and frees them with the graph; a call that
-// finds them taken by another thread's allocates its own.
+// costs 0.25 ms.  It holds one of each at most, up to the sizes below and where device memory is not short, and frees them
+// with the graph; a call that finds them taken by another thread's allocates its own.
 struct OrderScratch {
     void *device = nullptr, *host = nullptr;
     size_t device_bytes = 0, host_bytes = 0;
@@ -74,6 +74,7 @@ struct OrderScratch {
 };
 constexpr size_t ORDER_KEEP_DEVICE_BYTES = (size_t)5 << 28;  // (1.25 GiB)
 constexpr size_t ORDER_KEEP_HOST_BYTES = (size_t)64 << 20;
+constexpr size_t ORDER_KEEP_ALWAYS_BYTES = (size_t)64 << 20;  // a larger block is kept while 16 times as much is free
 int order_scratch_take(const bgl_graph *g, size_t device_bytes, size_t host_bytes, OrderScratch &s);
 // False: not kept, s is still the caller's.  Nothing enqueued may use s any more.
 bool order_scratch_put(const bgl_graph *g, OrderScratch &s);

@@ -22,10 +22,12 @@
 // a power law, and with a fixed number of lanes per node the longest row sets the
 // pace (16 lanes on a row of 20,000 edges: 1.9 ms for one level).  Measured, two
 // sequences on 2.45 M nodes / 122 M edges: 26 to 28 ms with 16 lanes per node and a
-// radix sort per level, 5.3 ms now (k_expand 2.8 ms, 89 G edges/s, bound by the
-// random reads of the visited bitmap and the keys, 87 % of which hit the L2);
-// five sequences on 100,000 nodes / 1 M edges, where launches and host round
-// trips count: 14 to 19 and 1.7 ms.
+// radix sort per level, 4.2 ms now (k_expand 2.4 ms, 100 G edges/s: 262 M reads that reach an L2, which serves
+// random ones at 265 G/s when they hit and memory at 60 to 105 G/s when they miss, 14 % of these, and 10 M atomics,
+// which the chip does 27 G/s of wherever they go); five sequences on 100,000 nodes / 1 M edges, where launches and
+// host round trips count: 14 to 19 and 0.58 ms.
+//   The sequences of a call are independent traversals and share their launches (blockIdx.y): one after the
+// other, the five took 1.7 ms, the two 4.8.
 //   A level is handled in windows of at most WINDOW edges, which bounds the lists whatever the
 // graph's size; a target reached in one window is visited in the next.
 //   When the frontier is empty the same three kernels restart the traversal.
