@@ -188,6 +188,34 @@ def test_sample_map_by_node_id_and_by_hash(B, torch_mod, num_nodes, num_seeds, f
     assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, fanouts, 77))
 
 
+@pytest.mark.parametrize("num_nodes", [2**22 - 4 * 1024, 2**22, 2**22 + 1, 2**22 + 4 * 1024 + 5])
+def test_sample_clears_the_whole_map(B, torch_mod, num_nodes):
+    """Maps of up to 16 MB are cleared with four stores per thread, larger ones with one non-temporal store:
+    around that size, in a workspace full of zeros (an id whose entry stays zero would take the first local
+    id), every node of the first and the last few thousand is met."""
+    import oracle
+    torch = torch_mod
+    rng = np.random.default_rng(num_nodes)
+    ends = np.concatenate([np.arange(9_000), np.arange(num_nodes - 9_000, num_nodes)]).astype(np.int32)
+    sources = np.sort(rng.choice(num_nodes, 600, replace=False))
+    deg = np.zeros(num_nodes, dtype=np.int64)
+    deg[sources] = 30
+    rp = np.zeros(num_nodes + 1, dtype=np.int32)
+    rp[1:] = np.cumsum(deg)
+    col = rng.permutation(ends)
+    seeds = rng.permutation(sources).astype(np.int32)
+    s = B.Sampler(B.Graph(rp, col), len(seeds), [32, 2])
+    s.workspace.zero_()
+    sb = s.sample(torch.from_numpy(seeds).cuda(), 9)
+    torch.cuda.synchronize()
+    nf, nnz = sb.sizes()
+    want = oracle.sample_khop(rp, col, seeds, [32, 2], 9)
+    assert nf.tolist() == want.n_frontier.tolist() and nnz.tolist() == list(want.nnz)
+    assert np.array_equal(sb.input_nodes(int(nf[2])).cpu().numpy(), want.input_nodes)
+    for h in range(2):
+        assert np.array_equal(sb.col_local(h, int(nnz[h])).cpu().numpy(), want.col_local[h])
+
+
 def _slot_of(ids, slots):
     """Where the workgroup's table of first occurrences starts to look for an id (MurmurHash3's finaliser)."""
     h = np.asarray(ids).astype(np.uint32)
