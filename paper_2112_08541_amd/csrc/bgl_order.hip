@@ -153,23 +153,33 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
     for (; i < n; i += stride) p[i] = v;
 }
 
-__global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uint32_t *bm, Progress *host)
+__global__ void k_set_bits(const int32_t *ids, int64_t n, int64_t num_nodes, uint32_t *bm, uint32_t *refused, Progress *host)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t v = ids[i];
-    if (v < 0 || (int64_t)v >= num_nodes) { host->status = BGL_EINVAL; return; }
-    const uint32_t old = atomicOr(&bm[(uint32_t)v >> 5], 1u << (v & 31));
-    if (old & (1u << (v & 31))) host->status = BGL_EINVAL;  // listed twice
+    const uint32_t bit = 1u << (v & 31);
+    if (v < 0 || (int64_t)v >= num_nodes || (atomicOr(&bm[(uint32_t)v >> 5], bit) & bit)) {  // foreign, or listed twice
+        *refused = 1;
+        host->status = BGL_EINVAL;
+    }
 }
 
 // A fresh traversal from its root: no keys, nothing visited but the root (bits at and above num_nodes
-// count as visited), the root's row as the first level.
+// count as visited), the root's row as the first level.  Where the training ids have been refused (the word
+// behind their bitmap) it is over before its first step.
 template <typename RP>
 __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, Roots roots, int64_t words, int64_t num_nodes,
                                               const uint32_t *__restrict__ train, Traversal all)
 {
     const Traversal me = all.mine();
+    if (train[words]) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            me.dev->step[0] = me.dev->step[1] = Step{0, 0, 0, 0, 0, 0, 0, 0, 1};
+            __hip_atomic_store(&me.host->done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        return;
+    }
     const int32_t root = roots.of[blockIdx.y];
     uint32_t *visited = me.visited, *closed = me.closed, *key = me.key;
     const Frontier f = me.f0;
@@ -641,7 +651,7 @@ struct OrderWork {
     const bgl_graph *g;
     Traversal t = {};            // of the first traversal
     int side = 1;                // traversals that run side by side
-    uint32_t *train = nullptr;
+    uint32_t *train = nullptr;   // a bit per node, then a word that says whether the ids were refused
     int32_t *train_ids = nullptr;
     Progress *host = nullptr;    // page-locked, one per traversal
     int32_t *seqs = nullptr;     // host memory: num_train ids per sequence of the call
@@ -671,7 +681,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
             total += round_up(n * sizeof(*p), 256);
         };
         total = 0;
-        take(w.train, (size_t)words);
+        take(w.train, (size_t)words + 1);
         take(w.train_ids, nt);
         take(w.t.seq, nt * (size_t)side);
         shared = total;
@@ -719,10 +729,10 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
         w.seqs = w.pageable.data();
     }
     BGL_HIP(hipMemcpyAsync(w.train_ids, ids, sizeof(int32_t) * (size_t)num_train, hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_fill_u32, dim3(std::min<int64_t>(ceil_div(words, BT), 4096)), dim3(BT), 0, st, w.train, words, 0u);
-    // (ids that are refused leave the traversals nothing to record: the status is looked at when they are over)
+    hipLaunchKernelGGL(k_fill_u32, dim3(std::min<int64_t>(ceil_div(words + 1, BT), 4096)), dim3(BT), 0, st, w.train, words + 1, 0u);
+    // (nobody waits here: ids that are refused end the traversals before their first step, and the host looks then)
     hipLaunchKernelGGL(k_set_bits, dim3((unsigned)ceil_div(num_train, BT)), dim3(BT), 0, st, w.train_ids, num_train, N, w.train,
-                       w.t.host);
+                       w.train + words, w.t.host);
     BGL_HIP(hipGetLastError());
     return BGL_OK;
 }

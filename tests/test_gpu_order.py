@@ -291,6 +291,36 @@ def test_host_pinned_graph_and_errors(B):
         B.order_proximity(g, [1, 2, 3], [0], [3], 3)  # shift out of range
 
 
+@pytest.mark.parametrize("bad", ["repeated", "foreign", "negative"])
+@pytest.mark.parametrize("sequences", [1, 3])
+def test_refused_training_ids_are_refused_at_once(B, bad, sequences):
+    """Training ids that are refused cost no traversal: on a path of 6,000 nodes, whose traversal is 6,000 steps of
+    three launches, the refusal takes a small part of the time (one traversal is some 500 times the checks: a tenth
+    leaves room for a busy host).  The graph serves valid calls as before."""
+    import oracle
+    N = 6_000
+    rp = np.minimum(np.arange(N + 1), N - 1).astype(np.int32)
+    col = np.arange(1, N, dtype=np.int32)
+    g = B.Graph(rp, col)
+    train = np.arange(0, N, 3)
+    wrong = np.concatenate([train, {"repeated": train[-1:], "foreign": [N], "negative": [-1]}[bad]])
+    roots, shifts = np.zeros(sequences, dtype=np.int64), np.arange(sequences) * 5
+    want = oracle.proximity_order(rp, col, train, roots, shifts, len(train))
+    assert np.array_equal(B.order_proximity(g, train, roots, shifts, len(train)), want)
+    t0 = time.perf_counter()
+    B.order_proximity(g, train, roots, shifts, len(train))
+    accepted = time.perf_counter() - t0
+    refused = []
+    for _ in range(3):
+        t0 = time.perf_counter()
+        with pytest.raises(B.BglError) as e:
+            B.order_proximity(g, wrong, roots, shifts, len(train))
+        refused.append(time.perf_counter() - t0)
+        assert e.value.code == B.BGL_EINVAL
+    assert min(refused) < accepted / 10
+    assert np.array_equal(B.order_proximity(g, train, roots, shifts, len(train)), want)
+
+
 def test_choose_sequences_matches_a_loop_over_the_oracle(B):
     import oracle
     rng = np.random.default_rng(12)
