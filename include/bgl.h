@@ -544,9 +544,9 @@ int bgl_host_tier_stats(bgl_host_tier_t *t, uint64_t *lookups, uint64_t *hits, d
  *   train_nodes   host, num_train distinct node ids
  *   seq           host, receives num_train ids
  * Synchronous (returns when seq is filled).  The graph keeps the scratch of its
- * last ordering call for the next one, until bgl_graph_destroy: at most 1.25 GiB
- * of device memory (beyond 64 MiB only while at least 16 times as much is free)
- * and 64 MiB of page-locked memory.  Calls of several threads may overlap.
+ * last ordering call for the next one, until bgl_graph_destroy: at most 512 MiB
+ * of device memory (beyond 64 MiB only while at least 64 times as much is free)
+ * and 32 MiB of page-locked memory.  Calls of several threads may overlap.
  * Errors: BGL_EINVAL (null pointers, root or a training id outside
  * [0, num_nodes), repeated training id, num_train outside [1, num_nodes]),
  * BGL_ENOMEM, BGL_EHIP.

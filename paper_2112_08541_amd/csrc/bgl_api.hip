@@ -52,14 +52,14 @@ int order_scratch_take(const bgl_graph *g, size_t device_bytes, size_t host_byte
 
 bool order_scratch_put(const bgl_graph *g, OrderScratch &s)
 {
-    if (s.device_bytes > ORDER_KEEP_DEVICE_BYTES || s.host_bytes > ORDER_KEEP_HOST_BYTES) return false;
+    if (s.device_bytes > ORDER_KEEP_DEVICE_BYTES) return false;
     if (s.device_bytes > ORDER_KEEP_ALWAYS_BYTES) {
         size_t free = 0, total = 0;
         if (hipMemGetInfo(&free, &total) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
-        if (free / 16 < s.device_bytes) return false;
+        if (free / ORDER_KEEP_SHARE < s.device_bytes) return false;
     }
     std::lock_guard<std::mutex> lk(g->order_guard);
     if (g->order_scratch.device) return false;

@@ -64,17 +64,20 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 namespace bgl {
 
 // Scratch of an ordering call: device memory, and page-locked host memory that is coherent whatever
-// HIP_HOST_COHERENT says.  A graph keeps what its last call used for the next one: freeing 100 MB or more
-// costs 0.25 ms.  It holds one of each at most, up to the sizes below and where device memory is not short, and frees them
-// with the graph; a call that finds them taken by another thread's allocates its own.
+// HIP_HOST_COHERENT says.  A graph keeps what its last call used for the next one: allocating and freeing it costs 0.1 to
+// 0.3 ms a call (2 sequences on 2.45 M nodes / 122 M edges, 310 MB: a first call 4.55 ms, further ones 4.25; 5 sequences on
+// 100,000 nodes, 60 MB: 0.69 and 0.59).  It holds one of each at most, up to the sizes below and where device memory is not
+// short, and frees them with the graph; a call that finds them taken by another thread's allocates its own.  The bounds keep
+// what a program that orders once cannot use afterwards small: a 64th of what it had left, never more than half a GiB (5
+// sequences on 2.45 M nodes take 775 MB and allocate it each time: 7.27 against 6.86 ms).
 struct OrderScratch {
     void *device = nullptr, *host = nullptr;
     size_t device_bytes = 0, host_bytes = 0;
     int ordinal = -1;  // the device's
 };
-constexpr size_t ORDER_KEEP_DEVICE_BYTES = (size_t)5 << 28;  // (1.25 GiB)
-constexpr size_t ORDER_KEEP_HOST_BYTES = (size_t)64 << 20;
-constexpr size_t ORDER_KEEP_ALWAYS_BYTES = (size_t)64 << 20;  // a larger block is kept while 16 times as much is free
+constexpr size_t ORDER_KEEP_DEVICE_BYTES = (size_t)512 << 20;
+constexpr size_t ORDER_KEEP_ALWAYS_BYTES = (size_t)64 << 20;  // a larger block is kept while ORDER_KEEP_SHARE times as much is free
+constexpr size_t ORDER_KEEP_SHARE = 64;
 int order_scratch_take(const bgl_graph *g, size_t device_bytes, size_t host_bytes, OrderScratch &s);
 // False: not kept, s is still the caller's.  Nothing enqueued may use s any more.
 bool order_scratch_put(const bgl_graph *g, OrderScratch &s);

@@ -248,6 +248,41 @@ def test_a_graph_s_scratch_serves_calls_of_all_sizes_and_threads(B):
         assert np.array_equal(order, calls[k][3])
 
 
+def test_large_scratch_and_many_recorded_ids(B):
+    """3 M nodes take 176 MB a traversal: seven sequences run five and two at a time, and record more ids than go to
+    page-locked memory (36 MB); what they used is given back, what two sequences used is kept (half a GiB at most) and
+    serves the next call, and the graph gives it back."""
+    import oracle
+    import torch
+    rng = np.random.default_rng(17)
+    N, sequences = 3_000_000, 7
+    rp = np.arange(N + 1, dtype=np.int32) * 6
+    col = rng.integers(0, N, 6 * N, dtype=np.int32)
+    train = rng.choice(N, 1_300_000, replace=False).astype(np.int32)
+    roots, shifts = rng.integers(0, N, sequences), rng.integers(0, len(train), sequences)
+    small = B.Graph(np.array([0, 1], dtype=np.int32), np.array([0], dtype=np.int32))
+    B.order_bfs_sequence(small, [0], 0)          # (the runtime's own first allocations)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    slack = 64 << 20
+    before = free()
+    g = B.Graph(rp, col)
+    loaded = free()
+    got = B.order_proximity(g, train, roots, shifts, len(train))
+    assert loaded - free() < slack
+    assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, len(train)))
+    want = oracle.proximity_order(rp, col, train, roots[:2], shifts[:2], len(train))
+    for _ in range(2):
+        assert np.array_equal(B.order_proximity(g, train, roots[:2], shifts[:2], len(train)), want)
+        assert 2 * 170e6 < loaded - free() <= (512 << 20) + slack
+    assert np.array_equal(B.order_bfs_sequence(g, train, int(roots[3])), oracle.bfs_sequence(rp, col, train, int(roots[3])))
+    g.close()
+    assert before - free() < slack
+
+
 def test_proximity_order_and_shuffling_error_mid_size(B):
     """The bfs configuration's graph at full size: 5 sequences over 204,800 training nodes."""
     import oracle
