@@ -89,11 +89,12 @@ struct bgl_cache {
     // Ordering between streams.  ev_listed: lists and hit rows of the last lookup are complete
     // (recorded on that lookup's main stream); ev_miss: its miss rows are complete and so are its hit
     // rows (recorded on the stream the fetch ran on, behind the hit gather: whoever waits for the rows,
-    // or is behind the call in that stream, has all of them); ev_map: the last FIFO update is complete
+    // or is behind the call in that stream, has all of them; not recorded where rows_split); ev_map: the last FIFO update is complete
     // (recorded on the update's stream), or ev_map_local: map_event says which (see LONG_LOOKUP_BYTES).
     // ev_fetched: a fetch that ran beside the hit gather is complete, whatever the gather does (for work
-    // that is behind the gather anyway).
-    hipEvent_t ev_listed = nullptr, ev_miss = nullptr, ev_map = nullptr, ev_fetched = nullptr;
+    // that is behind the gather anyway, and where rows_split for everyone, together with ev_listed).  ev_behind: nothing
+    // waits for it (see BESIDE_BYTES).
+    hipEvent_t ev_listed = nullptr, ev_miss = nullptr, ev_map = nullptr, ev_fetched = nullptr, ev_behind = nullptr;
     hipEvent_t ev_map_local = nullptr, map_event = nullptr;
     hipEvent_t ev_ids = nullptr;     // the lists of a lookup are complete (tiered: the missed ids have reached the host)
     hipEvent_t ev_lists = nullptr;   // the same for this cache's own miss fetch on the side stream
@@ -105,6 +106,7 @@ struct bgl_cache {
     bool fetch_reads_caller_lists = true;  // that fetch reads the caller's miss_pos (not the library's copy)
     bool map_pending = false;        // map_event marks a FIFO update the next lookup has to wait for
     bool ev_listed_valid = false;    // a lookup has recorded ev_listed
+    bool streaming = false;          // the caller enqueues batch after batch and waits for no stream meanwhile (the overlapped loop)
     bool write_through = false;      // the miss fetch also fills the cache buffer (see bgl_cache_set_write_through)
     bool awaiting_insert = false;    // write-through: a lookup's misses are in the buffer but not in the map yet
     const void *wt_ids = nullptr, *wt_miss_pos = nullptr;  // arguments of that lookup
@@ -411,7 +413,7 @@ constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
 // link, beside some 10 us that a copy costs whatever its size).
 constexpr int64_t LINK_CHUNK_BYTES = 2 << 20;
 // Lookups that ask for more bytes than this keep the GPU busy for longer than the host takes to enqueue
-// them.  Two things pay only there:
+// them.  Three things pay only there:
 //  - the FIFO update's event without a release to the system (only this library's kernels on this device
 //    wait for it).  A row of calls saves 5 us of each (lookup + update of 302,709 hits of 1,024 bytes), but a host that waits for a stream whose last command it is enqueues another one first: 500
 //    ids of 400 bytes, each call waited for, 63 / 70 us; hidden once the kernels outlast the host.  (Always
@@ -423,15 +425,23 @@ constexpr int64_t LINK_CHUNK_BYTES = 2 << 20;
 //    for 60 / 83, one after the other 59 / 67; 41 MB 71 / 86, 70 / 66; 82 MB 80 / 95, 75 / 70; 120 MB 101 /
 //    100, 90 / 80; 205 MB 114 / 110, 101 / 94; with 2 % misses 120 MB 157 / 135, 205 MB 187 / 150; with half
 //    of the ids missed the link sets the time either way.
+//  - the own event of a fetch behind the gather: 100,000 ids x 400 B, all hits, 70 / 62 with an event behind it, 74 / 59
+//    with its own; 250,000 x 64 B 70 / 68, 76 / 63.
 constexpr int64_t LONG_LOOKUP_BYTES = 100ll << 20;
-// Lookups that ask for more than this, or whose updates have a stream of their own, mark the end of their miss
-// fetch with the launch's own event (launch_marked).  Lookup + update, each waited for / one after the other, event behind |
-// own: 2,000 ids x 400 B 70 / 66 | 79 / 64 us; 5,000 ids 100 / 88 | 100 / 84.
-constexpr int64_t OWN_EVENT_BYTES = 3 << 19;
 // Lookups of up to this many bytes whose miss fetch has the cache's own side stream start it beside the hit
-// gather.  Lookup + update, behind the gather | beside it, each waited for / one after the other: 5,000 ids x 400 B 99 / 85 | 98 / 82 us,
-// 20,000 ids 206 / 188 | 201 / 183, 100,000 ids 793 / 769 | 783 / 764; with 70 % hits 40,000 ids x 1,024 B 135 / 137 | 135 / 126.
-// Beyond, a short gather is held up by the host reads (428,377 ids x 400 B 20 -> 140 us) and the whole gains nothing.
+// gather.  Its end is the launch's own event, which the update waits for, and an event that nothing waits for is recorded
+// behind it, so that a host that waits finds one (see launch_marked).  Lookup + update, each waited for / one after the
+// other, us: fetch behind the gather with no own event | beside, event behind | beside, own event | beside, both:
+//   ids x bytes   10 % hits                                   50 % hits                               all hits
+//   500 x 400     75 / 71 | 75 / 69 | 71 / 61 | 63 / 58       71 / 68 | 70 / 64 | 60 / 53 | 57 / 56   70 / 68 | 55 / 56 | 62 / 55 | 54 / 57
+//   2,000 x 400   76 / 71 | 75 / 72 | 75 / 71 | 75 / 72       68 / 70 | 73 / 70 | 79 / 70 | 74 / 70   70 / 67 | 55 / 57 | 62 / 55 | 55 / 58
+//   5,000 x 400   103 / 92 | 97 / 84 | 97 / 81 | 98 / 81      84 / 75 | 80 / 71 | 82 / 70 | 80 / 72   72 / 66 | 55 / 55 | 61 / 55 | 55 / 56
+//   20,000 x 400  230 / 219 | 227 / 213 | 224 / 209 | 224 / 209   154 / 143 | 150 / 136 | 149 / 133 | 148 / 133   72 / 67 | 56 / 56 | 62 / 54 | 55 / 55
+//   10,000 x 1024 226 / 216 | 223 / 211 | 221 / 206 | 221 / 206   153 / 142 | 149 / 136 | 147 / 133 | 147 / 132   72 / 62 | 63 / 57 | 61 / 53 | 55 / 55
+//   30,000 x 64   148 / 135 | 144 / 127 | 144 / 124 | 144 / 123   110 / 97 | 108 / 89 | 110 / 86 | 109 / 88   63 / 72 | 61 / 62 | 69 / 61 | 62 / 63
+// (no lower bound: 200 ids x 64 / 400 / 1,024 B, 10 % hits, behind | beside 67 / 67 | 62 / 61, 66 / 61 | 62 / 57, 73 / 74 | 71 / 69;
+// 160,000 ids x 400 B 1,441 / 1,439 | 1,420 / 1,419.)  Beyond, a short gather is held up by the host reads (428,377 ids x 400 B 20 -> 140 us)
+// and the whole gains nothing.
 constexpr int64_t BESIDE_BYTES = 64 << 20;
 // Hit gather: largest output (of the hits) whose rows are read with ordinary loads, and largest one that is
 // written with ordinary stores (the size of the last-level cache).
@@ -1101,9 +1111,12 @@ void launch(bgl_cache *c, hipStream_t st, void (*kernel)(P...), dim3 grid, dim3 
 // The same, and `mark` says when the kernel is over: with `own` as the launch's own completion event, else (and
 // where the launch is captured or timed) as a command behind it.  Its own event reaches a stream that waits for it
 // 2 us earlier (a 5 us kernel, a hand-over, a 5 us kernel, a hand-over back, a 5 us kernel: 43 instead of 47 us).
-// But a host that waits for a stream whose last event is a kernel's own enqueues another command first: lookup
-// + update of 500 ids x 400 B, each call waited for, 62 us with the hit gather's own event and the fetch's and the
-// update's behind them, 70 with all their own (62 with none; 5,000 ids, one call after the other, 87 / 83 / 92).
+// But a host that waits for a stream whose last event is a kernel's own enqueues another command first, and waits 4 to
+// 15 us longer.  So an event is recorded behind as well where the launch is the last of its stream (BESIDE_BYTES), and where the
+// updates have a stream of their own no launch marks its end itself unless the calls stream (bgl_cache::streaming): lookup
+// + update on another stream, each waited for / one after the other, none own | all own: 500 ids x 400 B, half hits, 71 / 70 |
+// 85 / 66 us; 2,000 ids, all hits, 70 / 68 | 85 / 66; 20,000 ids x 1,024 B, half hits, 257 / 234 | 265 / 232.  The overlapped loop, us
+// a batch of 512 seeds, fanout 10,5: 10,000 nodes x 400 B 82.0 | 79.7, x 64 B 72.5 | 67.1; 100 seeds, fanout 8,4, 90,000 nodes 74.8 | 69.0.
 template <typename... P, typename... A>
 int launch_marked(bgl_cache *c, hipStream_t st, hipEvent_t mark, bool own, void (*kernel)(P...), dim3 grid, dim3 block, A &&...a)
 {
@@ -1210,6 +1223,7 @@ try {
     if (hipEventCreateWithFlags(&c->ev_listed, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_miss, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_fetched, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->ev_behind, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_map, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_ids, hipEventDisableTiming) != hipSuccess ||
         // only this library's kernels on this device wait for these two: no release to the system (LONG_LOOKUP_BYTES)
@@ -1239,6 +1253,7 @@ try {
     if (c->ev_listed) (void)hipEventDestroy(c->ev_listed);
     if (c->ev_miss) (void)hipEventDestroy(c->ev_miss);
     if (c->ev_fetched) (void)hipEventDestroy(c->ev_fetched);
+    if (c->ev_behind) (void)hipEventDestroy(c->ev_behind);
     if (c->ev_map) (void)hipEventDestroy(c->ev_map);
     if (c->ev_map_local) (void)hipEventDestroy(c->ev_map_local);
     if (c->ev_ids) (void)hipEventDestroy(c->ev_ids);
@@ -1516,8 +1531,9 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
                       (beside || few_bytes) && n > 0);
     if (rc != BGL_OK) return rc;
     const hipEvent_t fetched = beside || few_bytes ? c->ev_fetched : c->ev_miss;
+    // (see launch_marked)
+    const bool own = update_beside || c->streaming ? c->streaming : few_bytes || n * c->row_bytes > LONG_LOOKUP_BYTES;
     auto fetch = [&]() -> int {
-        const bool own = update_beside || n * c->row_bytes > OWN_EVENT_BYTES;
         {
             Prof p(c, BGL_STAGE_FETCH_MISS, ss);
             // The small grid and the dealing of whole rows to wavefronts are for the host link only; an
@@ -1549,7 +1565,7 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
         BGL_HIP(hipStreamWaitEvent(ss, c->ev_lists, 0));
         if ((rc = fetch()) != BGL_OK) return rc;
     }
-    if ((rc = gather_phase(c, n, out_rows, ms, hits, true)) != BGL_OK) return rc;
+    if ((rc = gather_phase(c, n, out_rows, ms, hits, !update_beside || c->streaming)) != BGL_OK) return rc;
     if (n > 0) {
         if (!beside && !few_bytes) {
             if (ss != ms) BGL_HIP(hipStreamWaitEvent(ss, c->ev_listed, 0));
@@ -1558,6 +1574,8 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
             // (ev_miss, and whatever the caller enqueues on the side stream, come behind the gather as well)
             BGL_HIP(hipStreamWaitEvent(ss, c->ev_listed, 0));
             BGL_HIP(hipEventRecord(c->ev_miss, ss));
+        } else if (own) {
+            BGL_HIP(hipEventRecord(c->ev_behind, ss));
         }
         c->fetch_pending = true;
         c->fetch_beside = beside || few_bytes;
@@ -2050,6 +2068,8 @@ hipEvent_t update_event(const bgl_cache *c, hipStream_t st)
 
 }  // namespace
 
+void bgl::cache_streaming(bgl_cache *c, bool on) { c->streaming = on; }
+
 extern "C" int bgl_cache_insert_fifo(bgl_cache_t *c, const int32_t *ids, const int32_t *miss_pos,
                                      int64_t n_miss, const void *out_rows, void *stream)
 try {
@@ -2068,6 +2088,7 @@ try {
     const int par = (int)(c->insert_calls & 1);
     const bool other_stream = st != c->last_main;
     const hipEvent_t done = update_event(c, st);
+    const bool own = done == c->ev_map_local && (!other_stream || c->streaming);  // (see launch_marked)
     int rc = BGL_OK;
     auto enqueued = [&]() -> int {
         c->insert_calls += 1;
@@ -2088,11 +2109,11 @@ try {
         c->awaiting_insert = false;
         if (eff > 0) {
             Prof p(c, BGL_STAGE_INSERT_MAP, st);
-            rc = launch_marked(c, st, done, done == c->ev_map_local, k_insert_map, dim3((unsigned)bgl::ceil_div(eff, MAP_THREADS)),
+            rc = launch_marked(c, st, done, own, k_insert_map, dim3((unsigned)bgl::ceil_div(eff, MAP_THREADS)),
                                dim3(MAP_THREADS), ids, miss_pos, n_miss, c->capacity, c->num_nodes, c->table,
                                c->num_buckets - 1, c->slot_to_node, c->slot_to_entry, c->dev, par, 1);
         } else {
-            rc = launch_marked(c, st, done, done == c->ev_map_local, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
+            rc = launch_marked(c, st, done, own, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
         }
         return enqueued();
     }
@@ -2108,14 +2129,14 @@ try {
         {
             Prof p(c, BGL_STAGE_INSERT_ROWS, st);
             dispatch_q(q, [&](auto Q) {
-                rc = launch_marked(c, st, done, done == c->ev_map_local, k_insert_rows<decltype(Q)::value>, dim3(copy_blocks(eff, q)), dim3(COPY_THREADS),
+                rc = launch_marked(c, st, done, own, k_insert_rows<decltype(Q)::value>, dim3(copy_blocks(eff, q)), dim3(COPY_THREADS),
                                    miss_pos, n_miss, c->capacity, c->rows, q, reinterpret_cast<const uint4 *>(out_rows),
                                    reinterpret_cast<uint4 *>(c->buffer), c->dev, par);
             });
         }
     } else {
         if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, misses_event(c), 0));
-        rc = launch_marked(c, st, done, done == c->ev_map_local, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
+        rc = launch_marked(c, st, done, own, k_advance_tail, dim3(1), dim3(64), c->dev, n_miss, par);
     }
     if (st == c->last_main) c->rows_joined = true;
     return enqueued();

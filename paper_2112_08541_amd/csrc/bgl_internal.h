@@ -83,6 +83,10 @@ int order_scratch_take(const bgl_graph *g, size_t device_bytes, size_t host_byte
 bool order_scratch_put(const bgl_graph *g, OrderScratch &s);
 void order_scratch_free(OrderScratch &s);
 
+// From here on (until told otherwise) the cache's calls follow one another and the host waits for none of their streams.  It decides which
+// kind of event marks the end of a launch, nothing else.
+void cache_streaming(bgl_cache *c, bool on);
+
 }  // namespace bgl
 
 struct bgl_graph {

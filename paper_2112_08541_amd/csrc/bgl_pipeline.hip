@@ -13,8 +13,8 @@
 // by batch.  Sampling runs two batches ahead, hence three workspaces; the host waits only for
 // each sampling call's sizes and, with a host tier, for each batch's lists.
 //
-// This file is a client of the library's own C ABI (include/bgl.h) and nothing else: it
-// enqueues exactly what a caller of those functions would.
+// This file is a client of the library's own C ABI (include/bgl.h): it enqueues what a caller of
+// those functions would, and only tells the cache besides that its calls follow one another.
 #include <algorithm>
 #include <new>
 
@@ -182,6 +182,11 @@ try {
         BGL_HIP(hipEventRecord(p->sampled[k], samp));
         return BGL_OK;
     };
+    struct Streaming {
+        bgl_cache_t *c;
+        ~Streaming() { bgl::cache_streaming(c, false); }
+    } streaming{c};
+    bgl::cache_streaming(c, true);
     int rc;
     if (steps > 0 && (rc = sample(0)) != BGL_OK) return rc;
     if (steps > 1 && (rc = sample(1)) != BGL_OK) return rc;
