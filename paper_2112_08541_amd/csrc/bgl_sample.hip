@@ -38,9 +38,17 @@ constexpr int MARK_TILES = 4;                  // tiles a workgroup of mark has 
 constexpr int SEEDS_LDS = 4096;                // seeds whose repeats one workgroup removes in LDS
 constexpr int PREP = 1024;                     // threads per workgroup of k_prepare
 constexpr int FILL_PER_THREAD = 4;             // 16-byte stores per thread that clears the map ...
-// ... up to this many; a larger map (16 MB) is cleared with one non-temporal store per thread: its lines do not stay in the L2s,
-// and the kernel's end waits for what is dirty in them (32 MB, 4,096 seeds: the call 94.6 -> 92.6 us; 9.8 MB: 123.5 / 124.4).
-constexpr int64_t FILL_CACHED_CHUNKS = 1 << 20;
+// ... up to this many (28 MiB); a larger map is cleared with one non-temporal store per thread: its lines do not stay in the
+// L2s, and the kernel's end waits for what is dirty in them.  Behind other work that has used the caches that is the
+// faster way from 16 MB on, but one call right after the other then finds less of a map that the last-level cache
+// could hold.  us, four stores / one non-temporal, behind other work | one call after the other:
+//   nodes (degree)   4,096 seeds, 25,10          1,024 seeds, 15,10,5        4,096 seeds, 10
+//   4.3 M (50)       72.9 / 71.8 | 63.6 / 67.3   83.2 / 82.4 | 81.7 / 81.2   31.4 / 30.7 | 25.3 / 24.7
+//   6 M (14)         68.7 / 67.1 | 59.9 / 61.0   76.5 / 75.2 | 74.2 / 74.1   31.7 / 30.6 | 25.7 / 24.4
+//   8 M (20)         73.2 / 70.6 | 61.7 / 62.4   82.7 / 81.4 | 80.7 / 80.8   33.5 / 32.1 | 26.6 / 24.7
+//   12 M (10)        69.5 / 67.9 | 58.6 / 57.7   75.8 / 74.4 | 73.7 / 73.5   35.1 / 32.2 | 26.6 / 24.3
+//   16 M (10)        70.8 / 67.9 | 59.0 / 57.9   78.9 / 77.4 | 74.1 / 74.4   35.0 / 32.7 | 26.9 / 24.6
+constexpr int64_t FILL_CACHED_CHUNKS = 7 << 18;
 constexpr uint64_t EMPTY64 = ~0ull;
 constexpr uint32_t EMPTY32 = ~0u;
 // Largest graph whose dedup map is indexed by node id.  Clearing it costs 4 bytes per node (4 us at

@@ -188,18 +188,22 @@ def test_sample_map_by_node_id_and_by_hash(B, torch_mod, num_nodes, num_seeds, f
     assert_sample_equal(res, oracle.sample_khop(rp, col, seeds, fanouts, 77))
 
 
-@pytest.mark.parametrize("num_nodes", [2**22 - 4 * 1024, 2**22, 2**22 + 1, 2**22 + 4 * 1024 + 5])
+@pytest.mark.parametrize("num_nodes", [2**22 - 4 * 1024, 2**22, 2**22 + 1, 2**22 + 4 * 1024 + 5, 7 * 2**20 - 4 * 1024 - 3,
+                                       7 * 2**20, 7 * 2**20 + 1, 7 * 2**20 + 4 * 1024 + 5])
 def test_sample_clears_the_whole_map(B, torch_mod, num_nodes):
-    """Maps of up to 16 MB are cleared with four stores per thread, larger ones with one non-temporal store:
+    """Maps of up to 28 MiB are cleared with four stores per thread, larger ones with one non-temporal store:
     around that size, in a workspace full of zeros (an id whose entry stays zero would take the first local
-    id), every node of the first and the last few thousand is met."""
+    id), every node of the first and the last few thousand is met, and in between every 1,021st, so that each
+    workgroup's 4,096 entries, and each of its four stores' where it has four, hold some."""
     import oracle
     torch = torch_mod
     rng = np.random.default_rng(num_nodes)
-    ends = np.concatenate([np.arange(9_000), np.arange(num_nodes - 9_000, num_nodes)]).astype(np.int32)
-    sources = np.sort(rng.choice(num_nodes, 600, replace=False))
+    ends = np.concatenate([np.arange(9_000), np.arange(9_000, num_nodes - 9_000, 1_021),
+                           np.arange(num_nodes - 9_000, num_nodes)]).astype(np.int32)
+    sources = np.sort(rng.choice(num_nodes, -(-len(ends) // 30), replace=False))
     deg = np.zeros(num_nodes, dtype=np.int64)
     deg[sources] = 30
+    deg[sources[-1]] -= 30 * len(sources) - len(ends)
     rp = np.zeros(num_nodes + 1, dtype=np.int32)
     rp[1:] = np.cumsum(deg)
     col = rng.permutation(ends)
