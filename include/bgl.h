@@ -175,10 +175,12 @@ int bgl_cache_destroy(bgl_cache_t *c);
  *                   order out_slot, miss_pos, the hit count and the rows of the
  *                   hits are complete when the call's work is done
  *   side_stream     the miss fetch runs here (NULL: a stream owned by the
- *                   cache), after the hit gather (beside it in calls of up to 64 MiB on the
- *                   cache's own stream without write-through mode, and in calls beyond 100 MiB when
- *                   the cache can hold every node; what is enqueued on side_stream behind the
- *                   call comes after both either way), so that work enqueued on
+ *                   cache), after the hit gather.  (Without write-through mode it
+ *                   runs beside the hit gather in calls of up to 64 MiB whose
+ *                   side_stream is NULL and whose backing store is in host memory,
+ *                   and in calls beyond 100 MiB of a cache that can hold every
+ *                   node; what is enqueued on a side_stream behind the call comes
+ *                   after both either way.)  So work enqueued on
  *                   main_stream afterwards (the next batch's sampling) overlaps
  *                   the host-link transfer.  The rows of the misses are complete
  *                   for a stream once it has passed bgl_cache_wait_rows or the
@@ -432,6 +434,10 @@ int bgl_host_tier_destroy(bgl_host_tier_t *t);
  * as they are packed, independent of the cache's kernels; kernels on
  * side_stream then scatter them from there.  With early lookups the link then
  * carries one batch after the other without a pause.
+ * (In modes 0 and 1, and in mode 2 where it behaves as mode 1: rows of whole
+ * 128-byte lines, up to 1,024 bytes, that the tier holds are neither packed nor
+ * copied in calls without an early lookup; a kernel on side_stream reads them
+ * where they lie in the tier's ring.)
  * 2: as 1, and where the tier keeps nothing (capacity_rows = 0) and the cache is
  * in write-through mode, the lookup has no hit gather of its own: once the rows
  * have landed one pass writes the whole of out_rows in its own order (a hit's
@@ -442,8 +448,9 @@ int bgl_host_tier_destroy(bgl_host_tier_t *t);
  * then complete when the rows of the misses are (bgl_cache_wait_rows), not
  * earlier.  Elsewhere mode 2 behaves as mode 1.
  * Results are identical in all modes.  Waits for the device to go idle.
- * BGL_STAGE_FETCH_MISS then times the scatter kernels, BGL_STAGE_LINK_COPY the
- * copies, BGL_STAGE_ASSEMBLE_PRE and BGL_STAGE_ASSEMBLE the two passes of mode 2.
+ * BGL_STAGE_FETCH_MISS then times the scatter kernels (and the kernel that reads
+ * the tier's ring, at the link's pace), BGL_STAGE_LINK_COPY the copies,
+ * BGL_STAGE_ASSEMBLE_PRE and BGL_STAGE_ASSEMBLE the two passes of mode 2.
  * Errors: BGL_EINVAL (null handle, a batch is being served, mode not 0..2),
  * BGL_ENOMEM, BGL_EHIP.
  */
@@ -460,7 +467,8 @@ int bgl_host_tier_set_copy_engine(bgl_host_tier_t *t, int mode);
  * looked up against the tier's state at entry, then its own misses inserted in
  * that order (the rule of bgl_cache_insert_fifo, tail advancing by their
  * number).  The call blocks the host until the lists are known and the rows
- * are packed; what moves them starts while the host threads are still copying
+ * are packed (all but those that a kernel reads in the tier's ring, see
+ * bgl_host_tier_set_copy_engine); what moves them starts while the host threads are still copying
  * (kernels on side_stream chunk by chunk, or with the copy-engine transport
  * copies on the tier's own stream followed by kernels on side_stream).  On
  * return the fetch of all miss rows is enqueued on side_stream
@@ -525,7 +533,8 @@ int bgl_host_tier_export_state(bgl_host_tier_t *t, int32_t *slot_to_node, uint64
 /*
  * Lifetime counters: ids looked up, ids found, host wall time spent packing rows
  * (milliseconds, per batch from the start of its copies to the moment the
- * calling thread sees the last row in place) over `batches` served batches; and
+ * calling thread sees the last row in place; rows that a kernel reads in the
+ * tier's ring are not packed and not in it) over `batches` served batches; and
  * the thread count in use.  Pointers may be null.
  */
 int bgl_host_tier_stats(bgl_host_tier_t *t, uint64_t *lookups, uint64_t *hits, double *copy_ms,

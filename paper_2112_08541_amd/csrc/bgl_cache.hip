@@ -410,7 +410,9 @@ constexpr int SMALL_FETCH_BLOCKS = 16;
 constexpr int64_t TIER_CHUNK_ROWS = 49152;
 constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
 // Copy-engine transport without the early lookup: bytes that are worth a copy of their own (35 us on the
-// link, beside some 10 us that a copy costs whatever its size).
+// link, beside some 10 us that a copy costs whatever its size).  Where it lies matters little: with 1, 2 and 4 MiB, rows of 16 to
+// 1,024 bytes and 500 to 150,000 ids differ by 2 % or less.  Against chunks that double up to TIER_CHUNK_ROWS no size lost (272 B x
+// 150,000 ids 1,074 -> 995 us, 400 B 1,449 -> 1,340, 528 B 1,871 -> 1,708, 60,000 ids x 528 B 891 -> 832; 5,000 ids and fewer: the same).
 constexpr int64_t LINK_CHUNK_BYTES = 2 << 20;
 // Lookups that ask for more bytes than this keep the GPU busy for longer than the host takes to enqueue
 // them.  Three things pay only there:
@@ -656,7 +658,8 @@ __global__ __launch_bounds__(COPY_THREADS) void k_fetch_link(
 // whole 128-byte lines, which cross the link in place as fast as packed.  The launch needs no host thread, so it is
 // under way while the first of the other rows are being packed, and it fills the moments between their copies.
 // Measured, 150,001 ids x 512 B of which 25,600 in the tier, copy engine 1,600 -> 1,390 us a call, kernels
-// reading the packed rows 1,560 -> 1,374; 100,000 ids x 1,024 B 1,960 -> 1,720; 20,000 ids x 512 B 387 -> 320.
+// reading the packed rows 1,560 -> 1,374; 100,000 ids x 1,024 B 1,960 -> 1,720; 20,000 ids x 512 B 387 -> 320; 60,000 x 128 B
+// 306 -> 280; 5,000 ids x 128 / 512 / 1,024 B 164 / 192 / 260 -> 159 / 163 / 213; 500 ids the same.
 template <bool WT>
 __global__ __launch_bounds__(COPY_THREADS) void k_fetch_ring(
     const int32_t *__restrict__ hit_rank, const int32_t *__restrict__ hit_ring, int64_t count, const int32_t *__restrict__ miss_pos,

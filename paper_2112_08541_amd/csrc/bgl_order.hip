@@ -22,10 +22,10 @@
 // a power law, and with a fixed number of lanes per node the longest row sets the
 // pace (16 lanes on a row of 20,000 edges: 1.9 ms for one level).  Measured, two
 // sequences on 2.45 M nodes / 122 M edges: 26 to 28 ms with 16 lanes per node and a
-// radix sort per level, 4.2 ms now (k_expand 2.4 ms, 100 G edges/s: 262 M reads that reach an L2, which serves
+// radix sort per level, 4.2 ms now (4.5 in a graph handle's first call, which allocates the scratch; k_expand 2.4 ms, 100 G edges/s: 262 M reads that reach an L2, which serves
 // random ones at 265 G/s when they hit and memory at 60 to 105 G/s when they miss, 14 % of these, and 10 M atomics,
 // which the chip does 27 G/s of wherever they go); five sequences on 100,000 nodes / 1 M edges, where launches and
-// host round trips count: 14 to 19 and 0.58 ms.
+// host round trips count: 14 to 19 and 0.58 ms (a first call 0.69).
 //   The sequences of a call are independent traversals and share their launches (blockIdx.y): one after the
 // other, the five took 1.7 ms, the two 4.8.
 //   A level is handled in windows of at most WINDOW edges, which bounds the lists whatever the
