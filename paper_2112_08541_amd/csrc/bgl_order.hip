@@ -57,6 +57,7 @@ constexpr int64_t WINDOW = 1 << 23;          // edges per step at most
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
 constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
+constexpr int64_t MERGE_TURNS = 2048;        // turns of the merge (some 3 us) between two looks at how far the device is
 constexpr int SIDE_BY_SIDE = 16;             // traversals that share their launches at most
 constexpr int64_t SIDE_BY_SIDE_BYTES = 1ll << 30;  // and the memory they may take together (one alone: whatever it needs)
 constexpr size_t PAGE_LOCKED_SEQ_BYTES = 32 << 20;  // sequences of a call that still go to page-locked memory
@@ -85,7 +86,7 @@ struct OrderDev {
 
 // What the host sees of a traversal (page-locked memory).
 struct Progress {
-    uint32_t step;    // the last step that has begun to append, from 1
+    uint64_t begun;   // the last step that has begun to append, from 1, << 32 | training nodes that the steps before it have recorded
     uint32_t done;    // the traversal has ended
     int32_t seq_len;  // then: training nodes recorded
     int32_t status;   // of the call, in the first one's
@@ -121,7 +122,7 @@ struct Traversal {
     Frontier f0, f1;
     Lists li;
     OrderDev *dev;
-    int32_t *seq;       // num_train ids each, densely packed
+    int32_t *seq;       // num_train ids each, densely packed (page-locked memory, unless they are too many)
     Progress *host;     // one each
     int64_t stride, num_train;
 
@@ -542,8 +543,13 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
         if (blockIdx.x == 0 && threadIdx.x == 0) next = st;
         return;
     }
-    // (the step is under way: the host may enqueue another)
-    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(&host->step, step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    // A workgroup beyond the others' says that the step is under way, so that the host may enqueue another, and what the
+    // ones before it have recorded, so that the host may read that part of the sequence.
+    if (blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x == 0)
+            __hip_atomic_store(&host->begun, (uint64_t)step << 32 | (uint32_t)st.seq_len, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        return;
+    }
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     if (st.rows == 0) {
         const int open = dev->open_min;
@@ -647,6 +653,52 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
     }
 }
 
+// Merge of the sequences: turn t takes the next node of sequence t mod S that no earlier turn has taken.  One bit per
+// node says which are taken (a byte each is eight times the cache: 2.45 M nodes, two sequences of 204,800: 0.4 ms instead of
+// 0.9).  It goes on as far as the sequences are there, so that most of it is done by the time the traversals end.
+class Merge {
+    const int32_t *seqs;
+    int64_t num_train, num_out;
+    int32_t *order;
+    std::vector<uint64_t> used;
+    std::vector<int64_t> at;   // next place of each sequence, cyclically from its shift
+    int64_t k = 0;             // turns taken
+    size_t j = 0;              // whose turn it is
+
+public:
+    std::vector<int64_t> there;  // leading entries of each sequence that may be read
+
+    Merge(const int32_t *seqs_, int32_t num_sequences, const int64_t *shifts, int64_t num_train_, int64_t num_nodes, int64_t num_out_,
+          int32_t *order_, int64_t there_)
+        : seqs(seqs_), num_train(num_train_), num_out(num_out_), order(order_), used((size_t)ceil_div(num_nodes, 64), 0),
+          at(shifts, shifts + num_sequences), there((size_t)num_sequences, there_)
+    {
+    }
+    // At most `turns` turns; false if there was nothing to do.
+    bool go_on(int64_t turns)
+    {
+        const int64_t end = std::min(num_out, k + turns), begin = k;
+        while (k < end) {
+            const int32_t *seq = seqs + j * (size_t)num_train;
+            int64_t c = at[j];
+            int32_t v = 0;
+            do {
+                if (c >= there[j]) {  // (what has been passed over is taken and stays so)
+                    at[j] = c;
+                    return k > begin;
+                }
+                v = seq[c];
+                c = c + 1 == num_train ? 0 : c + 1;
+            } while (used[(size_t)v / 64] >> (v % 64) & 1u);
+            at[j] = c;
+            used[(size_t)v / 64] |= 1ull << (v % 64);
+            order[k++] = v;
+            j = j + 1 == at.size() ? 0 : j + 1;
+        }
+        return k > begin;
+    }
+};
+
 struct OrderWork {
     const bgl_graph *g;
     Traversal t = {};            // of the first traversal
@@ -655,6 +707,7 @@ struct OrderWork {
     int32_t *train_ids = nullptr;
     Progress *host = nullptr;    // page-locked, one per traversal
     int32_t *seqs = nullptr;     // host memory: num_train ids per sequence of the call
+    int32_t *seqs_device = nullptr;  // the same as the device sees it, where it is page-locked: the kernels write there
     std::vector<int32_t> pageable;  // the same where they are too many to be page-locked
     bgl::OrderScratch scratch;   // what all of the above are carved from
     bool keep = false;           // nothing enqueued uses the scratch any more
@@ -673,6 +726,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
     // the traversals share, then one equal part per traversal
     const size_t nt = (size_t)std::max<int64_t>(num_train, 1);
     const size_t win = (size_t)std::max<int64_t>(std::min<int64_t>(g->num_edges, WINDOW), 1);
+    const size_t seq_bytes = sizeof(int32_t) * nt * (size_t)num_sequences;
     size_t shared = 0, total = 0;
     char *at = nullptr;
     auto carve = [&](int side) {
@@ -683,7 +737,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
         total = 0;
         take(w.train, (size_t)words + 1);
         take(w.train_ids, nt);
-        take(w.t.seq, nt * (size_t)side);
+        if (seq_bytes > PAGE_LOCKED_SEQ_BYTES) take(w.t.seq, nt * (size_t)side);
         shared = total;
         take(w.t.visited, (size_t)words);
         take(w.t.closed, (size_t)words);
@@ -706,7 +760,6 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
     // Side by side a traversal's small steps, which are launches and latency, cost next to nothing beside
     // the others'.  Where the memory for that is not there, fewer at a time.
     w.side = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(num_sequences, SIDE_BY_SIDE), SIDE_BY_SIDE_BYTES / w.t.stride));
-    const size_t seq_bytes = sizeof(int32_t) * nt * (size_t)num_sequences;
     const size_t host_bytes = sizeof(Progress) * SIDE_BY_SIDE + (seq_bytes <= PAGE_LOCKED_SEQ_BYTES ? seq_bytes : 0);
     for (;; w.side = (w.side + 1) / 2) {
         carve(w.side);
@@ -723,6 +776,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
     const int32_t *ids = train_nodes;
     if (seq_bytes <= PAGE_LOCKED_SEQ_BYTES) {
         w.seqs = reinterpret_cast<int32_t *>(w.host + SIDE_BY_SIDE);
+        w.seqs_device = reinterpret_cast<int32_t *>(w.t.host + SIDE_BY_SIDE);
         ids = static_cast<const int32_t *>(std::memcpy(w.seqs, train_nodes, sizeof(int32_t) * (size_t)num_train));
     } else {
         w.pageable.resize(nt * (size_t)num_sequences);
@@ -739,48 +793,57 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
 
 // `count` <= w.side traversals side by side: sequences number first, first + 1, ... of the call.
 template <typename RP>
-int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count, int64_t num_train, OrderWork &w, hipStream_t st)
+int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count, int64_t num_train, OrderWork &w, hipStream_t st,
+                  Merge *merge)
 {
     const int64_t N = g->num_nodes, words = round_up(ceil_div(N, 32), 2);
     const RP *rp = static_cast<const RP *>(g->row_ptr);
+    const size_t one = (size_t)num_train;
+    Traversal t = w.t;
+    if (w.seqs_device) t.seq = w.seqs_device + one * (size_t)first;
     Roots r = {};
     for (int j = 0; j < count; ++j) {
         r.of[j] = (int32_t)roots[first + j];
-        w.host[j].step = w.host[j].done = 0;
+        w.host[j].begun = w.host[j].done = 0;
     }
     const dim3 reset_grid((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096), (unsigned)count);
-    hipLaunchKernelGGL(k_reset<RP>, reset_grid, dim3(BT), 0, st, rp, r, words, N, w.train, w.t);
+    hipLaunchKernelGGL(k_reset<RP>, reset_grid, dim3(BT), 0, st, rp, r, words, N, w.train, t);
     // As many workgroups as the largest step of this graph has shares for.
     const int64_t shares = std::max({ceil_div(std::min(g->num_edges, WINDOW), WTILE * BW), ceil_div(words, BT),
                                      std::min<int64_t>(ceil_div(N, 64 * BW), SEARCH_BLOCKS), (int64_t)1});
     const dim3 grid((unsigned)std::min<int64_t>(shares, BLOCKS), (unsigned)count);
     // The device says in page-locked words which step each traversal has come to and when it has ended; the
     // host stays STEPS_AHEAD steps ahead of the foremost, so the queue never runs empty and at most that many steps,
-    // whose launches return at once, are enqueued beyond the end.  The calling thread spins meanwhile.  (A
+    // whose launches return at once, are enqueued beyond the end.  The calling thread merges what there is of the sequences
+    // meanwhile (two of 204,800 on 2.45 M nodes: 4.25 -> 3.8 ms a call), or spins.  (A
     // synchronisation every 8 to 32 steps instead: 2.2 ms for five sequences of 13 steps on 100,000 nodes
     // one after the other, 1.7 with the words.)  Every step visits a
     // node or ends the traversal or is one of a level's windows.
     const int64_t most = 2 * N + g->num_edges / WINDOW + 4;
-    auto word = [](const uint32_t &x) { return __atomic_load_n(&x, __ATOMIC_ACQUIRE); };
+    auto word = [](const auto &x) { return __atomic_load_n(&x, __ATOMIC_ACQUIRE); };
     auto all_done = [&] {
         for (int j = 0; j < count; ++j)
             if (!word(w.host[j].done)) return false;
         return true;
     };
     auto come_to = [&] {
-        uint32_t s = 0;
-        for (int j = 0; j < count; ++j) s = std::max(s, word(w.host[j].step));
+        uint64_t s = 0;
+        for (int j = 0; j < count; ++j) {
+            const uint64_t begun = word(w.host[j].begun);
+            s = std::max(s, begun >> 32);
+            if (merge && w.seqs_device) merge->there[(size_t)(first + j)] = (int64_t)(uint32_t)begun;
+        }
         return (int64_t)s;
     };
     for (int64_t step = 1; !all_done(); ++step) {
         if (step > most + STEPS_AHEAD) BGL_FAIL(BGL_EHIP, "the traversal did not end");
         const int par = (int)((step - 1) & 1);
-        hipLaunchKernelGGL(k_expand<RP>, grid, dim3(BT), 0, st, rp, g->col, N, w.t, par);
-        hipLaunchKernelGGL(k_count<RP>, grid, dim3(BT), 0, st, rp, words, w.train, w.t, par);
-        hipLaunchKernelGGL(k_append<RP>, grid, dim3(BT), 0, st, rp, words, w.train, w.t, par, (uint32_t)step);
+        hipLaunchKernelGGL(k_expand<RP>, grid, dim3(BT), 0, st, rp, g->col, N, t, par);
+        hipLaunchKernelGGL(k_count<RP>, grid, dim3(BT), 0, st, rp, words, w.train, t, par);
+        hipLaunchKernelGGL(k_append<RP>, dim3(grid.x + 1, grid.y), dim3(BT), 0, st, rp, words, w.train, t, par, (uint32_t)step);
         BGL_HIP(hipGetLastError());
         for (int64_t spins = 1; !all_done() && step - come_to() >= STEPS_AHEAD; ++spins) {
-            __builtin_ia32_pause();
+            if (!merge || !merge->go_on(MERGE_TURNS)) __builtin_ia32_pause();
             // a stream that has nothing left to do, or has failed, will not come to the step waited for
             if (spins % 65536 == 0) {
                 const hipError_t e = hipStreamQuery(st);
@@ -791,8 +854,10 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
             }
         }
     }
-    const size_t one = (size_t)num_train;
-    BGL_HIP(hipMemcpyAsync(w.seqs + one * (size_t)first, w.t.seq, sizeof(int32_t) * one * (size_t)count, hipMemcpyDeviceToHost, st));
+    if (!w.seqs_device)
+        BGL_HIP(hipMemcpyAsync(w.seqs + one * (size_t)first, t.seq, sizeof(int32_t) * one * (size_t)count, hipMemcpyDeviceToHost, st));
+    else if (merge)
+        while (come_to(), merge->go_on(num_train)) {}  // (while the last launches return)
     BGL_HIP(hipStreamSynchronize(st));  // the steps beyond the end too; w.host may be written anew
     if (w.host->status != 0) {
         w.keep = true;
@@ -801,19 +866,19 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
     for (int j = 0; j < count; ++j)
         if (w.host[j].seq_len != num_train)
             BGL_FAIL(BGL_EHIP, "the traversal recorded %d of %lld training nodes", w.host[j].seq_len, (long long)num_train);
+    if (merge) std::fill_n(merge->there.begin() + first, count, num_train);
     return BGL_OK;
 }
 
-// Leaves sequence j, num_train ids, at w.seqs[j * num_train].
-int compute_sequences(const bgl_graph_t *g, const int32_t *train_nodes, int64_t num_train, int32_t num_sequences,
-                      const int64_t *roots, hipStream_t st, OrderWork &w)
+// Behind prepare: leaves sequence j, num_train ids, at w.seqs[j * num_train].  A merge goes on meanwhile and may go to its end
+// afterwards.
+int compute_sequences(const bgl_graph_t *g, int64_t num_train, int32_t num_sequences, const int64_t *roots, hipStream_t st,
+                      OrderWork &w, Merge *merge)
 {
-    int rc = prepare(g, train_nodes, num_train, num_sequences, w, st);
-    if (rc != BGL_OK) return rc;
     for (int j = 0; j < num_sequences; j += w.side) {
         const int count = std::min(num_sequences - j, w.side);
-        rc = g->bits == 64 ? bfs_sequences<int64_t>(g, roots, j, count, num_train, w, st)
-                           : bfs_sequences<int32_t>(g, roots, j, count, num_train, w, st);
+        const int rc = g->bits == 64 ? bfs_sequences<int64_t>(g, roots, j, count, num_train, w, st, merge)
+                                     : bfs_sequences<int32_t>(g, roots, j, count, num_train, w, st, merge);
         if (rc != BGL_OK) return rc;
     }
     w.keep = true;
@@ -839,7 +904,8 @@ try {
     if (!seq) BGL_FAIL(BGL_EINVAL, "seq is null");
     hipStream_t st = static_cast<hipStream_t>(stream);
     OrderWork w(g);
-    if ((rc = compute_sequences(g, train_nodes, num_train, 1, &root, st, w)) != BGL_OK) return rc;
+    if ((rc = prepare(g, train_nodes, num_train, 1, w, st)) != BGL_OK) return rc;
+    if ((rc = compute_sequences(g, num_train, 1, &root, st, w, nullptr)) != BGL_OK) return rc;
     std::memcpy(seq, w.seqs, sizeof(int32_t) * (size_t)num_train);
     return BGL_OK;
 } BGL_NOTHROW_END
@@ -859,30 +925,6 @@ int check_proximity_args(const bgl_graph_t *g, const int32_t *train_nodes, int64
     return BGL_OK;
 }
 
-// Turn t takes the next node of sequence t mod S that no earlier turn has taken.  One bit per node says
-// which are taken (a byte each is eight times the cache: 2.45 M nodes, two sequences of 204,800: the merge
-// takes 0.4 ms instead of 0.9).
-void merge_sequences(const int32_t *seqs, int32_t num_sequences, const int64_t *shifts,
-                     int64_t num_train, int64_t num_nodes, int64_t num_out, int32_t *order)
-{
-    std::vector<uint64_t> used((size_t)ceil_div(num_nodes, 64), 0);
-    std::vector<int64_t> at(shifts, shifts + num_sequences);  // next place of each sequence, cyclically from its shift
-    for (int64_t k = 0; k < num_out;) {
-        for (int32_t j = 0; j < num_sequences && k < num_out; ++j, ++k) {
-            const int32_t *seq = seqs + (size_t)j * (size_t)num_train;
-            int64_t c = at[(size_t)j];
-            int32_t v;
-            do {
-                v = seq[c];
-                c = c + 1 == num_train ? 0 : c + 1;
-            } while (used[(size_t)v / 64] >> (v % 64) & 1u);
-            at[(size_t)j] = c;
-            used[(size_t)v / 64] |= 1ull << (v % 64);
-            order[k] = v;
-        }
-    }
-}
-
 }  // namespace
 
 extern "C" int bgl_order_proximity(const bgl_graph_t *g, const int32_t *train_nodes, int64_t num_train,
@@ -894,9 +936,11 @@ try {
     if (num_out < 0 || num_out > num_train) BGL_FAIL(BGL_EINVAL, "num_out must be in [0, num_train]");
     if (num_out > 0 && !order) BGL_FAIL(BGL_EINVAL, "order is null");
     OrderWork w(g);
-    rc = compute_sequences(g, train_nodes, num_train, num_sequences, roots, static_cast<hipStream_t>(stream), w);
-    if (rc != BGL_OK) return rc;
-    merge_sequences(w.seqs, num_sequences, shifts, num_train, g->num_nodes, num_out, order);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if ((rc = prepare(g, train_nodes, num_train, num_sequences, w, st)) != BGL_OK) return rc;
+    Merge merge(w.seqs, num_sequences, shifts, num_train, g->num_nodes, num_out, order, 0);
+    if ((rc = compute_sequences(g, num_train, num_sequences, roots, st, w, &merge)) != BGL_OK) return rc;
+    merge.go_on(num_out);
     return BGL_OK;
 } BGL_NOTHROW_END
 
@@ -910,10 +954,11 @@ try {
     if (rc != BGL_OK) return rc;
     if (!labels || !chosen || !order) BGL_FAIL(BGL_EINVAL, "labels, chosen and order must not be null");
     OrderWork w(g);
-    rc = compute_sequences(g, train_nodes, num_train, max_sequences, roots, static_cast<hipStream_t>(stream), w);
-    if (rc != BGL_OK) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if ((rc = prepare(g, train_nodes, num_train, max_sequences, w, st)) != BGL_OK) return rc;
+    if ((rc = compute_sequences(g, num_train, max_sequences, roots, st, w, nullptr)) != BGL_OK) return rc;
     for (int32_t s = 1; s <= max_sequences; ++s) {
-        merge_sequences(w.seqs, s, shifts, num_train, g->num_nodes, num_train, order);
+        Merge(w.seqs, s, shifts, num_train, g->num_nodes, num_train, order, num_train).go_on(num_train);
         double mean_tv = 0.0, max_tv = 0.0;
         rc = bgl_order_shuffling_error(order, num_train, batch, labels, g->num_nodes, num_classes, &mean_tv, &max_tv);
         if (rc != BGL_OK) return rc;

@@ -211,6 +211,26 @@ def test_traversals_side_by_side_are_independent(B, sequences):
     assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, len(train)))
 
 
+@pytest.mark.parametrize("sequences,num_out", [(1, 20_000), (2, 20_000), (2, 1), (3, 9_999), (3, 0), (18, 20_000)])
+def test_merge_beside_the_traversals(B, sequences, num_out):
+    """The merge follows the traversals as they record: sequences that grow slowly (a path, one node a step) beside ones that
+    are there early, read from their first and from their last entry on, orders that are cut short."""
+    import oracle
+    rng = np.random.default_rng(sequences)
+    path, N = 400, 20_000
+    rp, col = random_graph(rng, N, 6)
+    adj = [[v + 1] for v in range(path)] + [(col[rp[v]:rp[v + 1]]).tolist() for v in range(path, N)]
+    rp[1:] = np.cumsum([len(a) for a in adj])
+    col = np.array([u for a in adj for u in a], dtype=np.int32)
+    g = B.Graph(rp, col)
+    train = rng.permutation(N)
+    roots = np.array([0, path, N - 1] * 6)[:sequences]
+    shifts = np.array([N - 1, 0, 1] * 6)[:sequences]
+    for _ in range(2):
+        got = B.order_proximity(g, train, roots, shifts, num_out)
+        assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, num_out))
+
+
 def test_a_graph_s_scratch_serves_calls_of_all_sizes_and_threads(B):
     """A graph keeps an ordering call's scratch for the next one: calls that need more or less of it, a call
     that is refused in between, and calls of several threads at the same time, each on its own stream."""
