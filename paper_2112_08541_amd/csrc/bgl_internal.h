@@ -65,11 +65,11 @@ namespace bgl {
 
 // Scratch of an ordering call: device memory, and page-locked host memory that is coherent whatever
 // HIP_HOST_COHERENT says.  A graph keeps what its last call used for the next one: allocating and freeing it costs 0.1 to
-// 0.3 ms a call (2 sequences on 2.45 M nodes / 122 M edges, 310 MB: a first call 4.55 ms, further ones 4.25; 5 sequences on
-// 100,000 nodes, 60 MB: 0.69 and 0.59).  It holds one of each at most, up to the sizes below and where device memory is not
+// 0.3 ms a call (2 sequences on 2.45 M nodes / 122 M edges, 380 MB: a first call 4.0 ms, further ones 3.6; 5 sequences on
+// 100,000 nodes, 50 MB: 0.69 and 0.59).  It holds one of each at most, up to the sizes below and where device memory is not
 // short, and frees them with the graph; a call that finds them taken by another thread's allocates its own.  The bounds keep
 // what a program that orders once cannot use afterwards small: a 64th of what it had left, never more than half a GiB (5
-// sequences on 2.45 M nodes take 775 MB and allocate it each time: 7.27 against 6.86 ms).
+// sequences on 2.45 M nodes take 940 MB and allocate it each time, 0.4 ms of 6.3).
 struct OrderScratch {
     void *device = nullptr, *host = nullptr;
     size_t device_bytes = 0, host_bytes = 0;

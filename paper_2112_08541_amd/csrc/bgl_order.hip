@@ -22,13 +22,13 @@
 // a power law, and with a fixed number of lanes per node the longest row sets the
 // pace (16 lanes on a row of 20,000 edges: 1.9 ms for one level).  Measured, two
 // sequences on 2.45 M nodes / 122 M edges: 26 to 28 ms with 16 lanes per node and a
-// radix sort per level, 4.2 ms now (4.5 in a graph handle's first call, which allocates the scratch; k_expand 2.4 ms, 100 G edges/s: 262 M reads that reach an L2, which serves
-// random ones at 265 G/s when they hit and memory at 60 to 105 G/s when they miss, 14 % of these, and 10 M atomics,
-// which the chip does 27 G/s of wherever they go); five sequences on 100,000 nodes / 1 M edges, where launches and
-// host round trips count: 14 to 19 and 0.58 ms (a first call 0.69).
+// radix sort per level, 3.3 to 3.8 ms now (4.0 in a graph handle's first call, which allocates the scratch; k_expand 2.3 ms,
+// 100 G edges/s: 262 M reads that reach an L2, which serves random ones at 267 G/s when they hit and 58 G/s when they miss, 14 %
+// of these, and 10 M atomics, which the chip does 27 G/s of wherever they go); five sequences on 100,000 nodes / 1 M edges,
+// where launches and host round trips count: 14 to 19 and 0.52 ms.
 //   The sequences of a call are independent traversals and share their launches (blockIdx.y): one after the
 // other, the five took 1.7 ms, the two 4.8.
-//   A level is handled in windows of at most WINDOW edges, which bounds the lists whatever the
+//   A level is handled in windows of at most WINDOW edges, which bounds the lists (6 bytes an edge) whatever the
 // graph's size; a target reached in one window is visited in the next.
 //   When the frontier is empty the same three kernels restart the traversal.
 // Nodes all of whose out-neighbors are visited ("closed") would each be a one-node
@@ -48,12 +48,17 @@ using namespace bgl;
 
 constexpr int BT = 256;
 constexpr int BW = BT / kWave;               // wavefronts per workgroup
-constexpr int BLOCKS = 2048;                 // workgroups of a step's kernels (those without a share leave at once)
+// Workgroups of a step's kernels for one or two traversals, half as many each where there are more (those without a share leave
+// at once, but 40,000 of them cost a launch 10 us).  k_expand, two on 2.45 M nodes, with 1,024 / 2,048 / 4,096: 2,533 / 2,400 / 2,355 us.
+constexpr int BLOCKS = 4096;
 constexpr int WAVES = BLOCKS * BW;
 constexpr int GROUPS = BLOCKS / kWave;       // groups of 64 workgroups whose totals are added up
 static_assert(GROUPS <= kWave && BW >= 2, "a wavefront sums the groups, another one a group's workgroups");
 constexpr int WTILE = 4 * kWave;             // edges a wavefront handles at a time, four per lane
-constexpr int64_t WINDOW = 1 << 23;          // edges per step at most
+// Edges per step at most: the larger window where the scratch of all traversals of a call fits then (fewer steps: two
+// sequences on 2.45 M nodes 3.8 -> 3.6 ms, k_expand 2,390 -> 2,300 us, k_count 545 -> 460, k_append 480 -> 410; twice as
+// large again 2,280 / 434 / 355), else the smaller one (ten on 1 M nodes, seven of them side by side: 6.1 -> 7.3).
+constexpr int64_t WINDOW = 1 << 24, SMALL_WINDOW = 1 << 23;
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
 constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
@@ -109,7 +114,8 @@ struct Totals {
 
 // The lists and totals of a step: one share per wavefront.
 struct Lists {
-    unsigned long long *cand;      // WINDOW entries: k_expand: target << 32 | edge; k_count: training bit << 63 | degree << 32 | node
+    uint32_t *node;                // as many entries as a window has edges: k_expand: targets; k_count: new nodes
+    uint16_t *edge;                // beside the targets: their edges, from the share's first one on
     uint32_t *n_cand, *n_win;      // per wavefront
     Totals *wave, *block;          // of a wavefront's, of a workgroup's first edges
     Totals *group;                 // of 64 workgroups'
@@ -124,8 +130,10 @@ struct Traversal {
     OrderDev *dev;
     int32_t *seq;       // num_train ids each, densely packed (page-locked memory, unless they are too many)
     Progress *host;     // one each
-    int64_t stride, num_train;
+    int64_t stride, num_train, window;
+    int32_t blocks;     // workgroups that a step is dealt to, at most BLOCKS
 
+    __device__ __forceinline__ uint32_t edges_of(const Step &st) const { return (uint32_t)min((unsigned long long)window, st.edges - st.win_lo); }
     __device__ __forceinline__ Traversal mine() const
     {
         Traversal t = *this;
@@ -133,7 +141,7 @@ struct Traversal {
         auto move = [&](auto *&p) { p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(reinterpret_cast<char *>(p) + by); };
         move(t.visited), move(t.closed), move(t.key);
         move(t.f0.off), move(t.f0.base), move(t.f1.off), move(t.f1.base);
-        move(t.li.cand), move(t.li.n_cand), move(t.li.n_win);
+        move(t.li.node), move(t.li.edge), move(t.li.n_cand), move(t.li.n_win);
         move(t.li.wave), move(t.li.block), move(t.li.group);
         move(t.dev);
         t.seq += (int64_t)blockIdx.y * num_train;
@@ -207,7 +215,11 @@ __global__ __launch_bounds__(BT) void k_reset(const RP *__restrict__ row_ptr, Ro
 }
 
 // The share of each wavefront in a step's window: a multiple of WTILE edges.
-__device__ __forceinline__ uint32_t edges_per_wave(uint32_t win) { return (win + WAVES * WTILE - 1) / (WAVES * WTILE) * WTILE; }
+__device__ __forceinline__ uint32_t edges_per_wave(uint32_t win, int blocks)
+{
+    const uint32_t all = (uint32_t)blocks * (BW * WTILE);
+    return (win + all - 1) / all * WTILE;
+}
 
 // Number of rows whose edges begin before x, by the whole wavefront: 64 probes a round.
 __device__ __forceinline__ uint32_t rows_before(const unsigned long long *off, uint32_t rows, unsigned long long x)
@@ -327,8 +339,8 @@ __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, c
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) dev->open_min = INT_MAX;  // for the next restart
     const Frontier f = st.buf ? me.f1 : me.f0;
-    const uint32_t win = (uint32_t)min((unsigned long long)WINDOW, st.edges - st.win_lo);
-    const uint32_t per = edges_per_wave(win);
+    const uint32_t win = me.edges_of(st);
+    const uint32_t per = edges_per_wave(win, me.blocks);
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const uint32_t wave = blockIdx.x * BW + w;
     const unsigned long long lo64 = (unsigned long long)wave * per;
@@ -385,9 +397,11 @@ __global__ __launch_bounds__(BT) void k_expand(const RP *__restrict__ row_ptr, c
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint64_t b = __ballot(cand[j]);
-            if (cand[j])
-                li.cand[lo + n_cand + __popcll(b & ((1ull << lane) - 1ull))] =
-                    (unsigned long long)u[j] << 32 | (t0 + j * kWave + lane);
+            if (cand[j]) {
+                const uint32_t at = lo + n_cand + (uint32_t)__popcll(b & ((1ull << lane) - 1ull));
+                li.node[at] = u[j];
+                li.edge[at] = (uint16_t)(t0 - lo + j * kWave + lane);
+            }
             n_cand += (uint32_t)__popcll(b);
         }
     }
@@ -405,12 +419,12 @@ __device__ __forceinline__ Totals wave_sum(const Totals &t) { return Totals{wave
 // Restart: the bitmap words that may hold closed nodes to take, an equal run of them per workgroup.
 struct WordRange {
     int64_t first, per, end;
-    __device__ __forceinline__ WordRange(int64_t scan_lo, int open_min, int64_t words)
+    __device__ __forceinline__ WordRange(int64_t scan_lo, int open_min, int64_t words, int blocks)
     {
         first = scan_lo >> 5;
         end = open_min == INT_MAX ? words : ((int64_t)open_min >> 5) + 1;
         const int64_t n = end - first;
-        per = (n + (int64_t)BLOCKS * BT - 1) / ((int64_t)BLOCKS * BT) * BT;
+        per = (n + (int64_t)blocks * BT - 1) / ((int64_t)blocks * BT) * BT;
     }
     __device__ __forceinline__ int64_t begin_of(int64_t block) const { return first + block * per; }
     __device__ __forceinline__ int64_t end_of(int64_t block) const { return min(first + (block + 1) * per, end); }
@@ -427,6 +441,7 @@ template <typename RP>
 __global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, int64_t words,
                                               const uint32_t *__restrict__ train, Traversal all, int par)
 {
+    typedef RP Ends __attribute__((ext_vector_type(2), aligned(sizeof(RP))));  // of a row, with one read
     __shared__ Totals sh[BW];
     const Traversal me = all.mine();
     const OrderDev *const dev = me.dev;
@@ -438,47 +453,47 @@ __global__ __launch_bounds__(BT) void k_count(const RP *__restrict__ row_ptr, in
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     Totals mine = {0, 0};
     if (st.rows == 0) {
-        const WordRange wr(st.scan_lo, dev->open_min, words);
+        const WordRange wr(st.scan_lo, dev->open_min, words, me.blocks);
         if (wr.begin_of(blockIdx.x) >= wr.end) return;
         for (int64_t i = wr.begin_of(blockIdx.x) + threadIdx.x; i < wr.end_of(blockIdx.x); i += BT)
             mine.nodes += (uint32_t)__popc(closed_bits(visited[i], i, dev->open_min) & train[i]);
         mine = wave_sum(mine);
     } else {
-        const uint32_t win = (uint32_t)min((unsigned long long)WINDOW, st.edges - st.win_lo);
-        const uint32_t per = edges_per_wave(win);
+        const uint32_t win = me.edges_of(st);
+        const uint32_t per = edges_per_wave(win, me.blocks);
         if ((unsigned long long)blockIdx.x * BW * per >= win) return;  // whole workgroups
         const uint32_t wave = blockIdx.x * BW + w;
         const bool active = (unsigned long long)wave * per < win;
         const uint32_t lo = active ? wave * per : 0, n = active ? li.n_cand[wave] : 0;
         uint32_t n_win = 0;
-        // First edges move to the front of the wavefront's own list, in order, with what k_append needs of
-        // them.  Four groups of 64 candidates at a time: their keys, then their rows, are in flight together.
+        // The nodes of first edges move to the front of the wavefront's own list, in order.  Four groups of 64 candidates at a
+        // time: their keys, then their rows, are in flight together.
         for (uint32_t i0 = 0; i0 < n; i0 += 4 * kWave) {
-            unsigned long long c[4];
-            uint32_t k[4];
+            uint32_t u[4], e[4], k[4], tr[4];
             bool first[4];
-            unsigned long long d[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) c[j] = li.cand[lo + min(i0 + j * kWave + lane, n - 1)];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) k[j] = key[(uint32_t)(c[j] >> 32)];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) first[j] = i0 + j * kWave + lane < n && k[j] == (uint32_t)c[j];
+            Ends ends[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t u = (uint32_t)(c[j] >> 32);
-                d[j] = 0;
-                if (first[j])  // (a row has at most 2^31 - 1 edges: checked when the graph is loaded)
-                    d[j] = (unsigned long long)((int64_t)row_ptr[u + 1] - (int64_t)row_ptr[u]) |
-                           (unsigned long long)(train[u >> 5] >> (u & 31) & 1u) << 31;
+                const uint32_t at = lo + min(i0 + j * kWave + lane, n - 1);
+                u[j] = li.node[at];
+                e[j] = lo + li.edge[at];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k[j] = key[u[j]];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {  // (candidates that are no first edge look at node 0)
+                first[j] = i0 + j * kWave + lane < n && k[j] == e[j];
+                const uint32_t v = first[j] ? u[j] : 0;
+                ends[j] = *reinterpret_cast<const Ends *>(row_ptr + v);
+                tr[j] = train[v >> 5] >> (v & 31) & 1u;
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint64_t b = __ballot(first[j]);
                 if (first[j]) {
-                    li.cand[lo + n_win + __popcll(b & ((1ull << lane) - 1ull))] = d[j] << 32 | c[j] >> 32;
-                    const uint32_t degree = (uint32_t)d[j] & 0x7fffffffu;
-                    mine += Totals{(unsigned long long)(degree > 0) << 32 | d[j] >> 31, degree};
+                    li.node[lo + n_win + __popcll(b & ((1ull << lane) - 1ull))] = u[j];
+                    const uint32_t degree = (uint32_t)(ends[j].y - ends[j].x);  // (less than 2^31: checked when the graph is loaded)
+                    mine += Totals{(unsigned long long)(degree > 0) << 32 | tr[j], degree};
                 }
                 n_win += (uint32_t)__popcll(b);
             }
@@ -526,9 +541,10 @@ struct Before {
 };
 
 template <typename RP>
-__global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, int64_t words, const uint32_t *__restrict__ train,
-                                               Traversal all, int par, uint32_t step)
+__global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, int64_t num_nodes, int64_t words,
+                                               const uint32_t *__restrict__ train, Traversal all, int par, uint32_t step)
 {
+    typedef RP Ends __attribute__((ext_vector_type(2), aligned(sizeof(RP))));  // of a row, with one read
     __shared__ Totals sh[3];
     __shared__ int sh_scan[BW];
     const Traversal me = all.mine();
@@ -553,7 +569,7 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     if (st.rows == 0) {
         const int open = dev->open_min;
-        const WordRange wr(st.scan_lo, open, words);
+        const WordRange wr(st.scan_lo, open, words, me.blocks);
         if (blockIdx.x > 0 && wr.begin_of(blockIdx.x) >= wr.end) return;
         const Before t(li, blockIdx.x, sh);
         int32_t o = st.seq_len + (int32_t)t.before.train();
@@ -589,8 +605,8 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
         }
         return;
     }
-    const uint32_t win = (uint32_t)min((unsigned long long)WINDOW, st.edges - st.win_lo);
-    const uint32_t per = edges_per_wave(win);
+    const uint32_t win = me.edges_of(st);
+    const uint32_t per = edges_per_wave(win, me.blocks);
     if ((unsigned long long)blockIdx.x * BW * per >= win) return;
     const Before t(li, blockIdx.x, sh);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -598,7 +614,7 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
         n.next_rows += t.all.rows();
         n.next_edges += t.all.edges;
         n.seq_len += (int32_t)t.all.train();
-        n.win_lo += WINDOW;
+        n.win_lo += (unsigned long long)me.window;
         if (n.win_lo >= st.edges) {  // that was the level's last window
             n.edges = n.next_edges;
             n.rows = n.next_rows;
@@ -609,6 +625,19 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
         next = n;
     }
     const uint32_t wave = blockIdx.x * BW + w;
+    // Where many nodes are new, the bitmap is brought up to date from the keys, 64 nodes a wavefront at a time, instead of with
+    // an atomic for each (the chip does 27 G/s): from a 32nd of the nodes on (2.45 M nodes, the largest steps 90 -> 52 us, all
+    // 447 -> 410), if enough wavefronts have a share for it (48 of them on 100,000 nodes: 8 -> 42).
+    const uint32_t waves = (win + per - 1) / per;
+    const bool bulk = t.all.rows() > (uint32_t)words && (int64_t)waves * (4 * kWave) >= num_nodes;
+    if (bulk) {
+        uint64_t *const visited64 = reinterpret_cast<uint64_t *>(visited);
+        for (int64_t i = wave; wave < waves && i * 64 < num_nodes; i += waves) {
+            const int64_t v = i * 64 + lane;
+            const uint64_t b = __ballot(v < num_nodes && me.key[v] < NO_KEY);
+            if (lane == 0 && b) visited64[i] |= b;
+        }
+    }
     if ((unsigned long long)wave * per >= win) return;
     Totals at = t.before;
     for (uint32_t k = blockIdx.x * BW; k < wave; ++k) at += li.wave[k];  // the wavefronts before this one in its workgroup
@@ -618,17 +647,20 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
     int32_t pos = st.seq_len + (int32_t)at.train();
     const uint32_t n = li.n_win[wave], lo = wave * per;
     for (uint32_t i0 = 0; i0 < n; i0 += 4 * kWave) {  // four groups of 64 at a time, as in k_count
-        unsigned long long c[4];
-        int64_t row_lo[4];
+        uint32_t nodes[4], trains[4];
+        Ends ends[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c[j] = li.cand[lo + min(i0 + j * kWave + lane, n - 1)];
+        for (int j = 0; j < 4; ++j) nodes[j] = li.node[lo + min(i0 + j * kWave + lane, n - 1)];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) row_lo[j] = (int64_t)row_ptr[(uint32_t)c[j]];
+        for (int j = 0; j < 4; ++j) {
+            ends[j] = *reinterpret_cast<const Ends *>(row_ptr + nodes[j]);
+            trains[j] = train[nodes[j] >> 5] >> (nodes[j] & 31) & 1u;
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool mine = i0 + j * kWave + lane < n;
-            const uint32_t u = (uint32_t)c[j], d = mine ? (uint32_t)(c[j] >> 32) & 0x7fffffffu : 0u;
-            const bool tr = mine && (c[j] >> 63) != 0;
+            const uint32_t u = nodes[j], d = mine ? (uint32_t)(ends[j].y - ends[j].x) : 0u;
+            const bool tr = mine && trains[j] != 0;
             const uint64_t has_row = __ballot(d > 0), is_train = __ballot(tr);
             const uint64_t below = (1ull << lane) - 1ull;
             unsigned long long inc = d;  // out-edges of the nodes up to this one
@@ -638,11 +670,11 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
                 if (lane >= s) inc += x;
             }
             if (mine) {
-                atomicOr(&visited[u >> 5], 1u << (u & 31));
+                if (!bulk) atomicOr(&visited[u >> 5], 1u << (u & 31));
                 if (d > 0) {
                     const uint32_t r = row + (uint32_t)__popcll(has_row & below);
                     f.off[r] = edge + inc - d;
-                    f.base[r] = row_lo[j] - (int64_t)(edge + inc - d);
+                    f.base[r] = (int64_t)ends[j].x - (int64_t)(edge + inc - d);
                 }
                 if (tr) seq[pos + __popcll(is_train & below)] = (int32_t)u;
             }
@@ -655,15 +687,59 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
 
 // Merge of the sequences: turn t takes the next node of sequence t mod S that no earlier turn has taken.  One bit per
 // node says which are taken (a byte each is eight times the cache: 2.45 M nodes, two sequences of 204,800: 0.4 ms instead of
-// 0.9).  It goes on as far as the sequences are there, so that most of it is done by the time the traversals end.
+// 0.9).  Many sequences are looked through 64 entries at a time, without a branch for each: all of them are read almost to
+// their end, and most entries are taken (ten of 100,000 on 1 M nodes: a call 6.4 -> 6.1 ms; two of 500,000 3.6 -> 3.75).
+// It goes on as far as the sequences are there, so that most of it is done by the time the traversals end.
 class Merge {
+    static constexpr size_t ONE_BY_ONE = 3;  // sequences that are looked through entry by entry
+    struct Reader {
+        int64_t at;         // next place to look at, cyclically from the shift
+        int64_t first = 0;  // the last 64 looked at begin here
+        uint64_t open = 0;  // those of them that were not taken then and have not been looked at again
+    };
     const int32_t *seqs;
     int64_t num_train, num_out;
     int32_t *order;
     std::vector<uint64_t> used;
-    std::vector<int64_t> at;   // next place of each sequence, cyclically from its shift
+    std::vector<Reader> readers;
     int64_t k = 0;             // turns taken
     size_t j = 0;              // whose turn it is
+
+    bool taken(int32_t v) const { return used[(size_t)v / 64] >> (v % 64) & 1u; }
+    // The next node of a sequence that nobody has taken, or -1 if its entry is not there yet.  (What has been passed over is
+    // taken and stays so.)
+    int32_t next(Reader &r, const int32_t *seq, int64_t limit) const
+    {
+        int64_t c = r.at;
+        int32_t v;
+        do {
+            if (c >= limit) {
+                r.at = c;
+                return -1;
+            }
+            v = seq[c];
+            c = c + 1 == num_train ? 0 : c + 1;
+        } while (taken(v));
+        r.at = c;
+        return v;
+    }
+    int32_t next_of_64(Reader &r, const int32_t *seq, int64_t limit) const
+    {
+        for (;;) {
+            for (; r.open; r.open &= r.open - 1) {
+                const int32_t v = seq[r.first + __builtin_ctzll(r.open)];
+                if (!taken(v)) {
+                    r.open &= r.open - 1;
+                    return v;
+                }
+            }
+            const int64_t n = std::min<int64_t>(limit - r.at, 64);
+            if (n <= 0) return -1;
+            for (int64_t i = 0; i < n; ++i) r.open |= (uint64_t)!taken(seq[r.at + i]) << i;
+            r.first = r.at;
+            r.at = r.at + n == num_train ? 0 : r.at + n;
+        }
+    }
 
 public:
     std::vector<int64_t> there;  // leading entries of each sequence that may be read
@@ -671,8 +747,9 @@ public:
     Merge(const int32_t *seqs_, int32_t num_sequences, const int64_t *shifts, int64_t num_train_, int64_t num_nodes, int64_t num_out_,
           int32_t *order_, int64_t there_)
         : seqs(seqs_), num_train(num_train_), num_out(num_out_), order(order_), used((size_t)ceil_div(num_nodes, 64), 0),
-          at(shifts, shifts + num_sequences), there((size_t)num_sequences, there_)
+          there((size_t)num_sequences, there_)
     {
+        for (int32_t s = 0; s < num_sequences; ++s) readers.push_back(Reader{shifts[s]});
     }
     // At most `turns` turns; false if there was nothing to do.
     bool go_on(int64_t turns)
@@ -680,20 +757,11 @@ public:
         const int64_t end = std::min(num_out, k + turns), begin = k;
         while (k < end) {
             const int32_t *seq = seqs + j * (size_t)num_train;
-            int64_t c = at[j];
-            int32_t v = 0;
-            do {
-                if (c >= there[j]) {  // (what has been passed over is taken and stays so)
-                    at[j] = c;
-                    return k > begin;
-                }
-                v = seq[c];
-                c = c + 1 == num_train ? 0 : c + 1;
-            } while (used[(size_t)v / 64] >> (v % 64) & 1u);
-            at[j] = c;
+            const int32_t v = readers.size() > ONE_BY_ONE ? next_of_64(readers[j], seq, there[j]) : next(readers[j], seq, there[j]);
+            if (v < 0) break;  // not there yet
             used[(size_t)v / 64] |= 1ull << (v % 64);
             order[k++] = v;
-            j = j + 1 == at.size() ? 0 : j + 1;
+            j = j + 1 == readers.size() ? 0 : j + 1;
         }
         return k > begin;
     }
@@ -725,7 +793,6 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
     // one device allocation for the whole call, sized up front and carved into 256-byte aligned parts: what
     // the traversals share, then one equal part per traversal
     const size_t nt = (size_t)std::max<int64_t>(num_train, 1);
-    const size_t win = (size_t)std::max<int64_t>(std::min<int64_t>(g->num_edges, WINDOW), 1);
     const size_t seq_bytes = sizeof(int32_t) * nt * (size_t)num_sequences;
     size_t shared = 0, total = 0;
     char *at = nullptr;
@@ -746,7 +813,9 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
             take(f->off, (size_t)N);
             take(f->base, (size_t)N);
         }
-        take(w.t.li.cand, win);
+        const size_t win = (size_t)std::max<int64_t>(std::min<int64_t>(g->num_edges, w.t.window), 1);
+        take(w.t.li.node, win);
+        take(w.t.li.edge, win);
         take(w.t.li.n_cand, WAVES);
         take(w.t.li.n_win, WAVES);
         take(w.t.li.wave, WAVES);
@@ -756,10 +825,16 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
         w.t.stride = (int64_t)(total - shared);
         total = shared + (total - shared) * (size_t)side;
     };
+    const int wanted = std::min(num_sequences, SIDE_BY_SIDE);
+    w.t.window = WINDOW;
     carve(1);
+    if (w.t.stride * wanted > SIDE_BY_SIDE_BYTES) {
+        w.t.window = SMALL_WINDOW;
+        carve(1);
+    }
     // Side by side a traversal's small steps, which are launches and latency, cost next to nothing beside
     // the others'.  Where the memory for that is not there, fewer at a time.
-    w.side = (int)std::max<int64_t>(1, std::min<int64_t>(std::min(num_sequences, SIDE_BY_SIDE), SIDE_BY_SIDE_BYTES / w.t.stride));
+    w.side = (int)std::max<int64_t>(1, std::min<int64_t>(wanted, SIDE_BY_SIDE_BYTES / w.t.stride));
     const size_t host_bytes = sizeof(Progress) * SIDE_BY_SIDE + (seq_bytes <= PAGE_LOCKED_SEQ_BYTES ? seq_bytes : 0);
     for (;; w.side = (w.side + 1) / 2) {
         carve(w.side);
@@ -809,9 +884,10 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
     const dim3 reset_grid((unsigned)std::min<int64_t>(ceil_div(N, BT), 4096), (unsigned)count);
     hipLaunchKernelGGL(k_reset<RP>, reset_grid, dim3(BT), 0, st, rp, r, words, N, w.train, t);
     // As many workgroups as the largest step of this graph has shares for.
-    const int64_t shares = std::max({ceil_div(std::min(g->num_edges, WINDOW), WTILE * BW), ceil_div(words, BT),
+    const int64_t shares = std::max({ceil_div(std::min(g->num_edges, w.t.window), WTILE * BW), ceil_div(words, BT),
                                      std::min<int64_t>(ceil_div(N, 64 * BW), SEARCH_BLOCKS), (int64_t)1});
-    const dim3 grid((unsigned)std::min<int64_t>(shares, BLOCKS), (unsigned)count);
+    t.blocks = count <= 2 ? BLOCKS : BLOCKS / 2;
+    const dim3 grid((unsigned)std::min<int64_t>(shares, t.blocks), (unsigned)count);
     // The device says in page-locked words which step each traversal has come to and when it has ended; the
     // host stays STEPS_AHEAD steps ahead of the foremost, so the queue never runs empty and at most that many steps,
     // whose launches return at once, are enqueued beyond the end.  The calling thread merges what there is of the sequences
@@ -819,7 +895,7 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
     // synchronisation every 8 to 32 steps instead: 2.2 ms for five sequences of 13 steps on 100,000 nodes
     // one after the other, 1.7 with the words.)  Every step visits a
     // node or ends the traversal or is one of a level's windows.
-    const int64_t most = 2 * N + g->num_edges / WINDOW + 4;
+    const int64_t most = 2 * N + g->num_edges / w.t.window + 4;
     auto word = [](const auto &x) { return __atomic_load_n(&x, __ATOMIC_ACQUIRE); };
     auto all_done = [&] {
         for (int j = 0; j < count; ++j)
@@ -840,7 +916,7 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
         const int par = (int)((step - 1) & 1);
         hipLaunchKernelGGL(k_expand<RP>, grid, dim3(BT), 0, st, rp, g->col, N, t, par);
         hipLaunchKernelGGL(k_count<RP>, grid, dim3(BT), 0, st, rp, words, w.train, t, par);
-        hipLaunchKernelGGL(k_append<RP>, dim3(grid.x + 1, grid.y), dim3(BT), 0, st, rp, words, w.train, t, par, (uint32_t)step);
+        hipLaunchKernelGGL(k_append<RP>, dim3(grid.x + 1, grid.y), dim3(BT), 0, st, rp, N, words, w.train, t, par, (uint32_t)step);
         BGL_HIP(hipGetLastError());
         for (int64_t spins = 1; !all_done() && step - come_to() >= STEPS_AHEAD; ++spins) {
             if (!merge || !merge->go_on(MERGE_TURNS)) __builtin_ia32_pause();
