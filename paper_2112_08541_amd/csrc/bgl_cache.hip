@@ -163,11 +163,12 @@ __global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
 // not zero.  A wavefront thus keeps 64 independent line reads in flight, which is
 // what a latency-bound random lookup needs.  The misses of a wavefront are
 // counted with one ballot; the bucket lines read are summed per workgroup for
-// the map statistics (the list kernel adds the sums up).
+// the map statistics (the list kernel adds the sums up).  own_slot: a second copy of the slots for a fetch on another stream
+// (k_fetch_slots), or null.
 __global__ __launch_bounds__(KEYS_PER_TILE) void k_probe(const int32_t *__restrict__ ids, int64_t n,
                                                          int64_t num_nodes,
                                                          const uint64_t *__restrict__ table,
-                                                         uint32_t bucket_mask, int32_t *out_slot,
+                                                         uint32_t bucket_mask, int32_t *out_slot, int32_t *own_slot,
                                                          int32_t *mbs, int32_t *tile_lines, CacheDev *dev)
 {
     __shared__ int sh_miss[KEYS_PER_TILE / kWave];
@@ -202,6 +203,7 @@ __global__ __launch_bounds__(KEYS_PER_TILE) void k_probe(const int32_t *__restri
             }
         }
         out_slot[i] = slot;
+        if (own_slot) own_slot[i] = slot;
     }
     const uint64_t missed = __ballot(i < n && slot < 0);
 #pragma unroll
@@ -290,83 +292,93 @@ struct RowRing {
     }
 };
 
-// Ordered lists of the miss positions and of the hits (position and slot side by
+// What the list kernels read and write.
+struct Lists {
+    const int32_t *out_slot;
+    int64_t n;
+    const int32_t *mbs, *tile_prefix, *tile_lines;  // of tiles of KEYS_PER_TILE ids: misses, misses before, bucket lines read
+    int32_t *miss_pos, *hit_pos, *hit_slot;
+    CacheDev *dev;
+    int64_t *n_hit_host;
+    const int32_t *ids;
+    int64_t num_nodes;
+    int32_t *miss_ids_host, *miss_pos_copy;
+    int gen;
+    int32_t *src_of;
+    int64_t capacity, rows;
+    int par;
+};
+
+// Ordered lists of the miss positions and (HITS) of the hits (position and slot side by
 // side, so the gather needs no dependent lookup).  A hit's rank is its position
 // minus the number of misses before it.  Every workgroup sums the miss counts of
 // the tiles before it (a few thousand ints at most), or reads the sum from
 // tile_prefix where the call has so many tiles that k_scan_tiles ran first; the
 // last one also publishes the call's counters.
-__global__ __launch_bounds__(KEYS_PER_TILE) void k_split_list(const int32_t *__restrict__ out_slot,
-                                                              int64_t n,
-                                                              const int32_t *__restrict__ mbs,
-                                                              const int32_t *__restrict__ tile_prefix,
-                                                              const int32_t *__restrict__ tile_lines,
-                                                              int32_t *miss_pos, int32_t *hit_pos,
-                                                              int32_t *hit_slot, CacheDev *dev,
-                                                              int64_t *n_hit_host,
-                                                              const int32_t *__restrict__ ids,
-                                                              int64_t num_nodes, int32_t *miss_ids_host,
-                                                              int32_t *miss_pos_copy, int gen, int32_t *src_of,
-                                                              int64_t capacity, int64_t rows, int par)
+template <bool HITS>
+__device__ __forceinline__ void list_tile(const Lists &l, int block, int blocks)
 {
     __shared__ int sh_scan[KEYS_PER_TILE / kWave];
     __shared__ int sh_base;
     int tot;
-    if (tile_prefix) {
-        if (threadIdx.x == 0) sh_base = tile_prefix[blockIdx.x];
+    if (l.tile_prefix) {
+        if (threadIdx.x == 0) sh_base = l.tile_prefix[block];
     } else {
         int part = 0;
-        for (int t = threadIdx.x; t < (int)blockIdx.x; t += KEYS_PER_TILE) part += mbs[t];
+        for (int t = threadIdx.x; t < block; t += KEYS_PER_TILE) part += l.mbs[t];
         (void)block_excl_scan<KEYS_PER_TILE>(part, sh_scan, tot);
         if (threadIdx.x == 0) sh_base = tot;
     }
-    const int64_t i = (int64_t)blockIdx.x * KEYS_PER_TILE + threadIdx.x;
-    const int slot = i < n ? out_slot[i] : 0;
-    const int flag = (i < n && slot < 0) ? 1 : 0;
+    const int64_t i = (int64_t)block * KEYS_PER_TILE + threadIdx.x;
+    const int slot = i < l.n ? l.out_slot[i] : 0;
+    const int flag = (i < l.n && slot < 0) ? 1 : 0;
     const int ex = block_excl_scan<KEYS_PER_TILE>(flag, sh_scan, tot);  // its barriers publish sh_base
     const int mrank = sh_base + ex;
     if (flag) {
-        miss_pos[mrank] = (int32_t)i;
-        if (miss_pos_copy) miss_pos_copy[mrank] = (int32_t)i;
-        if (miss_ids_host) {  // a host tier that keeps nothing: it only wants the ids of the misses, in order
-            const int32_t id = ids[i];
-            miss_ids_host[mrank] = id;
-            if (id < 0 || (int64_t)id >= num_nodes) n_hit_host[3] = 1;  // the host refuses the batch
+        l.miss_pos[mrank] = (int32_t)i;
+        if (HITS && l.miss_pos_copy) l.miss_pos_copy[mrank] = (int32_t)i;
+        if (HITS && l.miss_ids_host) {  // a host tier that keeps nothing: it only wants the ids of the misses, in order
+            const int32_t id = l.ids[i];
+            l.miss_ids_host[mrank] = id;
+            if (id < 0 || (int64_t)id >= l.num_nodes) l.n_hit_host[3] = 1;  // the host refuses the batch
         }
-    } else if (i < n) {
+    } else if (HITS && i < l.n) {
         // the kernels that read the row get its position in the cache buffer (see RowRing)
-        const int32_t pos = rows == capacity ? slot : (int32_t)RowRing(dev->tail[par], capacity, rows).pos_of_slot(slot);
-        if (!src_of) {
-            hit_pos[i - mrank] = (int32_t)i;
-            hit_slot[i - mrank] = pos;
+        const int32_t pos = l.rows == l.capacity ? slot : (int32_t)RowRing(l.dev->tail[l.par], l.capacity, l.rows).pos_of_slot(slot);
+        if (!l.src_of) {
+            l.hit_pos[i - mrank] = (int32_t)i;
+            l.hit_slot[i - mrank] = pos;
         } else {
-            src_of[i] = pos;
+            l.src_of[i] = pos;
         }
     }
     // assembled output (k_assemble_rows): the source of every position's row, a row position of the
     // cache buffer (>= 0) or, as -(r + 1), miss number r, whose row comes in with the packed miss rows
-    if (src_of && flag) src_of[i] = -(mrank + 1);
-    if (blockIdx.x != gridDim.x - 1) return;
+    if (HITS && l.src_of && flag) l.src_of[i] = -(mrank + 1);
+    if (block != blocks - 1) return;
     // the last workgroup publishes the call's counters
     int lines = 0, all_lines;
-    for (int t = threadIdx.x; t < (int)gridDim.x; t += KEYS_PER_TILE) lines += tile_lines[t];
+    for (int t = threadIdx.x; t < blocks; t += KEYS_PER_TILE) lines += l.tile_lines[t];
     (void)block_excl_scan<KEYS_PER_TILE>(lines, sh_scan, all_lines);
     if (threadIdx.x == 0) {
+        CacheDev *const dev = l.dev;
         const long long n_miss = sh_base + tot;
         dev->probe_lines += (unsigned long long)all_lines;
         dev->n_miss_last = n_miss;
-        dev->n_miss_gen[gen] = n_miss;
-        dev->n_hit_last = n - n_miss;
-        dev->lookups += (unsigned long long)n;
-        dev->hits += (unsigned long long)(n - n_miss);
+        dev->n_miss_gen[l.gen] = n_miss;
+        dev->n_hit_last = l.n - n_miss;
+        dev->lookups += (unsigned long long)l.n;
+        dev->hits += (unsigned long long)(l.n - n_miss);
         // page-locked host memory: visible to the host once the kernel has completed
-        if (n_hit_host) *n_hit_host = n - n_miss;
-        if (miss_ids_host) {  // the tier's counts: nothing found there, everything to be brought in
-            n_hit_host[1] = 0;
-            n_hit_host[2] = n_miss;
+        if (l.n_hit_host) *l.n_hit_host = l.n - n_miss;
+        if (HITS && l.miss_ids_host) {  // the tier's counts: nothing found there, everything to be brought in
+            l.n_hit_host[1] = 0;
+            l.n_hit_host[2] = n_miss;
         }
     }
 }
+
+__global__ __launch_bounds__(KEYS_PER_TILE) void k_split_list(Lists l) { list_tile<true>(l, blockIdx.x, gridDim.x); }
 
 // Row copies move 16-byte chunks; a row has Q = row_bytes / 16 of them.  Chunk
 // index -> (row, chunk in row) with a compile-time Q where the width is a
@@ -391,6 +403,8 @@ constexpr int COPY_UNROLL = 4;  // (the kernels name the four chunks of a lane b
 // needs half as much in flight; with 64 workgroups there the next batch's
 // lookup, and with it the packing of its rows, starts late.
 constexpr int FETCH_BLOCKS = 64;
+// Misses a wavefront of k_fetch_slots may have queued: less than a round of its fetch, and 64 more.
+__host__ __device__ constexpr int slots_queue(int q) { return COPY_UNROLL * (kWave / q) + kWave; }
 constexpr int RING_FETCH_BLOCKS = 32;
 // The overlapped loop's small batches (write-through mode, FIFO updates on another stream than the fetches:
 // the update and the next batch's sampling run beside the fetch): the bytes a lookup asks for at most, and
@@ -445,6 +459,7 @@ constexpr int64_t LONG_LOOKUP_BYTES = 100ll << 20;
 // 160,000 ids x 400 B 1,441 / 1,439 | 1,420 / 1,419.)  Beyond, a short gather is held up by the host reads (428,377 ids x 400 B 20 -> 140 us)
 // and the whole gains nothing.
 constexpr int64_t BESIDE_BYTES = 64 << 20;
+constexpr int64_t FROM_SLOTS_BYTES = 32 << 20;  // of those, the ones whose fetch reads the probe's slots (lookup_gather_impl)
 // Hit gather: largest output (of the hits) whose rows are read with ordinary loads, and largest one that is
 // written with ordinary stores (the size of the last-level cache).
 constexpr int64_t GATHER_CACHED_ROWS_BYTES = 96ll << 20;
@@ -527,6 +542,60 @@ __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
         asm volatile("; end of rows");
     };
     const int64_t bytes = total * 16;  // uniform
+    if (bytes > GATHER_CACHED_OUTPUT_BYTES) copy(std::true_type{}, std::true_type{});
+    else if (bytes > GATHER_CACHED_ROWS_BYTES) copy(std::true_type{}, std::false_type{});
+    else copy(std::false_type{}, std::false_type{});
+}
+
+// The miss list and the hit gather in one launch: the first workgroups are k_split_list's without the list of the hits, the
+// others copy the rows in the order of the positions, from the slots that the probe has left.  The gather then need not wait
+// for the lists, which are 4 to 6 us and a launch.  For calls that ask for little or hit for the most part: the positions of
+// misses cost reads and idle lanes, and the hits' number, which k_gather_hits chooses its accesses by, is not known: here
+// that is the number asked for.
+template <int Q>
+__global__ __launch_bounds__(COPY_THREADS) void k_list_and_hits(Lists l, int tiles, int q, const uint4 *__restrict__ buffer,
+                                                                uint4 *__restrict__ out)
+{
+    static_assert(COPY_THREADS == KEYS_PER_TILE && COPY_UNROLL == 4, "both kinds of workgroups have one size");
+    if ((int)blockIdx.x < tiles) {
+        list_tile<false>(l, blockIdx.x, tiles);
+        return;
+    }
+    const int qq = Q > 0 ? Q : q;
+    const int64_t last = l.n * qq - 1;
+    const int64_t base = (int64_t)(blockIdx.x - tiles) * (COPY_THREADS * COPY_UNROLL) + threadIdx.x;
+    // Phase by phase, as in k_gather_hits; positions of misses read a row that is not stored.
+    const int64_t x0 = min(base, last), x1 = min(base + COPY_THREADS, last), x2 = min(base + 2 * COPY_THREADS, last),
+                  x3 = min(base + 3 * COPY_THREADS, last);
+    int64_t i0, i1, i2, i3;
+    int c0, c1, c2, c3;
+    RowSplit<Q>::split(x0, q, i0, c0);
+    RowSplit<Q>::split(x1, q, i1, c1);
+    RowSplit<Q>::split(x2, q, i2, c2);
+    RowSplit<Q>::split(x3, q, i3, c3);
+    const int32_t s0 = l.out_slot[i0], s1 = l.out_slot[i1], s2 = l.out_slot[i2], s3 = l.out_slot[i3];
+    int64_t p0 = max(s0, 0), p1 = max(s1, 0), p2 = max(s2, 0), p3 = max(s3, 0);
+    if (l.rows != l.capacity) {  // uniform
+        const RowRing ring(l.dev->tail[l.par], l.capacity, l.rows);
+        p0 = s0 < 0 ? 0 : ring.pos_of_slot(s0);
+        p1 = s1 < 0 ? 0 : ring.pos_of_slot(s1);
+        p2 = s2 < 0 ? 0 : ring.pos_of_slot(s2);
+        p3 = s3 < 0 ? 0 : ring.pos_of_slot(s3);
+    }
+    auto copy = [&](auto nt_loads, auto nt_stores) {
+        // (the markers keep the compiler from merging the branches' accesses into ordinary ones)
+        asm volatile("; rows");
+        const uint4 v0 = ld16<nt_loads.value>(&buffer[p0 * qq + c0]);
+        const uint4 v1 = ld16<nt_loads.value>(&buffer[p1 * qq + c1]);
+        const uint4 v2 = ld16<nt_loads.value>(&buffer[p2 * qq + c2]);
+        const uint4 v3 = ld16<nt_loads.value>(&buffer[p3 * qq + c3]);
+        if (s0 >= 0) st16<nt_stores.value>(&out[x0], v0);
+        if (s1 >= 0) st16<nt_stores.value>(&out[x1], v1);
+        if (s2 >= 0) st16<nt_stores.value>(&out[x2], v2);
+        if (s3 >= 0) st16<nt_stores.value>(&out[x3], v3);
+        asm volatile("; end of rows");
+    };
+    const int64_t bytes = (last + 1) * 16;  // uniform
     if (bytes > GATHER_CACHED_OUTPUT_BYTES) copy(std::true_type{}, std::true_type{});
     else if (bytes > GATHER_CACHED_ROWS_BYTES) copy(std::true_type{}, std::false_type{});
     else copy(std::false_type{}, std::false_type{});
@@ -650,6 +719,66 @@ __global__ __launch_bounds__(COPY_THREADS) void k_fetch_link(
         if (base - sub >= n_miss) return;
         m0 = p0; m1 = p1; m2 = p2; m3 = p3;
         i0 = j0; i1 = j1; i2 = j2; i3 = j3;
+    }
+}
+
+// k_fetch_link without a list, for rows that go to out alone: a wavefront takes `per` positions at a time (at most 64) and
+// queues the misses among them in LDS, so that the fetch need not wait for the lists (4 us and a launch), and fetches them
+// as many at a time as k_fetch_link does.  (Every 64 positions' misses by themselves, the last few with lanes to spare: 20,000 ids of
+// 400 bytes, 90 % missed, 204.9 -> 209.9 us a call.)
+__global__ __launch_bounds__(COPY_THREADS) void k_fetch_slots(
+    const int32_t *__restrict__ own_slot, const int32_t *__restrict__ ids, int64_t n, int per, int q, int64_t num_nodes,
+    const uint4 *__restrict__ features, uint4 *__restrict__ out)
+{
+    extern __shared__ int2 sh_queue[];          // (id, position); slots_queue(q) per wavefront
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int group = kWave / q, round = COPY_UNROLL * group;  // rows side by side, rows at a time
+    const int sub = lane / q, c = lane - sub * q;
+    int2 *const queue = sh_queue + w * slots_queue(q);
+    const int64_t step = (int64_t)gridDim.x * (COPY_THREADS / kWave) * per;
+    int64_t first = ((int64_t)blockIdx.x * (COPY_THREADS / kWave) + w) * per;
+    auto mine = [&](int64_t at) { return lane < per && at + lane < n ? at + lane : -1; };
+    int64_t i = mine(first);
+    int32_t slot = i >= 0 ? own_slot[i] : 0, id = i >= 0 ? ids[i] : 0;
+    int queued = 0;
+    while (first < n) {
+        // (an id outside the table has been reported by the lookup: nothing is fetched for it)
+        const bool miss = slot < 0 && id >= 0 && (int64_t)id < num_nodes;
+        const uint64_t mask = __ballot(miss);
+        if (miss) queue[queued + __popcll(mask & ((1ull << lane) - 1ull))] = int2{id, (int)i};
+        queued += __popcll(mask);
+        first += step;
+        i = mine(first);  // the next positions' slots are read while these rows are on the link
+        slot = i >= 0 ? own_slot[i] : 0;
+        id = i >= 0 ? ids[i] : 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        int r = 0;
+        for (; queued - r >= round || (first >= n && r < queued); r += round) {
+            const int r0 = r + sub, r1 = r0 + group, r2 = r1 + group, r3 = r2 + group;
+            const bool ok0 = sub < group && r0 < queued, ok1 = sub < group && r1 < queued, ok2 = sub < group && r2 < queued,
+                       ok3 = sub < group && r3 < queued;
+            const int2 none = {0, 0};
+            const int2 m0 = ok0 ? queue[r0] : none, m1 = ok1 ? queue[r1] : none, m2 = ok2 ? queue[r2] : none, m3 = ok3 ? queue[r3] : none;
+            uint4 v0 = {0, 0, 0, 0}, v1 = v0, v2 = v0, v3 = v0;
+            if (ok0) v0 = features[(int64_t)m0.x * q + c];
+            if (ok1) v1 = features[(int64_t)m1.x * q + c];
+            if (ok2) v2 = features[(int64_t)m2.x * q + c];
+            if (ok3) v3 = features[(int64_t)m3.x * q + c];
+            // (the four reads stay above the branches that follow: the values are needed here)
+            asm volatile("" : "+v"(v0.x), "+v"(v0.y), "+v"(v0.z), "+v"(v0.w), "+v"(v1.x), "+v"(v1.y), "+v"(v1.z), "+v"(v1.w),
+                              "+v"(v2.x), "+v"(v2.y), "+v"(v2.z), "+v"(v2.w), "+v"(v3.x), "+v"(v3.y), "+v"(v3.z), "+v"(v3.w));
+            if (ok0) out[(int64_t)m0.y * q + c] = v0;
+            if (ok1) out[(int64_t)m1.y * q + c] = v1;
+            if (ok2) out[(int64_t)m2.y * q + c] = v2;
+            if (ok3) out[(int64_t)m3.y * q + c] = v3;
+        }
+        // what is left, less than a round, moves to the front (r is 0, or at least a round: the two parts do not overlap)
+        queued = max(queued - r, 0);
+        if (r > 0)
+            for (int k = lane; k < queued; k += kWave) queue[k] = queue[r + k];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -1097,17 +1226,23 @@ struct Prof {
     }
 };
 
+struct Grid {
+    dim3 grid;
+    size_t lds;  // dynamic
+    Grid(dim3 grid_, size_t lds_ = 0) : grid(grid_), lds(lds_) {}
+};
+
 // Kernel launch; inside a Prof scope of a one-kernel stage the dispatch records its
 // own begin and end into that scope's events.
 template <typename... P, typename... A>
-void launch(bgl_cache *c, hipStream_t st, void (*kernel)(P...), dim3 grid, dim3 block, A &&...a)
+void launch(bgl_cache *c, hipStream_t st, void (*kernel)(P...), const Grid &grid, dim3 block, A &&...a)
 {
     if (c->timed_start) {
         hipEvent_t e0 = c->timed_start, e1 = c->timed_stop;
         c->timed_start = c->timed_stop = nullptr;
-        hipExtLaunchKernelGGL(kernel, grid, block, 0, st, e0, e1, 0, static_cast<P>(a)...);
+        hipExtLaunchKernelGGL(kernel, grid.grid, block, grid.lds, st, e0, e1, 0, static_cast<P>(a)...);
     } else {
-        hipLaunchKernelGGL(kernel, grid, block, 0, st, static_cast<P>(a)...);
+        hipLaunchKernelGGL(kernel, grid.grid, block, grid.lds, st, static_cast<P>(a)...);
     }
 }
 
@@ -1123,7 +1258,7 @@ void launch(bgl_cache *c, hipStream_t st, void (*kernel)(P...), dim3 grid, dim3 
 // (The same loop written in Python over the public calls, which nothing tells apart from calls that are waited for, keeps the first of the
 // two: 512 seeds, 10,000 nodes x 400 B 99 | 92.)
 template <typename... P, typename... A>
-int launch_marked(bgl_cache *c, hipStream_t st, hipEvent_t mark, bool own, void (*kernel)(P...), dim3 grid, dim3 block, A &&...a)
+int launch_marked(bgl_cache *c, hipStream_t st, hipEvent_t mark, bool own, void (*kernel)(P...), const Grid &grid, dim3 block, A &&...a)
 {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (own && hipStreamIsCapturing(st, &capture) != hipSuccess) {
@@ -1134,7 +1269,7 @@ int launch_marked(bgl_cache *c, hipStream_t st, hipEvent_t mark, bool own, void 
         launch(c, st, kernel, grid, block, std::forward<A>(a)...);
         BGL_HIP(hipEventRecord(mark, st));
     } else {
-        hipExtLaunchKernelGGL(kernel, grid, block, 0, st, nullptr, mark, 0, static_cast<P>(a)...);
+        hipExtLaunchKernelGGL(kernel, grid.grid, block, grid.lds, st, nullptr, mark, 0, static_cast<P>(a)...);
     }
     return BGL_OK;
 }
@@ -1295,6 +1430,8 @@ struct LookupLists {
 struct HitList {
     const int32_t *pos = nullptr, *slot = nullptr;
     const int32_t *src_of = nullptr;  // assembled output: there is no hit gather
+    bool with_lists = false;          // the lists are made in the gather's launch (k_list_and_hits)
+    Lists lists = {};
 };
 
 // Make stream st wait for what a lookup that has not been joined yet still does on other streams: its miss
@@ -1319,7 +1456,7 @@ int join_rows(bgl_cache *c, hipStream_t st)
 // fetch while this one's lists are written.
 int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, int32_t *out_slot, int32_t *miss_pos, int64_t *n_hit_dev, hipStream_t ms, hipStream_t ls, bgl_host_tier *tier,
                  const int32_t **mpos_used, int *gen_used, HitList *hits, const LookupLists *fixed = nullptr,
-                 bool assemble = false, bool record_lists = false)
+                 bool assemble = false, bool record_lists = false, bool lists_with_hits = false, bool record_slots = false)
 {
     const bool early = ls != ms;
     const int gen = (int)(c->lookup_calls & 1);  // which copy of the per-call device state this call owns
@@ -1379,7 +1516,7 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, int32_t *out_slot,
     const int64_t mbs_cap = fixed ? fixed->mbs_cap : c->mbs_cap;
     int32_t *const hit_pos = fixed ? fixed->hit_pos : c->hit_pos;
     const int64_t hit_cap = fixed ? fixed->hit_cap : c->hit_cap;
-    *hits = HitList{hit_pos, hit_pos + hit_cap, src_of};
+    *hits = HitList{hit_pos, hit_pos + hit_cap, src_of, false, {}};
     c->lookup_calls += 1;
     c->last_n = n;
     if (tier) bgl::tier_prepare(tier);
@@ -1392,8 +1529,15 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, int32_t *out_slot,
     if (n > 0) {
         {
             Prof p(c, BGL_STAGE_PROBE, ls);
-            launch(c, ls, k_probe, dim3((unsigned)tiles), dim3(KEYS_PER_TILE), ids, n, c->num_nodes, c->table,
-                   c->num_buckets - 1, out_slot, mbs, mbs + 2 * mbs_cap, c->dev);
+            auto probe = [&](auto &&launch_it, int32_t *own_slot) {
+                return launch_it(k_probe, dim3((unsigned)tiles), dim3(KEYS_PER_TILE), ids, n, c->num_nodes, c->table,
+                                 c->num_buckets - 1, out_slot, own_slot, mbs, mbs + 2 * mbs_cap, c->dev);
+            };
+            if (record_slots)  // (the hits' list has no other use then)
+                rc = probe([&](auto kernel, auto &&...a) { return launch_marked(c, ls, c->ev_lists, true, kernel, a...); }, hit_pos);
+            else
+                probe([&](auto kernel, auto &&...a) { launch(c, ls, kernel, a...); }, (int32_t *)nullptr);
+            if (rc != BGL_OK) return rc;
         }
         {
             Prof p(c, BGL_STAGE_MISS_LIST, ls, false);
@@ -1402,17 +1546,17 @@ int lookup_phase(bgl_cache *c, const int32_t *ids, int64_t n, int32_t *out_slot,
                 tile_prefix = mbs + mbs_cap;
                 hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanThreads), 0, ls, mbs, tiles, tile_prefix);
             }
-            auto split = [&](auto &&launch_it) {
-                return launch_it(k_split_list, dim3((unsigned)tiles), dim3(KEYS_PER_TILE), out_slot, n, mbs, tile_prefix,
-                                 mbs + 2 * mbs_cap, miss_pos, hit_pos, hit_pos + hit_cap, c->dev, n_hit_dev, ids, c->num_nodes,
-                                 tier ? bgl::tier_ids_device_if_passthrough(tier) : nullptr, mpos_copy, gen, src_of,
-                                 c->capacity, c->rows, (int)(c->insert_calls & 1));
-            };
-            rc = split([&](auto kernel, auto &&...a) {
-                if (record_lists) return launch_marked(c, ls, c->ev_lists, true, kernel, a...);
-                launch(c, ls, kernel, a...);
-                return (int)BGL_OK;
-            });
+            const Lists lists{out_slot, n, mbs, tile_prefix, mbs + 2 * mbs_cap, miss_pos, hit_pos, hit_pos + hit_cap, c->dev, n_hit_dev, ids,
+                              c->num_nodes, tier ? bgl::tier_ids_device_if_passthrough(tier) : nullptr, mpos_copy, gen, src_of,
+                              c->capacity, c->rows, (int)(c->insert_calls & 1)};
+            if (lists_with_hits) {
+                hits->with_lists = true;
+                hits->lists = lists;
+            } else if (record_lists) {
+                rc = launch_marked(c, ls, c->ev_lists, true, k_split_list, dim3((unsigned)tiles), dim3(KEYS_PER_TILE), lists);
+            } else {
+                launch(c, ls, k_split_list, dim3((unsigned)tiles), dim3(KEYS_PER_TILE), lists);
+            }
             if (rc != BGL_OK) return rc;
         }
     } else {
@@ -1443,6 +1587,13 @@ int gather_phase(bgl_cache *c, int64_t n, void *out_rows, hipStream_t ms, const 
         Prof p(c, BGL_STAGE_GATHER_HIT, ms);
         int rc = BGL_OK;
         dispatch_q(q, [&](auto Q) {
+            if (hits.with_lists) {
+                const int tiles = (int)bgl::ceil_div(n, KEYS_PER_TILE);
+                rc = launch_marked(c, ms, c->ev_listed, own, k_list_and_hits<decltype(Q)::value>, dim3(tiles + copy_blocks(n, q)),
+                                   dim3(COPY_THREADS), hits.lists, tiles, q, reinterpret_cast<const uint4 *>(c->buffer),
+                                   reinterpret_cast<uint4 *>(out_rows));
+                return;
+            }
             rc = launch_marked(c, ms, c->ev_listed, own, k_gather_hits<decltype(Q)::value>, dim3(copy_blocks(n, q)), dim3(COPY_THREADS),
                                hits.pos, hits.slot, q, reinterpret_cast<const uint4 *>(c->buffer),
                                reinterpret_cast<uint4 *>(out_rows), c->dev);
@@ -1531,9 +1682,22 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
     // So does the fetch of a small one on the cache's own side stream: there the host's calls set the pace, and
     // those for the side stream come before the gather's.
     const bool few_bytes = ss != ms && !side_stream && !c->write_through && !c->features_in_hbm && n * c->row_bytes <= BESIDE_BYTES;
+    const bool mostly_hits = c->capacity >= c->num_nodes;
+    // A fetch over the link beside the gather waits for the slots alone (k_fetch_slots), unless it may be long: then the lists
+    // deal the misses more evenly (60,000 ids of 1,024 bytes, 90 % missed, from the slots / from lists: 1,084 / 1,077 us).
+    // Lookup + update from lists | from slots with k_list_and_hits, each waited for / one after the other, us: 200 x 400 B 57 / 54 |
+    // 54 / 49; 5,000 x 400 B, 90 % missed 97 / 83 | 93 / 77, half 83 / 70 | 77 / 64, none 59 / 59 | 56 / 54; 20,000 x 64 B, half 94 / 77 |
+    // 89 / 70; 20,000 x 400 B, 90 % missed 220 / 205 | 220 / 204; 302,709 hits of 1,024 B 163 / 144 | 161 / 140.
+    // (Timed stages have launches of their own; the lists that allocate nothing are read until the gather has ended, no longer.)
+    const bool timed_lists = c->profiling & (1u << BGL_STAGE_MISS_LIST | 1u << BGL_STAGE_GATHER_HIT);
+    const bool from_slots = (beside || few_bytes) && !timed_lists && !fixed && !c->features_in_hbm && q <= kWave && n > 0 &&
+                            (mostly_hits || n * c->row_bytes <= FROM_SLOTS_BYTES);
+    // The lists in the gather's launch (k_list_and_hits), unless the fetch waits for them beside it.
+    const bool with_hits = !early && !timed_lists && (from_slots || !(beside || few_bytes)) &&
+                           (mostly_hits || n * c->row_bytes <= GATHER_CACHED_ROWS_BYTES);
     HitList hits;
     rc = lookup_phase(c, ids, n, out_slot, miss_pos, n_hit_dev, ms, ls, nullptr, &mpos, &gen, &hits, fixed, false,
-                      (beside || few_bytes) && n > 0);
+                      (beside || few_bytes) && n > 0 && !from_slots, with_hits, from_slots);
     if (rc != BGL_OK) return rc;
     const hipEvent_t fetched = beside || few_bytes ? c->ev_fetched : c->ev_miss;
     // (see launch_marked)
@@ -1547,7 +1711,15 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
             const int par = (int)(c->insert_calls & 1);
             const uint4 *features = reinterpret_cast<const uint4 *>(c->features);
             uint4 *out = reinterpret_cast<uint4 *>(out_rows), *buffer = reinterpret_cast<uint4 *>(c->buffer);
-            if (!c->features_in_hbm && q <= kWave) {
+            if (from_slots) {
+                // as many positions for every wavefront, and for each of its turns
+                const int64_t waves = (int64_t)FETCH_BLOCKS * (COPY_THREADS / kWave), turns = bgl::ceil_div(n, waves * kWave);
+                const int per = (int)bgl::ceil_div(n, waves * turns);
+                const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, (int64_t)per * (COPY_THREADS / kWave)), FETCH_BLOCKS);
+                const size_t lds = sizeof(int2) * (size_t)slots_queue(q) * (COPY_THREADS / kWave);
+                rc = launch_marked(c, ss, fetched, own, k_fetch_slots, Grid(dim3(blocks), lds), dim3(COPY_THREADS), hits.pos, ids, n, per, q,
+                                   c->num_nodes, features, out);
+            } else if (!c->features_in_hbm && q <= kWave) {
                 const bool few = c->write_through && update_beside && n * c->row_bytes <= SMALL_LOOKUP_BYTES;
                 const int64_t rows_per_block = (int64_t)(COPY_THREADS / kWave) * COPY_UNROLL * (kWave / q);
                 const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, rows_per_block), few ? SMALL_FETCH_BLOCKS : FETCH_BLOCKS);

@@ -1320,3 +1320,76 @@ def test_stage_timers_count_their_launches_and_leave_results_alone(B, torch_mod)
         cache.set_profiling_every("gather_hit", 0)
     rc = B.lib().bgl_cache_set_profiling_every(cache._h, 99, 1)
     assert rc == B.BGL_EINVAL
+
+
+@pytest.mark.parametrize("n,row_bytes,spare,write_through,whole", [
+    (1, 400, 0, False, False), (63, 16, 0, False, True), (65, 64, 0, False, False), (255, 272, 7, False, False),
+    (257, 1024, 0, False, True), (300, 1040, 0, False, False), (4_100, 528, 0, True, False), (4_100, 400, 5_000, True, False),
+    (16_385, 16, 0, False, False), (16_385, 400, 100, False, False), (33_000, 272, 0, False, True), (33_000, 1024, 0, False, True),
+    (33_100, 1024, 0, False, False)])
+def test_lists_beside_the_rows_against_the_oracle(B, torch_mod, n, row_bytes, spare, write_through, whole):
+    """Lookups whose lists are made in the hit gather's launch, and whose fetch reads the probe's slots: one position, edges of a
+    wavefront's and a workgroup's share, several turns per wavefront, rows of 1 to 64 and of 65 chunks, spare positions in the
+    buffer, write-through, a cache that holds every node (`whole`), and a size beyond which the fetch goes back to the lists.
+    Cold, mixed and all-hit batches against the oracle; timed stages (separate launches) once."""
+    import oracle
+    torch = torch_mod
+    rng = np.random.default_rng(n + row_bytes)
+    N = 2 * n + 5
+    feats = torch.from_numpy(rng.integers(0, 256, (N, row_bytes), dtype=np.uint8)).pin_memory()
+    cap = N if whole else n + n // 3 + 1
+    cache = B.Cache(cap, feats)
+    if spare:
+        cache.set_spare_rows(spare)
+    if write_through:
+        cache.set_write_through(True)
+    ref = oracle.Cache(cap, feats.numpy().view(np.float32))
+    out = torch.empty((n, row_bytes), dtype=torch.uint8, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    miss = torch.empty(n, dtype=torch.int32, device="cuda")
+    kept = rng.permutation(N)[:n]
+    batches = [kept, rng.permutation(kept)] + [rng.permutation(N)[:n] for _ in range(2)] + [kept]
+    for k, ids_np in enumerate(batches):
+        if k == 3:
+            cache.set_profiling(True)
+        ids = torch.from_numpy(ids_np.astype(np.int32)).cuda()
+        out.fill_(0xAB)
+        cache.lookup_gather(ids, n, out, slot, miss)
+        cache.insert_fifo(ids, miss, -1, out)
+        cache.wait_rows()
+        torch.cuda.synchronize()
+        want, want_slot, want_miss, want_hits = ref.lookup_gather(ids_np.astype(np.int32))
+        ref.insert_fifo(ids_np.astype(np.int32), want_miss, want)
+        assert int(cache.n_hit_host[0]) == want_hits, k
+        assert np.array_equal(slot.cpu().numpy(), want_slot), k
+        assert np.array_equal(miss[: n - want_hits].cpu().numpy(), want_miss), k
+        assert np.array_equal(out.cpu().numpy(), feats.numpy()[ids_np]), k
+        if k == 3:
+            cache.set_profiling(False)
+    s2n, tail, buf = cache.export_state(True)
+    assert tail == ref.tail and np.array_equal(s2n, ref.slot_to_node)
+    assert np.array_equal(buf[s2n >= 0], feats.numpy()[s2n[s2n >= 0]])
+
+
+def test_foreign_ids_are_left_untouched_where_the_fetch_reads_the_slots(B, torch_mod):
+    """Ids outside the table among misses and hits: reported, listed as misses, their rows not written."""
+    torch = torch_mod
+    N, n, rb = 3_000, 1_000, 400
+    feats = torch.randint(0, 256, (N, rb), dtype=torch.uint8).pin_memory()
+    cache = B.Cache(2_000, feats)
+    ids_np = np.random.default_rng(0).permutation(N)[:n].astype(np.int32)
+    bad = np.array([0, 63, 64, 500, 999])
+    ids_np[bad] = [-1, N, 2**31 - 1, -2**31, N + 1]
+    ids = torch.from_numpy(ids_np).cuda()
+    out = torch.full((n, rb), 0xAB, dtype=torch.uint8, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    miss = torch.empty(n, dtype=torch.int32, device="cuda")
+    cache.lookup_gather(ids, n, out, slot, miss)
+    cache.wait_rows()
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    good = np.setdiff1d(np.arange(n), bad)
+    assert np.array_equal(got[good], feats.numpy()[ids_np[good]])
+    assert (got[bad] == 0xAB).all() and (slot.cpu().numpy()[bad] == -1).all()
+    assert int(cache.n_hit_host[0]) == 0 and np.array_equal(miss.cpu().numpy(), np.arange(n))
+    assert cache.stats()["status"] != 0
