@@ -418,8 +418,12 @@ constexpr int RING_FETCH_BLOCKS = 32;
 // it (16 MB asked, fetch with 16 / 64 workgroups: 400-byte rows 427 / 391 us, 528 bytes 433 / 369, 1,024
 // bytes 317 / 301).  (More workgroups where lanes stay idle, so that as many bytes are in flight: 528-byte
 // rows 16 MB 374 -> 369 us, but 64 MB 1,448 -> 1,483.)
+// Below 3 MiB fewer still, one for every 192 KiB: us a batch with 8 / 10 / 12 / 16 workgroups, 0.4 MB asked for 59.4 / 59.7 / 59.3 / 60.8, 0.7 MB
+// 48.2 / 48.7 / 49.1 / 48.8, 1.6 MB 67.9 / 67.9 / 66.9 / 67.2, 2.3 MB 68.3 / 67.5 / 70.5 / 74.6, 2.4 MB 84.1 / 77.4 / 77.1 / 79.2, 3.3 MB
+// 109.9 / 98.3 / 95.5 / 92.3, 6.1 MB 143 / 130 / 124 / 122.
 constexpr int64_t SMALL_LOOKUP_BYTES = 16 << 20;
-constexpr int SMALL_FETCH_BLOCKS = 16;
+constexpr int SMALL_FETCH_BLOCKS = 16, LEAST_FETCH_BLOCKS = 8;
+constexpr int64_t SMALL_FETCH_BYTES_PER_BLOCK = 192 << 10;
 // Tiered lookup: rows the host threads copy per chunk before that chunk's fetch is launched.
 constexpr int64_t TIER_CHUNK_ROWS = 49152;
 constexpr int64_t TIER_FIRST_CHUNK_ROWS = 3072;
@@ -1722,7 +1726,10 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
             } else if (!c->features_in_hbm && q <= kWave) {
                 const bool few = c->write_through && update_beside && n * c->row_bytes <= SMALL_LOOKUP_BYTES;
                 const int64_t rows_per_block = (int64_t)(COPY_THREADS / kWave) * COPY_UNROLL * (kWave / q);
-                const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, rows_per_block), few ? SMALL_FETCH_BLOCKS : FETCH_BLOCKS);
+                const int64_t most = !few ? FETCH_BLOCKS
+                                          : std::clamp<int64_t>(bgl::ceil_div(n * c->row_bytes, SMALL_FETCH_BYTES_PER_BLOCK), LEAST_FETCH_BLOCKS,
+                                                                SMALL_FETCH_BLOCKS);
+                const int blocks = (int)std::min<int64_t>(bgl::ceil_div(n, rows_per_block), most);
                 rc = launch_marked(c, ss, fetched, own, c->write_through ? k_fetch_link<true> : k_fetch_link<false>, dim3(blocks),
                                    dim3(COPY_THREADS), mpos, ids, q, c->num_nodes, features, out, c->dev, buffer, c->capacity,
                                    c->rows, par, gen);
