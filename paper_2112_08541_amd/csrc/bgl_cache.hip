@@ -1160,6 +1160,28 @@ __global__ __launch_bounds__(COPY_THREADS) void k_insert_rows(
     insert_rows_part<Q>(blockIdx.x, miss_pos, n_miss, start, tail, capacity, rows, q, out, buffer);
 }
 
+// Both in one launch, for caches that can hold every node: once such a cache is warm its updates find little or nothing to
+// do, and a map update ahead of the wait for the fetch hides nothing.  Lookup + update of 302,709 hits of 1,024 bytes 138.2 -> 136.5 us,
+// each waited for 168 -> 166; a first lookup, all missed, 5,000 x 400 B 109 -> 107, 300,000 the same.
+template <int Q>
+__global__ __launch_bounds__(COPY_THREADS) void k_insert_both(
+    const int32_t *__restrict__ ids, const int32_t *__restrict__ miss_pos, int64_t n_miss_arg, int map_blocks, int64_t capacity,
+    int64_t rows, int64_t num_nodes, uint64_t *table, uint32_t bucket_mask, int32_t *slot_to_node, uint32_t *slot_to_entry, int q,
+    const uint4 *__restrict__ out, uint4 *__restrict__ buffer, CacheDev *dev, int par)
+{
+    const int64_t n_miss = n_miss_arg >= 0 ? n_miss_arg : dev->n_miss_last;
+    const int64_t start = n_miss > capacity ? n_miss - capacity : 0;
+    const unsigned long long tail = dev->tail[par];
+    if (blockIdx.x == 0 && threadIdx.x == 0) dev->tail[par ^ 1] = tail + (unsigned long long)n_miss;
+    if ((int)blockIdx.x >= map_blocks) {
+        insert_rows_part<Q>(blockIdx.x - map_blocks, miss_pos, n_miss, start, tail, capacity, rows, q, out, buffer);
+        return;
+    }
+    const int64_t r = start + (int64_t)blockIdx.x * MAP_THREADS + threadIdx.x;  // (as many rows a workgroup as k_insert_map)
+    if (threadIdx.x < MAP_THREADS && r < n_miss)
+        insert_map_part(r, ids, miss_pos, start, uniform(tail), capacity, num_nodes, table, bucket_mask, slot_to_node, slot_to_entry, dev);
+}
+
 // FIFO update when the launches above are skipped (nothing can be inserted).
 __global__ void k_advance_tail(CacheDev *dev, int64_t n_miss_arg, int par)
 {
@@ -2301,7 +2323,17 @@ try {
         }
         return enqueued();
     }
-    if (eff > 0) {
+    const bool timed = c->profiling & (1u << BGL_STAGE_INSERT_MAP | 1u << BGL_STAGE_INSERT_ROWS);
+    if (eff > 0 && c->capacity >= c->num_nodes && !other_stream && !timed) {
+        if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, misses_event(c), 0));
+        const int map_blocks = (int)bgl::ceil_div(eff, MAP_THREADS);
+        dispatch_q(q, [&](auto Q) {
+            rc = launch_marked(c, st, done, own, k_insert_both<decltype(Q)::value>, dim3(map_blocks + copy_blocks(eff, q)), dim3(COPY_THREADS),
+                               ids, miss_pos, n_miss, map_blocks, c->capacity, c->rows, c->num_nodes, c->table, c->num_buckets - 1,
+                               c->slot_to_node, c->slot_to_entry, q, reinterpret_cast<const uint4 *>(out_rows),
+                               reinterpret_cast<uint4 *>(c->buffer), c->dev, par);
+        });
+    } else if (eff > 0) {
         {
             Prof p(c, BGL_STAGE_INSERT_MAP, st);
             launch(c, st, k_insert_map, dim3((unsigned)bgl::ceil_div(eff, MAP_THREADS)),
