@@ -464,15 +464,14 @@ constexpr int64_t LONG_LOOKUP_BYTES = 100ll << 20;
 // and the whole gains nothing.
 constexpr int64_t BESIDE_BYTES = 64 << 20;
 constexpr int64_t FROM_SLOTS_BYTES = 32 << 20;  // of those, the ones whose fetch reads the probe's slots (lookup_gather_impl)
-// Hit gather: largest output (of the hits) whose rows are read with ordinary loads, and largest one that is
-// written with ordinary stores (the size of the last-level cache).
-constexpr int64_t GATHER_CACHED_ROWS_BYTES = 96ll << 20;
+// Hit gather: largest output (of the hits) whose rows are read and written with ordinary accesses, and largest one that is not
+// written non-temporally (the size of the last-level cache).
+constexpr int64_t GATHER_CACHED_ROWS_BYTES = 64ll << 20;
 constexpr int64_t GATHER_CACHED_OUTPUT_BYTES = 256ll << 20;
 // Assembled output: largest out_rows of a call that is still written with ordinary stores.
 constexpr int64_t ASSEMBLE_CACHED_OUTPUT_BYTES = 128ll << 20;
 
 // 16-byte accesses that say "not needed again soon" (NT) or nothing.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 template <bool NT>
 __device__ __forceinline__ void st16(uint4 *p, const uint4 &v)
 {
@@ -487,6 +486,25 @@ __device__ __forceinline__ uint4 ld16(const uint4 *p)
         return uint4{t.x, t.y, t.z, t.w};
     }
     return *p;
+}
+
+// How the gathered rows are stored.
+enum Stores { ORDINARY, THROUGH, NON_TEMPORAL };
+template <int S>
+__device__ __forceinline__ void st_gathered(uint4 *out, int64_t at, const uint4 &v)
+{
+    if constexpr (S == THROUGH) store16_through(out, (uint32_t)at * 16u, v);
+    else st16<S == NON_TEMPORAL>(out + at, v);
+}
+// The accesses for `bytes` of gathered rows in an output of out_bytes (both the same for all lanes; a buffer store's offset has 32 bits).
+template <typename F>
+__device__ __forceinline__ void by_gather_size(int64_t bytes, int64_t out_bytes, F &&copy)
+{
+    using std::integral_constant;
+    if (bytes <= GATHER_CACHED_ROWS_BYTES) copy(std::false_type{}, integral_constant<int, ORDINARY>{});
+    else if (bytes > GATHER_CACHED_OUTPUT_BYTES) copy(std::true_type{}, integral_constant<int, NON_TEMPORAL>{});
+    else if (out_bytes > (int64_t)UINT32_MAX) copy(std::true_type{}, integral_constant<int, ORDINARY>{});
+    else copy(std::true_type{}, integral_constant<int, THROUGH>{});
 }
 
 // out[i] = the cached row of ids[i] for every hit i (taken from the hit list, which holds the
@@ -507,10 +525,17 @@ __device__ __forceinline__ uint4 ld16(const uint4 *p)
 //   1.6 GB (400 bytes), 4.1 GB      after a copy: 688 / 649 / 661 / 626, 1,584 / 1,522 / 1,556 / 1,484
 // (Non-temporal stores alone are the fastest where nothing else has used the caches since the last launch,
 // and the slowest where something has.)
+//   Between the two bounds the rows are written through the L2s (store16_through): launches in a row | behind a copy | launch and
+// a reader of its output, loads non-temporal, stores ordinary / through:
+//   72 MB from 614 MB               25.1 / 22.9 | 28.4 / 25.6 | 36.8 / 34.3
+//   160 MB (400 bytes) from 800     58.0 / 54.3 | 64.1 / 58.9 | 81.4 / 77.7
+//   256 MB from 614 MB              76.6 / 73.5 | 81.0 / 77.5 | 113 / 110
+// Below 64 MB ordinary accesses are as fast (44 MB 16.4 / 17.2 | 24.5 / 19.8 | 24.4 / 25.3); beyond 256 MB non-temporal stores written
+// through or not differ by 1 %.
 template <int Q>
 __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
     const int32_t *__restrict__ hit_pos, const int32_t *__restrict__ hit_slot, int q,
-    const uint4 *__restrict__ buffer, uint4 *__restrict__ out, const CacheDev *dev)
+    const uint4 *__restrict__ buffer, uint4 *__restrict__ out, int64_t out_bytes, const CacheDev *dev)
 {
     static_assert(COPY_UNROLL == 4, "the four chunks of a lane are written out by hand");
     const int qq = Q > 0 ? Q : q;
@@ -532,23 +557,19 @@ __global__ __launch_bounds__(COPY_THREADS) void k_gather_hits(
     RowSplit<Q>::split(min(base + 3 * COPY_THREADS, last), q, r3, c3);
     const int32_t s0 = hit_slot[r0], s1 = hit_slot[r1], s2 = hit_slot[r2], s3 = hit_slot[r3];
     const int32_t p0 = hit_pos[r0], p1 = hit_pos[r1], p2 = hit_pos[r2], p3 = hit_pos[r3];
-    auto copy = [&](auto nt_loads, auto nt_stores) {
+    by_gather_size(total * 16, out_bytes, [&](auto nt_loads, auto stores) {
         // (the markers keep the compiler from merging the branches' accesses into ordinary ones)
         asm volatile("; rows");
         const uint4 v0 = ld16<nt_loads.value>(&buffer[(int64_t)s0 * qq + c0]);
         const uint4 v1 = ld16<nt_loads.value>(&buffer[(int64_t)s1 * qq + c1]);
         const uint4 v2 = ld16<nt_loads.value>(&buffer[(int64_t)s2 * qq + c2]);
         const uint4 v3 = ld16<nt_loads.value>(&buffer[(int64_t)s3 * qq + c3]);
-        st16<nt_stores.value>(&out[(int64_t)p0 * qq + c0], v0);
-        st16<nt_stores.value>(&out[(int64_t)p1 * qq + c1], v1);
-        st16<nt_stores.value>(&out[(int64_t)p2 * qq + c2], v2);
-        st16<nt_stores.value>(&out[(int64_t)p3 * qq + c3], v3);
+        st_gathered<stores.value>(out, (int64_t)p0 * qq + c0, v0);
+        st_gathered<stores.value>(out, (int64_t)p1 * qq + c1, v1);
+        st_gathered<stores.value>(out, (int64_t)p2 * qq + c2, v2);
+        st_gathered<stores.value>(out, (int64_t)p3 * qq + c3, v3);
         asm volatile("; end of rows");
-    };
-    const int64_t bytes = total * 16;  // uniform
-    if (bytes > GATHER_CACHED_OUTPUT_BYTES) copy(std::true_type{}, std::true_type{});
-    else if (bytes > GATHER_CACHED_ROWS_BYTES) copy(std::true_type{}, std::false_type{});
-    else copy(std::false_type{}, std::false_type{});
+    });
 }
 
 // The miss list and the hit gather in one launch: the first workgroups are k_split_list's without the list of the hits, the
@@ -586,23 +607,19 @@ __global__ __launch_bounds__(COPY_THREADS) void k_list_and_hits(Lists l, int til
         p2 = s2 < 0 ? 0 : ring.pos_of_slot(s2);
         p3 = s3 < 0 ? 0 : ring.pos_of_slot(s3);
     }
-    auto copy = [&](auto nt_loads, auto nt_stores) {
+    by_gather_size((last + 1) * 16, l.n * qq * 16, [&](auto nt_loads, auto stores) {
         // (the markers keep the compiler from merging the branches' accesses into ordinary ones)
         asm volatile("; rows");
         const uint4 v0 = ld16<nt_loads.value>(&buffer[p0 * qq + c0]);
         const uint4 v1 = ld16<nt_loads.value>(&buffer[p1 * qq + c1]);
         const uint4 v2 = ld16<nt_loads.value>(&buffer[p2 * qq + c2]);
         const uint4 v3 = ld16<nt_loads.value>(&buffer[p3 * qq + c3]);
-        if (s0 >= 0) st16<nt_stores.value>(&out[x0], v0);
-        if (s1 >= 0) st16<nt_stores.value>(&out[x1], v1);
-        if (s2 >= 0) st16<nt_stores.value>(&out[x2], v2);
-        if (s3 >= 0) st16<nt_stores.value>(&out[x3], v3);
+        if (s0 >= 0) st_gathered<stores.value>(out, x0, v0);
+        if (s1 >= 0) st_gathered<stores.value>(out, x1, v1);
+        if (s2 >= 0) st_gathered<stores.value>(out, x2, v2);
+        if (s3 >= 0) st_gathered<stores.value>(out, x3, v3);
         asm volatile("; end of rows");
-    };
-    const int64_t bytes = (last + 1) * 16;  // uniform
-    if (bytes > GATHER_CACHED_OUTPUT_BYTES) copy(std::true_type{}, std::true_type{});
-    else if (bytes > GATHER_CACHED_ROWS_BYTES) copy(std::true_type{}, std::false_type{});
-    else copy(std::false_type{}, std::false_type{});
+    });
 }
 
 // out[miss_pos[r]] = features[ids[miss_pos[r]]] for every miss r; the loads cross
@@ -1622,7 +1639,7 @@ int gather_phase(bgl_cache *c, int64_t n, void *out_rows, hipStream_t ms, const 
             }
             rc = launch_marked(c, ms, c->ev_listed, own, k_gather_hits<decltype(Q)::value>, dim3(copy_blocks(n, q)), dim3(COPY_THREADS),
                                hits.pos, hits.slot, q, reinterpret_cast<const uint4 *>(c->buffer),
-                               reinterpret_cast<uint4 *>(out_rows), c->dev);
+                               reinterpret_cast<uint4 *>(out_rows), n * c->row_bytes, c->dev);
         });
         return rc;
     }

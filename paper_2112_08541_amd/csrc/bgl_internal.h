@@ -173,6 +173,18 @@ __device__ __forceinline__ void scan_tile_counts(const int32_t *counts, int64_t 
     }
 }
 
+// 16-byte store that is written through the XCD's L2 (agent scope) instead of staying there dirty: a kernel is not over
+// before the L2s have written back what is dirty in them, and with ordinary stores that comes behind its last wavefront.
+// `base` is the same for all lanes, `offset` in bytes.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store16_through(void *base, uint32_t offset, const uint4 &v)
+{
+    constexpr int SC1 = 16;                 // cache policy bit of a buffer store
+    constexpr int RAW_DWORDS = 0x00020000;  // untyped, no swizzle
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{v.x, v.y, v.z, v.w}, __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, RAW_DWORDS),
+                                           (int)offset, 0, SC1);
+}
+
 constexpr int kScanThreads = 1024;
 // From this many tiles on the list kernels read prefixes made by scan_tile_counts.
 constexpr int64_t kSelfSumTiles = 4096;

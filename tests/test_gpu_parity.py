@@ -1393,3 +1393,34 @@ def test_foreign_ids_are_left_untouched_where_the_fetch_reads_the_slots(B, torch
     assert (got[bad] == 0xAB).all() and (slot.cpu().numpy()[bad] == -1).all()
     assert int(cache.n_hit_host[0]) == 0 and np.array_equal(miss.cpu().numpy(), np.arange(n))
     assert cache.stats()["status"] != 0
+
+
+@pytest.mark.parametrize("hits,others", [(65_536, 0), (65_537, 0), (262_144, 0), (262_145, 0), (70_000, 4_130_000)])
+def test_gathered_rows_around_the_bounds_of_their_accesses(B, torch_mod, hits, others):
+    """Rows of 1,024 bytes: 64 and 256 MiB of hits, where the gather's loads and stores change, one row more of each, and hits
+    in between in an output of more than 4 GiB, which buffer stores do not reach."""
+    torch = torch_mod
+    rb, n = 1024, hits + others
+    N = n + 10
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(hits)
+    table = torch.randint(-2**31, 2**31 - 1, (N, rb // 4), generator=gen, device="cuda", dtype=torch.int32)
+    cache = B.Cache(hits, table.data_ptr(), num_nodes=N, row_bytes=rb)
+    out = torch.empty((n, rb), dtype=torch.uint8, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    miss = torch.empty(n, dtype=torch.int32, device="cuda")
+    first = torch.randperm(N, generator=gen, device="cuda")[:hits].to(torch.int32)
+    cache.lookup_gather(first, hits, out, slot, miss)
+    cache.insert_fifo(first, miss, -1, out)
+    cache.wait_rows()
+    rest = torch.ones(N, dtype=torch.bool, device="cuda")
+    rest[first.long()] = False
+    ids = torch.cat([first, torch.nonzero(rest).squeeze(1)[:others].to(torch.int32)])
+    ids = ids[torch.randperm(n, generator=gen, device="cuda")].contiguous()
+    out.fill_(0xAB)
+    cache.lookup_gather(ids, n, out, slot, miss)
+    cache.wait_rows()
+    torch.cuda.synchronize()
+    assert int(cache.n_hit_host[0]) == hits
+    for at in range(0, n, 500_000):
+        assert torch.equal(out[at:at + 500_000].view(torch.int32), table[ids[at:at + 500_000].long()]), at
