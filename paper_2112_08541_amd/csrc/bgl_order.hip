@@ -51,6 +51,13 @@ constexpr int BW = BT / kWave;               // wavefronts per workgroup
 // Workgroups of a step's kernels for one or two traversals, half as many each where there are more (those without a share leave
 // at once, but 40,000 of them cost a launch 10 us).  k_expand, two on 2.45 M nodes, with 1,024 / 2,048 / 4,096: 2,533 / 2,400 / 2,355 us.
 constexpr int BLOCKS = 4096;
+// Of all traversals of a launch together on a graph of few edges, whose steps are launches and latency: as many as run at a time.
+// Before / with these, us a call: five on 100,000 nodes / 1 M edges 523 / 473, 3 M edges 612 / 497, 300,000 nodes / 6 M 1,153 / 1,016;
+// ten 765 / 635, 906 / 700, 1,807 / 1,642; two on 6 M edges 710 / 668, 12 M 843 / 792.  Elsewhere the larger steps lose as much as the small
+// ones gain (five on 24 M edges 3,001 / 3,120, two on 3 M 390 / 402, on 24 M 1,589 / 1,595), and one traversal is level throughout.
+// (No multiple of 8 each, or the first workgroups of all traversals, in small steps the only ones with work, share an XCD: ten on
+// 30,000 nodes / 0.3 M edges with 256 each 466 instead of 360.)
+constexpr int RESIDENT_BLOCKS = 2048;
 constexpr int WAVES = BLOCKS * BW;
 constexpr int GROUPS = BLOCKS / kWave;       // groups of 64 workgroups whose totals are added up
 static_assert(GROUPS <= kWave && BW >= 2, "a wavefront sums the groups, another one a group's workgroups");
@@ -64,6 +71,7 @@ constexpr int SHORT_ROW = 32;                // edges of a row that one lane wal
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
 constexpr int64_t MERGE_TURNS = 2048;        // turns of the merge (some 3 us) between two looks at how far the device is
 constexpr int SIDE_BY_SIDE = 16;             // traversals that share their launches at most
+static_assert((1 << 23) / ((RESIDENT_BLOCKS / SIDE_BY_SIDE / 8 * 8 - 3) * BW) + WTILE <= 1 << 16, "a share's edges have 16 bits");
 constexpr int64_t SIDE_BY_SIDE_BYTES = 1ll << 30;  // and the memory they may take together (one alone: whatever it needs)
 constexpr size_t PAGE_LOCKED_SEQ_BYTES = 32 << 20;  // sequences of a call that still go to page-locked memory
 // A node's key: below WINDOW the smallest edge of the current window that reaches it (it is visited by the
@@ -886,7 +894,8 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
     // As many workgroups as the largest step of this graph has shares for.
     const int64_t shares = std::max({ceil_div(std::min(g->num_edges, w.t.window), WTILE * BW), ceil_div(words, BT),
                                      std::min<int64_t>(ceil_div(N, 64 * BW), SEARCH_BLOCKS), (int64_t)1});
-    t.blocks = count <= 2 ? BLOCKS : BLOCKS / 2;
+    const bool small = count > 2 ? g->num_edges <= 1 << 23 : count == 2 && g->num_edges > 1 << 22 && g->num_edges <= 1 << 24;
+    t.blocks = small ? RESIDENT_BLOCKS / count / 8 * 8 - 3 : count <= 2 ? BLOCKS : BLOCKS / 2;
     const dim3 grid((unsigned)std::min<int64_t>(shares, t.blocks), (unsigned)count);
     // The device says in page-locked words which step each traversal has come to and when it has ended; the
     // host stays STEPS_AHEAD steps ahead of the foremost, so the queue never runs empty and at most that many steps,

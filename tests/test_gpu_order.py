@@ -211,6 +211,26 @@ def test_traversals_side_by_side_are_independent(B, sequences):
     assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, len(train)))
 
 
+@pytest.mark.parametrize("sequences,edges", [(2, 1 << 22), (2, (1 << 22) + 1), (2, 1 << 24), (2, (1 << 24) + 1),
+                                             (3, 1 << 23), (3, (1 << 23) + 1), (16, 40_000), (16, 1 << 23)])
+def test_shares_of_small_and_large_graphs(B, sequences, edges):
+    """Numbers of edges at the bounds where the steps are dealt to fewer workgroups, on few nodes with rows of hundreds of
+    edges and of none; 16 traversals with the fewest workgroups each."""
+    import oracle
+    rng = np.random.default_rng(edges + sequences)
+    N = 30_000
+    rp = np.zeros(N + 1, dtype=np.int64)
+    rp[1:-1] = np.sort(rng.integers(0, edges + 1, N - 1))
+    rp[1:-1:5] = rp[0:-2:5]
+    rp[-1] = edges
+    col = rng.integers(0, N, edges, dtype=np.int32)
+    g = B.Graph(rp, col)
+    train = rng.choice(N, 4_000, replace=False)
+    roots, shifts = rng.integers(0, N, sequences), rng.integers(0, len(train), sequences)
+    got = B.order_proximity(g, train, roots, shifts, len(train))
+    assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, len(train)))
+
+
 @pytest.mark.parametrize("sequences,num_out", [(1, 20_000), (2, 20_000), (2, 1), (3, 9_999), (3, 0), (18, 20_000)])
 def test_merge_beside_the_traversals(B, sequences, num_out):
     """The merge follows the traversals as they record: sequences that grow slowly (a path, one node a step) beside ones that
