@@ -41,6 +41,7 @@
 #include <vector>
 
 #include "bgl_internal.h"
+#include "bgl_order_plan.h"
 
 namespace {
 
@@ -62,17 +63,13 @@ constexpr int WAVES = BLOCKS * BW;
 constexpr int GROUPS = BLOCKS / kWave;       // groups of 64 workgroups whose totals are added up
 static_assert(GROUPS <= kWave && BW >= 2, "a wavefront sums the groups, another one a group's workgroups");
 constexpr int WTILE = 4 * kWave;             // edges a wavefront handles at a time, four per lane
-// Edges per step at most: the larger window where the scratch of all traversals of a call fits then (fewer steps: two
-// sequences on 2.45 M nodes 3.8 -> 3.6 ms, k_expand 2,390 -> 2,300 us, k_count 545 -> 460, k_append 480 -> 410; twice as
-// large again 2,280 / 434 / 355), else the smaller one (ten on 1 M nodes, seven of them side by side: 6.1 -> 7.3).
-constexpr int64_t WINDOW = 1 << 24, SMALL_WINDOW = 1 << 23;
+constexpr int64_t WINDOW = ORDER_WINDOW;       // edges per step at most (bgl_order_plan.h)
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
 constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
 constexpr int64_t MERGE_TURNS = 2048;        // turns of the merge (some 3 us) between two looks at how far the device is
-constexpr int SIDE_BY_SIDE = 16;             // traversals that share their launches at most
+constexpr int SIDE_BY_SIDE = ORDER_SIDE_BY_SIDE;
 static_assert((1 << 23) / ((RESIDENT_BLOCKS / SIDE_BY_SIDE / 8 * 8 - 3) * BW) + WTILE <= 1 << 16, "a share's edges have 16 bits");
-constexpr int64_t SIDE_BY_SIDE_BYTES = 1ll << 30;  // and the memory they may take together (one alone: whatever it needs)
 constexpr size_t PAGE_LOCKED_SEQ_BYTES = 32 << 20;  // sequences of a call that still go to page-locked memory
 // A node's key: below WINDOW the smallest edge of the current window that reaches it (it is visited by the
 // end of the step), else none, and the excess says how many leading edges of its own row are known to end
@@ -833,23 +830,20 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
         w.t.stride = (int64_t)(total - shared);
         total = shared + (total - shared) * (size_t)side;
     };
-    const int wanted = std::min(num_sequences, SIDE_BY_SIDE);
-    w.t.window = WINDOW;
-    carve(1);
-    if (w.t.stride * wanted > SIDE_BY_SIDE_BYTES) {
-        w.t.window = SMALL_WINDOW;
+    const auto plans = order_plans(num_sequences, g->num_edges, [&](int64_t window) {
+        w.t.window = window;
         carve(1);
-    }
-    // Side by side a traversal's small steps, which are launches and latency, cost next to nothing beside
-    // the others'.  Where the memory for that is not there, fewer at a time.
-    w.side = (int)std::max<int64_t>(1, std::min<int64_t>(wanted, SIDE_BY_SIDE_BYTES / w.t.stride));
+        return w.t.stride;
+    });
     const size_t host_bytes = sizeof(Progress) * SIDE_BY_SIDE + (seq_bytes <= PAGE_LOCKED_SEQ_BYTES ? seq_bytes : 0);
-    for (;; w.side = (w.side + 1) / 2) {
+    int rc = BGL_ENOMEM;
+    for (size_t k = 0; k < plans.size() && rc == BGL_ENOMEM; ++k) {
+        w.t.window = plans[k].window;
+        w.side = plans[k].side;
         carve(w.side);
-        const int rc = bgl::order_scratch_take(g, total, host_bytes, w.scratch);
-        if (rc == BGL_OK) break;
-        if (rc != BGL_ENOMEM || w.side == 1) return rc;
+        rc = bgl::order_scratch_take(g, total, host_bytes, w.scratch);
     }
+    if (rc != BGL_OK) return rc;
     at = static_cast<char *>(w.scratch.device);
     carve(w.side);
     w.t.num_train = num_train;
