@@ -13,6 +13,7 @@
 #include <new>
 
 #include "bgl.h"
+#include "bgl_order_plan.h"
 
 namespace bgl {
 
@@ -75,7 +76,7 @@ struct OrderScratch {
     size_t device_bytes = 0, host_bytes = 0;
     int ordinal = -1;  // the device's
 };
-constexpr size_t ORDER_KEEP_DEVICE_BYTES = (size_t)512 << 20;
+constexpr size_t ORDER_KEEP_DEVICE_BYTES = (size_t)ORDER_KEEP_BYTES;
 constexpr size_t ORDER_KEEP_ALWAYS_BYTES = (size_t)64 << 20;  // a larger block is kept while ORDER_KEEP_SHARE times as much is free
 constexpr size_t ORDER_KEEP_SHARE = 64;
 int order_scratch_take(const bgl_graph *g, size_t device_bytes, size_t host_bytes, OrderScratch &s);

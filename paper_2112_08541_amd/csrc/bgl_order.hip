@@ -41,7 +41,6 @@
 #include <vector>
 
 #include "bgl_internal.h"
-#include "bgl_order_plan.h"
 
 namespace {
 
@@ -830,7 +829,8 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
         w.t.stride = (int64_t)(total - shared);
         total = shared + (total - shared) * (size_t)side;
     };
-    const auto plans = order_plans(num_sequences, g->num_edges, [&](int64_t window) {
+    carve(1);  // (what is shared)
+    const auto plans = order_plans(num_sequences, g->num_edges, (int64_t)shared, [&](int64_t window) {
         w.t.window = window;
         carve(1);
         return w.t.stride;

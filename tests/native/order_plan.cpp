@@ -20,10 +20,11 @@ int main()
             bad = 1;
         }
     };
-    for (int64_t nodes : {1ll, 100'000ll, 1'000'000ll, 2'450'000ll, 5'000'000ll, 30'000'000ll, 111'000'000ll})
+    for (int64_t nodes : {1ll, 100'000ll, 1'000'000ll, 2'000'000ll, 2'450'000ll, 5'000'000ll, 30'000'000ll, 111'000'000ll})
         for (int64_t edges : {0ll, 1ll << 20, 1ll << 23, (1ll << 23) + 1, 1ll << 24, 1ll << 27})
             for (int sequences : {1, 2, 3, 5, 10, 16, 17, 100}) {
-                const auto plans = order_plans(sequences, edges, [&](int64_t w) { return traversal(nodes, edges, w); });
+                const int64_t shared = nodes / 8 + 4 * (nodes / 10);
+                const auto plans = order_plans(sequences, edges, shared, [&](int64_t w) { return traversal(nodes, edges, w); });
                 const int64_t least = traversal(nodes, edges, ORDER_SMALL_WINDOW);
                 check(!plans.empty(), "no plan", nodes, edges, sequences);
                 int64_t before = INT64_MAX;
@@ -35,6 +36,11 @@ int main()
                     check(all < before, "asked for as much again", nodes, edges, sequences);
                     before = all;
                 }
+                // what the graph can keep with one of the windows is kept
+                const int all_of_them = std::min(sequences, ORDER_SIDE_BY_SIDE);
+                if (shared + all_of_them * least <= ORDER_KEEP_BYTES)
+                    check(plans[0].side == all_of_them && shared + all_of_them * traversal(nodes, edges, plans[0].window) <= ORDER_KEEP_BYTES,
+                          "allocated in each call", nodes, edges, sequences);
                 // nothing smaller would do: a call that fits with one traversal and the smaller window goes through
                 check(before == least, "not the least a call can do with", nodes, edges, sequences);
                 // no traversal is given up where the smaller window makes room

@@ -289,9 +289,9 @@ def test_a_graph_s_scratch_serves_calls_of_all_sizes_and_threads(B):
 
 
 def test_large_scratch_and_many_recorded_ids(B):
-    """3 M nodes take 176 MB a traversal: seven sequences run five and two at a time, and record more ids than go to
-    page-locked memory (36 MB); what they used is given back, what two sequences used is kept (half a GiB at most) and
-    serves the next call, and the graph gives it back."""
+    """3 M nodes and 18 M edges take 159 MB a traversal, or 210 MB where fewer steps are worth it: seven sequences run six
+    and one at a time, and record more ids than go to page-locked memory (36 MB); what they used is given back, what three
+    or two sequences used is kept (half a GiB at most) and serves the next call, and the graph gives it back."""
     import oracle
     import torch
     rng = np.random.default_rng(17)
@@ -314,6 +314,9 @@ def test_large_scratch_and_many_recorded_ids(B):
     got = B.order_proximity(g, train, roots, shifts, len(train))
     assert loaded - free() < slack
     assert np.array_equal(got, oracle.proximity_order(rp, col, train, roots, shifts, len(train)))
+    want = oracle.proximity_order(rp, col, train, roots[:3], shifts[:3], len(train))
+    assert np.array_equal(B.order_proximity(g, train, roots[:3], shifts[:3], len(train)), want)
+    assert 3 * 150e6 < loaded - free() <= (512 << 20) + slack     # three sequences' as well: with steps of fewer edges
     want = oracle.proximity_order(rp, col, train, roots[:2], shifts[:2], len(train))
     for _ in range(2):
         assert np.array_equal(B.order_proximity(g, train, roots[:2], shifts[:2], len(train)), want)
