@@ -360,6 +360,10 @@ int bgl_cache_map_stats(bgl_cache_t *c, uint64_t *ids_looked_up, uint64_t *bucke
  * pair of events: the figure is the kernel's own duration, the one a kernel
  * trace shows.  BGL_STAGE_MISS_LIST (several small kernels) is bracketed by two
  * event records on its stream, which also times the launch gaps around them.
+ * A stage that is timed in a call is a launch of its own there; other calls may run
+ * it together with a neighbour (the lists with the hit gather, the two halves of a
+ * FIFO update) and start the miss fetch before the lists are written.  Results are
+ * the same.
  * bgl_cache_profile synchronises the device and returns the summed milliseconds
  * and the number of launches of one stage since profiling was (re-)enabled.
  */
@@ -385,7 +389,7 @@ int bgl_cache_profile(bgl_cache_t *c, int stage, double *total_ms, int64_t *laun
  * Time `stage` only in every `every`-th call (lookups and FIFO updates are counted
  * separately, from the cache's creation, starting at 1): a timed launch holds its
  * stream up for a few microseconds, which a stage of many launches per call would
- * feel.  Default 1.  Errors: BGL_EINVAL.
+ * feel.  The other calls run as without profiling.  Default 1.  Errors: BGL_EINVAL.
  */
 int bgl_cache_set_profiling_every(bgl_cache_t *c, int stage, int every);
 

@@ -1230,6 +1230,11 @@ __global__ void k_map_census(const uint64_t *__restrict__ table, uint32_t num_bu
 // own begin and end on the device.  A stage of several launches (exact = false)
 // is bracketed by two event records on the stream, which also times the launch
 // gaps around it.
+// Is a stage timed in this lookup or update?  `call` counts the lookups or the updates, from 1.
+bool timed(const bgl_cache *c, int stage, uint64_t call)
+{
+    return (c->profiling & (1u << stage)) && (c->prof_every[stage] <= 1 || call % (uint64_t)c->prof_every[stage] == 0);
+}
 struct Prof {
     bgl_cache *c;
     hipStream_t st;
@@ -1237,10 +1242,8 @@ struct Prof {
     bool exact;
     Prof(bgl_cache *c_, int stage, hipStream_t st_, bool exact_ = true) : c(c_), st(st_), exact(exact_)
     {
-        if (!(c->profiling & (1u << stage))) return;
         const bool of_update = stage == BGL_STAGE_INSERT_MAP || stage == BGL_STAGE_INSERT_ROWS;
-        const uint64_t call = of_update ? c->insert_calls + 1 : c->lookup_calls;
-        if (c->prof_every[stage] > 1 && call % (uint64_t)c->prof_every[stage] != 0) return;
+        if (!timed(c, stage, of_update ? c->insert_calls + 1 : c->lookup_calls)) return;
         if (2 * (c->prof_rec.size() + 1) > c->prof_ev.size()) {  // more timed launches than events: add some
             const size_t old = c->prof_ev.size();
             c->prof_ev.resize(old + 2 * PROF_RING, nullptr);
@@ -1731,8 +1734,10 @@ int lookup_gather_impl(bgl_cache_t *c, const int32_t *ids, int64_t n, void *out_
     // Lookup + update from lists | from slots with k_list_and_hits, each waited for / one after the other, us: 200 x 400 B 57 / 54 |
     // 54 / 49; 5,000 x 400 B, 90 % missed 97 / 83 | 93 / 77, half 83 / 70 | 77 / 64, none 59 / 59 | 56 / 54; 20,000 x 64 B, half 94 / 77 |
     // 89 / 70; 20,000 x 400 B, 90 % missed 220 / 205 | 220 / 204; 302,709 hits of 1,024 B 163 / 144 | 161 / 140.
-    // (Timed stages have launches of their own; the lists that allocate nothing are read until the gather has ended, no longer.)
-    const bool timed_lists = c->profiling & (1u << BGL_STAGE_MISS_LIST | 1u << BGL_STAGE_GATHER_HIT);
+    // (Stages timed in this call have launches of their own; the lists that allocate nothing are read until the gather has ended, no
+    // longer.)
+    const uint64_t call = c->lookup_calls + 1;
+    const bool timed_lists = timed(c, BGL_STAGE_MISS_LIST, call) || timed(c, BGL_STAGE_GATHER_HIT, call);
     const bool from_slots = (beside || few_bytes) && !timed_lists && !fixed && !c->features_in_hbm && q <= kWave && n > 0 &&
                             (mostly_hits || n * c->row_bytes <= FROM_SLOTS_BYTES);
     // The lists in the gather's launch (k_list_and_hits), unless the fetch waits for them beside it.
@@ -2340,8 +2345,9 @@ try {
         }
         return enqueued();
     }
-    const bool timed = c->profiling & (1u << BGL_STAGE_INSERT_MAP | 1u << BGL_STAGE_INSERT_ROWS);
-    if (eff > 0 && c->capacity >= c->num_nodes && !other_stream && !timed) {
+    const uint64_t call = c->insert_calls + 1;
+    const bool timed_parts = timed(c, BGL_STAGE_INSERT_MAP, call) || timed(c, BGL_STAGE_INSERT_ROWS, call);
+    if (eff > 0 && c->capacity >= c->num_nodes && !other_stream && !timed_parts) {
         if (c->fetch_pending && c->fetch_stream != st) BGL_HIP(hipStreamWaitEvent(st, misses_event(c), 0));
         const int map_blocks = (int)bgl::ceil_div(eff, MAP_THREADS);
         dispatch_q(q, [&](auto Q) {

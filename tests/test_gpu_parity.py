@@ -1322,6 +1322,51 @@ def test_stage_timers_count_their_launches_and_leave_results_alone(B, torch_mod)
     assert rc == B.BGL_EINVAL
 
 
+@pytest.mark.parametrize("whole,kernels", [(True, 4), (False, 5)])
+def test_calls_between_the_timed_ones_run_as_without_timers(B, torch_mod, whole, kernels):
+    """Lookup and FIFO update captured as a graph, and its kernels counted: probe, lists with hits, fetch, update (map and
+    rows in one launch for a cache that can hold every node).  A stage that is timed in another call than this one changes
+    nothing, whichever it is."""
+    import ctypes
+    torch = torch_mod
+    hip = B.lib()                       # (finds the HIP functions in the runtime the library is linked to)
+    N, n, rb = 4_000, 1_000, 400
+    feats = torch.randint(0, 256, (N, rb), dtype=torch.uint8).pin_memory()
+    out = torch.empty((n, rb), dtype=torch.uint8, device="cuda")
+    slot, miss = torch.empty(n, dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+    ids = torch.randperm(N, device="cuda")[:n].to(torch.int32)
+    st = torch.cuda.Stream()
+
+    def launched(stage):
+        cache = B.Cache(N if whole else N // 2, feats)
+        cache.lookup_gather(ids, n, out, slot, miss, main_stream=st)
+        cache.insert_fifo(ids, miss, -1, out, stream=st)
+        torch.cuda.synchronize()
+        if stage:
+            cache.set_profiling((stage,))
+            cache.set_profiling_every(stage, 1_000)
+        graph, count, kind, found = ctypes.c_void_p(), ctypes.c_size_t(0), ctypes.c_int(0), 0
+        handle = ctypes.c_void_p(st.cuda_stream)
+        assert hip.hipStreamBeginCapture(handle, 1) == 0
+        try:
+            cache.lookup_gather(ids, n, out, slot, miss, main_stream=st)
+            cache.insert_fifo(ids, miss, -1, out, stream=st)
+        finally:
+            assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) == 0
+        assert hip.hipGraphGetNodes(graph, None, ctypes.byref(count)) == 0
+        nodes = (ctypes.c_void_p * count.value)()
+        assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(count)) == 0
+        for node in nodes:
+            assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+            found += kind.value == 0    # hipGraphNodeTypeKernel
+        assert hip.hipGraphDestroy(graph) == 0
+        return found
+
+    assert launched(None) == kernels
+    for stage in B.STAGE_NAMES[:6]:
+        assert launched(stage) == kernels, stage
+
+
 @pytest.mark.parametrize("n,row_bytes,spare,write_through,whole", [
     (1, 400, 0, False, False), (63, 16, 0, False, True), (65, 64, 0, False, False), (255, 272, 7, False, False),
     (257, 1024, 0, False, True), (300, 1040, 0, False, False), (4_100, 528, 0, True, False), (4_100, 400, 5_000, True, False),
