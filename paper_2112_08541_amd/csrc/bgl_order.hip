@@ -41,6 +41,7 @@
 #include <vector>
 
 #include "bgl_internal.h"
+#include "bgl_order_merge.h"
 
 namespace {
 
@@ -66,7 +67,7 @@ constexpr int64_t WINDOW = ORDER_WINDOW;       // edges per step at most (bgl_or
 constexpr int SEARCH_BLOCKS = 256;           // workgroups that look for the restart node
 constexpr int SHORT_ROW = 32;                // edges of a row that one lane walks by itself
 constexpr int64_t STEPS_AHEAD = 4;           // steps the host enqueues ahead of the device
-constexpr int64_t MERGE_TURNS = 2048;        // turns of the merge (some 3 us) between two looks at how far the device is
+constexpr int64_t MERGE_ENTRIES = 2048;      // entries the merge looks at (1.5 to 4 ns each) between two looks at how far the device is
 constexpr int SIDE_BY_SIDE = ORDER_SIDE_BY_SIDE;
 static_assert((1 << 23) / ((RESIDENT_BLOCKS / SIDE_BY_SIDE / 8 * 8 - 3) * BW) + WTILE <= 1 << 16, "a share's edges have 16 bits");
 constexpr size_t PAGE_LOCKED_SEQ_BYTES = 32 << 20;  // sequences of a call that still go to page-locked memory
@@ -689,88 +690,6 @@ __global__ __launch_bounds__(BT) void k_append(const RP *__restrict__ row_ptr, i
     }
 }
 
-// Merge of the sequences: turn t takes the next node of sequence t mod S that no earlier turn has taken.  One bit per
-// node says which are taken (a byte each is eight times the cache: 2.45 M nodes, two sequences of 204,800: 0.4 ms instead of
-// 0.9).  Many sequences are looked through 64 entries at a time, without a branch for each: all of them are read almost to
-// their end, and most entries are taken (ten of 100,000 on 1 M nodes: a call 6.4 -> 6.1 ms; two of 500,000 3.6 -> 3.75).
-// It goes on as far as the sequences are there, so that most of it is done by the time the traversals end.
-class Merge {
-    static constexpr size_t ONE_BY_ONE = 3;  // sequences that are looked through entry by entry
-    struct Reader {
-        int64_t at;         // next place to look at, cyclically from the shift
-        int64_t first = 0;  // the last 64 looked at begin here
-        uint64_t open = 0;  // those of them that were not taken then and have not been looked at again
-    };
-    const int32_t *seqs;
-    int64_t num_train, num_out;
-    int32_t *order;
-    std::vector<uint64_t> used;
-    std::vector<Reader> readers;
-    int64_t k = 0;             // turns taken
-    size_t j = 0;              // whose turn it is
-
-    bool taken(int32_t v) const { return used[(size_t)v / 64] >> (v % 64) & 1u; }
-    // The next node of a sequence that nobody has taken, or -1 if its entry is not there yet.  (What has been passed over is
-    // taken and stays so.)
-    int32_t next(Reader &r, const int32_t *seq, int64_t limit) const
-    {
-        int64_t c = r.at;
-        int32_t v;
-        do {
-            if (c >= limit) {
-                r.at = c;
-                return -1;
-            }
-            v = seq[c];
-            c = c + 1 == num_train ? 0 : c + 1;
-        } while (taken(v));
-        r.at = c;
-        return v;
-    }
-    int32_t next_of_64(Reader &r, const int32_t *seq, int64_t limit) const
-    {
-        for (;;) {
-            for (; r.open; r.open &= r.open - 1) {
-                const int32_t v = seq[r.first + __builtin_ctzll(r.open)];
-                if (!taken(v)) {
-                    r.open &= r.open - 1;
-                    return v;
-                }
-            }
-            const int64_t n = std::min<int64_t>(limit - r.at, 64);
-            if (n <= 0) return -1;
-            for (int64_t i = 0; i < n; ++i) r.open |= (uint64_t)!taken(seq[r.at + i]) << i;
-            r.first = r.at;
-            r.at = r.at + n == num_train ? 0 : r.at + n;
-        }
-    }
-
-public:
-    std::vector<int64_t> there;  // leading entries of each sequence that may be read
-
-    Merge(const int32_t *seqs_, int32_t num_sequences, const int64_t *shifts, int64_t num_train_, int64_t num_nodes, int64_t num_out_,
-          int32_t *order_, int64_t there_)
-        : seqs(seqs_), num_train(num_train_), num_out(num_out_), order(order_), used((size_t)ceil_div(num_nodes, 64), 0),
-          there((size_t)num_sequences, there_)
-    {
-        for (int32_t s = 0; s < num_sequences; ++s) readers.push_back(Reader{shifts[s]});
-    }
-    // At most `turns` turns; false if there was nothing to do.
-    bool go_on(int64_t turns)
-    {
-        const int64_t end = std::min(num_out, k + turns), begin = k;
-        while (k < end) {
-            const int32_t *seq = seqs + j * (size_t)num_train;
-            const int32_t v = readers.size() > ONE_BY_ONE ? next_of_64(readers[j], seq, there[j]) : next(readers[j], seq, there[j]);
-            if (v < 0) break;  // not there yet
-            used[(size_t)v / 64] |= 1ull << (v % 64);
-            order[k++] = v;
-            j = j + 1 == readers.size() ? 0 : j + 1;
-        }
-        return k > begin;
-    }
-};
-
 struct OrderWork {
     const bgl_graph *g;
     Traversal t = {};            // of the first traversal
@@ -871,7 +790,7 @@ int prepare(const bgl_graph *g, const int32_t *train_nodes, int64_t num_train, i
 // `count` <= w.side traversals side by side: sequences number first, first + 1, ... of the call.
 template <typename RP>
 int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count, int64_t num_train, OrderWork &w, hipStream_t st,
-                  Merge *merge)
+                  OrderMerge *merge)
 {
     const int64_t N = g->num_nodes, words = round_up(ceil_div(N, 32), 2);
     const RP *rp = static_cast<const RP *>(g->row_ptr);
@@ -922,7 +841,7 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
         hipLaunchKernelGGL(k_append<RP>, dim3(grid.x + 1, grid.y), dim3(BT), 0, st, rp, N, words, w.train, t, par, (uint32_t)step);
         BGL_HIP(hipGetLastError());
         for (int64_t spins = 1; !all_done() && step - come_to() >= STEPS_AHEAD; ++spins) {
-            if (!merge || !merge->go_on(MERGE_TURNS)) __builtin_ia32_pause();
+            if (!merge || merge->go_on(MERGE_ENTRIES) == 0) __builtin_ia32_pause();
             // a stream that has nothing left to do, or has failed, will not come to the step waited for
             if (spins % 65536 == 0) {
                 const hipError_t e = hipStreamQuery(st);
@@ -936,7 +855,7 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
     if (!w.seqs_device)
         BGL_HIP(hipMemcpyAsync(w.seqs + one * (size_t)first, t.seq, sizeof(int32_t) * one * (size_t)count, hipMemcpyDeviceToHost, st));
     else if (merge)
-        while (come_to(), merge->go_on(num_train)) {}  // (while the last launches return)
+        while (come_to(), merge->go_on(MERGE_ENTRIES) > 0) {}  // (while the last launches return)
     BGL_HIP(hipStreamSynchronize(st));  // the steps beyond the end too; w.host may be written anew
     if (w.host->status != 0) {
         w.keep = true;
@@ -952,7 +871,7 @@ int bfs_sequences(const bgl_graph *g, const int64_t *roots, int first, int count
 // Behind prepare: leaves sequence j, num_train ids, at w.seqs[j * num_train].  A merge goes on meanwhile and may go to its end
 // afterwards.
 int compute_sequences(const bgl_graph_t *g, int64_t num_train, int32_t num_sequences, const int64_t *roots, hipStream_t st,
-                      OrderWork &w, Merge *merge)
+                      OrderWork &w, OrderMerge *merge)
 {
     for (int j = 0; j < num_sequences; j += w.side) {
         const int count = std::min(num_sequences - j, w.side);
@@ -1017,9 +936,9 @@ try {
     OrderWork w(g);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if ((rc = prepare(g, train_nodes, num_train, num_sequences, w, st)) != BGL_OK) return rc;
-    Merge merge(w.seqs, num_sequences, shifts, num_train, g->num_nodes, num_out, order, 0);
+    OrderMerge merge(w.seqs, num_sequences, shifts, num_train, g->num_nodes, num_out, order, 0);
     if ((rc = compute_sequences(g, num_train, num_sequences, roots, st, w, &merge)) != BGL_OK) return rc;
-    merge.go_on(num_out);
+    merge.finish();
     return BGL_OK;
 } BGL_NOTHROW_END
 
@@ -1037,7 +956,7 @@ try {
     if ((rc = prepare(g, train_nodes, num_train, max_sequences, w, st)) != BGL_OK) return rc;
     if ((rc = compute_sequences(g, num_train, max_sequences, roots, st, w, nullptr)) != BGL_OK) return rc;
     for (int32_t s = 1; s <= max_sequences; ++s) {
-        Merge(w.seqs, s, shifts, num_train, g->num_nodes, num_train, order, num_train).go_on(num_train);
+        OrderMerge(w.seqs, s, shifts, num_train, g->num_nodes, num_train, order, num_train).finish();
         double mean_tv = 0.0, max_tv = 0.0;
         rc = bgl_order_shuffling_error(order, num_train, batch, labels, g->num_nodes, num_classes, &mean_tv, &max_tv);
         if (rc != BGL_OK) return rc;

@@ -9,7 +9,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2112_08541_amd", "csrc")
 
 
-@pytest.mark.parametrize("program", ["order_plan"])
+@pytest.mark.parametrize("program", ["order_plan", "order_merge"])
 def test_order_program(tmp_path, program):
     gxx = shutil.which("g++")
     if gxx is None:
