@@ -576,7 +576,8 @@ int bgl_order_bfs_sequence(const bgl_graph_t *g, const int32_t *train_nodes, int
  * The random roots and shifts are the caller's draws.
  *   roots, shifts host, num_sequences values; 0 <= shifts[j] < num_train
  *   order         host, receives the first num_out <= num_train nodes of the order
- * Synchronous.  Errors as above.
+ * Synchronous.  Errors as above; after BGL_EHIP, order may hold part of the order
+ * (it is filled while the traversals run), after any other error it is untouched.
  */
 int bgl_order_proximity(const bgl_graph_t *g, const int32_t *train_nodes, int64_t num_train,
                         int32_t num_sequences, const int64_t *roots, const int64_t *shifts,
