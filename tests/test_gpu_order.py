@@ -62,11 +62,12 @@ def test_bfs_sequence_random_graphs(B, N, max_deg, dtype):
 
 
 @pytest.mark.parametrize("degrees,hub,dtype", [((0, 1, 2), 300_000, np.int32), ((64, 256, 0), 5_000, np.int64),
-                                               ((1,), 1_100_000, np.int32), ((255, 257), 0, np.int32)])
+                                               ((1,), 1_100_000, np.int32), ((255, 257), 0, np.int32),
+                                               ((1,), 2_200_000, np.int32), ((0, 3), 2_300_000, np.int64)])
 def test_bfs_sequence_rows_across_wavefront_shares(B, degrees, hub, dtype):
     """Edges are dealt to wavefronts in runs of multiples of 256, whatever the rows: rows that end on
-    such a boundary or one beside it, rows of many shares, levels of more than a share per wavefront,
-    and nodes without out-edges between them."""
+    such a boundary or one beside it, rows of many shares, levels of more than 256 edges per wavefront (4,194,304 in all,
+    which three rows make together), and nodes without out-edges between them."""
     import oracle
     rng = np.random.default_rng(len(degrees) * 1000 + hub)
     N = 12_000
