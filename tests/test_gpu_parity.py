@@ -645,11 +645,11 @@ def test_waiting_for_the_device_costs_a_small_lookup_no_more_than_waiting_for_it
     assert extra < 4e-6
 
 
-@pytest.mark.parametrize("limit_mib", [96, 256])
+@pytest.mark.parametrize("limit_mib", [64, 96, 256])
 @pytest.mark.parametrize("row_bytes", [400, 1024, 4096])
 def test_cache_hit_gather_around_its_limits(B, torch_mod, limit_mib, row_bytes):
-    """The hit gather changes its loads beyond 96 MiB of hits and its stores beyond 256 MiB: exactly the
-    limit (or the last row below it), one row more, and misses between the hits."""
+    """The hit gather changes its loads and stores beyond 64 MiB of hits and its stores again beyond 256 MiB: exactly the
+    limit (or the last row below it), one row more, and misses between the hits; 96 MiB lies between the two."""
     torch = torch_mod
     most = (limit_mib << 20) // row_bytes
     N = most + 5_000
@@ -1440,10 +1440,11 @@ def test_foreign_ids_are_left_untouched_where_the_fetch_reads_the_slots(B, torch
     assert cache.stats()["status"] != 0
 
 
-@pytest.mark.parametrize("hits,others", [(65_536, 0), (65_537, 0), (262_144, 0), (262_145, 0), (70_000, 4_130_000)])
+@pytest.mark.parametrize("hits,others", [(65_536, 0), (65_537, 0), (262_144, 0), (262_145, 0), (70_000, 3_500_000),
+                                         (70_000, 4_130_000)])
 def test_gathered_rows_around_the_bounds_of_their_accesses(B, torch_mod, hits, others):
     """Rows of 1,024 bytes: 64 and 256 MiB of hits, where the gather's loads and stores change, one row more of each, and hits
-    in between in an output of more than 4 GiB, which buffer stores do not reach."""
+    in between in outputs of 2 to 4 GiB, the upper half of a buffer store's offsets, and of more, which these do not reach."""
     torch = torch_mod
     rb, n = 1024, hits + others
     N = n + 10
@@ -1469,3 +1470,91 @@ def test_gathered_rows_around_the_bounds_of_their_accesses(B, torch_mod, hits, o
     assert int(cache.n_hit_host[0]) == hits
     for at in range(0, n, 500_000):
         assert torch.equal(out[at:at + 500_000].view(torch.int32), table[ids[at:at + 500_000].long()]), at
+
+
+@pytest.mark.parametrize("table", ["page-locked", "device"])
+@pytest.mark.parametrize("n", [65_536, 65_537, 262_144, 262_145])
+def test_rows_gathered_beside_their_lists_around_the_bounds_of_their_accesses(B, torch_mod, n, table):
+    """A cache that can hold every node chooses the accesses by the rows asked for: 64 and 256 MiB of them (1,024 bytes a row)
+    and one row more of each, all hits and with a few misses, the fetch beside the gather (page-locked table) and on
+    the lookup's own stream behind it (table in device memory, the call that allocates nothing)."""
+    torch = torch_mod
+    rb, N = 1024, n + 1_000
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    rows = torch.randint(-2**31, 2**31 - 1, (N, rb // 4), generator=gen, device="cuda", dtype=torch.int32).view(torch.uint8)
+    host = None
+    if table == "page-locked":
+        host = torch.empty((N, rb), dtype=torch.uint8, pin_memory=True)
+        host.copy_(rows)
+    cache = B.Cache(N, rows.data_ptr() if host is None else host, num_nodes=N, row_bytes=rb)
+    out = torch.empty((n, rb), dtype=torch.uint8, device="cuda")
+    slot = torch.empty(n, dtype=torch.int32, device="cuda")
+    miss = torch.empty(n, dtype=torch.int32, device="cuda")
+    first = torch.randperm(N - 1_000, generator=gen, device="cuda")[:n].to(torch.int32)
+    cache.lookup_gather(first, n, out, slot, miss)
+    cache.insert_fifo(first, miss, -1, out)
+    mixed = first[torch.randperm(n, generator=gen, device="cuda")].clone()
+    at = torch.randperm(n, generator=gen, device="cuda")[:700]
+    mixed[at] = (N - 1_000 + torch.arange(700, device="cuda")).to(torch.int32)
+    for ids, hits in ((first, n), (mixed, n - 700)):
+        out.fill_(0xAB)
+        cache.lookup_gather(ids, n, out, slot, miss, noalloc=table == "device")
+        cache.wait_rows()
+        torch.cuda.synchronize()
+        assert int(cache.n_hit_host[0]) == hits
+        assert torch.equal(out.view(torch.int32), rows.view(torch.int32)[ids.long()])
+        assert torch.equal(miss[:n - hits].long(), torch.nonzero(slot < 0).squeeze(1))
+
+
+@pytest.mark.parametrize("whole", [False, True])
+@pytest.mark.parametrize("form", ["plain", "timed", "noalloc", "another main stream", "a side stream", "early", "update"])
+def test_a_pending_fetch_reads_its_own_lookup_s_slots(B, torch_mod, whole, form):
+    """The miss fetch of a small lookup reads a copy of the slots that the next lookup of the same cache writes anew: one
+    that only hits follows at once, in every form that a lookup has, and must not take the misses' slots away.  (20,000 rows
+    are 200 us on the link, the next lookup's kernels 10.)"""
+    torch = torch_mod
+    rng = np.random.default_rng(5)
+    n, rb, rounds = 20_000, 400, 3
+    N = n * (rounds + 1) + 1
+    feats = torch.from_numpy(rng.integers(0, 256, (N, rb), dtype=np.uint8)).pin_memory()
+    cache = B.Cache(N if whole else N - 1, feats)
+    order = torch.from_numpy(rng.permutation(N).astype(np.int32)).cuda()
+    known = order[:n].contiguous()
+
+    def buffers():
+        return (torch.empty((n, rb), dtype=torch.uint8, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda"),
+                torch.empty(n, dtype=torch.int32, device="cuda"))
+
+    first, second = buffers(), buffers()
+    cache.lookup_gather(known, n, *first)
+    cache.insert_fifo(known, first[2], -1, first[0])
+    cache.lookup_gather(known, n, *first)
+    other = torch.cuda.Stream()
+    if form == "timed":                     # lookups 4, 6, ...: those that follow the one with the misses
+        cache.set_profiling(("gather_hit", "miss_list"))
+        cache.set_profiling_every("gather_hit", 2)
+        cache.set_profiling_every("miss_list", 2)
+    for r in range(rounds):
+        missing = order[n * (r + 1):n * (r + 2)].contiguous()
+        again = known[torch.from_numpy(rng.permutation(n)).cuda()].contiguous()
+        for b in (first, second):
+            b[0].fill_(0xAB)
+        torch.cuda.synchronize()
+        cache.lookup_gather(missing, n, *first)
+        if form == "update":
+            cache.insert_fifo(missing, first[2], -1, first[0])
+        if form == "early":
+            cache.set_write_through(True)
+        cache.lookup_gather(again, n, *second,
+                            main_stream=other if form == "another main stream" else None,
+                            side_stream=other if form == "a side stream" else None,
+                            lookup_stream=other if form == "early" else None, noalloc=form == "noalloc")
+        if form == "early":
+            cache.insert_fifo(again, second[2], -1, second[0])
+            cache.set_write_through(False)
+        torch.cuda.synchronize()
+        assert int(cache.n_hit_host[0]) == n, r
+        assert torch.equal(first[0].cpu(), feats[missing.cpu().long()]), r
+        assert torch.equal(second[0].cpu(), feats[again.cpu().long()]), r
+        assert torch.equal(first[2], torch.arange(n, dtype=torch.int32, device="cuda")), r
