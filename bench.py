@@ -112,6 +112,9 @@ def hit_gather_sweep(torch, np, B):
         (400, 4_000_000, 4_000_000, 1.0),
         (512, 4_000_000, 1_000_000, 1.0),
         (512, 4_000_000, 4_000_000, 1.0),
+        (512, 25_000_000, 600_000, 0.33),    # `large`'s cache: 200 K ids a lookup and its neighbours
+        (512, 25_000_000, 200_000, 1.0),
+        (512, 25_000_000, 400_000, 1.0),
         (1024, 4_000_000, 285_000, 0.37),    # `wide`: 106 K hits among 285 K ids
         (1024, 4_000_000, 250_000, 1.0),
         (1024, 4_000_000, 1_000_000, 1.0),

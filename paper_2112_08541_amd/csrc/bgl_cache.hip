@@ -530,6 +530,7 @@ __device__ __forceinline__ void by_gather_size(int64_t bytes, int64_t out_bytes,
 //   72 MB from 614 MB               25.1 / 22.9 | 28.4 / 25.6 | 36.8 / 34.3
 //   160 MB (400 bytes) from 800     58.0 / 54.3 | 64.1 / 58.9 | 81.4 / 77.7
 //   256 MB from 614 MB              76.6 / 73.5 | 81.0 / 77.5 | 113 / 110
+//   (the kernel alone) 102, 205 MB (512 bytes) from 12.8 GB  35.2 / 33.4, 63.6 / 61.1 | 35.9 / 34.9, 64.9 / 62.2 | 35.6 / 34.0, 63.3 / 61.6
 // Below 64 MB ordinary accesses are as fast (44 MB 16.4 / 17.2 | 24.5 / 19.8 | 24.4 / 25.3); beyond 256 MB non-temporal stores written
 // through or not differ by 1 %.
 template <int Q>
