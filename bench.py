@@ -388,7 +388,7 @@ def run_config(cfg, args, torch, np, B, inputs, MinibatchPipeline, want_cpu):
                 "bytes_per_launch": 2.0 * rb * g_hit / max(g_n, 1),
                 "avg_launch_us": 1e3 * g_kernel_ms / max(g_n, 1), "launches": g_n,
                 "bytes": "per launch: 2 x row_bytes x hits",
-                "timing": timing,
+                "timing": timing + "; small lookups that are not timed copy their hits in k_list_and_hits",
             }
         skip = ("fetch_miss", "link_copy", "gather_hit", "assemble", "assemble_pre")
         result["stage_ms_per_step"] = {k: (v[0] / steps if k != "event_overhead" else v[0])

@@ -65,12 +65,12 @@ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 namespace bgl {
 
 // Scratch of an ordering call: device memory, and page-locked host memory that is coherent whatever
-// HIP_HOST_COHERENT says.  A graph keeps what its last call used for the next one: allocating and freeing it costs 0.1 to
-// 0.3 ms a call (2 sequences on 2.45 M nodes / 122 M edges, 380 MB: a first call 4.0 ms, further ones 3.6; 5 sequences on
-// 100,000 nodes, 50 MB: 0.69 and 0.59).  It holds one of each at most, up to the sizes below and where device memory is not
+// HIP_HOST_COHERENT says.  A graph keeps what its last call used for the next one: allocating and freeing it costs 0.2 to
+// 1 ms a call (2 sequences on 2.45 M nodes / 122 M edges, 380 MB: first calls 3.3 to 4.0 ms, further ones 2.5 to 3.8; 5 sequences on
+// 100,000 nodes, 50 MB: 0.68 to 0.82 and 0.46 to 0.50).  It holds one of each at most, up to the sizes below and where device memory is not
 // short, and frees them with the graph; a call that finds them taken by another thread's allocates its own.  The bounds keep
 // what a program that orders once cannot use afterwards small: a 64th of what it had left, never more than half a GiB (5
-// sequences on 2.45 M nodes take 940 MB and allocate it each time, 0.4 ms of 6.3).
+// sequences on 2.45 M nodes take 940 MB and allocate it each time, some 0.4 ms of 5.5 to 6.3).
 struct OrderScratch {
     void *device = nullptr, *host = nullptr;
     size_t device_bytes = 0, host_bytes = 0;

@@ -22,10 +22,10 @@
 // a power law, and with a fixed number of lanes per node the longest row sets the
 // pace (16 lanes on a row of 20,000 edges: 1.9 ms for one level).  Measured, two
 // sequences on 2.45 M nodes / 122 M edges: 26 to 28 ms with 16 lanes per node and a
-// radix sort per level, 3.3 to 3.8 ms now (4.0 in a graph handle's first call, which allocates the scratch; k_expand 2.3 ms,
+// radix sort per level, 2.5 to 3.8 ms now, by the host (a graph handle's first call: OrderScratch; k_expand 2.3 ms,
 // 100 G edges/s: 262 M reads that reach an L2, which serves random ones at 267 G/s when they hit and 58 G/s when they miss, 14 %
 // of these, and 10 M atomics, which the chip does 27 G/s of wherever they go); five sequences on 100,000 nodes / 1 M edges,
-// where launches and host round trips count: 14 to 19 and 0.52 ms.
+// where launches and host round trips count: 14 to 19 and 0.46 to 0.50 ms.
 //   The sequences of a call are independent traversals and share their launches (blockIdx.y): one after the
 // other, the five took 1.7 ms, the two 4.8.
 //   A level is handled in windows of at most WINDOW edges, which bounds the lists (6 bytes an edge) whatever the
@@ -56,6 +56,8 @@ constexpr int BLOCKS = 4096;
 // Before / with these, us a call: five on 100,000 nodes / 1 M edges 523 / 473, 3 M edges 612 / 497, 300,000 nodes / 6 M 1,153 / 1,016;
 // ten 765 / 635, 906 / 700, 1,807 / 1,642; two on 6 M edges 710 / 668, 12 M 843 / 792.  Elsewhere the larger steps lose as much as the small
 // ones gain (five on 24 M edges 3,001 / 3,120, two on 3 M 390 / 402, on 24 M 1,589 / 1,595), and one traversal is level throughout.
+// Within, a few large steps lose too: two on 100,000 nodes / 16 M edges 390 / 413, sixteen on 400,000 / 7 M 4,150 / 4,250; three, four and
+// seven on 0.2 to 8 M edges 250 to 2,410 / 256 to 2,240.
 // (No multiple of 8 each, or the first workgroups of all traversals, in small steps the only ones with work, share an XCD: ten on
 // 30,000 nodes / 0.3 M edges with 256 each 466 instead of 360.)
 constexpr int RESIDENT_BLOCKS = 2048;
